@@ -1,0 +1,106 @@
+"""fp32 path at the edges of its dispatch: tile counts and remainders of both block sides, the key
+ranges on either side of the one-pass refine kernel, feature counts that are padded or not a
+multiple of four, rows that are not 16-byte aligned, bf16 storage, underflowing columns of L.
+
+The bar is relative (2-norm): an fp32 dot product of 128 terms carries about 3e-7, two or three such
+stages in a row 1e-6; five times that."""
+import pytest
+import torch
+
+import paper_2602_12271_amd as pkg
+from oracle import monarch_oracle as mo
+from workloads import synthetic as syn
+
+from gpu_harness import oracle_dense_head, oracle_monarch_head, run_dense_gpu, run_monarch_gpu, to_device
+
+pytestmark = pytest.mark.gpu
+
+REL = 5e-6
+
+
+def case(f, h, w, b1, b2, *, d=64, f_kv=None, tile=0, iters=2, chunk=0, off=0, dtype="f32", heads=2, **kw):
+    return syn.Workload("edge", 1, heads, d, f, f_kv or f, h, w, b1, b2, tile, iters, chunk, off, dtype, d ** -0.5,
+                        True, **kw)
+
+
+CASES = {
+    "b1-16-b2-16": case(2, 8, 16, 16, 16),
+    "b1-17-b2-17": case(1, 17, 17, 17, 17),
+    "one-row": case(1, 1, 5, 1, 5),
+    "b2-1-cols": case(3, 4, 1, 12, 1),
+    "b1-33-b2-65-d128": case(3, 11, 65, 33, 65, d=128),
+    "b1-97-b2-96": case(1, 97, 96, 97, 96, heads=1, iters=1),
+    "b1-192": case(2, 96, 8, 192, 8, d=128),
+    "one-pass-192-keys": case(2, 48, 10, 96, 5, tile=1),
+    "streamed-208-keys": case(4, 13, 8, 13, 2, tile=1),
+    "streamed-long-mask": case(2, 9, 12, 9, 4, f_kv=10, tile=1, iters=3, chunk=2, off=4),
+    "streamed-b1-180": case(2, 90, 4, 180, 2, tile=1, d=128),
+    "regular-mask": case(6, 7, 9, 42, 9, chunk=2, iters=3),
+    "d-100": case(2, 5, 9, 10, 9, d=100),
+    "d-36-tiles": case(2, 6, 8, 6, 4, d=36, tile=1),
+    "d-38-elements": case(3, 7, 10, 21, 5, d=38, tile=1, iters=3),
+    "d-7-long": case(2, 20, 12, 20, 2, d=6, tile=1),
+    "bf16-storage": case(2, 10, 20, 20, 20, dtype="bf16"),
+    "fw_h": case(2, 6, 13, 26, 6, assign="fw_h"),
+}
+
+
+def distance(wl, arrays, out, oracle):
+    num = den = 0.0
+    for hd in range(wl.heads):
+        ref = oracle(wl, *(x[0, hd] for x in arrays))
+        num += (out[0, hd].double().cpu() - ref).pow(2).sum().item()
+        den += ref.pow(2).sum().item()
+    return (num / den) ** 0.5
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_forward(name):
+    wl = CASES[name]
+    arrays = syn.make_inputs(wl)
+    print(f"case {name}: {wl}", flush=True)
+    out = run_monarch_gpu(wl, *to_device(wl, arrays), compute=pkg.MRT_COMPUTE_F32)
+    err = distance(wl, arrays, out, oracle_monarch_head)
+    print(f"  rel {err:.2e}", flush=True)
+    assert err <= (REL if wl.dtype == "f32" else 3e-3)      # bf16 storage: one rounding of the output, 2^-9
+
+
+@pytest.mark.parametrize("name", ["b1-17-b2-17", "streamed-long-mask", "d-38-elements", "b1-33-b2-65-d128"])
+def test_dense(name):
+    wl = CASES[name]
+    arrays = syn.make_inputs(wl)
+    out = run_dense_gpu(wl, *to_device(wl, arrays))
+    assert distance(wl, arrays, out, oracle_dense_head) <= REL
+
+
+def test_unaligned_rows_give_the_same_result():
+    # the tensors start one element off a 16-byte boundary: single-element loads and stores
+    wl = CASES["b1-17-b2-17"]
+    arrays = syn.make_inputs(wl)
+    dev = to_device(wl, arrays)
+    aligned = run_monarch_gpu(wl, *dev)
+    odd = []
+    for x in dev:
+        buf = torch.zeros(x.numel() + 1, device=x.device)
+        odd.append(buf[1:].view(x.shape).copy_(x))
+    out = torch.zeros(dev[0].numel() + 1, device="cuda:0")[1:].view(dev[0].shape)
+    pkg.monarch_attn_fwd(*odd, f_q=wl.f_q, f_kv=wl.f_kv, h=wl.h, w=wl.w, b1=wl.b1, b2=wl.b2, tile=wl.tile,
+                         iters=wl.iters, scale=wl.scale, out=out)
+    torch.cuda.synchronize()
+    assert ((out - aligned).norm() / aligned.norm()).item() <= REL
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+def test_underflowing_columns(tile):
+    # one key row is so unlikely that every weight of its column of L underflows in fp32: its share
+    # of the next iteration's abar must stay finite
+    wl = case(2, 5, 8, 10, 8, iters=2) if tile == 0 else case(21, 10, 4, 10, 2, tile=1, iters=2)
+    arrays = tuple(x.copy() for x in syn.make_inputs(wl))
+    Q, K, _ = arrays
+    Q[..., 0] = 40.0
+    K[..., 0] = 0.0
+    K[:, :, 3 * wl.w:4 * wl.w, 0] = -80.0
+    out = run_monarch_gpu(wl, *to_device(wl, arrays))
+    assert torch.isfinite(out).all()
+    # logits of magnitude 400: their fp32 rounding (2.4e-5) is the bar
+    assert distance(wl, arrays, out, oracle_monarch_head) <= 2e-4
