@@ -310,8 +310,7 @@ static StreamPool* get_pool() {
   return p;
 }
 
-// Compute units of the current device (256 on MI355X); queried once per process.
-static int compute_units() {
+int compute_units() {
   static const int n = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

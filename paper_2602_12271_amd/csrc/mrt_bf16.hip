@@ -234,7 +234,7 @@ __global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) 
 }
 
 // ---------------------------------------------------------------------------------------
-// flash loop shared by stage L (out), stage L (refine, pass 1) and the dense baseline
+// flash loop shared by stage L (out) and stage L (refine, pass 1)
 // ---------------------------------------------------------------------------------------
 constexpr int kHK = 32;    // keys per pipeline step (one register set, one LDS slot)
 constexpr int kRing = 4;   // LDS slots
@@ -1368,60 +1368,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void k_bf16_stage_l_refin
   MRT_STAMP(6);
 }
 
-// dense baseline: 128 queries per workgroup (4 waves x 2 tiles of 16), flash loop over all
-// visible keys
-constexpr int kDenseQT = 2, kDenseQ = 64 * kDenseQT;
-
-template <int D>
-__global__ __launch_bounds__(256, 2) void k_bf16_dense(KParams p) {
-  constexpr int KS1 = D / 32, NVT = D / 16, QT = kDenseQT;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[FlashLds<D, true>::kBytes];
-  FlashLds<D, true> lds(smem);
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
-  const int q0 = blockIdx.x * kDenseQ, bh = blockIdx.y;
-  const int b = bh / p.H, hd = bh - b * p.H;
-  const int qtiles = (p.Nq - q0 + 15) >> 4;
-  const WaveTiles<QT> wt(wave, 4, qtiles < 4 * QT ? qtiles : 4 * QT);
-  const u16* Qp = (const u16*)p.Q + b * p.qs.batch + hd * p.qs.head;
-  bf16x8 qv[QT][KS1];
-  int qchunk[QT];
-#pragma unroll
-  for (int q = 0; q < QT; ++q) {
-    const int qi = q0 + 16 * wt.lt[q] + c;
-    const int qc = qi < p.Nq ? qi : p.Nq - 1;
-    qchunk[q] = p.cc > 0 ? (p.qoff + qc / p.hw) / p.cc : 0x7fffffff;
-#pragma unroll
-    for (int ks = 0; ks < KS1; ++ks)
-      qv[q][ks] = ld_global_16B(Qp + (long long)qc * p.qs.token + 32 * ks + 8 * g);
-  }
-  const u16* Kp = (const u16*)p.K + b * p.ks.batch + hd * p.ks.head;
-  const u16* Vp = (const u16*)p.V + b * p.vs.batch + hd * p.vs.head;
-  int nkeys = p.Nkv;
-  if (p.cc > 0) {
-    const int qlast = (q0 + kDenseQ - 1 < p.Nq ? q0 + kDenseQ - 1 : p.Nq - 1);
-    const long long lim = (long long)((p.qoff + qlast / p.hw) / p.cc + 1) * p.cc * p.hw;
-    if (lim < nkeys) nkeys = (int)lim;
-  }
-  FlashState<QT> st;
-  f32x4 o[QT][NVT];
-#pragma unroll
-  for (int q = 0; q < QT; ++q)
-#pragma unroll
-    for (int vt = 0; vt < NVT; ++vt) o[q][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int cc = p.cc, hw = p.hw;
-  auto meta = [&](int key, float& raw, int& chunk) { raw = 0.f; chunk = cc > 0 ? (key / hw) / cc : 0; };
-  flash_loop<D, QT, true, true, 256>(Kp, p.ks.token, Vp, p.vs.token, nkeys, meta, lds, qv, wt.nq,
-                                     p.scale * kLog2e, qchunk, st, o, tid, lane);
-  u16* Op = (u16*)p.O + b * p.os.batch + hd * p.os.head;
-#pragma unroll
-  for (int q = 0; q < QT; ++q) {
-    const int qi = q0 + 16 * wt.lt[q] + c;
-    const float lsum = xsum(st.lrun[q]);
-    if (q < wt.nq && qi < p.Nq)
-      store_rows<D>(Op + (long long)qi * p.os.token, o[q], lsum > 0.f ? 1.0f / lsum : 0.f, g);
-  }
-}
-
 template <int NT, int D>
 hipError_t launch_r(const KParams& kp, dim3 grid, int gs, bool first, bool last, hipStream_t s) {
   const size_t lds = last ? stage_r_last_lds_bytes<NT, D>(kp.b2) : 0;
@@ -1787,13 +1733,6 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
                                    : launch_l_out<64, 2, 256>(kp, grid, s);
   return kp.d == 128 ? launch_l_out<128, 2, 512>(kp, grid, s)
                      : launch_l_out<64, 2, 512>(kp, grid, s);
-}
-
-hipError_t launch_bf16_dense(const KParams& kp, int nbh, hipStream_t s) {
-  dim3 grid((kp.Nq + kDenseQ - 1) / kDenseQ, nbh);
-  if (kp.d == 128) k_bf16_dense<128><<<grid, 256, 0, s>>>(kp);
-  else k_bf16_dense<64><<<grid, 256, 0, s>>>(kp);
-  return hipGetLastError();
 }
 
 }  // namespace mrt

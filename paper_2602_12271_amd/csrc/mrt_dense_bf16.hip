@@ -1,0 +1,318 @@
+// Dense softmax attention baseline on the bf16 matrix unit (Sec. 2.2), chunk-causal by token.
+// See the head of mrt_bf16.hip for the register layouts.
+//
+// Eight waves, two to a SIMD, each owning QT query tiles of 16.  A step of 64 keys is a vector phase
+// (maxima, exponentials, packing, the refill of the LDS ring) and a matrix phase (first product of the
+// next step, second product of this one, their LDS reads), and the two halves of the workgroup run one
+// phase apart: one wave of a SIMD feeds the matrix unit while the other one has the vector ALU.  The
+// barrier that ends every phase keeps them so.  (Without it the waves drift into step and the two
+// units take turns: a matrix unit busy 35 % of the time.)  What bounds the kernel then is the vector
+// phase (52 vector instructions per 32 keys and two tiles, which issue at half rate under the other
+// wave's products) and about 150 clocks of barrier per phase; hence phases of 64 keys (two chunks) and
+// no vector work that the matrix unit can do (the sums of the probabilities).
+//
+// LDS rows are padded to D + 16 elements (288 bytes at D = 128): the 16-byte key reads and the
+// transposed value reads of 16 contiguous features then both run free of bank conflicts (4.0 and 2.8
+// clocks per wave instruction and CU measured; a 16-byte XOR swizzle 6.0 and 4.0).
+//
+// WK = 1: every wave sees all keys.  WK = 2: waves w and w + 4 share their queries and take one half of
+// every 64 keys (half the queries per workgroup, so twice the workgroups); the halves are merged at the
+// end.
+#include "mrt_internal.hpp"
+#include "mrt_bf16_tiles.hpp"
+
+namespace mrt {
+
+namespace {
+
+// A query's softmax reference is raised only when a logit exceeds it by more than this (base 2):
+// every probability is then at most 2^kGrow, and the ratio sum(p v) / sum(p) does not depend on it.
+constexpr float kGrow = 8.0f;
+constexpr int kDenseWaves = 8, kDenseThreads = 64 * kDenseWaves;
+// LDS ring of 64-key pairs of chunks: while pair i is consumed, pair i + 1 is resident, pair i + 2 is
+// being written and pair i + 3 is in flight from global memory.
+constexpr int kDenseSlots = 4;
+constexpr int kAhead = 5;    // operand reads ahead of their products (3, 5 and 7 measured alike)
+template <int D> constexpr int kDenseLd = D + 16;                          // elements per LDS row
+template <int D> constexpr int kDenseSlot = 2 * 64 * kDenseLd<D>;          // 64 keys, then 64 values
+template <int D> constexpr size_t kDenseLds = (size_t)kDenseSlots * kDenseSlot<D> * 2;
+
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+// 64 rows of D bf16 between global memory and LDS.  Buffer loads return zeros beyond the last row, so
+// no load is clamped or conditional.
+template <int D>
+struct DenseTile {
+  static constexpr int CPR = D / 8, N = 64 * CPR / kDenseThreads, RSTEP = kDenseThreads / CPR;
+  u32x4 v[N];
+  // at: byte offset of the tile's first row
+  __device__ inline void load(__amdgpu_buffer_rsrc_t rsrc, unsigned voff, unsigned at, unsigned rowbytes) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + (at + (unsigned)(i * RSTEP) * rowbytes), 0, 0);
+  }
+  __device__ inline void store(u16* dst, int tid) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) *(u32x4*)(dst + (tid / CPR + i * RSTEP) * kDenseLd<D> + 8 * (tid % CPR)) = v[i];
+  }
+};
+
+template <int D, int QT, int WK>
+__global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
+  using Tile = DenseTile<D>;
+  constexpr int KS1 = D / 32, NVT = D / 16, LD = kDenseLd<D>, WQ = kDenseWaves / WK, WGQ = 16 * QT * WQ;
+  constexpr int NS = 2 / WK, NT = 2 * NS;                 // 32-key chunks / 16-key tiles of a wave's step
+  extern __shared__ __attribute__((aligned(16))) u16 dense_lds[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wq = wave % WQ, wk = wave / WQ;
+  const bool second = wave >= kDenseWaves / 2;           // the half that runs one phase behind
+  // keys a query sees: the frames up to the end of its own chunk, a prefix
+  auto visible = [&](int q) {
+    if (p.cc == 0) return p.Nkv;
+    const long long lim = (long long)((p.qoff + q / p.hw) / p.cc + 1) * p.cc * p.hw;
+    return lim < p.Nkv ? (int)lim : p.Nkv;
+  };
+  // Workgroups reach the eight XCDs in turn: hand each XCD a contiguous run of (head, query tile)
+  // units, so that the units that stream the same keys share its L2.  (Under a mask that gives the
+  // query tiles of a head different key counts the natural order spreads the long ones evenly.)
+  const int nx = (p.Nq + WGQ - 1) / WGQ, total = gridDim.x, xcd = blockIdx.x & 7;
+  int unit = blockIdx.x;
+  if (visible(0) == visible(p.Nq - 1)) unit = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)) + (blockIdx.x >> 3);
+  const int bh = unit / nx, q0 = (unit - bh * nx) * WGQ;
+  const int b = bh / p.H, hd = bh - b * p.H;
+  const int qw0 = q0 + 16 * QT * wq;                      // this wave's first query
+  const int nkeys = visible(q0 + WGQ - 1 < p.Nq ? q0 + WGQ - 1 : p.Nq - 1), nfree = visible(q0);
+
+  const u16* Qp = (const u16*)p.Q + b * p.qs.batch + hd * p.qs.head;
+  bf16x8 qv[QT][KS1];
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    const int qi = qw0 + 16 * q + c, qc = qi < p.Nq ? qi : p.Nq - 1;
+#pragma unroll
+    for (int ks = 0; ks < KS1; ++ks) qv[q][ks] = ld_global_16B(Qp + (long long)qc * p.qs.token + 32 * ks + 8 * g);
+  }
+
+  const unsigned krow = (unsigned)p.ks.token * 2u, vrow = (unsigned)p.vs.token * 2u;     // bytes per token
+  const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const u16*)p.K + b * p.ks.batch + hd * p.ks.head), 0, (unsigned)(nkeys - 1) * krow + 2 * D, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const u16*)p.V + b * p.vs.batch + hd * p.vs.head), 0, (unsigned)(nkeys - 1) * vrow + 2 * D, 0x00020000);
+  const unsigned kvoff = (unsigned)(tid / Tile::CPR) * krow + 16u * (tid % Tile::CPR);
+  const unsigned vvoff = (unsigned)(tid / Tile::CPR) * vrow + 16u * (tid % Tile::CPR);
+  const int npairs = (nkeys + 63) >> 6;
+  Tile kt, vt;
+  // (pairs past the end re-read the last one; nobody reads their slot, or only as masked keys)
+  auto fetch = [&](int pr) {
+    const unsigned at = (unsigned)(pr < npairs ? pr : npairs - 1) * 64u;
+    kt.load(kr, kvoff, at * krow, krow);
+    vt.load(vr, vvoff, at * vrow, vrow);
+  };
+  auto commit = [&](int slot) {
+    u16* at = dense_lds + slot * kDenseSlot<D>;
+    kt.store(at, tid);
+    vt.store(at + 64 * LD, tid);
+  };
+
+  const float scale2 = p.scale * kLog2e;
+  bf16x8 pb[QT][NS];
+  f32x4 s[QT][NT], o[QT][NVT];
+  float mref[QT], thr[QT];                // reference, the raw logit that would raise it
+  f32x4 lrun[QT];                         // sum of the probabilities (the same in all four registers)
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    mref[q] = -1e30f; thr[q] = -INFINITY; lrun[q] = f32x4{0.f, 0.f, 0.f, 0.f};   // (finite: no key seen yet)
+#pragma unroll
+    for (int vt = 0; vt < NVT; ++vt) o[q][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
+  // A wave's keys of a pair start at row 32 wk (WK = 2) or 0.
+  const int koff = (WK == 2 ? 32 * wk * LD : 0) + c * LD + 8 * g;
+  const int voff = 64 * LD + (WK == 2 ? 32 * wk * LD : 0) + (4 * g + (c >> 2)) * LD + 4 * (c & 3);
+  // The matrix phase: s = logits of the next step's keys (pair in kslot), o += the probabilities'
+  // product with this step's values (pair in vslot), lrun += their sums (a product with ones: the sum
+  // of what the second product weighs with, without a vector instruction).  Operands are read from
+  // LDS kAhead groups of products ahead of their use, in this fixed order.
+  constexpr int NK_OPS = NT * KS1, NV_OPS = NS * NVT, OPS = NK_OPS + NV_OPS;
+  bf16x8 op[OPS];
+  auto read_op = [&](int i, const u16* ka, const u16* va) {
+    if (i < NK_OPS) {
+      op[i] = ld_lds_16B(ka + 16 * (i % NT) * LD + 32 * (i / NT));
+    } else {
+      const u16* at = va + 32 * ((i - NK_OPS) / NVT) * LD + 16 * ((i - NK_OPS) % NVT);
+      op[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(ld_lds_tr(at), ld_lds_tr(at + 16 * LD), 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+  };
+  auto matrix = [&](int kslot, int vslot, bool with_v) {
+    const u16* ka = dense_lds + kslot * kDenseSlot<D> + koff;
+    const u16* va = dense_lds + vslot * kDenseSlot<D> + voff;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) read_op(i, ka, va);
+#pragma unroll
+    for (int i = 0; i < OPS; ++i) {
+      if (!with_v && i >= NK_OPS) break;
+      if (i + kAhead < (with_v ? OPS : NK_OPS)) read_op(i + kAhead, ka, va);
+      if (i < NK_OPS) {
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+          s[q][i % NT] = mfma(op[i], qv[q][i / NT], i < NT ? f32x4{0.f, 0.f, 0.f, 0.f} : s[q][i % NT]);
+      } else {
+        const int st = (i - NK_OPS) / NVT, vt = (i - NK_OPS) % NVT;
+        if (vt == 0) {
+#pragma unroll
+          for (int q = 0; q < QT; ++q) lrun[q] = mfma(ones, pb[q][st], lrun[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) o[q][vt] = mfma(op[i], pb[q][st], o[q][vt]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto top = [&](int q) {
+    float m = fmaxf(s[q][0][0], s[q][0][1]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t > 0) m = fmaxf(m, fmaxf(s[q][t][0], s[q][t][1]));
+      m = fmaxf(m, fmaxf(s[q][t][2], s[q][t][3]));
+    }
+    return m;
+  };
+  // the raw logits of the keys from c0 on are complete: mask them where they reach beyond a query's
+  // keys, raise the references they exceed, and form the probabilities
+  auto soften = [&](int c0) {
+    if (c0 + 16 * NT > nfree) {
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+        const int qi = qw0 + 16 * q + c, lim = visible(qi < p.Nq ? qi : p.Nq - 1);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (c0 + 16 * t + 4 * g + r >= lim) s[q][t][r] = -INFINITY;
+      }
+    }
+    bool above = false;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) above |= top(q) > thr[q];
+    if (__builtin_amdgcn_ballot_w64(above) != 0) {
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+        const float mnew = fmaxf(mref[q], xmax(top(q)) * scale2);
+        const float f = exp2_fast(mref[q] - mnew);
+        mref[q] = mnew;
+        thr[q] = (mnew + kGrow) / scale2;
+        lrun[q] = lrun[q] * f;
+#pragma unroll
+        for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[q][t][r] = exp2_fast(fmaf(s[q][t][r], scale2, -mref[q]));
+#pragma unroll
+      for (int st = 0; st < NS; ++st) pb[q][st] = pack8(s[q][2 * st], s[q][2 * st + 1]);
+    }
+  };
+  auto phase_end = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  fetch(0);
+  commit(0);
+  fetch(1);
+  commit(1);
+  fetch(2);
+  __syncthreads();
+  matrix(0, 0, false);
+  if (second) __syncthreads();
+  for (int i = 0; i < npairs; ++i) {
+    soften(64 * i + (WK == 2 ? 32 * wk : 0));
+    // pair i + 2 into the slot of pair i - 2, which both halves left at least a phase ago (the other
+    // half may still be reading pairs i - 1 and i)
+    commit((i + 2) & (kDenseSlots - 1));
+    fetch(i + 3);
+    phase_end();
+    __builtin_amdgcn_s_setprio(1);
+    matrix((i + 1) & (kDenseSlots - 1), i & (kDenseSlots - 1), true);
+    __builtin_amdgcn_s_setprio(0);
+    phase_end();
+  }
+  if (!second) __syncthreads();
+
+  if constexpr (WK == 2) {
+    // the second half's reference, sum and accumulators, merged into the first half's
+    f32x4* xo = (f32x4*)dense_lds + (size_t)wq * (QT * (NVT + 1)) * 64 + lane;
+    __syncthreads();
+    if (wk == 1) {
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+#pragma unroll
+        for (int vt = 0; vt < NVT; ++vt) xo[(q * (NVT + 1) + vt) * 64] = o[q][vt];
+        xo[(q * (NVT + 1) + NVT) * 64] = f32x4{mref[q], lrun[q][0], 0.f, 0.f};
+      }
+    }
+    __syncthreads();
+    if (wk == 1) return;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      const f32x4 ml = xo[(q * (NVT + 1) + NVT) * 64];
+      const float m = fmaxf(mref[q], ml[0]), f0 = exp2_fast(mref[q] - m), f1 = exp2_fast(ml[0] - m);
+      lrun[q][0] = lrun[q][0] * f0 + ml[1] * f1;
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f0 + xo[(q * (NVT + 1) + vt) * 64] * f1;
+    }
+  }
+  u16* Op = (u16*)p.O + b * p.os.batch + hd * p.os.head;
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    const int qi = qw0 + 16 * q + c;
+    const float lsum = lrun[q][0], inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    if (qi < p.Nq) {
+      u16* row = Op + (long long)qi * p.os.token + 4 * g;
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) {
+        const f32x4 x = o[q][vt] * inv;
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+        *(bf16x4*)(row + 16 * vt) = bf16x4{(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+      }
+    }
+  }
+}
+
+template <int D, int QT, int WK>
+hipError_t run_dense(const KParams& kp, int nbh, hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute((const void*)k_bf16_dense<D, QT, WK>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDenseLds<D>);
+  if (e != hipSuccess) return e;
+  constexpr int wgq = 16 * QT * kDenseWaves / WK;
+  k_bf16_dense<D, QT, WK><<<(kp.Nq + wgq - 1) / wgq * nbh, kDenseThreads, kDenseLds<D>, s>>>(kp);
+  return hipGetLastError();
+}
+
+// One workgroup occupies a compute unit, so a call takes as many rounds as its workgroups fill the
+// chip; a round costs 112, 78 and 58 us at 4680 keys of 128 features for workgroups of 256 (QT = 2),
+// 128 (QT = 2, WK = 2) and 64 (QT = 1, WK = 2) queries.  The variant with the least rounds x cost
+// (one head of 4680 tokens: 58 us against 112, the previous kernel 121; 5 heads: 79 against 113 and 114;
+// 12 heads: 121 against 154, previous kernel 174, 62 of it matrix time).
+template <int D>
+hipError_t run_dense_d(const KParams& kp, int nbh, hipStream_t s) {
+  auto cost = [&](int queries, long long unit) {
+    const long long wgs = (long long)((kp.Nq + queries - 1) / queries) * nbh, cus = compute_units();
+    return (wgs + cus - 1) / cus * unit;
+  };
+  const long long c256 = cost(256, 112), c128 = cost(128, 78), c64 = cost(64, 58);
+  if (c64 < c128 && c64 < c256) return run_dense<D, 1, 2>(kp, nbh, s);
+  return c128 < c256 ? run_dense<D, 2, 2>(kp, nbh, s) : run_dense<D, 2, 1>(kp, nbh, s);
+}
+
+}  // namespace
+
+hipError_t launch_bf16_dense(const KParams& kp, int nbh, hipStream_t s) {
+  return kp.d == 128 ? run_dense_d<128>(kp, nbh, s) : run_dense_d<64>(kp, nbh, s);
+}
+
+}  // namespace mrt

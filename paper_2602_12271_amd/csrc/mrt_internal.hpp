@@ -132,6 +132,7 @@ struct Plan {
 };
 
 void set_error(const char* fmt, ...);
+int compute_units();   // of the current device (256 on MI355X); queried once per process
 
 // The forward call behind monarch_attn_fwd and monarch_attn_fwd_noalloc (mrt_api.cpp).
 mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const mrt_problem* p, int b1,
