@@ -1405,7 +1405,7 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------
-// stage L for medium key ranges (96 < NK <= 192, b1 <= 128): still one workgroup per (m, j) and
+// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 with four waves, b1 > 144 with six): still one workgroup per (m, j) and
 // three workgroups per compute unit, with ONE 52 KB LDS tile used twice.  Last iteration: the
 // tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one or two query
 // tiles against all keys and keeps the probabilities as packed bf16 in registers), then Y[m, j]
@@ -1413,6 +1413,7 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 // for the second pass, which streams alpha_L again from global memory.
 // ---------------------------------------------------------------------------------------
 constexpr int kMidRows = 192;
+constexpr int kMidWideB1 = 144;   // beyond: no bf16 backward pass
 
 // Base-2 logits (bias added, -inf beyond the last key) of one query tile against NTK resident key
 // tiles (NTK <= 12), and their column maximum.
@@ -1457,15 +1458,16 @@ __device__ inline float mid_logits(const u16* Ks, const float* bias, const bf16x
   return xmax(mx);
 }
 
-template <int D, int NTK, bool RMASK>
-__global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_mid(KParams p) {
+template <int D, int NTK, int NW, bool RMASK>
+__global__ __launch_bounds__(64 * NW, 3) void k_bf16_stage_l_out_mid(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
   constexpr bool SWZ = ResTile<D>::SWZ;
   constexpr int QT = 2;
   __shared__ __attribute__((aligned(16))) u16 tile[ROWS * LD];
   __shared__ __attribute__((aligned(16))) float bias[ROWS];
 
-  const int tid = threadIdx.x, nthr = blockDim.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
+  constexpr int nthr = 64 * NW;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int b1 = p.b1, b2 = p.b2;
   const int j = blockIdx.x, ml = blockIdx.y, m = p.m0 + ml, bhl = last_head_first(), bh = p.bh0 + bhl;
@@ -1473,7 +1475,7 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_mid(KParams p) {
   const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;   // <= 16*NTK
   const size_t NKtot = (size_t)p.ntk * b1;
   const int b = bh / p.H, hd = bh - b * p.H;
-  const WaveTiles<QT> wt(wave, nwaves, (b1 + 15) >> 4);      // b1 <= 128: at most two tiles a wave
+  const WaveTiles<QT> wt(wave, NW, (b1 + 15) >> 4);          // b1 <= 32 NW: at most two tiles a wave
 
   const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot;
   const u16* aLp = (const u16*)p.aL + row0 * D;
@@ -1493,7 +1495,7 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_mid(KParams p) {
 #pragma unroll
     for (int ks = 0; ks < KS1; ++ks) qv[q][ks] = ld_global_16B(Qp + qrow(lc) + 32 * ks + 8 * g);
   }
-  stage_rows_batched<D, LD, ROWS, 256, SWZ>(tile, aLp, PlainRows{D}, NK, tid);
+  stage_rows_batched<D, LD, ROWS, nthr, SWZ>(tile, aLp, PlainRows{D}, NK, tid);
   for (int i = tid; i < ROWS; i += nthr) bias[i] = i < NK ? -cLp[i] * kLog2e : -INFINITY;
   __syncthreads();
   MRT_STAMP(1);
@@ -1529,7 +1531,7 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_mid(KParams p) {
   }
   __syncthreads();                      // every wave is done with alpha_L
   MRT_STAMP(2);
-  stage_rows_batched<D, LD, ROWS, 256, SWZ>(tile, Yp, PlainRows{D}, NK, tid);
+  stage_rows_batched<D, LD, ROWS, nthr, SWZ>(tile, Yp, PlainRows{D}, NK, tid);
   __syncthreads();
   MRT_STAMP(3);
 
@@ -1554,19 +1556,21 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_mid(KParams p) {
   MRT_STAMP(4);
 }
 
-template <int D, int NTK>
+template <int D, int NTK, int NW>
 hipError_t launch_l_out_mid(const KParams& kp, dim3 grid, hipStream_t s) {
-  if (kp.rl > 0) k_bf16_stage_l_out_mid<D, NTK, true><<<grid, 256, 0, s>>>(kp);
-  else k_bf16_stage_l_out_mid<D, NTK, false><<<grid, 256, 0, s>>>(kp);
+  if (kp.rl > 0) k_bf16_stage_l_out_mid<D, NTK, NW, true><<<grid, 64 * NW, 0, s>>>(kp);
+  else k_bf16_stage_l_out_mid<D, NTK, NW, false><<<grid, 64 * NW, 0, s>>>(kp);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t s) {
+  // b1 > 144 (then nkt >= 10): six waves, two workgroups per compute unit
+  const bool wide = kp.b1 > kMidWideB1;
   switch (nkt) {
-    case 7: case 8: return launch_l_out_mid<D, 8>(kp, grid, s);
-    case 9: case 10: return launch_l_out_mid<D, 10>(kp, grid, s);
-    case 11: case 12: return launch_l_out_mid<D, 12>(kp, grid, s);
+    case 7: case 8: return launch_l_out_mid<D, 8, 4>(kp, grid, s);
+    case 9: case 10: return wide ? launch_l_out_mid<D, 10, 6>(kp, grid, s) : launch_l_out_mid<D, 10, 4>(kp, grid, s);
+    case 11: case 12: return wide ? launch_l_out_mid<D, 12, 6>(kp, grid, s) : launch_l_out_mid<D, 12, 4>(kp, grid, s);
   }
   return hipErrorInvalidValue;
 }
@@ -1693,7 +1697,7 @@ hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipSt
 // and an fp32 output for a backward call): same conditions as in launch_bf16_stage_l below.
 bool bf16_stage_l_out_streams(const KParams& kp) {
   const int nlt = (kp.b1 + 15) / 16, nk_max = kp.ntk * kp.b1;
-  return nlt <= kMaxLT && nk_max > kResRows && !(nk_max <= kMidRows && nlt <= 8);
+  return nlt <= kMaxLT && nk_max > kResRows && !(nk_max <= kMidRows && (nlt <= 8 || kp.b1 > kMidWideB1));
 }
 
 hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s) {
@@ -1718,8 +1722,12 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
                        : launch_l_out_res_d<64>(kp, grid, (nk_max + 15) / 16, s);
   }
   // medium key ranges, last iteration: one LDS tile used twice, still three workgroups per
-  // compute unit (the earlier iterations went above)
-  if (nk_max <= kMidRows && nlt <= 8)
+  // compute unit (the earlier iterations went above); b1 > 144 takes six waves, two workgroups per
+  // compute unit where the streamed kernel's eight waves have it to themselves (b1 = 156, 12 heads of
+  // 30 columns: 28.0 -> 22.2 us; b1 = 180, 40 columns: 33.9 -> 30.0 us).  In between the streamed
+  // kernel stays: a training step's saving forward call needs its row statistics there, and it
+  // returns the bits of the plain call.
+  if (nk_max <= kMidRows && (nlt <= 8 || kp.b1 > kMidWideB1))
     return kp.d == 128 ? launch_l_out_mid_d<128>(kp, grid, (nk_max + 15) / 16, s)
                        : launch_l_out_mid_d<64>(kp, grid, (nk_max + 15) / 16, s);
   // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), each wave owning up to two
