@@ -138,12 +138,14 @@ __device__ inline void rows_dot(const u16* rows, const bf16x8 (&qv)[D / 32], f32
   }
 }
 
-// The same with the LDS reads of the next pair of row tiles issued ahead of the current pair's
-// MFMAs (two sets of operand registers).  For kernels that run one wave per SIMD: there nothing else
-// hides the latency of an LDS read, and the compiler's own schedule waits for every read right
-// before the MFMA that uses it.
-template <int D, int NTK, int LD>
-__device__ inline void rows_dot_ahead(const u16* rows, const bf16x8 (&qv)[D / 32], f32x4 (&out)[NTK], int lane) {
+// NQ operands against the same row tiles, added to what `out` holds: every LDS read serves them all.
+// AHEAD: the LDS reads of the next pair of row tiles are issued ahead of the current pair's MFMAs (two
+// sets of operand registers), for kernels that run one wave per SIMD: there nothing else hides the
+// latency of an LDS read, and the compiler's own schedule waits for every read right before the MFMA
+// that uses it.
+template <int D, int NTK, int LD, int NQ, bool AHEAD>
+__device__ inline void rows_dot_add(const u16* rows, const bf16x8 (*const (&qv)[NQ])[D / 32], f32x4 (*const (&out)[NQ])[NTK],
+                                    int lane) {
   constexpr int KS1 = D / 32, NP = (NTK + 1) / 2;
   const int g = lane >> 4, c = lane & 15;
   bf16x8 a[2][2][KS1];
@@ -155,20 +157,30 @@ __device__ inline void rows_dot_ahead(const u16* rows, const bf16x8 (&qv)[D / 32
         for (int ks = 0; ks < KS1; ++ks) dst[t][ks] = ld_lds_16B(rows + (16 * (2 * kp + t) + c) * LD + 32 * ks + 8 * g);
       }
   };
-#pragma unroll
-  for (int kt = 0; kt < NTK; ++kt) out[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  fetch(0, a[0]);
+  if (AHEAD) fetch(0, a[0]);
 #pragma unroll
   for (int kp = 0; kp < NP; ++kp) {
-    if (kp + 1 < NP) fetch(kp + 1, a[(kp + 1) & 1]);
-    __builtin_amdgcn_sched_barrier(0);
+    if (!AHEAD) fetch(kp, a[kp & 1]);
+    else if (kp + 1 < NP) fetch(kp + 1, a[(kp + 1) & 1]);
+    if (AHEAD) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KS1; ++ks)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
-        if (2 * kp + t < NTK) out[2 * kp + t] = mfma(a[kp & 1][t][ks], qv[ks], out[2 * kp + t]);
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+          if (2 * kp + t < NTK) (*out[n])[2 * kp + t] = mfma(a[kp & 1][t][ks], (*qv[n])[ks], (*out[n])[2 * kp + t]);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// Matrix operand from a row-major LDS tile X[j][i]: lane (g, c) receives column i0 + c of the rows
+// j = 16 (e / 4) + 4 g + e % 4, e = 0 .. 7 (the slots of pv_step).
+template <int PITCH>
+__device__ inline bf16x8 ld_columns(const u16* tile, int i0, int lane) {
+  const int g = lane >> 4, s = lane & 15;
+  const u16* at = tile + (4 * g + (s >> 2)) * PITCH + i0 + 4 * (s & 3);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(ld_lds_tr(at), ld_lds_tr(at + 16 * PITCH), 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // Second-product step with the contraction slots in natural order (slot (g, e) <-> row 8g + e of
@@ -1161,7 +1173,8 @@ __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams
 // stage R backward.  Work item = one key block (batch*head, n, k); for each the workgroup (NT waves)
 // loops over the query tiles m that see it.  Wave w owns query columns j = 16w + c for the softmax
 // side (as the forward stage R) and key rows i = 16w + c for the dK / dV accumulation, whose
-// contraction runs over j: R and scale dS pass through LDS transposed ([i][j], bf16) in between.
+// contraction runs over j: R and scale dS pass through LDS ([j][i], bf16: eight-byte writes of a lane's
+// four rows i) and come back as columns through the transposed read.
 //
 // The grid is persistent: workgroup g takes items g, g + gridDim.x, ...  The global loads of the
 // next step (the next query tile, or the next item's K / V and first tile) are issued as soon as
@@ -1177,25 +1190,38 @@ __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams
 // it overlaps the arithmetic.  Both kinds of waves run the same step sequence and meet at the
 // same three barriers per step.
 // ---------------------------------------------------------------------------------------
+// What bounds it is the latency of a step's sections, one after the other on the only wave of a SIMD
+// (a step of the 480p clip: 5.7 us, 0.75 us of it matrix time, 3.6 us memory time at the copy rate), so
+// the sections are kept short: K's tile is read once for both of its products, R is the kept
+// exponential times 1 / sum, R and scale dS leave as eight-byte pieces (instead of 32 two-byte writes
+// per lane), and the LDS rows are conflict-free.  480p clip, t = T: 685 -> 587 us; 480p chunk: 42.0 ->
+// 38.5 us (t = T) and 42.7 -> 40.5 us.
+//
 // Five and six waves (64 < b2 <= 96) always run with loader waves, three and two of them (eight
 // waves in all: a third wave on a SIMD would leave 168 registers each); at t = T and head_dim 128 their five tiles and two transposed
-// arrays exceed LDS, so scale dS^T takes the place of the V tile once V's logit products are done
+// arrays exceed LDS, so scale dS takes the place of the V tile once V's logit products are done
 // (one more barrier per step; the loader waves write V again every step).
+// Row padding of this kernel's LDS tiles: rows of 288 (or 160) bytes, free of bank conflicts for the
+// 16-byte operand reads (4 clocks of the CU's LDS per wave instruction against 6 with rows of 272) and
+// the transposed reads of rows 4g + e (4.0 against 6.4).  One and two waves keep the smaller rows,
+// which let a fifth workgroup onto the compute unit.
+template <int NT> constexpr int kRPad = NT <= 2 ? 8 : 16;
 template <int NT> constexpr int kLoaderThreads = NT == 5 ? 192 : NT == 6 ? 128 : 64 * NT;
 template <int NT, int D, bool LAST, typename TW, bool LW = false>
 __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (LAST ? 1 : 2)) void k_bwdm_r(BwdParams bp, int first, int nitems) {
   const KParams& p = bp.k;
-  constexpr int LD = D + kBPad, KS1 = D / 32, NVT = D / 16, KS2 = (NT + 1) / 2, ROWS = 32 * KS2;
-  constexpr int LR = ROWS + 8, NTHR = 64 * NT, LTHR = LW ? kLoaderThreads<NT> : NTHR;
+  constexpr int LD = D + kRPad<NT>, KS1 = D / 32, NVT = D / 16, KS2 = (NT + 1) / 2, ROWS = 32 * KS2;
+  constexpr int LR = ROWS + kRPad<NT>, NTHR = 64 * NT, LTHR = LW ? kLoaderThreads<NT> : NTHR;
   constexpr bool kAlias = LAST && NT >= 5 && D == 128;
-  static_assert(!kAlias || (LW && ROWS * LR <= ROWS * LD), "scale dS^T in the V tile");
+  static_assert(!kAlias || (LW && ROWS <= LD), "scale dS in the V tile");
+  constexpr int LS = kAlias ? LD : LR;          // row pitch of the scale dS tile
   __shared__ __attribute__((aligned(16))) u16 Ks[ROWS * LD];              // K[n, k, i, :]
   __shared__ __attribute__((aligned(16))) u16 Vs[LAST ? ROWS * LD : 8];   // V[n, k, i, :]
   __shared__ __attribute__((aligned(16))) u16 As[ROWS * LD];              // abar[m, n, k, j, :]
   __shared__ __attribute__((aligned(16))) u16 Gs[ROWS * LD];              // d alpha_L[m, n, j, k, :]
   __shared__ __attribute__((aligned(16))) u16 Ys[LAST ? ROWS * LD : 8];   // d Y[m, n, j, k, :]
   __shared__ __attribute__((aligned(16))) u16 RT[ROWS * LR];              // R[j, i] as [i][j]
-  __shared__ __attribute__((aligned(16))) u16 ST_own[kAlias ? 8 : ROWS * LR];   // scale dS[j, i] as [i][j]
+  __shared__ __attribute__((aligned(16))) u16 ST_own[kAlias ? 8 : ROWS * LR];   // scale dS[j][i]
   u16* ST = kAlias ? Vs : ST_own;
   __shared__ float dcls[LW ? ROWS : 1];                                   // d c_L of the step's columns (LW)
 
@@ -1437,30 +1463,13 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
           if (LAST) yv[ks] = ld_lds_16B(Ys + j * LD + 32 * ks + 8 * g);
         }
         f32x4 s[NT], dr[NT];
+#pragma unroll
+        for (int it = 0; it < NT; ++it) s[it] = dr[it] = f32x4{0.f, 0.f, 0.f, 0.f};
         // (t = T: one workgroup per compute unit, one wave per SIMD: LDS reads issued ahead)
         constexpr bool kAhead = LAST && NT <= 4;       // (beyond four waves the registers are needed elsewhere)
-        if constexpr (kAhead) rows_dot_ahead<D, NT, LD>(Ks, qv, s, lane);
-        else rows_dot<D, NT, LD>(Ks, qv, s, lane);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kAhead) rows_dot_ahead<D, NT, LD>(Ks, gv, dr, lane);
-        else rows_dot<D, NT, LD>(Ks, gv, dr, lane);
-        __builtin_amdgcn_sched_barrier(0);
-        if (LAST) {
-          f32x4 dy[NT];
-          if constexpr (kAhead) rows_dot_ahead<D, NT, LD>(Vs, yv, dy, lane);
-          else rows_dot<D, NT, LD>(Vs, yv, dy, lane);
-#pragma unroll
-          for (int it = 0; it < NT; ++it) dr[it] += dy[it];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (kAlias) {
-          __syncthreads();                     // every wave is done with V: its tile now takes scale dS^T
-          // columns 16 NT .. ROWS - 1 of the rows this wave writes are read as zeros below
-          if constexpr (ROWS > 16 * NT) {
-            for (int idx = lane; idx < 16 * (ROWS - 16 * NT); idx += 64)
-              ST[(16 * wave + idx / (ROWS - 16 * NT)) * LR + 16 * NT + idx % (ROWS - 16 * NT)] = 0;
-          }
-        }
+        rows_dot_add<D, NT, LD, 2, kAhead>(Ks, {&qv, &gv}, {&s, &dr}, lane);
+        if (LAST) rows_dot_add<D, NT, LD, 1, kAhead>(Vs, {&yv}, {&dr}, lane);
+        if constexpr (kAlias) __syncthreads();   // every wave is done with V: its tile now takes scale dS
         float mx = -INFINITY;
 #pragma unroll
         for (int it = 0; it < NT; ++it)
@@ -1472,11 +1481,17 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
           }
         mx = xmax(mx);
         float sum = 0.f;
+        f32x4 ex[NT];                                  // 2^(logit - maximum): R times the sum
 #pragma unroll
         for (int it = 0; it < NT; ++it)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) sum += exp2_fast(s[it][r] - mx);
-        const float lse2 = mx + log2_fast(xsum(sum));
+          for (int r = 0; r < 4; ++r) {
+            s[it][r] -= mx;
+            ex[it][r] = exp2_fast(s[it][r]);
+            sum += ex[it][r];
+          }
+        sum = xsum(sum);
+        const float inv = live ? 1.0f / sum : 0.f, lsum = log2_fast(sum);
         // R, dR (with the entropy term), dS
         float dot = 0.f;
 #pragma unroll
@@ -1484,24 +1499,21 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const bool ok = live && 16 * it + 4 * g + r < b2;
-            const float logr2 = s[it][r] - lse2;                     // log2 R, -inf beyond b2
-            const float R = ok ? exp2_fast(logr2) : 0.f;
-            const float dR = ok ? dr[it][r] + dcl * fmaf(logr2, kLn2, 1.0f) : 0.f;
-            s[it][r] = R;
+            const float R = ex[it][r] * inv;                         // 0 beyond b2
+            const float dR = ok ? dr[it][r] + dcl * fmaf(s[it][r] - lsum, kLn2, 1.0f) : 0.f;
+            ex[it][r] = R;
             dr[it][r] = dR;
             dot = fmaf(R, dR, dot);
           }
         dot = xsum(dot);
 #pragma unroll
-        for (int it = 0; it < NT; ++it)
+        for (int it = 0; it < NT; ++it) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float ds = p.scale * s[it][r] * (dr[it][r] - dot);   // scale dS
-            dr[it][r] = ds;
-            const int i = 16 * it + 4 * g + r;
-            RT[i * LR + j] = f2bf(s[it][r]);
-            ST[i * LR + j] = f2bf(ds);
-          }
+          for (int r = 0; r < 4; ++r) dr[it][r] = p.scale * ex[it][r] * (dr[it][r] - dot);   // scale dS
+          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+          *(bf16x4*)(RT + j * LR + 16 * it + 4 * g) = bf16x4{(__bf16)ex[it][0], (__bf16)ex[it][1], (__bf16)ex[it][2], (__bf16)ex[it][3]};
+          *(bf16x4*)(ST + j * LS + 16 * it + 4 * g) = bf16x4{(__bf16)dr[it][0], (__bf16)dr[it][1], (__bf16)dr[it][2], (__bf16)dr[it][3]};
+        }
         // d abar[j] = sum_i (scale dS[j, i]) K[i]
         f32x4 o[NVT];
 #pragma unroll
@@ -1534,14 +1546,14 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
       // ---- accumulation side: lanes own key row i = j
 #pragma unroll
       for (int st = 0; st < KS2; ++st) {
-        const bf16x8 bR[1] = {ld_lds_16B(RT + j * LR + 32 * st + 8 * g)};
-        const bf16x8 bS[1] = {ld_lds_16B(ST + j * LR + 32 * st + 8 * g)};
-        pv_step_nat<D, 1, LD>(Gs + 32 * st * LD, bR, 1, oK, lane);     // dK += R^T d alpha_L
+        const bf16x8 bR = ld_columns<LR>(RT + 32 * st * LR, 16 * wave, lane);
+        const bf16x8 bS = ld_columns<LS>(ST + 32 * st * LS, 16 * wave, lane);
+        pv_step<D, LD>(Gs + 32 * st * LD, bR, oK[0], lane);     // dK += R^T d alpha_L
         __builtin_amdgcn_sched_barrier(0);
-        pv_step_nat<D, 1, LD>(As + 32 * st * LD, bS, 1, oK, lane);     // dK += scale dS^T abar
+        pv_step<D, LD>(As + 32 * st * LD, bS, oK[0], lane);     // dK += scale dS^T abar
         __builtin_amdgcn_sched_barrier(0);
         if (LAST) {
-          pv_step_nat<D, 1, LD>(Ys + 32 * st * LD, bR, 1, oV, lane);   // dV += R^T d Y
+          pv_step<D, LD>(Ys + 32 * st * LD, bR, oV[0], lane);   // dV += R^T d Y
           __builtin_amdgcn_sched_barrier(0);
         }
       }
