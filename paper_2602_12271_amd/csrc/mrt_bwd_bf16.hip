@@ -732,7 +732,11 @@ template <int D, bool LAST, int NQT, int KSPLIT>
 __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdParams bp, u16* Pw, u16* Zw) {
   const KParams& p = bp.k;
   constexpr int NW = NQT * KSPLIT;
-  constexpr int LD = D + kBPad, KS1 = D / 32, NVT = D / 16, NTK = kSegTiles / KSPLIT, KS2 = NTK / 2;
+  // Row padding: rows of 288 bytes are free of LDS bank conflicts (see kRPad); ten query tiles leave no
+  // room for them.  With them and dZ / L passed to the column side in eight-byte pieces instead of
+  // sixteen two-byte writes per lane and step, the training step of the 480p clip went 1927 -> 1804 us:
+  // a step is bounded by its serial sections and barriers, not by memory.
+  constexpr int LD = D + (NQT <= 6 ? 16 : kBPad), KS1 = D / 32, NVT = D / 16, NTK = kSegTiles / KSPLIT, KS2 = NTK / 2;
   constexpr int NTHR = 64 * NW, CPR = D / 8, TOTAL = kSeg * CPR;
   constexpr int LP = NQT <= 6 ? kLP : kLPWide;
   static_assert(NTK % 2 == 0 && 4 * kSeg * LD * 2 >= (KSPLIT - 1) * NQT * NVT * 64 * 16, "LDS reuse");
@@ -747,13 +751,14 @@ __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdPa
   // here, from the segment's dZ (and L) left transposed in LDS instead of in global scratch
   // (ten query tiles: only at t < T, where one transposed array and the Q tile fit beside the ring)
   constexpr bool kFuse = (KSPLIT == 2 && NQT == 6) || (NQT == 10 && KSPLIT == 1 && !LAST);
-  constexpr int QROWS = 16 * NQT, LPZ = QROWS + 8, KSC = NQT / 2;
+  constexpr int QROWS = 16 * NQT, LPZ = kSeg + (NQT > 6 ? 4 : LAST ? 8 : 16), KSC = NQT / 2;
   __shared__ __attribute__((aligned(16))) u16 Qs[kFuse ? QROWS * LD : 8];             // Q[m, :, j, :]
   __shared__ __attribute__((aligned(16))) u16 dOs[kFuse && LAST ? QROWS * LD : 8];    // dO[m, :, j, :]
-  // dZ as [nk][l] of a segment: two buffers at t < T (the column side of a step then runs beside the
-  // next step's row side), one at t = T, where L needs one too
-  __shared__ __attribute__((aligned(16))) u16 Zs[kFuse ? (LAST ? 1 : 2) * kSeg * LPZ : 8];
-  __shared__ __attribute__((aligned(16))) u16 Ws[kFuse && LAST ? kSeg * LPZ : 8];
+  // dZ as [l][nk] of a segment (a lane's four keys are one eight-byte write; the column side reads its
+  // operands transposed): two buffers at t < T (the column side of a step then runs beside the next
+  // step's row side), one at t = T, where L needs one too
+  __shared__ __attribute__((aligned(16))) u16 Zs[kFuse ? (LAST ? 1 : 2) * QROWS * LPZ : 8];
+  __shared__ __attribute__((aligned(16))) u16 Ws[kFuse && LAST ? QROWS * LPZ : 8];
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
@@ -996,11 +1001,14 @@ __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdPa
           const float dz = w * (dl[kt][r] - tc[r]) - L * delta;
           wq[kt][r] = w;
           dl[kt][r] = dz;
-          if constexpr (kFuse) {
-            const int at = (koff + 16 * kt + 4 * g + r) * LPZ + l;
-            Zs[(LAST ? 0 : (sg & 1) * kSeg * LPZ) + at] = f2bf(dz);
-            if (LAST) Ws[at] = f2bf(w);
-          }
+        }
+        if constexpr (kFuse) {
+          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+          const int at = l * LPZ + koff + 16 * kt + 4 * g;
+          *(bf16x4*)(Zs + (LAST ? 0 : (sg & 1) * QROWS * LPZ) + at) =
+              bf16x4{(__bf16)dl[kt][0], (__bf16)dl[kt][1], (__bf16)dl[kt][2], (__bf16)dl[kt][3]};
+          if (LAST)
+            *(bf16x4*)(Ws + at) = bf16x4{(__bf16)wq[kt][0], (__bf16)wq[kt][1], (__bf16)wq[kt][2], (__bf16)wq[kt][3]};
         }
         if constexpr (!kFuse) {
           if (LAST) store_tile_transposed(Pt, LP, k0 + 16 * kt, NK, 16 * lt, wq[kt], c, g);   // only dY is formed from it
@@ -1031,30 +1039,29 @@ __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdPa
         if (duty < (LAST ? 8 : 4)) {
           const bool second = duty >= 4;                 // dY
           const int t = duty & 3, nk = kSeg * sg + 16 * t + c;
-          const u16* src = (second ? Ws : Zs + (LAST ? 0 : (sg & 1) * kSeg * LPZ)) + (16 * t + c) * LPZ;
+          const u16* src = second ? Ws : Zs + (LAST ? 0 : (sg & 1) * QROWS * LPZ);
           bf16x8 zb[KSC];
           float zsum = 0.f;
 #pragma unroll
           for (int st = 0; st < KSC; ++st) {
-            zb[st] = ld_lds_16B(src + 32 * st + 8 * g);
+            zb[st] = ld_columns<LPZ>(src + 32 * st * LPZ, 16 * t, lane);
 #pragma unroll
             for (int e = 0; e < 8; ++e) zsum += (float)zb[st][e];
           }
           zsum = xsum(zsum);
           if (!second && g == 0 && nk < NK) bp.dcL[row0 + nk] = -zsum;
-          f32x4 oc[1][NVT];
+          f32x4 oc[NVT];
 #pragma unroll
-          for (int vt = 0; vt < NVT; ++vt) oc[0][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int vt = 0; vt < NVT; ++vt) oc[vt] = f32x4{0.f, 0.f, 0.f, 0.f};
           const u16* tile = second ? dOs : Qs;
 #pragma unroll
           for (int st = 0; st < KSC; ++st) {
-            const bf16x8 one[1] = {zb[st]};
-            pv_step_nat<D, 1, LD>(tile + 32 * st * LD, one, 1, oc, lane);
+            pv_step<D, LD>(tile + 32 * st * LD, zb[st], oc, lane);
             __builtin_amdgcn_sched_barrier(0);
           }
           if (nk < NK) {
-            if (second) store_ws_row<D>((u16*)bp.dY + (row0 + nk) * d, oc[0], 1.0f, g);
-            else store_ws_row<D>((u16*)bp.daL + (row0 + nk) * d, oc[0], p.scale, g);
+            if (second) store_ws_row<D>((u16*)bp.dY + (row0 + nk) * d, oc, 1.0f, g);
+            else store_ws_row<D>((u16*)bp.daL + (row0 + nk) * d, oc, p.scale, g);
           }
         }
         if (LAST) __syncthreads();        // one buffer: the next step's row side writes it again
