@@ -184,6 +184,40 @@ def _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, 
                         assign=assign, tile_h=tile_h, head_groups=head_groups)
 
 
+# Problem descriptors of recent calls, by the VALUES they are built from (shapes, strides, types and
+# arguments, never a tensor's identity): a decoding loop describes the same problem on every call, and
+# building and checking the descriptor took 5 of the 10 microseconds a small call spent in Python.
+# Read-only once built; bounded.
+_problems: dict = {}
+_MAX_PROBLEMS = 256
+
+
+def _call_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign="fh_w", tile_h=0,
+                  head_groups=0):
+    if not (type(f_q) is type(f_kv) is type(h) is type(w) is type(q_frame_offset) is type(compute) is type(tile_h)
+            is type(head_groups) is int and type(scale) is float and type(assign) is str):   # (others: no key to trust)
+        return _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h, head_groups)
+    key = (Q.shape, Q.stride(), Q.dtype, Q.is_cuda, K.shape, K.stride(), K.dtype, K.is_cuda,
+           V.shape, V.stride(), V.dtype, V.is_cuda, O.shape, O.stride(), O.dtype, O.is_cuda,
+           f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h, head_groups)
+    prob = _problems.get(key)
+    if prob is None:
+        prob = _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h, head_groups)
+        if len(_problems) >= _MAX_PROBLEMS:
+            _problems.clear()
+        _problems[key] = prob
+    return prob
+
+
+def _stream_of(Q, stream):
+    """The stream the call runs on: the caller's, or the current one of Q's device."""
+    if stream is not None:
+        return stream
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # 0.06 us; the public way takes 1.9
+    return raw(Q.get_device()) if raw is not None else torch.cuda.current_stream(Q.device).cuda_stream
+
+
 def monarch_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, b1, b2, tile, iters, causal_chunk=0,
                      q_frame_offset=0, scale=1.0, compute=MRT_COMPUTE_DEFAULT, out=None,
                      workspace=None, stream=None, assign="fh_w", tile_h=0, head_groups=0):
@@ -191,14 +225,14 @@ def monarch_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, b1, b2, tile, iters, causal_ch
     import torch
     lib = load_library()
     O = torch.empty_like(Q) if out is None else out
-    prob = _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h,
-                          head_groups)
+    prob = _call_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h,
+                         head_groups)
     if workspace is None:
         nbytes = lib.monarch_attn_workspace_bytes(ctypes.byref(prob), b1, b2, tile, iters)
         if nbytes == 0:
             _raise(lib, lib.monarch_attn_check(ctypes.byref(prob), b1, b2, tile, iters, causal_chunk))
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=Q.device)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    s = _stream_of(Q, stream)
     st = lib.monarch_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                               ctypes.byref(prob), b1, b2, tile, iters, causal_chunk,
                               workspace.data_ptr(), workspace.numel() * workspace.element_size(), s)
@@ -214,8 +248,8 @@ def monarch_attn_fwd_noalloc(Q, K, V, out, *, f_q, f_kv, h, w, b1, b2, tile, ite
     output tensor must be passed in."""
     import torch
     lib = load_library()
-    prob = _torch_problem(Q, K, V, out, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    prob = _call_problem(Q, K, V, out, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
+    s = _stream_of(Q, stream)
     st = lib.monarch_attn_fwd_noalloc(Q.data_ptr(), K.data_ptr(), V.data_ptr(), out.data_ptr(),
                                       ctypes.byref(prob), b1, b2, tile, iters, causal_chunk, s)
     if st != MRT_OK:
@@ -232,7 +266,7 @@ def monarch_attn_bwd(Q, K, V, dO, *, f_q, f_kv, h, w, b1, b2, tile, iters, causa
     import torch
     lib = load_library()
     assert dO.shape == Q.shape and dO.dtype == Q.dtype and dO.is_cuda
-    prob = _torch_problem(Q, K, V, dO, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
+    prob = _call_problem(Q, K, V, dO, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
     if workspace is None:
         nbytes = lib.monarch_attn_bwd_workspace_bytes(ctypes.byref(prob), b1, b2, tile, iters)
         if nbytes == 0:
@@ -242,7 +276,7 @@ def monarch_attn_bwd(Q, K, V, dO, *, f_q, f_kv, h, w, b1, b2, tile, iters, causa
     dQ = torch.empty(Q.shape, dtype=torch.float32, device=Q.device)
     dK = torch.empty(K.shape, dtype=torch.float32, device=Q.device)
     dV = torch.empty(V.shape, dtype=torch.float32, device=Q.device)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    s = _stream_of(Q, stream)
     st = lib.monarch_attn_bwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), dO.data_ptr(), dQ.data_ptr(),
                               dK.data_ptr(), dV.data_ptr(), ctypes.byref(prob), b1, b2, tile, iters,
                               causal_chunk, workspace.data_ptr(),
@@ -260,14 +294,14 @@ def monarch_attn_fwd_save(Q, K, V, *, f_q, f_kv, h, w, b1, b2, tile, iters, caus
     import torch
     lib = load_library()
     O = torch.empty_like(Q) if out is None else out
-    prob = _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
+    prob = _call_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
     if workspace is None:
         nbytes = lib.monarch_attn_bwd_saved_workspace_bytes(ctypes.byref(prob), b1, b2, tile, iters)
         if nbytes == 0:
             st = lib.monarch_attn_check(ctypes.byref(prob), b1, b2, tile, iters, causal_chunk)
             _raise(lib, st if st != MRT_OK else MRT_ERR_UNSUPPORTED)
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=Q.device)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    s = _stream_of(Q, stream)
     st = lib.monarch_attn_fwd_save(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), ctypes.byref(prob),
                                    b1, b2, tile, iters, causal_chunk, workspace.data_ptr(),
                                    workspace.numel() * workspace.element_size(), s)
@@ -284,11 +318,11 @@ def monarch_attn_bwd_saved(Q, K, V, dO, workspace, *, f_q, f_kv, h, w, b1, b2, t
     import torch
     lib = load_library()
     assert dO.shape == Q.shape and dO.dtype == Q.dtype and dO.is_cuda
-    prob = _torch_problem(Q, K, V, dO, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
+    prob = _call_problem(Q, K, V, dO, f_q, f_kv, h, w, q_frame_offset, scale, compute, assign, tile_h)
     dQ = torch.empty(Q.shape, dtype=torch.float32, device=Q.device)
     dK = torch.empty(K.shape, dtype=torch.float32, device=Q.device)
     dV = torch.empty(V.shape, dtype=torch.float32, device=Q.device)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    s = _stream_of(Q, stream)
     st = lib.monarch_attn_bwd_saved(Q.data_ptr(), K.data_ptr(), V.data_ptr(), dO.data_ptr(), dQ.data_ptr(),
                                     dK.data_ptr(), dV.data_ptr(), ctypes.byref(prob), b1, b2, tile, iters,
                                     causal_chunk, workspace.data_ptr(),
@@ -304,8 +338,8 @@ def dense_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, causal_chunk=0, q_frame_offset=0
     import torch
     lib = load_library()
     O = torch.empty_like(Q) if out is None else out
-    prob = _torch_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute)
-    s = torch.cuda.current_stream(Q.device).cuda_stream if stream is None else stream
+    prob = _call_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute)
+    s = _stream_of(Q, stream)
     st = lib.dense_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                             ctypes.byref(prob), causal_chunk, s)
     if st != MRT_OK:
