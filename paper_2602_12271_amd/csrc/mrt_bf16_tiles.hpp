@@ -103,13 +103,13 @@ __device__ inline float row8_sum(float x) {
 }
 
 // Swizzled LDS tiles (SWZ = true; rows of 128 bf16 = 256 bytes = all 64 banks, NOT padded): the
-// 16-byte piece p of row r sits at piece index p ^ swz16(r), swz16(r) = 4 (r mod 4) ^ (r / 4 mod 4).
-// Both ways a tile is read are then free of bank conflicts: a matrix operand read of one piece
-// column from 8 consecutive rows (ds_read_b128: 8 lanes per clock; swz16 takes 8 different values
-// on rows 8a .. 8a + 7) and a transposed read (ds_read_b64_tr_b16: 16 lanes per clock on rows
-// 4g .. 4g + 3, four pieces q + 4k each: (q + 4k) ^ swz16 = (q ^ g) + 4 (k ^ e) covers all 16
-// pieces).  With padded rows one of the two always conflicts (two- to four-fold).
-__device__ inline int swz16(int row) { return ((row & 3) << 2) ^ ((row >> 2) & 3); }
+// 16-byte piece p of row r sits at piece index p ^ swz16(r), i.e. its 32-byte pair of pieces at pair
+// index (p / 2) ^ (r mod 8).  Eight consecutive rows then hold one pair column in eight different
+// places: a matrix operand read of a piece column (ds_read_b128) takes 4.0 clocks of the CU's LDS per
+// wave instruction, the rate of a linear read (an XOR of single pieces, 4 (r mod 4) ^ (r / 4 mod 4),
+// took 6.0), and a transposed read (ds_read_b64_tr_b16) 4.0 as before.  480p chunk as (156,30) 71.3 ->
+// 70.5 us, tiles (90,26) 73.3 -> 72.5 us.
+__device__ inline int swz16(int row) { return (row & 7) << 1; }
 template <int LD, bool SWZ>
 __device__ inline int tile_off(int row, int piece) {
   return row * LD + 8 * (SWZ ? piece ^ swz16(row) : piece);
