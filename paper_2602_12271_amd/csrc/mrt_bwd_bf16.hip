@@ -274,10 +274,12 @@ __device__ inline void store_tile_transposed(u16* arr, int pitch, int nk0, int N
 // ---------------------------------------------------------------------------------------
 // TW: storage type of the forward intermediates alpha_L, Y and abar in the workspace (fp32 when
 // the fp32 kernels recomputed them, bf16 when the bf16 forward kernels did).
-template <int D, int NTK, bool LAST, typename TW>
-__global__ __launch_bounds__(256, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u16* Zw) {
+// NW waves; six (one query tile each instead of two on half of four waves) where every workgroup is
+// resident at once and its own latency is the launch.
+template <int D, int NTK, bool LAST, typename TW, int NW>
+__global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u16* Zw) {
   const KParams& p = bp.k;
-  constexpr int LD = D + kBPad, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
+  constexpr int NTHR = 64 * NW, LD = D + kBPad, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
   __shared__ __attribute__((aligned(16))) u16 Ks[ROWS * LD];    // alpha_L rows
   __shared__ __attribute__((aligned(16))) u16 Vs[ROWS * LD];    // Y rows (LAST) or d abar rows
   __shared__ __attribute__((aligned(16))) float bias[ROWS];     // -c_L log2(e), -inf beyond NK
@@ -306,16 +308,16 @@ __global__ __launch_bounds__(256, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u
   const u16* dOp = (const u16*)bp.dO + b * p.os.batch + hd * p.os.head + qcol * p.os.token;
   const TokRows qrow = tile_rows(p, a, p.qs.token), orow = tile_rows(p, a, p.os.token);
 
-  stage_ws<D, LD, ROWS, 256>(Ks, aLp, PlainRows{D}, NK, tid);
+  stage_ws<D, LD, ROWS, NTHR>(Ks, aLp, PlainRows{D}, NK, tid);
   if (LAST) {
-    stage_ws<D, LD, ROWS, 256>(Vs, Yp, PlainRows{D}, NK, tid);
+    stage_ws<D, LD, ROWS, NTHR>(Vs, Yp, PlainRows{D}, NK, tid);
   } else {
     // d abar rows (fp32) into LDS as bf16; d abar . abar is formed on the way: the D/8 consecutive
     // lanes that share a row hold 8 features each
-    constexpr int CPR = D / 8, TOTAL = ROWS * CPR, NI = (TOTAL + 255) / 256;
+    constexpr int CPR = D / 8, TOTAL = ROWS * CPR, NI = (TOTAL + NTHR - 1) / NTHR;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int idx = tid + i * 256;
+      const int idx = tid + i * NTHR;
       const bool in = idx < TOTAL;
       const int r = (in ? idx : TOTAL - 1) / CPR, ch = idx % CPR;
       const bool ok = in && r < NK;
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(256, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u
       }
     }
   }
-  for (int i = tid; i < ROWS; i += 256) {
+  for (int i = tid; i < ROWS; i += NTHR) {
     bias[i] = i < NK ? -cLp[i] * kLog2e : -INFINITY;
     if (!LAST) {
       const size_t at = arow0 + (size_t)(i < NK ? i : 0) * b2 + j;
@@ -351,7 +353,7 @@ __global__ __launch_bounds__(256, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u
   u16* Pt = Pw + row0 * kLP;
   u16* Zt = Zw + row0 * kLP;
   // the cols kernel reads query rows in steps of 32: an odd tile count leaves one tile of zeros
-  for (int lt = wave; lt < 2 * ((nlt + 1) / 2); lt += 4) {
+  for (int lt = wave; lt < 2 * ((nlt + 1) / 2); lt += NW) {
     const int l = 16 * lt + c;
     if (lt >= nlt) {
       for (int nk = g; nk < NK; nk += 4) {
@@ -1591,9 +1593,16 @@ size_t bwd_bf16_scratch_bytes(const KParams& kp, int ntq_total) {
 template <int D, bool LAST, typename TW>
 static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, u16* Zw, hipStream_t s) {
   switch (nkt) {
-    case 1: case 2: k_bwdm_l_rows<D, 2, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 3: case 4: k_bwdm_l_rows<D, 4, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 5: case 6: k_bwdm_l_rows<D, 6, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
+    case 1: case 2: k_bwdm_l_rows<D, 2, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
+    case 3: case 4: k_bwdm_l_rows<D, 4, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
+    case 5: case 6:
+      // two six-wave workgroups fit a compute unit, three of four waves: 3 heads of 52 columns, training
+      // step 118 -> 109 us; 12 heads (624 workgroups, a second round) 218 -> 234 us, so four waves there
+      if ((long long)grid.x * grid.y * grid.z <= 2LL * compute_units())
+        k_bwdm_l_rows<D, 6, LAST, TW, 6><<<grid, 384, 0, s>>>(bp, Pw, Zw);
+      else
+        k_bwdm_l_rows<D, 6, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
