@@ -278,8 +278,9 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
   const int lane = tid & 63, g = lane >> 4, c = lane & 15;
   Rows32<D, kChunk32, NTHR, VEC, TK> rk, rv;
   float rb = 0.f;
+  int valid = 0;                  // rows of the fetched chunk
   auto fetch = [&](int c0) {
-    const int left = nkeys - c0, valid = left < kChunk32 ? left : kChunk32;
+    valid = nkeys - c0 < kChunk32 ? nkeys - c0 : kChunk32;
     rk.load(kbase + c0 * kstride, [&](int r) { return r * kstride; }, valid, d, tid);
     if (WITH_V) rv.load(vbase + c0 * vstride, [&](int r) { return r * vstride; }, valid, d, tid);
     const int r = tid & 15;
@@ -288,7 +289,8 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
   };
   auto commit = [&](float* slot) {
     rk.store(slot, kChunk32, tid);
-    if (WITH_V) rv.store(slot + kChunk32 * LD, kChunk32, tid);
+    // value rows past the end are zeros: a copy of the last one times a weight of zero is NaN where it holds an infinity
+    if (WITH_V) rv.store(slot + kChunk32 * LD, valid, tid);
     if (tid < kChunk32) slot[kChunk32 * LD * (WITH_V ? 2 : 1) + tid] = rb;
   };
   fetch(0);
