@@ -44,6 +44,14 @@ __device__ inline f32x4 mfma4(f32x4 a, f32x4 b, f32x4 acc) {
   return acc;
 }
 
+// x y rounded to fp32.  A logit that its own maximum is subtracted from must be the number the maximum
+// was taken over: contracted with that subtraction into one fma, the product keeps bits the maximum
+// lost, and beyond 1e9 the exponent of the largest logit is not 0 but hundreds.
+__device__ inline float mul_rounded(float x, float y) {
+#pragma clang fp contract(off)
+  return x * y;
+}
+
 // ---- rows of four features -------------------------------------------------------------------
 template <typename T> struct Quad;
 template <> struct Quad<float> {
@@ -215,7 +223,7 @@ __global__ __launch_bounds__(64 * NT, 3) void k_f32_stage_r(KParams p, int first
   for (int it = 0; it < NT; ++it)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      s[it][r] = 16 * it + 4 * g + r < b2 ? p.scale * s[it][r] : -INFINITY;
+      s[it][r] = 16 * it + 4 * g + r < b2 ? mul_rounded(p.scale, s[it][r]) : -INFINITY;
       mx = fmaxf(mx, s[it][r]);
     }
   mx = xmax(mx);

@@ -3,6 +3,9 @@ import pytest
 import torch
 
 import paper_2602_12271_amd as pkg
+from workloads import synthetic as syn
+
+from gpu_harness import oracle_dense_head, oracle_monarch_head, run_dense_gpu, run_monarch_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +43,41 @@ def test_fp32_infinite_last_value_row(rows, cols, d):
     expect = torch.full_like(out, INF)
     expect[..., 1] = -INF
     assert torch.equal(out, expect)
+
+
+HUGE = {
+    "resident": dict(f_q=3, f_kv=3, h=10, b1=30, w=13, b2=13, head_dim=64, tile=0),
+    "three-frames": dict(f_q=3, f_kv=3, h=30, b1=90, w=20, b2=20, head_dim=128, tile=0),
+    "full-column-tiles": dict(f_q=1, f_kv=1, h=12, b1=12, w=32, b2=32, head_dim=128, tile=0),
+    "streamed": dict(f_q=1, f_kv=9, h=27, b1=27, w=8, b2=8, head_dim=128, tile=1),
+}
+
+
+def huge(dtype, magnitude, **kw):
+    wl = syn.Workload(name="huge", batch=1, heads=2, dtype=dtype, rope=False, scale=kw["head_dim"] ** -0.5, sigma_qk=1.0,
+                      sigma_v=1.0, causal_chunk=0, q_frame_offset=0, **kw)
+    q, k, v = syn.make_inputs(wl)
+    return wl, (q * magnitude, k * magnitude, v)
+
+
+def distance(wl, arrays, out, oracle):
+    num = den = 0.0
+    for hd in range(wl.heads):
+        ref = oracle(wl, *(x[0, hd] for x in arrays))
+        num += (out[0, hd].double().cpu() - ref).pow(2).sum().item()
+        den += ref.pow(2).sum().item()
+    return (num / den) ** 0.5
+
+
+# logits of 1e10 and 1e14: every softmax is a choice of one key (the largest two differ by parts in a
+# thousand, an fp32 logit by parts in 1e7), so the bar of ordinary values holds.  (Of two iterations
+# only that they stay finite: the reference's column sums underflow there.)
+@pytest.mark.parametrize("magnitude", [2.0 ** 15, 2.0 ** 22])
+@pytest.mark.parametrize("name", list(HUGE))
+def test_fp32_huge_logits(name, magnitude):
+    wl, arrays = huge("f32", magnitude, iters=1, **HUGE[name])
+    out = run_monarch_gpu(wl, *to_device(wl, arrays))
+    assert distance(wl, arrays, out, oracle_monarch_head) <= 5e-6
+    assert distance(wl, arrays, run_dense_gpu(wl, *to_device(wl, arrays)), oracle_dense_head) <= 5e-6
+    wl, arrays = huge("f32", magnitude, iters=2, **HUGE[name])
+    assert torch.isfinite(run_monarch_gpu(wl, *to_device(wl, arrays))).all()
