@@ -276,11 +276,14 @@ struct Online32 {
   float m = -INFINITY, l = 0.f;   // reference (same in the four lanes of a query), this lane's sum
 };
 
-// NW waves; `active`: this wave owns a query tile.  bias(key) is subtracted from the scaled logits,
-// hide(key) hides a key from the lane's query.
+// NW waves; `wkeys`: the keys from here on are hidden from every query of this wave, which leaves out the
+// chunks that start there (0: the wave owns no query).  `cut`, then every `step` keys: a chunk ends there
+// too (0: nowhere).  bias(key) is subtracted from the scaled logits, hide(key) hides a key from the
+// lane's query.
 template <int D, int NW, bool WITH_V, bool VEC, typename TK, typename Bias, typename Hide>
 __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vbase, long long vstride, int nkeys, int d,
-                               float scale, const f32x4 (&q)[D / 16], bool active, float* lds, Bias bias, Hide hide,
+                               float scale, const f32x4 (&q)[D / 16], int wkeys, int cut, int step, float* lds, Bias bias,
+                               Hide hide,
                                Online32& st, f32x4 (&o)[D / 64][4], int tid) {
   constexpr int KS = D / 16, NTHR = 64 * NW, LD = kLd<D>, SLOT = kSlot32<D, WITH_V>;
   const int lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -288,7 +291,9 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
   float rb = 0.f;
   int valid = 0;                  // rows of the fetched chunk
   auto fetch = [&](int c0) {
-    valid = nkeys - c0 < kChunk32 ? nkeys - c0 : kChunk32;
+    if (step > 0 && c0 >= cut) cut += step;
+    const int end = step > 0 && cut < nkeys ? cut : nkeys;
+    valid = end - c0 < kChunk32 ? end - c0 : kChunk32;
     rk.load(kbase + c0 * kstride, [&](int r) { return r * kstride; }, valid, d, tid);
     if (WITH_V) rv.load(vbase + c0 * vstride, [&](int r) { return r * vstride; }, valid, d, tid);
     const int r = tid & 15;
@@ -305,11 +310,11 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
   commit(lds);
   __syncthreads();
   int cur = 0;
-  for (int c0 = 0; c0 < nkeys; c0 += kChunk32, cur ^= 1) {
+  for (int c0 = 0, next; c0 < nkeys; c0 = next, cur ^= 1) {
     const float* slot = lds + cur * SLOT;
-    const int next = c0 + kChunk32 < nkeys ? c0 + kChunk32 : c0;   // past the end: the last chunk again
-    fetch(next);
-    if (active) {
+    next = c0 + valid;
+    fetch(next < nkeys ? next : c0);                               // past the end: the last chunk again
+    if (c0 < wkeys) {
       f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
       for (int ks = 0; ks < KS; ks += 2) {
@@ -400,7 +405,7 @@ __global__ __launch_bounds__(64 * NW, NW > 8 ? 3 : (NW > 2 ? 4 : 2)) void k_f32_
   zero<D>(o);
   Online32 st;
   const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
-  flash32<D, NW, true, VEC>(col.aL, d, col.Y, d, col.NK, d, p.scale, q, 16 * wave < b1, lds,
+  flash32<D, NW, true, VEC>(col.aL, d, col.Y, d, col.NK, d, p.scale, q, 16 * wave < b1 ? col.NK : 0, 0, 0, lds,
                             [&](int key) { return col.cL[key]; }, [&](int key) { return key >= lim; }, st, o, tid);
   const float lsum = xsum(st.l);
   const TokRows orow = tile_rows(p, col.a, p.os.token);
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(64 * NW, NW > 8 ? 3 : 4) void k_f32_stage_l_refine(
     stage_q32<D, VEC>(Qs, col.Q, qrow, 16 * nlt, b1, d, tid, 64 * NW);
     Online32 st;
     const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
-    flash32<D, NW, false, VEC>(col.aL, d, col.aL, d, NK, d, p.scale, q, 16 * wave < b1, ring,
+    flash32<D, NW, false, VEC>(col.aL, d, col.aL, d, NK, d, p.scale, q, 16 * wave < b1 ? NK : 0, 0, 0, ring,
                                [&](int key) { return col.cL[key]; }, [&](int key) { return key >= lim; }, st, o, tid);
     const float lsum = xsum(st.l);
     if (wave < nlt && g == 0) lse[l] = st.m + logf(lsum);
@@ -663,18 +668,20 @@ __global__ __launch_bounds__(64 * kDenseWaves32, 4) void k_f32_dense(KParams p) 
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) q[ks] = ld4<VEC>(Qp + (long long)qc * p.qs.token, 16 * ks + 4 * g, d);
   zero<D>(o);
-  // keys beyond the last visible chunk of the LAST query row of this block are never needed
-  int nkeys = p.Nkv;
-  long long lim = nkeys;
-  if (p.cc > 0) {
-    const int qlast = q0 + kDenseQ32 - 1 < p.Nq ? q0 + kDenseQ32 - 1 : p.Nq - 1;
-    const long long most = (long long)((p.qoff + qlast / p.hw) / p.cc + 1) * p.cc * p.hw;
-    if (most < nkeys) nkeys = (int)most;
-    lim = (long long)((p.qoff + qc / p.hw) / p.cc + 1) * p.cc * p.hw;   // this query's own visible prefix
-  }
+  // the keys query row r sees: a prefix, up to the end of its own chunk
+  auto visible = [&](int r) {
+    if (p.cc == 0) return p.Nkv;
+    const long long most = (long long)((p.qoff + r / p.hw) / p.cc + 1) * p.cc * p.hw;
+    return most < p.Nkv ? (int)most : p.Nkv;
+  };
+  auto last_of = [&](int r) { return r < p.Nq ? r : p.Nq - 1; };
+  const int nkeys = visible(last_of(q0 + kDenseQ32 - 1)), lim = visible(qc);
+  const int wkeys = q0 + 16 * wave < p.Nq ? __builtin_amdgcn_readfirstlane(visible(last_of(q0 + 16 * wave + 15))) : 0;
   Online32 st;
-  flash32<D, kDenseWaves32, true, VEC>(Kp, p.ks.token, Vp, p.vs.token, nkeys, d, p.scale, q, q0 + 16 * wave < p.Nq, lds,
-                                       [](int) { return 0.f; }, [&](int key) { return key >= lim; }, st, o, tid);
+  // chunks end where a query of this workgroup stops seeing keys: a wave whose queries stop there leaves the
+  // next chunk out, and no value hidden from all of them gets to meet their weights of zero (0 x inf)
+  flash32<D, kDenseWaves32, true, VEC>(Kp, p.ks.token, Vp, p.vs.token, nkeys, d, p.scale, q, wkeys, visible(q0),
+                                       p.cc * p.hw, lds, [](int) { return 0.f; }, [&](int key) { return key >= lim; }, st, o, tid);
   const float lsum = xsum(st.l);
   TIn* Op = (TIn*)p.O + b * p.os.batch + hd * p.os.head;
   if (qi < p.Nq) store_out<D, VEC>(Op + (long long)qi * p.os.token, o, lsum > 0.f ? 1.0f / lsum : 0.f, g, d);

@@ -45,6 +45,25 @@ def test_fp32_infinite_last_value_row(rows, cols, d):
     assert torch.equal(out, expect)
 
 
+# 16 queries of a wave that see the same keys do not touch what is hidden from all of them, whatever
+# the other queries of the call see: frames of 144 tokens end with a group of 16, frames of 117 do not
+@pytest.mark.parametrize("h,w", [(9, 16), (9, 13)])
+def test_fp32_dense_infinite_value_of_a_later_chunk(h, w):
+    f, chunk, d = 6, 2, 64
+    n = f * h * w
+    q, k, v = tensors(h, n, n, d)
+    at = (f - 2) * h * w                       # first key of the last chunk
+    v[:, :, at, 3] = INF
+    out = pkg.dense_attn_fwd(q, k, v, f_q=f, f_kv=f, h=h, w=w, causal_chunk=chunk, scale=d ** -0.5)
+    clean = at - at % 16
+    assert torch.isfinite(out[:, :, :clean]).all()
+    assert (out[:, :, at:, 3] == INF).all()
+    frame = torch.arange(n, device="cuda:0") // (h * w) // chunk
+    ref = softmax_rows(q, k, v, d ** -0.5, hidden=frame[None, :] > frame[:, None])
+    seen = out.isfinite()
+    assert ((out - ref)[seen].norm() / ref[seen].norm()).item() <= 5e-6
+
+
 HUGE = {
     "resident": dict(f_q=3, f_kv=3, h=10, b1=30, w=13, b2=13, head_dim=64, tile=0),
     "three-frames": dict(f_q=3, f_kv=3, h=30, b1=90, w=20, b2=20, head_dim=128, tile=0),
