@@ -7,9 +7,10 @@
 // phase apart: one wave of a SIMD feeds the matrix unit while the other one has the vector ALU.  The
 // barrier that ends every phase keeps them so.  (Without it the waves drift into step and the two
 // units take turns: a matrix unit busy 35 % of the time.)  What bounds the kernel then is the vector
-// phase (52 vector instructions per 32 keys and two tiles, which issue at half rate under the other
-// wave's products) and about 150 clocks of barrier per phase; hence phases of 64 keys (two chunks) and
-// no vector work that the matrix unit can do (the sums of the probabilities).
+// phase (vector instructions issue at half rate under the other wave's products) and about 150 clocks
+// of barrier per phase; hence phases of 64 keys (two chunks).  The sums of the probabilities are fp32
+// additions of the unrounded values: a product with ones over the rounded ones takes them off the
+// vector ALU (3 to 6 % of a call), but shortens the denominator by up to 2^-8 where the roundings agree.
 //
 // LDS rows are padded to D + 16 elements (288 bytes at D = 128): the 16-byte key reads and the
 // transposed value reads of 16 contiguous features then both run free of bank conflicts (4.0 and 2.8
@@ -117,21 +118,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
   bf16x8 pb[QT][NS];
   f32x4 s[QT][NT], o[QT][NVT];
   float mref[QT], thr[QT];                // reference, the raw logit that would raise it
-  f32x4 lrun[QT];                         // sum of the probabilities (the same in all four registers)
+  float lrun[QT];                         // this lane's sum of the (unrounded) probabilities
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
-    mref[q] = -1e30f; thr[q] = -INFINITY; lrun[q] = f32x4{0.f, 0.f, 0.f, 0.f};   // (finite: no key seen yet)
+    mref[q] = -1e30f; thr[q] = -INFINITY; lrun[q] = 0.f;   // (finite: no key seen yet)
 #pragma unroll
     for (int vt = 0; vt < NVT; ++vt) o[q][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
   // A wave's keys of a pair start at row 32 wk (WK = 2) or 0.
   const int koff = (WK == 2 ? 32 * wk * LD : 0) + c * LD + 8 * g;
   const int voff = 64 * LD + (WK == 2 ? 32 * wk * LD : 0) + (4 * g + (c >> 2)) * LD + 4 * (c & 3);
   // The matrix phase: s = logits of the next step's keys (pair in kslot), o += the probabilities'
-  // product with this step's values (pair in vslot), lrun += their sums (a product with ones: the sum
-  // of what the second product weighs with, without a vector instruction).  Operands are read from
-  // LDS kAhead groups of products ahead of their use, in this fixed order.
+  // product with this step's values (pair in vslot).  Operands are read from LDS kAhead groups of
+  // products ahead of their use, in this fixed order.
   constexpr int NK_OPS = NT * KS1, NV_OPS = NS * NVT, OPS = NK_OPS + NV_OPS;
   bf16x8 op[OPS];
   auto read_op = [&](int i, const u16* ka, const u16* va) {
@@ -157,10 +156,6 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
           s[q][i % NT] = mfma(op[i], qv[q][i / NT], i < NT ? f32x4{0.f, 0.f, 0.f, 0.f} : s[q][i % NT]);
       } else {
         const int st = (i - NK_OPS) / NVT, vt = (i - NK_OPS) % NVT;
-        if (vt == 0) {
-#pragma unroll
-          for (int q = 0; q < QT; ++q) lrun[q] = mfma(ones, pb[q][st], lrun[q]);
-        }
 #pragma unroll
         for (int q = 0; q < QT; ++q) o[q][vt] = mfma(op[i], pb[q][st], o[q][vt]);
       }
@@ -200,17 +195,22 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
         const float f = exp2_fast(mref[q] - mnew);
         mref[q] = mnew;
         thr[q] = (mnew + kGrow) / scale2;
-        lrun[q] = lrun[q] * f;
+        lrun[q] *= f;
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f;
       }
     }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
+      float sum = 0.f;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[q][t][r] = exp2_fast(fmaf(s[q][t][r], scale2, -mref[q]));
+        for (int r = 0; r < 4; ++r) {
+          s[q][t][r] = exp2_fast(fmaf(s[q][t][r], scale2, -mref[q]));
+          sum += s[q][t][r];
+        }
+      lrun[q] += sum;
 #pragma unroll
       for (int st = 0; st < NS; ++st) pb[q][st] = pack8(s[q][2 * st], s[q][2 * st + 1]);
     }
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
       for (int q = 0; q < QT; ++q) {
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) xo[(q * (NVT + 1) + vt) * 64] = o[q][vt];
-        xo[(q * (NVT + 1) + NVT) * 64] = f32x4{mref[q], lrun[q][0], 0.f, 0.f};
+        xo[(q * (NVT + 1) + NVT) * 64] = f32x4{mref[q], lrun[q], 0.f, 0.f};
       }
     }
     __syncthreads();
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
     for (int q = 0; q < QT; ++q) {
       const f32x4 ml = xo[(q * (NVT + 1) + NVT) * 64];
       const float m = fmaxf(mref[q], ml[0]), f0 = exp2_fast(mref[q] - m), f1 = exp2_fast(ml[0] - m);
-      lrun[q][0] = lrun[q][0] * f0 + ml[1] * f1;
+      lrun[q] = lrun[q] * f0 + ml[1] * f1;
 #pragma unroll
       for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f0 + xo[(q * (NVT + 1) + vt) * 64] * f1;
     }
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
     const int qi = qw0 + 16 * q + c;
-    const float lsum = lrun[q][0], inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    const float lsum = xsum(lrun[q]), inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     if (qi < p.Nq) {
       u16* row = Op + (long long)qi * p.os.token + 4 * g;
 #pragma unroll

@@ -3,6 +3,8 @@ keys between two waves), each at ragged query and key counts, under the chunk-ca
 keys, with a query range whose key counts differ, and with rows that are not packed; against plain
 torch in float64.  Bar: the probabilities and the output are rounded once each to 2^-9, which shows as
 2.4e-3 (2-norm); four times that."""
+import math
+
 import pytest
 import torch
 
@@ -71,3 +73,27 @@ def test_rising_logits_raise_the_reference():
     out = pkg.dense_attn_fwd(q, k, v, f_q=1, f_kv=1, h=60, w=11, scale=1.0)
     ref = reference(q, k, v, n, 0, 0, 1.0)
     assert ((out.double() - ref).norm() / ref.norm()).item() <= 1e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [1, 5, 12])
+def test_sum_of_the_unrounded_probabilities(heads, d):
+    # Two keys of probability 1 (one in either half of the first 64 keys) hold the values; every other key
+    # has p = 0.50176, which bf16 rounds to 0.5.  The second product weighs the others' zeros with that, but
+    # the denominator is a sum of fp32 numbers: a sum of the rounded ones would be 3.5e-3 short.  The
+    # output's own rounding (1.1e-3 rms) averages out over the features to 1e-4.
+    h, w, p = 90, 52, 0.5 * (1 + 0.9 * 2.0 ** -8)
+    n = h * w
+    q = torch.zeros(1, heads, n, d, device="cuda:0")
+    q[..., 0] = 1.0
+    k = torch.zeros_like(q)
+    k[..., 0] = -1.0
+    k[:, :, [0, 32]] = 0.0
+    v = torch.zeros_like(q)
+    value = 1.0 + torch.rand(1, heads, 1, d, generator=torch.Generator(device="cuda:0").manual_seed(heads), device="cuda:0")
+    v[:, :, [0, 32]] = value
+    out = pkg.dense_attn_fwd(q.bfloat16(), k.bfloat16(), v.bfloat16(), f_q=1, f_kv=1, h=h, w=w, scale=-math.log(p))
+    exact = 2 * v.bfloat16()[:, :, :1].double() / (2 + (n - 2) * p)
+    bias = (out.double() / exact - 1).mean().item()
+    print(f"  mean relative error {bias:.1e}", flush=True)
+    assert abs(bias) <= 8e-4
