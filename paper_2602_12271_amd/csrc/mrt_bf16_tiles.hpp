@@ -102,6 +102,14 @@ __device__ inline float row8_sum(float x) {
   return x + dpp_mov<0x141>(x);
 }
 
+// x y rounded to fp32.  A logit that its own maximum is subtracted from must be the number the maximum
+// was taken over: contracted with that subtraction into one fma, the product keeps bits the maximum
+// lost, and beyond 1e9 the exponent of the largest logit is not 0 but hundreds.
+__device__ inline float mul_rounded(float x, float y) {
+#pragma clang fp contract(off)
+  return x * y;
+}
+
 // Swizzled LDS tiles (SWZ = true; rows of 128 bf16 = 256 bytes = all 64 banks, NOT padded): the
 // 16-byte piece p of row r sits at piece index p ^ swz16(r), i.e. its 32-byte pair of pieces at pair
 // index (p / 2) ^ (r mod 8).  Eight consecutive rows then hold one pair column in eight different

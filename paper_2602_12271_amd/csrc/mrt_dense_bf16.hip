@@ -29,6 +29,10 @@ namespace {
 // A query's softmax reference is raised only when a logit exceeds it by more than this (base 2):
 // every probability is then at most 2^kGrow, and the ratio sum(p v) / sum(p) does not depend on it.
 constexpr float kGrow = 8.0f;
+constexpr float kNoKey = -__FLT_MAX__;   // reference of a query that has seen no key
+// Beyond this the rounding of a reference, which its own logit's exponent would contain (one fma), is no
+// longer small beside kGrow: the logits are then rounded first and the maximum followed exactly.
+constexpr float kFarRef = 0x1p20f;
 constexpr int kDenseWaves = 8, kDenseThreads = 64 * kDenseWaves;
 // LDS ring of 64-key pairs of chunks: while pair i is consumed, pair i + 1 is resident, pair i + 2 is
 // being written and pair i + 3 is in flight from global memory.
@@ -121,7 +125,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
   float lrun[QT];                         // this lane's sum of the (unrounded) probabilities
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
-    mref[q] = -1e30f; thr[q] = -INFINITY; lrun[q] = 0.f;   // (finite: no key seen yet)
+    mref[q] = kNoKey; thr[q] = -INFINITY; lrun[q] = 0.f;
 #pragma unroll
     for (int vt = 0; vt < NVT; ++vt) o[q][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -171,6 +175,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
     }
     return m;
   };
+  bool far = false;                       // a query of this wave has a reference beyond kFarRef
   // the raw logits of the keys from c0 on are complete: mask them where they reach beyond a query's
   // keys, raise the references they exceed, and form the probabilities
   auto soften = [&](int c0) {
@@ -191,14 +196,31 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
     if (__builtin_amdgcn_ballot_w64(above) != 0) {
 #pragma unroll
       for (int q = 0; q < QT; ++q) {
-        const float mnew = fmaxf(mref[q], xmax(top(q)) * scale2);
+        const float mnew = fmaxf(mref[q], mul_rounded(xmax(top(q)), scale2));
         const float f = exp2_fast(mref[q] - mnew);
+        const bool beyond = mnew > kNoKey && fabsf(mnew) > kFarRef;
         mref[q] = mnew;
-        thr[q] = (mnew + kGrow) / scale2;
+        thr[q] = beyond ? -INFINITY : (mnew + kGrow) / scale2;
+        far |= __builtin_amdgcn_ballot_w64(beyond) != 0;
         lrun[q] *= f;
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f;
       }
+    }
+    if (__builtin_expect(far, 0)) {
+#pragma unroll
+      for (int q = 0; q < QT; ++q)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[q][t][r] = mul_rounded(s[q][t][r], scale2) - mref[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < QT; ++q)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[q][t][r] = fmaf(s[q][t][r], scale2, -mref[q]);
     }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
@@ -207,7 +229,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
       for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          s[q][t][r] = exp2_fast(fmaf(s[q][t][r], scale2, -mref[q]));
+          s[q][t][r] = exp2_fast(s[q][t][r]);
           sum += s[q][t][r];
         }
       lrun[q] += sum;

@@ -44,14 +44,6 @@ __device__ inline f32x4 mfma4(f32x4 a, f32x4 b, f32x4 acc) {
   return acc;
 }
 
-// x y rounded to fp32.  A logit that its own maximum is subtracted from must be the number the maximum
-// was taken over: contracted with that subtraction into one fma, the product keeps bits the maximum
-// lost, and beyond 1e9 the exponent of the largest logit is not 0 but hundreds.
-__device__ inline float mul_rounded(float x, float y) {
-#pragma clang fp contract(off)
-  return x * y;
-}
-
 // ---- rows of four features -------------------------------------------------------------------
 template <typename T> struct Quad;
 template <> struct Quad<float> {

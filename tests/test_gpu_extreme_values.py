@@ -100,3 +100,29 @@ def test_fp32_huge_logits(name, magnitude):
     assert distance(wl, arrays, run_dense_gpu(wl, *to_device(wl, arrays)), oracle_dense_head) <= 5e-6
     wl, arrays = huge("f32", magnitude, iters=2, **HUGE[name])
     assert torch.isfinite(run_monarch_gpu(wl, *to_device(wl, arrays))).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,chunk", [(1, 0), (2, 1), (5, 0), (7, 0)])
+def test_bf16_dense_extreme_logits(heads, chunk, d):
+    # one feature carries the logits, in steps far above the rounding of the output, so every softmax is a
+    # choice of the largest visible key; 1e11, 1e38 and every logit below -1e30
+    f, h, w = 3, 30, 52
+    n = f * h * w
+    gen = torch.Generator(device="cuda:0").manual_seed(d)
+    order = torch.randperm(n, generator=gen, device="cuda:0")
+    v = torch.randn(1, heads, n, d, generator=gen, device="cuda:0").bfloat16()
+    frame = torch.arange(n, device="cuda:0") // (h * w)
+    for big, low in ((2.0 ** 15, 0.0), (2.0 ** 58, 0.0), (2.0 ** 52, -2.0 ** 57)):
+        q = torch.zeros(1, heads, n, d, device="cuda:0")
+        k = torch.zeros_like(q)
+        q[..., 0], q[..., 1] = big, big
+        # key i: big (order / 256) in two bf16 numbers, of which the sum is exact
+        k[..., 0] = low + big * (order // 256)
+        k[..., 1] = big * (order % 256) / 256
+        out = pkg.dense_attn_fwd(q.bfloat16(), k.bfloat16(), v, f_q=f, f_kv=f, h=h, w=w, causal_chunk=chunk, scale=1.0)
+        for c in range(f if chunk else 1):
+            seen = (frame <= c) if chunk else torch.ones_like(frame, dtype=torch.bool)
+            best = torch.where(seen, order, torch.full_like(order, -1)).argmax()
+            rows = frame == c if chunk else torch.ones_like(seen)
+            assert torch.equal(out[:, :, rows], v[:, :, best:best + 1].expand(-1, -1, int(rows.sum()), -1))
