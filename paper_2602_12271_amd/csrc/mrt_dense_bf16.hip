@@ -31,7 +31,9 @@ namespace {
 constexpr float kGrow = 8.0f;
 constexpr float kNoKey = -__FLT_MAX__;   // reference of a query that has seen no key
 // Beyond this the rounding of a reference, which its own logit's exponent would contain (one fma), is no
-// longer small beside kGrow: the logits are then rounded first and the maximum followed exactly.
+// longer small beside kGrow: every step then counts as one that raises it, and there the exponents are
+// formed from logits that are rounded first.  (A choice between the two on the common path costs a
+// quarter of the call at 64 features: it parts the exponentials from the rest of the vector phase.)
 constexpr float kFarRef = 0x1p20f;
 constexpr int kDenseWaves = 8, kDenseThreads = 64 * kDenseWaves;
 // LDS ring of 64-key pairs of chunks: while pair i is consumed, pair i + 1 is resident, pair i + 2 is
@@ -121,11 +123,12 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
   const float scale2 = p.scale * kLog2e;
   bf16x8 pb[QT][NS];
   f32x4 s[QT][NT], o[QT][NVT];
-  float mref[QT], thr[QT];                // reference, the raw logit that would raise it
+  float mref[QT], thr[QT];                // reference, the raw logit that would raise it (kFarRef: any would)
+  float mul[QT], off[QT];                 // a step's exponents are s mul - off: scale and reference, or 1 and 0 (kFarRef)
   float lrun[QT];                         // this lane's sum of the (unrounded) probabilities
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
-    mref[q] = kNoKey; thr[q] = -INFINITY; lrun[q] = 0.f;
+    mref[q] = off[q] = kNoKey; mul[q] = scale2; thr[q] = -INFINITY; lrun[q] = 0.f;
 #pragma unroll
     for (int vt = 0; vt < NVT; ++vt) o[q][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -175,7 +178,6 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
     }
     return m;
   };
-  bool far = false;                       // a query of this wave has a reference beyond kFarRef
   // the raw logits of the keys from c0 on are complete: mask them where they reach beyond a query's
   // keys, raise the references they exceed, and form the probabilities
   auto soften = [&](int c0) {
@@ -198,29 +200,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
       for (int q = 0; q < QT; ++q) {
         const float mnew = fmaxf(mref[q], mul_rounded(xmax(top(q)), scale2));
         const float f = exp2_fast(mref[q] - mnew);
-        const bool beyond = mnew > kNoKey && fabsf(mnew) > kFarRef;
+        const bool far = mnew > kNoKey && fabsf(mnew) > kFarRef;
         mref[q] = mnew;
-        thr[q] = beyond ? -INFINITY : (mnew + kGrow) / scale2;
-        far |= __builtin_amdgcn_ballot_w64(beyond) != 0;
+        mul[q] = far ? 1.0f : scale2;
+        off[q] = far ? 0.0f : mnew;
+        thr[q] = (mnew + (far ? -INFINITY : kGrow)) / scale2;     // (no branch: it would part the loop)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[q][t][r] = far ? mul_rounded(s[q][t][r], scale2) - mnew : s[q][t][r];
         lrun[q] *= f;
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f;
       }
-    }
-    if (__builtin_expect(far, 0)) {
-#pragma unroll
-      for (int q = 0; q < QT; ++q)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) s[q][t][r] = mul_rounded(s[q][t][r], scale2) - mref[q];
-    } else {
-#pragma unroll
-      for (int q = 0; q < QT; ++q)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) s[q][t][r] = fmaf(s[q][t][r], scale2, -mref[q]);
     }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
@@ -229,7 +221,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
       for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          s[q][t][r] = exp2_fast(s[q][t][r]);
+          s[q][t][r] = exp2_fast(fmaf(s[q][t][r], mul[q], -off[q]));
           sum += s[q][t][r];
         }
       lrun[q] += sum;
