@@ -64,8 +64,16 @@ struct DenseTile {
   }
 };
 
+// Keys query q sees: the frames up to the end of its own chunk, a prefix.
+__host__ __device__ inline int dense_visible(const KParams& p, int q) {
+  if (p.cc == 0) return p.Nkv;
+  const long long lim = (long long)((p.qoff + q / p.hw) / p.cc + 1) * p.cc * p.hw;
+  return lim < p.Nkv ? (int)lim : p.Nkv;
+}
+
+// (64 features: two workgroups to a compute unit)
 template <int D, int QT, int WK>
-__global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
+__global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(KParams p) {
   using Tile = DenseTile<D>;
   constexpr int KS1 = D / 32, NVT = D / 16, LD = kDenseLd<D>, WQ = kDenseWaves / WK, WGQ = 16 * QT * WQ;
   constexpr int NS = 2 / WK, NT = 2 * NS;                 // 32-key chunks / 16-key tiles of a wave's step
@@ -73,12 +81,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void k_bf16_dense(KParams p) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wq = wave % WQ, wk = wave / WQ;
   const bool second = wave >= kDenseWaves / 2;           // the half that runs one phase behind
-  // keys a query sees: the frames up to the end of its own chunk, a prefix
-  auto visible = [&](int q) {
-    if (p.cc == 0) return p.Nkv;
-    const long long lim = (long long)((p.qoff + q / p.hw) / p.cc + 1) * p.cc * p.hw;
-    return lim < p.Nkv ? (int)lim : p.Nkv;
-  };
+  auto visible = [&](int q) { return dense_visible(p, q); };
   // Workgroups reach the eight XCDs in turn: hand each XCD a contiguous run of (head, query tile)
   // units, so that the units that stream the same keys share its L2.  (Under a mask that gives the
   // query tiles of a head different key counts the natural order spreads the long ones evenly.)
@@ -307,20 +310,37 @@ hipError_t run_dense(const KParams& kp, int nbh, hipStream_t s) {
   return hipGetLastError();
 }
 
-// One workgroup occupies a compute unit, so a call takes as many rounds as its workgroups fill the
-// chip; a round costs 112, 78 and 58 us at 4680 keys of 128 features for workgroups of 256 (QT = 2),
-// 128 (QT = 2, WK = 2) and 64 (QT = 1, WK = 2) queries.  The variant with the least rounds x cost
-// (one head of 4680 tokens: 58 us against 112, the previous kernel 121; 5 heads: 79 against 113 and 114;
-// 12 heads: 121 against 154, previous kernel 174, 62 of it matrix time).
+// A call takes as many rounds as its workgroups fill the chip; the shape with the least rounds x cost.
+//
+// 128 features: a workgroup occupies a compute unit.  A round of 4680 keys costs 61, 79 and 126 us for
+// workgroups of 64 (QT = 1, WK = 2), 128 (QT = 2, WK = 2) and 256 (QT = 2) queries (one head of 4680
+// tokens 59 | 78 | 122 us, 5 heads 120 | 80 | 123, 12 heads 233 | 159 | 130, 16 heads 294 | 238 | 256).
+// Where a mask gives the query tiles different key counts the short ones fill the last round, and the
+// largest shape, which reads the keys least often, is taken at 112 (24 heads of 12 one-frame chunks of
+// 320 tokens 203 | 173 | 162, 10 heads of 2 chunks of 4680 tokens 575 | 444 | 399).
+//
+// 64 features: two workgroups of 64 or 128 queries share a compute unit; a round of up to one per unit
+// costs 40 and 57 us, of up to two 54 and 90 (one head of 4680 tokens 38 | 57, 5 heads 53 | 58, 8 heads
+// 92 | 87, 16 heads 145 | 134; 40 heads of 1560 tokens 43 | 52).  Workgroups of 256, one per unit, take
+// 88 a round: never ahead of 128 by more than 3 %, behind by up to 1.5 x.  Under a mask the workgroups
+// count by their share of the longest one's keys (12 heads of 3 chunks of 1040 tokens 50 | 63, 16 heads
+// 63 | 64, 32 heads 101 | 98).
 template <int D>
 hipError_t run_dense_d(const KParams& kp, int nbh, hipStream_t s) {
-  auto cost = [&](int queries, long long unit) {
-    const long long wgs = (long long)((kp.Nq + queries - 1) / queries) * nbh, cus = compute_units();
-    return (wgs + cus - 1) / cus * unit;
-  };
-  const long long c256 = cost(256, 112), c128 = cost(128, 78), c64 = cost(64, 58);
-  if (c64 < c128 && c64 < c256) return run_dense<D, 1, 2>(kp, nbh, s);
-  return c128 < c256 ? run_dense<D, 2, 2>(kp, nbh, s) : run_dense<D, 2, 1>(kp, nbh, s);
+  const long long cus = compute_units(), first = dense_visible(kp, 0), last = dense_visible(kp, kp.Nq - 1);
+  auto wgs = [&](int queries) { return (long long)((kp.Nq + queries - 1) / queries) * nbh; };
+  if constexpr (D == 64) {
+    auto cost = [&](int queries, long long one, long long two) {
+      const long long n = wgs(queries) * (first + last) / (2 * last), rest = n % (2 * cus);
+      return n / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0);
+    };
+    return cost(64, 40, 54) < cost(128, 57, 90) ? run_dense<64, 1, 2>(kp, nbh, s) : run_dense<64, 2, 2>(kp, nbh, s);
+  } else {
+    auto cost = [&](int queries, long long unit) { return (wgs(queries) + cus - 1) / cus * unit; };
+    const long long c256 = cost(256, first == last ? 126 : 112), c128 = cost(128, 79), c64 = cost(64, 61);
+    if (c64 < c128 && c64 < c256) return run_dense<D, 1, 2>(kp, nbh, s);
+    return c128 < c256 ? run_dense<D, 2, 2>(kp, nbh, s) : run_dense<D, 2, 1>(kp, nbh, s);
+  }
 }
 
 }  // namespace

@@ -1,5 +1,5 @@
-"""The bf16 dense baseline's three workgroup shapes (256, 128 and 64 queries; the last two split the
-keys between two waves), each at ragged query and key counts, under the chunk-causal mask with hidden
+"""The bf16 dense baseline's workgroup shapes (256, 128 and 64 queries; the last two split the keys
+between two waves; 64 features take the last two only, two workgroups to a compute unit), each at ragged query and key counts, under the chunk-causal mask with hidden
 keys, with a query range whose key counts differ, and with rows that are not packed; against plain
 torch in float64.  Bar: the probabilities and the output are rounded once each to 2^-9, which shows as
 2.4e-3 (2-norm); four times that."""
@@ -24,7 +24,10 @@ CASES = {
     "128-steps": (5, 64, 6, 6, 19, 41, 2, 0),
     "256": (7, 128, 3, 3, 30, 52, 0, 0),
     "256-hidden": (12, 128, 3, 5, 29, 53, 1, 1),
-    "256-steps": (9, 64, 9, 9, 13, 41, 3, 0),
+    "256-steps": (9, 128, 9, 9, 13, 41, 3, 0),
+    "d64-second-round": (14, 64, 3, 3, 30, 52, 0, 0),
+    "d64-steps": (9, 64, 9, 9, 13, 41, 3, 0),
+    "d64-64-many": (20, 64, 1, 1, 30, 52, 0, 0),
 }
 
 
