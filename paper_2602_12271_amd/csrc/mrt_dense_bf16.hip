@@ -103,19 +103,22 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   }
 
   const unsigned krow = (unsigned)p.ks.token * 2u, vrow = (unsigned)p.vs.token * 2u;     // bytes per token
-  const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const u16*)p.K + b * p.ks.batch + hd * p.ks.head), 0, (unsigned)(nkeys - 1) * krow + 2 * D, 0x00020000);
-  const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)((const u16*)p.V + b * p.vs.batch + hd * p.vs.head), 0, (unsigned)(nkeys - 1) * vrow + 2 * D, 0x00020000);
+  // 256 queries: the first half's 128 stop at key `mid`, and a pair of chunks ends there, so that no value
+  // hidden from all of them meets their weights of zero (0 x inf); the rest is the second half's alone
+  const int mid = WK == 1 ? visible(q0 + WGQ / 2 - 1 < p.Nq ? q0 + WGQ / 2 - 1 : p.Nq - 1) : nkeys;
+  const int nmid = (mid + 63) >> 6, npairs = nmid + ((nkeys - mid + 63) >> 6);
+  auto first_key = [&](int pr) { return pr < nmid ? 64 * pr : mid + 64 * (pr - nmid); };
+  const u16* Kp = (const u16*)p.K + b * p.ks.batch + hd * p.ks.head;
+  const u16* Vp = (const u16*)p.V + b * p.vs.batch + hd * p.vs.head;
   const unsigned kvoff = (unsigned)(tid / Tile::CPR) * krow + 16u * (tid % Tile::CPR);
   const unsigned vvoff = (unsigned)(tid / Tile::CPR) * vrow + 16u * (tid % Tile::CPR);
-  const int npairs = (nkeys + 63) >> 6;
   Tile kt, vt;
   // (pairs past the end re-read the last one; nobody reads their slot, or only as masked keys)
   auto fetch = [&](int pr) {
-    const unsigned at = (unsigned)(pr < npairs ? pr : npairs - 1) * 64u;
-    kt.load(kr, kvoff, at * krow, krow);
-    vt.load(vr, vvoff, at * vrow, vrow);
+    const int at = pr < npairs ? pr : npairs - 1, end = at < nmid ? mid : nkeys;
+    const unsigned key = (unsigned)first_key(at), rows = (unsigned)(end - 1);
+    kt.load(__builtin_amdgcn_make_buffer_rsrc((void*)Kp, 0, rows * krow + 2 * D, 0x00020000), kvoff, key * krow, krow);
+    vt.load(__builtin_amdgcn_make_buffer_rsrc((void*)Vp, 0, rows * vrow + 2 * D, 0x00020000), vvoff, key * vrow, vrow);
   };
   auto commit = [&](int slot) {
     u16* at = dense_lds + slot * kDenseSlot<D>;
@@ -182,12 +185,12 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
     return m;
   };
   // the raw logits of the keys from c0 on are complete: mask them where they reach beyond a query's
-  // keys, raise the references they exceed, and form the probabilities
-  auto soften = [&](int c0) {
+  // keys or the pair's end, raise the references they exceed, and form the probabilities
+  auto soften = [&](int c0, int end) {
     if (c0 + 16 * NT > nfree) {
 #pragma unroll
       for (int q = 0; q < QT; ++q) {
-        const int qi = qw0 + 16 * q + c, lim = visible(qi < p.Nq ? qi : p.Nq - 1);
+        const int qi = qw0 + 16 * q + c, seen = visible(qi < p.Nq ? qi : p.Nq - 1), lim = seen < end ? seen : end;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -246,17 +249,21 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   __syncthreads();
   matrix(0, 0, false);
   if (second) __syncthreads();
-  for (int i = 0; i < npairs; ++i) {
-    soften(64 * i + (WK == 2 ? 32 * wk : 0));
+  auto step = [&](int i, int end, bool mine) {
+    if (mine) soften(first_key(i) + (WK == 2 ? 32 * wk : 0), end);
     // pair i + 2 into the slot of pair i - 2, which both halves left at least a phase ago (the other
     // half may still be reading pairs i - 1 and i)
     commit((i + 2) & (kDenseSlots - 1));
     fetch(i + 3);
     phase_end();
     __builtin_amdgcn_s_setprio(1);
-    matrix((i + 1) & (kDenseSlots - 1), i & (kDenseSlots - 1), true);
+    if (mine) matrix((i + 1) & (kDenseSlots - 1), i & (kDenseSlots - 1), true);
     __builtin_amdgcn_s_setprio(0);
     phase_end();
+  };
+  for (int i = 0; i < nmid; ++i) step(i, mid, true);
+  if constexpr (WK == 1) {
+    for (int i = nmid; i < npairs; ++i) step(i, nkeys, second);
   }
   if (!second) __syncthreads();
 

@@ -64,6 +64,29 @@ def test_fp32_dense_infinite_value_of_a_later_chunk(h, w):
     assert ((out - ref)[seen].norm() / ref[seen].norm()).item() <= 5e-6
 
 
+# 128 queries of the bf16 dense baseline that see the same keys, in the shape that takes 256 to a workgroup:
+# chunks of 640 tokens end with a group of 128, chunks of 680 do not
+@pytest.mark.parametrize("h", [16, 17])
+@pytest.mark.parametrize("c", [1, 2])
+def test_bf16_dense_infinite_value_of_a_later_chunk(h, c):
+    f, chunk, w, d, heads = 6, 2, 20, 128, 18
+    n = f * h * w
+    q, k, v = tensors(h, n, n, d, torch.bfloat16, heads)
+    at = c * chunk * h * w                     # first key of chunk c
+    v[:, :, at, 3] = INF
+    out = pkg.dense_attn_fwd(q, k, v, f_q=f, f_kv=f, h=h, w=w, causal_chunk=chunk, scale=d ** -0.5)
+    clean = at - at % 128
+    assert torch.isfinite(out[:, :, :clean]).all()
+    assert (out[:, :, at:, 3] == INF).all()
+    frame = torch.arange(n, device="cuda:0") // (h * w) // chunk
+    for head in range(0, heads, 6):
+        one = [x[:, head:head + 1] for x in (q, k, v)]
+        ref = softmax_rows(*one, d ** -0.5, hidden=frame[None, :] > frame[:, None])
+        got = out[:, head:head + 1].double()
+        seen = got.isfinite()
+        assert ((got - ref)[seen].norm() / ref[seen].norm()).item() <= 1e-2
+
+
 HUGE = {
     "resident": dict(f_q=3, f_kv=3, h=10, b1=30, w=13, b2=13, head_dim=64, tile=0),
     "three-frames": dict(f_q=3, f_kv=3, h=30, b1=90, w=20, b2=20, head_dim=128, tile=0),
