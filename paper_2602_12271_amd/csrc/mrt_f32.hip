@@ -696,30 +696,33 @@ bool vec_ok(const KParams& kp) {
   return true;
 }
 
-// The element-by-element variant exists for one (the largest) size of each kernel only.
+// Rows that cannot be moved so take the element-by-element variants of the same sizes.  (One variant, of the
+// largest size, for all of them made small problems pay for it: blocks of 16 x 16 at 6 features 28 -> 91 us,
+// 40 heads of them 67 -> 256; unaligned 24 x 24 at 64 features 56 -> 88.)
 template <int NT, int D, typename TIn, bool VEC>
 hipError_t run_r(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s) {
   if (last) k_f32_stage_r<NT, D, TIn, true, VEC><<<grid, 64 * NT, 0, s>>>(kp, first);
   else k_f32_stage_r<NT, D, TIn, false, VEC><<<grid, 64 * NT, 0, s>>>(kp, first);
   return hipGetLastError();
 }
-template <int D, typename TIn>
+template <int D, typename TIn, bool VEC>
 hipError_t run_r_d(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s) {
   switch ((kp.b2 + 15) / 16) {
-    case 1: return run_r<1, D, TIn, true>(kp, grid, first, last, s);
-    case 2: return run_r<2, D, TIn, true>(kp, grid, first, last, s);
-    case 3: return run_r<3, D, TIn, true>(kp, grid, first, last, s);
-    case 4: return run_r<4, D, TIn, true>(kp, grid, first, last, s);
-    case 5: return run_r<5, D, TIn, true>(kp, grid, first, last, s);
-    case 6: return run_r<6, D, TIn, true>(kp, grid, first, last, s);
+    case 1: return run_r<1, D, TIn, VEC>(kp, grid, first, last, s);
+    case 2: return run_r<2, D, TIn, VEC>(kp, grid, first, last, s);
+    case 3: return run_r<3, D, TIn, VEC>(kp, grid, first, last, s);
+    case 4: return run_r<4, D, TIn, VEC>(kp, grid, first, last, s);
+    case 5: return run_r<5, D, TIn, VEC>(kp, grid, first, last, s);
+    case 6: return run_r<6, D, TIn, VEC>(kp, grid, first, last, s);
   }
   return hipErrorInvalidValue;
 }
 template <typename TIn>
 hipError_t run_r_t(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s) {
   if (kp.b2 > 96 || kp.d > 128) return hipErrorInvalidValue;
-  if (!vec_ok<TIn>(kp)) return run_r<6, 128, TIn, false>(kp, grid, first, last, s);
-  return kp.d <= 64 ? run_r_d<64, TIn>(kp, grid, first, last, s) : run_r_d<128, TIn>(kp, grid, first, last, s);
+  if (vec_ok<TIn>(kp))
+    return kp.d <= 64 ? run_r_d<64, TIn, true>(kp, grid, first, last, s) : run_r_d<128, TIn, true>(kp, grid, first, last, s);
+  return kp.d <= 64 ? run_r_d<64, TIn, false>(kp, grid, first, last, s) : run_r_d<128, TIn, false>(kp, grid, first, last, s);
 }
 
 // Key ranges the one-pass refine kernel takes: twelve waves of one key tile each is the largest
@@ -749,23 +752,23 @@ hipError_t run_l(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
   k_f32_stage_l_refine<NW, D, TIn, VEC><<<grid, 64 * NW, lds, s>>>(kp);
   return hipGetLastError();
 }
-template <int D, typename TIn>
+template <int D, typename TIn, bool VEC>
 hipError_t run_l_d(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
   switch ((kp.b1 + 31) / 32) {
-    case 1: return run_l<2, D, TIn, true>(kp, grid, last, s);
-    case 2: return run_l<4, D, TIn, true>(kp, grid, last, s);
-    case 3: return run_l<6, D, TIn, true>(kp, grid, last, s);
-    case 4: return run_l<8, D, TIn, true>(kp, grid, last, s);
-    case 5: return run_l<10, D, TIn, true>(kp, grid, last, s);
-    case 6: return run_l<12, D, TIn, true>(kp, grid, last, s);
+    case 1: return run_l<2, D, TIn, VEC>(kp, grid, last, s);
+    case 2: return run_l<4, D, TIn, VEC>(kp, grid, last, s);
+    case 3: return run_l<6, D, TIn, VEC>(kp, grid, last, s);
+    case 4: return run_l<8, D, TIn, VEC>(kp, grid, last, s);
+    case 5: return run_l<10, D, TIn, VEC>(kp, grid, last, s);
+    case 6: return run_l<12, D, TIn, VEC>(kp, grid, last, s);
   }
   return hipErrorInvalidValue;
 }
 template <typename TIn>
 hipError_t run_l_t(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
   if (kp.b1 > 192 || kp.d > 128) return hipErrorInvalidValue;
-  if (!vec_ok<TIn>(kp)) return run_l<12, 128, TIn, false>(kp, grid, last, s);
-  return kp.d <= 64 ? run_l_d<64, TIn>(kp, grid, last, s) : run_l_d<128, TIn>(kp, grid, last, s);
+  if (vec_ok<TIn>(kp)) return kp.d <= 64 ? run_l_d<64, TIn, true>(kp, grid, last, s) : run_l_d<128, TIn, true>(kp, grid, last, s);
+  return kp.d <= 64 ? run_l_d<64, TIn, false>(kp, grid, last, s) : run_l_d<128, TIn, false>(kp, grid, last, s);
 }
 
 template <int D, typename TIn, bool VEC>
@@ -775,8 +778,8 @@ hipError_t run_dense(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 template <typename TIn>
 hipError_t run_dense_t(const KParams& kp, dim3 grid, hipStream_t s) {
-  if (!vec_ok<TIn>(kp)) return run_dense<128, TIn, false>(kp, grid, s);
-  return kp.d <= 64 ? run_dense<64, TIn, true>(kp, grid, s) : run_dense<128, TIn, true>(kp, grid, s);
+  if (vec_ok<TIn>(kp)) return kp.d <= 64 ? run_dense<64, TIn, true>(kp, grid, s) : run_dense<128, TIn, true>(kp, grid, s);
+  return kp.d <= 64 ? run_dense<64, TIn, false>(kp, grid, s) : run_dense<128, TIn, false>(kp, grid, s);
 }
 
 }  // namespace

@@ -20,7 +20,7 @@ REL = 5e-6
 
 def case(f, h, w, b1, b2, *, d=64, f_kv=None, tile=0, iters=2, chunk=0, off=0, dtype="f32", heads=2, **kw):
     return syn.Workload("edge", 1, heads, d, f, f_kv or f, h, w, b1, b2, tile, iters, chunk, off, dtype, d ** -0.5,
-                        True, **kw)
+                        d % 2 == 0, **kw)
 
 
 CASES = {
@@ -88,6 +88,39 @@ def test_unaligned_rows_give_the_same_result():
                          iters=wl.iters, scale=wl.scale, out=out)
     torch.cuda.synchronize()
     assert ((out - aligned).norm() / aligned.norm()).item() <= REL
+
+
+# rows moved element by element: each number of tiles of both block sides, either padded length, one-pass
+# and streamed refine
+ELEMENTS = {
+    "r1-l2": case(1, 16, 16, 16, 16, d=6),
+    "r2-l4": case(1, 33, 17, 33, 17, d=62),
+    "r3-l6": case(1, 70, 40, 70, 40, d=37, iters=1),
+    "r4-l8": case(1, 97, 49, 97, 49, d=63, heads=1),
+    "r5-l10": case(1, 130, 65, 130, 65, d=30, heads=1),
+    "r6-l12": case(1, 170, 81, 170, 81, d=10, heads=1, iters=1),
+    "r1-l2-d127": case(2, 6, 16, 12, 16, d=127),
+    "r2-l4-d66": case(2, 24, 18, 48, 18, d=66),
+    "r3-l6-d70": case(1, 81, 47, 81, 47, d=70, heads=1),
+    "r4-l8-d126": case(1, 113, 50, 113, 50, d=126, heads=1, iters=1),
+    "r5-l10-d125": case(1, 145, 79, 145, 79, d=125, heads=1, iters=1),
+    "r6-l12-d99": case(1, 161, 96, 161, 96, d=99, heads=1, iters=1),
+    "streamed-l2": case(14, 15, 4, 15, 2, d=38, tile=1),
+    "streamed-l6-d67": case(3, 70, 6, 70, 3, d=67, tile=1),
+    "streamed-l12": case(2, 176, 4, 176, 2, d=18, tile=1),
+    "bf16-storage": case(2, 20, 18, 40, 18, d=35, dtype="bf16"),
+}
+
+
+@pytest.mark.parametrize("name", list(ELEMENTS))
+def test_rows_moved_by_elements(name):
+    wl = ELEMENTS[name]
+    arrays = syn.make_inputs(wl)
+    print(f"case {name}: {wl}", flush=True)
+    dev = to_device(wl, arrays)
+    bar = REL if wl.dtype == "f32" else 3e-3
+    assert distance(wl, arrays, run_monarch_gpu(wl, *dev, compute=pkg.MRT_COMPUTE_F32), oracle_monarch_head) <= bar
+    assert distance(wl, arrays, run_dense_gpu(wl, *dev, compute=pkg.MRT_COMPUTE_F32), oracle_dense_head) <= bar
 
 
 @pytest.mark.parametrize("tile", [0, 1])
