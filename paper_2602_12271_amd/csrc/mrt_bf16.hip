@@ -1405,8 +1405,8 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------
-// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 with four waves, b1 > 144 with six): still one workgroup per (m, j) and
-// three workgroups per compute unit, with ONE 52 KB LDS tile used twice.  Last iteration: the
+// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 with four waves, b1 > 144 with six): still one
+// workgroup per (m, j) and three (of four waves) or two (of six) workgroups per compute unit, with ONE 52 KB LDS tile used twice.  Last iteration: the
 // tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one or two query
 // tiles against all keys and keeps the probabilities as packed bf16 in registers), then Y[m, j]
 // (second product).  Earlier iterations: the tile holds alpha_L for the row log-sum-exp, then Q
@@ -1414,6 +1414,21 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 // ---------------------------------------------------------------------------------------
 constexpr int kMidRows = 192;
 constexpr int kMidWideB1 = 144;   // beyond: no bf16 backward pass
+
+// Last iterations of at most 192 key rows that take the one-tile-twice kernel: b1 <= 128 with four waves,
+// three workgroups per compute unit; b1 > 144 with six, two workgroups per compute unit where the
+// streamed kernel's eight waves have it to themselves (b1 = 156, 12 heads of 30 columns: launch 28.0 ->
+// 22.2 us; b1 = 180, 40 columns: 33.9 -> 30.0 us; masked b1 = 156, one to 40 heads: calls 4 to 7 %
+// shorter).  In between the streamed kernel stays: a training step's saving forward call needs its row
+// statistics there, and it returns the bits of the plain call.  It also stays for masked blocks of more
+// than 160 rows at 128 features, where the other one runs out of registers (b1 = 180 and 192, one to 40
+// heads: within 1 % at most sizes, up to 3.5 % longer at one workgroup per compute unit).
+static bool l_out_mid(const KParams& kp) {
+  const int nk_max = kp.ntk * kp.b1;
+  if (nk_max > kMidRows) return false;
+  if (kp.b1 > kMidWideB1) return !(kp.rl > 0 && kp.d == 128 && nk_max > 160);
+  return kp.b1 <= 128;
+}
 
 // Base-2 logits (bias added, -inf beyond the last key) of one query tile against NTK resident key
 // tiles (NTK <= 12), and their column maximum.
@@ -1558,8 +1573,13 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bf16_stage_l_out_mid(KParams p) 
 
 template <int D, int NTK, int NW>
 hipError_t launch_l_out_mid(const KParams& kp, dim3 grid, hipStream_t s) {
-  if (kp.rl > 0) k_bf16_stage_l_out_mid<D, NTK, NW, true><<<grid, 64 * NW, 0, s>>>(kp);
-  else k_bf16_stage_l_out_mid<D, NTK, NW, false><<<grid, 64 * NW, 0, s>>>(kp);
+  constexpr bool kMasked = !(D == 128 && NTK == 12 && NW == 6);        // (l_out_mid)
+  if (kp.rl > 0) {
+    if constexpr (kMasked) k_bf16_stage_l_out_mid<D, NTK, NW, true><<<grid, 64 * NW, 0, s>>>(kp);
+    else return hipErrorInvalidValue;
+  } else {
+    k_bf16_stage_l_out_mid<D, NTK, NW, false><<<grid, 64 * NW, 0, s>>>(kp);
+  }
   return hipGetLastError();
 }
 
@@ -1697,7 +1717,7 @@ hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipSt
 // and an fp32 output for a backward call): same conditions as in launch_bf16_stage_l below.
 bool bf16_stage_l_out_streams(const KParams& kp) {
   const int nlt = (kp.b1 + 15) / 16, nk_max = kp.ntk * kp.b1;
-  return nlt <= kMaxLT && nk_max > kResRows && !(nk_max <= kMidRows && (nlt <= 8 || kp.b1 > kMidWideB1));
+  return nlt <= kMaxLT && nk_max > kResRows && !l_out_mid(kp);
 }
 
 hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s) {
@@ -1721,13 +1741,8 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
     return kp.d == 128 ? launch_l_out_res_d<128>(kp, grid, (nk_max + 15) / 16, s)
                        : launch_l_out_res_d<64>(kp, grid, (nk_max + 15) / 16, s);
   }
-  // medium key ranges, last iteration: one LDS tile used twice, still three workgroups per
-  // compute unit (the earlier iterations went above); b1 > 144 takes six waves, two workgroups per
-  // compute unit where the streamed kernel's eight waves have it to themselves (b1 = 156, 12 heads of
-  // 30 columns: 28.0 -> 22.2 us; b1 = 180, 40 columns: 33.9 -> 30.0 us).  In between the streamed
-  // kernel stays: a training step's saving forward call needs its row statistics there, and it
-  // returns the bits of the plain call.
-  if (nk_max <= kMidRows && (nlt <= 8 || kp.b1 > kMidWideB1))
+  // medium key ranges, last iteration: one LDS tile used twice (the earlier iterations went above)
+  if (l_out_mid(kp))
     return kp.d == 128 ? launch_l_out_mid_d<128>(kp, grid, (nk_max + 15) / 16, s)
                        : launch_l_out_mid_d<64>(kp, grid, (nk_max + 15) / 16, s);
   // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), each wave owning up to two
