@@ -1,11 +1,11 @@
-"""GPU parity cases aimed at the streamed kernels' chunk pipeline (ring of four 32-key LDS slots, two or
-four register sets in flight, chunks consumed in pairs) and at its online softmax, which takes the
-exponentials against a lazily raised reference instead of the running maximum.
+"""GPU parity cases aimed at the chunk pipelines: that of the bf16 dense baseline (64-key pairs of chunks, a
+ring of four, an online softmax against a lazily raised reference) and that of the streamed stage L
+kernels (ring of four 32-key LDS slots, two or four register sets in flight, chunks consumed in pairs; its
+own raised reference is driven by test_gpu_moving_maxima.py).
 
-* The in-library dense baseline runs the same pipeline on logits we control directly
-  (softmax(scale Q K^T) V, Sec. 2.2): key logits that rise steadily (the reference is raised many times),
-  fall steadily (raised once), zig-zag, or hold one spike far above everything else.  Key counts are
-  chosen so that the number of 32-key chunks is odd and even, below and above the ring's four slots.
+* The dense baseline (softmax(scale Q K^T) V, Sec. 2.2) on logits we control directly: key logits that rise
+  steadily (the reference is raised many times), fall steadily (raised once), zig-zag, or hold one spike far
+  above everything else, at odd and even numbers of chunks and pairs, ragged and not.
 * MonarchRT shapes whose stage L key range sits just above the one-pass kernels' limit (192 rows), with
   a single query tile (three of the four waves own no tile), with 9 to 12 query tiles (eight-wave
   workgroups, four register sets, head_dim 64: fewer 16-byte pieces per chunk than threads), and with
@@ -81,8 +81,7 @@ def test_dense_baseline_with_moving_maxima(grid, profile):
 
 
 def test_dense_baseline_chunk_causal_rows_see_different_prefixes():
-    # chunk-causal mask: queries of the first chunk see 2 of 6 frames; the per-key chunk comparison hides
-    # the rest inside the pipeline (fully hidden chunks leave a query's reference at -inf for a while)
+    # chunk-causal mask: queries of the first chunk see 2 of 6 frames; the rest is hidden inside the pipeline
     wl = workload(head_dim=64, f_q=6, f_kv=6, h=5, w=9, causal_chunk=2)
     arrays = syn.make_inputs(wl)
     O = run_dense_gpu(wl, *to_device(wl, arrays))
