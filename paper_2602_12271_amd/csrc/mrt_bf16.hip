@@ -1395,8 +1395,14 @@ template <int D, int QT, int NT>
 hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
   const bool stats = kp.lse_out != nullptr && kp.o32_out != nullptr;
   if (kp.rl > 0) {
-    if (stats) k_bf16_stage_l_out<D, QT, NT, true, true><<<grid, NT, 0, s>>>(kp);
-    else k_bf16_stage_l_out<D, QT, NT, true><<<grid, NT, 0, s>>>(kp);
+    // (regular Monarch: one key tile of b1 rows, and up to eight query tiles of it are resident or take
+    // the one-tile-twice kernel)
+    if constexpr (NT == 512) {
+      if (stats) k_bf16_stage_l_out<D, QT, NT, true, true><<<grid, NT, 0, s>>>(kp);
+      else k_bf16_stage_l_out<D, QT, NT, true><<<grid, NT, 0, s>>>(kp);
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else {
     if (stats) k_bf16_stage_l_out<D, QT, NT, false, true><<<grid, NT, 0, s>>>(kp);
     else k_bf16_stage_l_out<D, QT, NT, false><<<grid, NT, 0, s>>>(kp);
