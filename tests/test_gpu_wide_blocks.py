@@ -2,7 +2,9 @@
 edges of its query and key tiles, with and without the chunk-causal mask, against the fp64 oracle.
 Bar: 2-norm, four times the 3.7e-3 the bf16 roundings of the forward pass show."""
 import pytest
+import torch
 
+import paper_2602_12271_amd as pkg
 from oracle import monarch_oracle as mo  # noqa: F401  (the oracle the harness compares with)
 from workloads import synthetic as syn
 
@@ -24,3 +26,28 @@ def test_forward(f, h, chunk, d):
         num += (out[0, hd].double().cpu() - ref).pow(2).sum().item()
         den += ref.pow(2).sum().item()
     assert (num / den) ** 0.5 <= 1.5e-2
+
+
+def test_weights_are_rounded_against_the_first_keys():
+    """One column, so that stage L weighs V by softmax(scale Q K^T) itself, and value row k is unit vector k:
+    the output holds the bf16 weights 2^(z - reference) over their fp32 sum.  They are rounded where the
+    streamed kernels round them, against the largest logit of the first 32 keys (few logits lie near a
+    rounding boundary within fp32 accuracy: 99 % of the outputs must agree)."""
+    rows, d, heads = 160, 128, 8
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    q, k = (torch.randn(1, heads, rows, d, generator=gen, device="cuda:0").bfloat16() for _ in range(2))
+    v = torch.zeros(1, heads, rows, d, device="cuda:0")
+    v[:, :, torch.arange(d), torch.arange(d)] = 1.0
+    out = pkg.monarch_attn_fwd(q, k, v.bfloat16(), f_q=1, f_kv=1, h=rows, w=1, b1=rows, b2=1, tile=0, iters=1, scale=0.25)
+    z = 0.25 * 1.4426950408889634 * torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous())
+
+    def weights(reference):
+        p = torch.exp2(z - reference)
+        return ((p.bfloat16().double() / p.sum(-1, keepdim=True))[..., :d]).bfloat16()
+
+    first, top = z[..., :32].amax(-1, keepdim=True), z.amax(-1, keepdim=True)
+    reference = torch.where(top <= first + 8, first, top)
+    agree = (out == weights(reference)).float().mean().item()
+    other = (out == weights(top)).float().mean().item()
+    print(f"  agree {agree:.4f} (against the column maximum: {other:.4f})", flush=True)
+    assert agree >= 0.99 and other < 0.9
