@@ -646,7 +646,9 @@ __global__ __launch_bounds__(64 * NW, NW > 8 ? 3 : 4) void k_f32_stage_l_refine(
 // ---------------------------------------------------------------------------------------
 constexpr int kDenseWaves32 = 8, kDenseQ32 = 16 * kDenseWaves32;
 
-template <int D, typename TIn, bool VEC>
+// MASKED: chunk-causal (a kernel of its own: the shorter chunks' bookkeeping costs 4 % of a
+// call at 64 features)
+template <int D, typename TIn, bool VEC, bool MASKED>
 __global__ __launch_bounds__(64 * kDenseWaves32, 4) void k_f32_dense(KParams p) {
   __shared__ __attribute__((aligned(16))) float lds[2 * kSlot32<D, true>];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -668,12 +670,14 @@ __global__ __launch_bounds__(64 * kDenseWaves32, 4) void k_f32_dense(KParams p) 
   };
   auto last_of = [&](int r) { return r < p.Nq ? r : p.Nq - 1; };
   const int nkeys = visible(last_of(q0 + kDenseQ32 - 1)), lim = visible(qc);
-  const int wkeys = q0 + 16 * wave < p.Nq ? __builtin_amdgcn_readfirstlane(visible(last_of(q0 + 16 * wave + 15))) : 0;
+  int wkeys = q0 + 16 * wave < p.Nq ? nkeys : 0;
+  if (MASKED && wkeys > 0) wkeys = __builtin_amdgcn_readfirstlane(visible(last_of(q0 + 16 * wave + 15)));
   Online32 st;
   // chunks end where a query of this workgroup stops seeing keys: a wave whose queries stop there leaves the
   // next chunk out, and no value hidden from all of them gets to meet their weights of zero (0 x inf)
-  flash32<D, kDenseWaves32, true, VEC>(Kp, p.ks.token, Vp, p.vs.token, nkeys, d, p.scale, q, wkeys, visible(q0),
-                                       p.cc * p.hw, lds, [](int) { return 0.f; }, [&](int key) { return key >= lim; }, st, o, tid);
+  flash32<D, kDenseWaves32, true, VEC>(Kp, p.ks.token, Vp, p.vs.token, nkeys, d, p.scale, q, wkeys, MASKED ? visible(q0) : 0,
+                                       MASKED ? p.cc * p.hw : 0, lds, [](int) { return 0.f; },
+                                       [&](int key) { return MASKED && key >= lim; }, st, o, tid);
   const float lsum = xsum(st.l);
   TIn* Op = (TIn*)p.O + b * p.os.batch + hd * p.os.head;
   if (qi < p.Nq) store_out<D, VEC>(Op + (long long)qi * p.os.token, o, lsum > 0.f ? 1.0f / lsum : 0.f, g, d);
@@ -773,7 +777,8 @@ hipError_t run_l_t(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
 
 template <int D, typename TIn, bool VEC>
 hipError_t run_dense(const KParams& kp, dim3 grid, hipStream_t s) {
-  k_f32_dense<D, TIn, VEC><<<grid, 64 * kDenseWaves32, 0, s>>>(kp);
+  if (kp.cc > 0) k_f32_dense<D, TIn, VEC, true><<<grid, 64 * kDenseWaves32, 0, s>>>(kp);
+  else k_f32_dense<D, TIn, VEC, false><<<grid, 64 * kDenseWaves32, 0, s>>>(kp);
   return hipGetLastError();
 }
 template <typename TIn>
