@@ -115,8 +115,8 @@ __device__ inline float mul_rounded(float x, float y) {
 // index (p / 2) ^ (r mod 8).  Eight consecutive rows then hold one pair column in eight different
 // places: a matrix operand read of a piece column (ds_read_b128) takes 4.0 clocks of the CU's LDS per
 // wave instruction, the rate of a linear read (an XOR of single pieces, 4 (r mod 4) ^ (r / 4 mod 4),
-// took 6.0), and a transposed read (ds_read_b64_tr_b16) 4.0 as before.  480p chunk as (156,30) 71.3 ->
-// 70.5 us, tiles (90,26) 73.3 -> 72.5 us.
+// took 6.0), and a transposed read (ds_read_b64_tr_b16) 4.0 as before.  Back-to-back calls
+// of the 480p chunk as (156,30) 71.3 -> 70.5 us, as tiles (90,26) 73.3 -> 72.5 us.
 __device__ inline int swz16(int row) { return (row & 7) << 1; }
 template <int LD, bool SWZ>
 __device__ inline int tile_off(int row, int piece) {

@@ -1229,7 +1229,7 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
   __shared__ __attribute__((aligned(16))) u16 As[ROWS * LD];              // abar[m, n, k, j, :]
   __shared__ __attribute__((aligned(16))) u16 Gs[ROWS * LD];              // d alpha_L[m, n, j, k, :]
   __shared__ __attribute__((aligned(16))) u16 Ys[LAST ? ROWS * LD : 8];   // d Y[m, n, j, k, :]
-  __shared__ __attribute__((aligned(16))) u16 RT[ROWS * LR];              // R[j, i] as [i][j]
+  __shared__ __attribute__((aligned(16))) u16 RT[ROWS * LR];              // R[j][i]
   __shared__ __attribute__((aligned(16))) u16 ST_own[kAlias ? 8 : ROWS * LR];   // scale dS[j][i]
   u16* ST = kAlias ? Vs : ST_own;
   __shared__ float dcls[LW ? ROWS : 1];                                   // d c_L of the step's columns (LW)

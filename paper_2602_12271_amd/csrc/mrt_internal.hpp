@@ -139,7 +139,7 @@ mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const m
                    int b2, int tile, int iters, int causal_chunk, void* workspace,
                    size_t workspace_bytes, void* hip_stream, bool own_stream_only);
 
-// fp32 SIMT path (mrt_f32.hip)
+// fp32 path (mrt_f32.hip)
 hipError_t launch_f32_stage_r(const KParams& kp, int dtype, int nbh, bool first, bool last,
                               hipStream_t s);
 hipError_t launch_f32_stage_l(const KParams& kp, int dtype, int nbh, bool last, hipStream_t s);
