@@ -1596,9 +1596,12 @@ static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, 
     case 1: case 2: k_bwdm_l_rows<D, 2, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
     case 3: case 4: k_bwdm_l_rows<D, 4, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
     case 5: case 6:
-      // two six-wave workgroups fit a compute unit, three of four waves: 3 heads of 52 columns, training
-      // step 118 -> 109 us; 12 heads (624 workgroups, a second round) 218 -> 234 us, so four waves there
-      if ((long long)grid.x * grid.y * grid.z <= 2LL * compute_units())
+      // two six-wave workgroups fit a compute unit, three of four waves.  Up to one workgroup per unit six
+      // waves shorten a training step by 7 to 10 % (3 heads of 52 columns, T = 2: 119 -> 110 us; 14 heads of
+      // 16: 130 -> 121), up to two per unit only this kernel's t = T launches (T = 1, 8 heads of 48: 81.2 ->
+      // 79.9; 20 heads of 14: 65.6 -> 63.1; T = 2 with both: 9 heads of 52 174 -> 177, 32 of 16 186 -> 190),
+      // beyond that a second round costs more (12 heads of 52 218 -> 234)
+      if ((long long)grid.x * grid.y * grid.z <= (LAST ? 2LL : 1LL) * compute_units())
         k_bwdm_l_rows<D, 6, LAST, TW, 6><<<grid, 384, 0, s>>>(bp, Pw, Zw);
       else
         k_bwdm_l_rows<D, 6, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw);

@@ -1,5 +1,5 @@
-"""Stage L backward on resident key ranges of five and six tiles, on either side of the grid size that
-picks six waves per workgroup instead of four (512 workgroups): both against the fp32 kernels on the
+"""Stage L backward on resident key ranges of five and six tiles, on either side of the grid sizes that
+pick six waves per workgroup instead of four (256 workgroups at t < T, 512 at t = T): all against the fp32 kernels on the
 same bf16 tensors.  Bar, in the 2-norm: one bf16 rounding is 1.1e-3 rms (2^-9 / sqrt 3), a gradient
 crosses about a dozen of them (every intermediate of the forward pass, both factors of every product of
 the reverse sweep), 4e-3 in quadrature; four times that.  (The largest single error is no measure here:
@@ -13,7 +13,7 @@ import paper_2602_12271_amd as pkg
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("heads", [2, 40])
+@pytest.mark.parametrize("heads", [2, 24, 40])
 @pytest.mark.parametrize("f,h,w,d,iters", [(3, 30, 15, 128, 2), (1, 65, 14, 64, 1), (2, 48, 13, 64, 2), (1, 81, 16, 128, 1)])
 def test_gradients(f, h, w, d, iters, heads):
     gen = torch.Generator(device="cuda:0").manual_seed(f * h + heads)
