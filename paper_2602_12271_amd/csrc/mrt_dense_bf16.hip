@@ -338,7 +338,7 @@ hipError_t run_dense_d(const KParams& kp, int nbh, hipStream_t s) {
   auto wgs = [&](int queries) { return (long long)((kp.Nq + queries - 1) / queries) * nbh; };
   if constexpr (D == 64) {
     auto cost = [&](int queries, long long one, long long two) {
-      const long long n = wgs(queries) * (first + last) / (2 * last), rest = n % (2 * cus);
+      const long long n = (wgs(queries) * (first + last) + 2 * last - 1) / (2 * last), rest = n % (2 * cus);
       return n / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0);
     };
     return cost(64, 40, 54) < cost(128, 57, 90) ? run_dense<64, 1, 2>(kp, nbh, s) : run_dense<64, 2, 2>(kp, nbh, s);
