@@ -140,6 +140,10 @@ mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const m
                    size_t workspace_bytes, void* hip_stream, bool own_stream_only);
 
 // fp32 path (mrt_f32.hip)
+// bf16 storage, fp32 arithmetic (called by the launchers below)
+hipError_t run_f32_stage_r_bf16(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s);
+hipError_t run_f32_stage_l_bf16(const KParams& kp, dim3 grid, bool last, hipStream_t s);
+hipError_t run_f32_dense_bf16(const KParams& kp, dim3 grid, hipStream_t s);
 hipError_t launch_f32_stage_r(const KParams& kp, int dtype, int nbh, bool first, bool last,
                               hipStream_t s);
 hipError_t launch_f32_stage_l(const KParams& kp, int dtype, int nbh, bool last, hipStream_t s);
