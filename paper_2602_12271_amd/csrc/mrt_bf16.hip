@@ -67,8 +67,16 @@ inline size_t stage_r_last_lds_bytes(int b2) {
   return (size_t)(32 * ((NT + 1) / 2) + b2) * (D + kPadRV<NT>) * 2;
 }
 
+// With five or six waves a workgroup takes three LDS-wise, but at four waves a SIMD only two of them fit
+// (five waves are 2, 1, 1, 1): the last iteration's variant writes the values to LDS together with the keys,
+// which frees the registers that held them through the first tile's softmax, and five waves a SIMD fit.
+// One-frame tiles (45,80), 12 heads against 21 frames of 720p: launch 522 -> 482 us, call 753 -> 722;
+// (135,80) 186 -> 172; (90,96) 166 -> 154.  Four waves have four workgroups a unit either way, and the
+// earlier wait for the values costs them 2 % (64 features: 1 %).
+template <int NT, int D, bool LAST> constexpr bool kEarlyV = LAST && NT >= 5 && D == 128;
+
 template <int NT, int D, bool FIRST, bool LAST>
-__global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) {
+__global__ __launch_bounds__(64 * NT, (kEarlyV<NT, D, LAST> ? 5 : 4)) void k_bf16_stage_r(KParams p, int gs) {
   constexpr int LD = D + (LAST ? kPadRV<NT> : kPad), KS1 = D / 32, KS2 = (NT + 1) / 2, ROWS = 32 * KS2, NVT = D / 16;
   constexpr int NTHR = 64 * NT;
   __shared__ __attribute__((aligned(16))) u16 Ks_static[LAST ? 8 : ROWS * LD];
@@ -129,6 +137,7 @@ __global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) 
   load_q(ml0);
   if (LAST) rv.load(Vp, TokRows{0, p.cmap, bn * b2, p.vs.token}, b2, tid);
   rk.template store<LD>(Ks, tid);
+  if constexpr (kEarlyV<NT, D, LAST>) rv.template store_rev<LD>(Vtop, tid);
   __syncthreads();
   MRT_STAMP(1);
 
@@ -149,13 +158,14 @@ __global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) 
       if (it % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // bound the operand reads in flight
     }
     __builtin_amdgcn_sched_barrier(0);
-    // softmax over i (rows of the tiles) for column j, and sum_i R log R (base-2 domain inside)
+    // softmax over i (rows of the tiles) for column j, and sum_i R log R (base-2 domain inside); only the
+    // last tile has rows past b2 (NT = ceil(b2 / 16))
     float mx = -INFINITY;
 #pragma unroll
     for (int it = 0; it < NT; ++it)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const bool ok = 16 * it + 4 * g + r < b2;
+        const bool ok = it < NT - 1 || 16 * it + 4 * g + r < b2;
         const float z = ok ? s[it][r] * scale2 : -INFINITY;
         s[it][r] = z;
         mx = fmaxf(mx, z);
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) 
     for (int it = 0; it < NT; ++it)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const bool ok = 16 * it + 4 * g + r < b2;
+        const bool ok = it < NT - 1 || 16 * it + 4 * g + r < b2;
         const float z = ok ? s[it][r] - mx : 0.f;
         const float e = ok ? exp2_fast(z) : 0.f;
         sum += e;
@@ -180,7 +190,7 @@ __global__ __launch_bounds__(64 * NT, 4) void k_bf16_stage_r(KParams p, int gs) 
     if (g == 0 && j < b2) p.cL[row] = kLn2 * (ent * inv - log2_fast(sum));
 
     __builtin_amdgcn_sched_barrier(0);
-    if (LAST && ml == ml0) {
+    if (LAST && !kEarlyV<NT, D, LAST> && ml == ml0) {
       // the values, requested with the keys, were still arriving during the first tile's logits and
       // softmax; they are needed from here on
       rv.template store_rev<LD>(Vtop, tid);
