@@ -11,7 +11,8 @@
 //   cols kernel  (lanes own key rows nk):   d aL[nk] = scale sum_l dZ[l,nk] Q[l],
 //                d cL[nk] = -sum_l dZ[l,nk], d Y[nk] = sum_l L[l,nk] dO[l]
 // so that every contraction has its summation index on the K side of an MFMA.  The rows kernel
-// holds the key range in LDS when it has at most 96 rows and streams it in segments otherwise.
+// holds the key range in LDS when it has at most 96 rows and streams it in segments otherwise.  On a bf16
+// workspace the two sides are one launch wherever LDS holds both (at most 96 key rows, or 96 query rows).
 #include "mrt_internal.hpp"
 #include <type_traits>
 
@@ -274,11 +275,15 @@ __device__ inline void store_tile_transposed(u16* arr, int pitch, int nk0, int N
 // ---------------------------------------------------------------------------------------
 // TW: storage type of the forward intermediates alpha_L, Y and abar in the workspace (fp32 when
 // the fp32 kernels recomputed them, bf16 when the bf16 forward kernels did).
-// NW waves; six (one query tile each instead of two on half of four waves) where every workgroup is
-// resident at once and its own latency is the launch.
-template <int D, int NTK, bool LAST, typename TW, int NW>
+// NW waves; six own one query tile each, four two on half of them.
+// COLS: the column side of the stage (k_bwdm_l_cols otherwise) follows in the same workgroup, at most one
+// query tile a wave: dZ reaches it through LDS, Q and dO take the places of alpha_L and Y, L follows dZ in
+// its place.  The contractions run in the order of the cols kernel: the same bits.
+template <int D, int NTK, bool LAST, typename TW, int NW, bool COLS = false>
 __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u16* Zw) {
   const KParams& p = bp.k;
+  // dZ[l][nk]: rows of 224 (or 160, 96) bytes, conflict-free for the eight-byte writes and transposed reads
+  constexpr int LZ = 16 * NTK + 16;
   constexpr int NTHR = 64 * NW, LD = D + kBPad, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
   __shared__ __attribute__((aligned(16))) u16 Ks[ROWS * LD];    // alpha_L rows
   __shared__ __attribute__((aligned(16))) u16 Vs[ROWS * LD];    // Y rows (LAST) or d abar rows
@@ -286,6 +291,7 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
   __shared__ __attribute__((aligned(16))) float tcs[ROWS];      // d abar . abar                  (not LAST)
   __shared__ __attribute__((aligned(16))) float cms[ROWS];      // max_l log2 L[l, nk]            (not LAST)
   __shared__ __attribute__((aligned(16))) float cis[ROWS];      // 1 / sum_l 2^(log2 L - max)     (not LAST)
+  __shared__ __attribute__((aligned(16))) u16 Zs[COLS ? ROWS * LZ : 8];   // dZ, then L                (COLS)
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int b1 = p.b1, b2 = p.b2, d = D;
@@ -352,9 +358,23 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
   float* dQp = bp.dQ + (size_t)bh * p.Nq * d;
   u16* Pt = Pw + row0 * kLP;
   u16* Zt = Zw + row0 * kLP;
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  [[maybe_unused]] bf16x4 Lq[NTK];       // COLS, LAST: this wave's rows of L until the column side takes them
+  // tile lt of X[l][nk] into LDS, four keys of a lane's row at a time
+  auto to_lds = [&](int lt, const bf16x4 (&x)[NTK]) {
+#pragma unroll
+    for (int kt = 0; kt < NTK; ++kt) *(bf16x4*)(Zs + (16 * lt + c) * LZ + 16 * kt + 4 * g) = x[kt];
+  };
   // the cols kernel reads query rows in steps of 32: an odd tile count leaves one tile of zeros
   for (int lt = wave; lt < 2 * ((nlt + 1) / 2); lt += NW) {
     const int l = 16 * lt + c;
+    if (COLS && lt >= nlt) {
+      bf16x4 none[NTK];
+#pragma unroll
+      for (int kt = 0; kt < NTK; ++kt) Lq[kt] = none[kt] = bf16x4{(__bf16)0.f, (__bf16)0.f, (__bf16)0.f, (__bf16)0.f};
+      to_lds(lt, none);
+      continue;
+    }
     if (lt >= nlt) {
       for (int nk = g; nk < NK; nk += 4) {
         if (LAST) Pt[(size_t)nk * kLP + l] = 0;
@@ -431,8 +451,18 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
     for (int kt = 0; kt < NTK; ++kt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) dl[kt][r] = dl[kt][r] - s[kt][r] * delta;
+      if constexpr (COLS) continue;
       if (LAST) store_tile_transposed(Pt, kLP, 16 * kt, NK, 16 * lt, wq[kt], c, g);   // only dY, at t = T, is formed from it
       store_tile_transposed(Zt, kLP, 16 * kt, NK, 16 * lt, dl[kt], c, g);
+    }
+    if constexpr (COLS) {
+      bf16x4 zq[NTK];
+#pragma unroll
+      for (int kt = 0; kt < NTK; ++kt) {
+        zq[kt] = bf16x4{(__bf16)dl[kt][0], (__bf16)dl[kt][1], (__bf16)dl[kt][2], (__bf16)dl[kt][3]};
+        if (LAST) Lq[kt] = bf16x4{(__bf16)wq[kt][0], (__bf16)wq[kt][1], (__bf16)wq[kt][2], (__bf16)wq[kt][3]};
+      }
+      to_lds(lt, zq);
     }
     __builtin_amdgcn_sched_barrier(0);
     // dQ[l] = scale sum_nk dZ[l,nk] aL[nk] (+ sum_nk w[l,nk] dA[nk])
@@ -453,6 +483,52 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
       }
     }
     if (l < b1) store_rows_f32<D>(dQp + (row_offset(p, a, l) + qcol) * d, o, 1.0f, g, bp.accumulate != 0);
+  }
+  if constexpr (COLS) {
+    RowRegs<D, ROWS, NTHR> rq, rd;
+    rq.load(Qp, qrow, b1, tid);
+    if (LAST) rd.load(dOp, orow, b1, tid);
+    __syncthreads();                       // dZ is complete, alpha_L and Y are done with
+    rq.template store<LD>(Ks, tid);
+    if (LAST) rd.template store<LD>(Vs, tid);
+    __syncthreads();
+    // column tile `wave`: contraction over the query rows (those of tiles beyond nlt are not read)
+    const int nk = 16 * wave + c, steps = (nlt + 1) >> 1;
+    const u16* zc = Zs + (8 * g + ((lane & 15) >> 2)) * LZ + 16 * wave + 4 * (lane & 3);
+    auto column = [&](const u16* rows, f32x4 (&o)[1][NVT], float& sum) {
+      sum = 0.f;
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) o[0][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int st = 0; st < KS2; ++st)
+        if (st < steps) {
+          const u16* at = zc + 32 * st * LZ;
+          const bf16x8 one[1] = {__builtin_bit_cast(
+              bf16x8, __builtin_shufflevector(ld_lds_tr(at), ld_lds_tr(at + 4 * LZ), 0, 1, 2, 3, 4, 5, 6, 7))};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sum += (float)one[0][e];
+          pv_step_nat<D, 1, LD>(rows + 32 * st * LD, one, 1, o, lane);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    f32x4 o[1][NVT];
+    float zsum;
+    const bool owns = 16 * wave < NK;
+    if (owns) {
+      column(Ks, o, zsum);
+      zsum = xsum(zsum);
+      if (g == 0 && nk < NK) bp.dcL[row0 + nk] = -zsum;
+      if (nk < NK) store_ws_row<D>((TW*)bp.daL + (row0 + nk) * d, o[0], p.scale, g);
+    }
+    if constexpr (LAST) {
+      __syncthreads();                     // every wave is done with dZ
+      if (wave < 2 * steps) to_lds(wave, Lq);
+      __syncthreads();
+      if (owns) {
+        column(Vs, o, zsum);
+        if (nk < NK) store_ws_row<D>((TW*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
+      }
+    }
   }
 }
 
@@ -1596,6 +1672,7 @@ static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, 
     case 1: case 2: k_bwdm_l_rows<D, 2, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
     case 3: case 4: k_bwdm_l_rows<D, 4, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
     case 5: case 6:
+      // (fp32 workspace; the figures are those of the bf16 one, before its two sides were one launch)
       // two six-wave workgroups fit a compute unit, three of four waves.  Up to one workgroup per unit six
       // waves shorten a training step by 7 to 10 % (3 heads of 52 columns, T = 2: 119 -> 110 us; 14 heads of
       // 16: 130 -> 121), up to two per unit only this kernel's t = T launches (T = 1, 8 heads of 48: 81.2 ->
@@ -1608,6 +1685,20 @@ static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, 
       break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+// Rows and columns of the resident stage L backward in one launch (bf16 workspace): no transposed scratch
+// (65 MB written and read in a step of the 480p chunk), no second read of Q and dO from global memory, one
+// launch less an iteration.  One query tile a wave, so six waves for five and six tiles: two such workgroups
+// share a compute unit with their 74 KB of LDS, and a 12-head chunk's 624 are one round and a fifth, which
+// takes back most of the gain there.  Training steps, T = 2, rows and cols launches before, now: heads of
+// (90,52) 1: 89 -> 81 us, 4: 115 -> 103, 12: 223 -> 221, 24: 433 -> 408; 64 features, 12: 141 -> 135;
+// (64,40), 12: 129 -> 117; (32,32), 12: 78 -> 71; (96,16) of 64 features, 12: 79 -> 67.
+template <int D, bool LAST>
+static hipError_t launch_rows_and_cols(const BwdParams& bp, dim3 grid, int nkt, hipStream_t s) {
+  if (nkt <= 2) k_bwdm_l_rows<D, 2, LAST, u16, 4, true><<<grid, 256, 0, s>>>(bp, nullptr, nullptr);
+  else if (nkt <= 4) k_bwdm_l_rows<D, 4, LAST, u16, 4, true><<<grid, 256, 0, s>>>(bp, nullptr, nullptr);
+  else k_bwdm_l_rows<D, 6, LAST, u16, 6, true><<<grid, 384, 0, s>>>(bp, nullptr, nullptr);
   return hipGetLastError();
 }
 template <int D, bool LAST, typename TW>
@@ -1735,6 +1826,8 @@ static hipError_t launch_l_d(const BwdParams& bp, dim3 grid, int nkt, int nlt, b
       else k_bwdm_l_rows_stream<D, false, TW, 10><<<grid, 640, 0, s>>>(bp, Pw, Zw);
     }
     e = hipGetLastError();
+  } else if constexpr (sizeof(TW) == 2) {
+    return last ? launch_rows_and_cols<D, true>(bp, grid, nkt, s) : launch_rows_and_cols<D, false>(bp, grid, nkt, s);
   } else {
     e = last ? launch_rows<D, true, TW>(bp, grid, nkt, Pw, Zw, s)
              : launch_rows<D, false, TW>(bp, grid, nkt, Pw, Zw, s);
