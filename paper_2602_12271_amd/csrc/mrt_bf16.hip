@@ -1499,11 +1499,11 @@ __device__ inline float mid_logits(const u16* Ks, const float* bias, const bf16x
 // Six waves take the place of the streamed kernel and its reference (FIRST): where the bf16 roundings of
 // the weights fall depends on it, and against the maximum over all keys the error of two and three
 // iterations came out 0.4 to 1 % larger (unit-normal queries and keys; 0.2 % smaller for one).
-template <int D, int NTK, int NW, bool RMASK>
-__global__ __launch_bounds__(64 * NW, 3) void k_bf16_stage_l_out_mid(KParams p) {
+// QT = 1: two workgroups share a column's rows, one query tile a wave.
+template <int D, int NTK, int NW, bool RMASK, int QT>
+__global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_mid(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
   constexpr bool SWZ = ResTile<D>::SWZ;
-  constexpr int QT = 2;
   __shared__ __attribute__((aligned(16))) u16 tile[ROWS * LD];
   __shared__ __attribute__((aligned(16))) float bias[ROWS];
 
@@ -1511,12 +1511,13 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bf16_stage_l_out_mid(KParams p) 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int b1 = p.b1, b2 = p.b2;
-  const int j = blockIdx.x, ml = blockIdx.y, m = p.m0 + ml, bhl = last_head_first(), bh = p.bh0 + bhl;
+  const int part = QT == 1 && (int)blockIdx.x >= p.b2;     // the second half of the rows
+  const int j = (int)blockIdx.x - (part ? p.b2 : 0), ml = blockIdx.y, m = p.m0 + ml, bhl = last_head_first(), bh = p.bh0 + bhl;
   const int a = m / p.c2, bq = m - a * p.c2;
   const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;   // <= 16*NTK
   const size_t NKtot = (size_t)p.ntk * b1;
   const int b = bh / p.H, hd = bh - b * p.H;
-  const WaveTiles<QT> wt(wave, NW, (b1 + 15) >> 4);          // b1 <= 32 NW: at most two tiles a wave
+  const WaveTiles<QT> wt(wave + part * NW, NW, (b1 + 15) >> 4);   // b1 <= 32 NW: at most two tiles a wave (or one)
 
   const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot;
   const u16* aLp = (const u16*)p.aL + row0 * D;
@@ -1597,14 +1598,15 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bf16_stage_l_out_mid(KParams p) 
   MRT_STAMP(4);
 }
 
-template <int D, int NTK, int NW>
+template <int D, int NTK, int NW, int QT = 2>
 hipError_t launch_l_out_mid(const KParams& kp, dim3 grid, hipStream_t s) {
   constexpr bool kMasked = !(D == 128 && NTK == 12 && NW == 6);        // (l_out_mid)
+  if (QT == 1) grid.x *= 2;
   if (kp.rl > 0) {
-    if constexpr (kMasked) k_bf16_stage_l_out_mid<D, NTK, NW, true><<<grid, 64 * NW, 0, s>>>(kp);
+    if constexpr (kMasked) k_bf16_stage_l_out_mid<D, NTK, NW, true, QT><<<grid, 64 * NW, 0, s>>>(kp);
     else return hipErrorInvalidValue;
   } else {
-    k_bf16_stage_l_out_mid<D, NTK, NW, false><<<grid, 64 * NW, 0, s>>>(kp);
+    k_bf16_stage_l_out_mid<D, NTK, NW, false, QT><<<grid, 64 * NW, 0, s>>>(kp);
   }
   return hipGetLastError();
 }
@@ -1616,7 +1618,17 @@ hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t
   switch (nkt) {
     case 7: case 8: return launch_l_out_mid<D, 8, 4>(kp, grid, s);
     case 9: case 10: return wide ? launch_l_out_mid<D, 10, 6>(kp, grid, s) : launch_l_out_mid<D, 10, 4>(kp, grid, s);
-    case 11: case 12: return wide ? launch_l_out_mid<D, 12, 6>(kp, grid, s) : launch_l_out_mid<D, 12, 4>(kp, grid, s);
+    case 11: case 12:
+      if constexpr (D == 128) {
+        // eleven and twelve tiles on six waves are two on every wave: with one, the rows in two workgroups, the
+        // chain of a workgroup is half as long (192 rows, 8 columns, calls of 1 to 40 heads 33.9 -> 30.5 us
+        // .. 81.3 -> 75.8; 180 rows, 40 columns, 8 heads 79.3 -> 73.2, 20 heads 160 -> 150), unless a launch
+        // of the whole columns fills the places of one round by itself (12 heads of them: 93.9 against
+        // 95.1).  Ten tiles leave two waves with one, and two workgroups of five waves gain nothing.
+        const long long wgs = (long long)grid.x * grid.y * grid.z, places = 2LL * compute_units();
+        if (wide && (4 * wgs <= 3 * places || wgs > places)) return launch_l_out_mid<D, 12, 6, 1>(kp, grid, s);
+      }
+      return wide ? launch_l_out_mid<D, 12, 6>(kp, grid, s) : launch_l_out_mid<D, 12, 4>(kp, grid, s);
   }
   return hipErrorInvalidValue;
 }
