@@ -1113,13 +1113,13 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_res(KParams p) {
   MRT_STAMP(3);
 }
 
-// Stage L of an earlier iteration for key ranges of at most 64 PT rows, in one pass over the
+// Stage L of an earlier iteration for key ranges of at most 16 PT NW rows, in one pass over the
 // logits: wave w owns key tiles PT w .. PT w + PT - 1 and forms their logits against every query
 // tile once, with queries on the accumulator rows.  The row statistics of the joint softmax over
 // the key range are reduced inside the wave and exchanged between the NW waves through LDS;
 // alpha_L goes from global memory straight into the matrix operands, only Q is staged.
 template <int D, int NLT, int PT, int NW, bool RMASK>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void k_bf16_stage_l_refine_one(KParams p) {
+__global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_stage_l_refine_one(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, QROWS = 32 * ((NLT + 1) / 2), LROWS = 16 * NLT;
   constexpr bool SWZ = ResTile<D>::SWZ;
   __shared__ __attribute__((aligned(16))) u16 Qs[QROWS * LD];
@@ -1732,18 +1732,27 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
     case 2: launch_refine_one_k<D, 2, PT, 4>(kp, grid, s); break;
     case 3: launch_refine_one_k<D, 3, PT, 4>(kp, grid, s); break;
     case 4: launch_refine_one_k<D, 4, PT, 4>(kp, grid, s); break;
-    case 5: launch_refine_one_k<D, 5, PT, 4>(kp, grid, s); break;
-    case 6: launch_refine_one_k<D, 6, PT, 4>(kp, grid, s); break;
-    default: return hipErrorInvalidValue;
+    default:
+      if constexpr (PT > 1) {
+        if (nlt == 5) launch_refine_one_k<D, 5, PT, 4>(kp, grid, s);
+        else if (nlt == 6) launch_refine_one_k<D, 6, PT, 4>(kp, grid, s);
+        else return hipErrorInvalidValue;
+      } else {
+        return hipErrorInvalidValue;
+      }
   }
   return hipGetLastError();
 }
-// 7 .. 12 query tiles (one key tile per query tile, so as many key tiles): six waves, two key
-// tiles each; an odd tile count runs as the next even one (the extra tile is masked rows)
+// 7 .. 12 query tiles (one key tile per query tile, so as many key tiles); an odd tile count runs as the
+// next even one (the extra tile is masked rows).  Eight: a wave per key tile (the rows of a wave are the
+// chain a workgroup waits for, and two such workgroups, or three, still share a compute unit; 112 rows, 40
+// columns, calls of 1 to 40 heads 0.98 .. 0.88 of the time of six waves with two tiles each, 12 heads 57.6
+// -> 52.6 us; 128 rows, 24 columns, 64 features 0.98 .. 0.92).  Ten and twelve: six waves with two key tiles
+// each (a wave per tile: 0.99 .. 1.02, a unit then holds one workgroup).
 template <int D>
 hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
   switch ((nlt + 1) / 2) {
-    case 4: launch_refine_one_k<D, 8, 2, 6>(kp, grid, s); break;
+    case 4: launch_refine_one_k<D, 8, 1, 8>(kp, grid, s); break;
     case 5: launch_refine_one_k<D, 10, 2, 6>(kp, grid, s); break;
     case 6: launch_refine_one_k<D, 12, 2, 6>(kp, grid, s); break;
     default: return hipErrorInvalidValue;
@@ -1764,8 +1773,12 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
   if (nlt > kMaxLT) return hipErrorInvalidValue;
   const int nk_max = kp.ntk * kp.b1;
   // earlier iterations, key range of at most 192 rows: one pass over the logits (four waves for
-  // b1 <= 96, six beyond)
+  // b1 <= 96, six or eight beyond).  Up to 64 key rows every wave has at most one key tile, instead of half the
+  // waves two (calls of one to 40 heads: 48 rows, 30 columns 0.93 .. 0.99 of the time, 30 and 64 rows 0.96 .. 0.99, 34 rows
+  // of 64 features 0.95 .. 1.01); six waves for 65 to 96 rows gain nothing (0.98 .. 1.03).
   if (!last && nk_max <= kMidRows && nlt <= 6) {
+    if (nk_max <= 64) return kp.d == 128 ? launch_l_refine_one<128, 1>(kp, grid, nlt, s)
+                                         : launch_l_refine_one<64, 1>(kp, grid, nlt, s);
     if (nk_max <= 128) return kp.d == 128 ? launch_l_refine_one<128, 2>(kp, grid, nlt, s)
                                           : launch_l_refine_one<64, 2>(kp, grid, nlt, s);
     return kp.d == 128 ? launch_l_refine_one<128, 3>(kp, grid, nlt, s)
