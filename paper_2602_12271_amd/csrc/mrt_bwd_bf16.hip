@@ -1690,9 +1690,8 @@ static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, 
 // Rows and columns of the resident stage L backward in one launch (bf16 workspace): no transposed scratch
 // (65 MB written and read in a step of the 480p chunk), no second read of Q and dO from global memory, one
 // launch less an iteration.  One query tile a wave, so six waves for five and six tiles: two such workgroups
-// share a compute unit with their 74 KB of LDS, and a 12-head chunk's 624 are one round and a fifth, which
-// takes back most of the gain there.  Training steps, T = 2, rows and cols launches before, now: heads of
-// (90,52) 1: 89 -> 81 us, 4: 115 -> 103, 12: 223 -> 221, 24: 433 -> 408; 64 features, 12: 141 -> 135;
+// share a compute unit with their 74 KB of LDS.  Training steps, T = 2, rows and cols launches before, now: heads of
+// (90,52) 1: 89 -> 81 us, 4: 115 -> 103, 12: 225 -> 220, 24: 433 -> 408; 64 features, 12: 141 -> 135;
 // (64,40), 12: 129 -> 117; (32,32), 12: 78 -> 71; (96,16) of 64 features, 12: 79 -> 67.
 template <int D, bool LAST>
 static hipError_t launch_rows_and_cols(const BwdParams& bp, dim3 grid, int nkt, hipStream_t s) {
@@ -1827,7 +1826,15 @@ static hipError_t launch_l_d(const BwdParams& bp, dim3 grid, int nkt, int nlt, b
     }
     e = hipGetLastError();
   } else if constexpr (sizeof(TW) == 2) {
-    return last ? launch_rows_and_cols<D, true>(bp, grid, nkt, s) : launch_rows_and_cols<D, false>(bp, grid, nkt, s);
+    if (last) return launch_rows_and_cols<D, true>(bp, grid, nkt, s);
+    // Five and six tiles at 128 features, t < T: where one launch would leave less than a quarter of a second
+    // round, the two launches (three workgroups of four waves a unit, one round) are ahead (training steps, one
+    // launch, two: 10 heads of (90,52) 199 -> 192 us, 12 222 -> 220, 13 of (80,40) 196 -> 189; beyond 2.5 a unit
+    // 14 heads of (90,52) 230 -> 231, 19 of (80,40) 220 -> 224).  Same bits.
+    const long long wgs = (long long)grid.x * grid.y * grid.z, cus = compute_units();
+    if (!(D == 128 && nkt > 4 && wgs > 2 * cus && 2 * wgs <= 5 * cus)) return launch_rows_and_cols<D, false>(bp, grid, nkt, s);
+    k_bwdm_l_rows<D, 6, false, u16, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw);
+    e = hipGetLastError();
   } else {
     e = last ? launch_rows<D, true, TW>(bp, grid, nkt, Pw, Zw, s)
              : launch_rows<D, false, TW>(bp, grid, nkt, Pw, Zw, s);
