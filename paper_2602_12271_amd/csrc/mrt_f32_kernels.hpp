@@ -19,7 +19,7 @@
 // error against 64 bits 3.0e-7 -> 2.7e-7.
 //
 // fp32 operands remain where rows are moved element by element, for the smallest blocks (see run_r) and
-// where a product was an infinity or a NaN.  The layout feeds the matrix unit from registers and 16-byte
+// where a product was an infinity or a NaN or an operand below 2^-100.  The layout feeds the matrix unit from registers and 16-byte
 // LDS reads with nothing in between: lane (g = lane / 16, c = lane % 16) supplies A[c][k = g] and
 // B[k = g][c] of a step and holds C[4g + r][c] in register r.
 //   * First products contract over features, which are contiguous in both operands: with feature
@@ -150,9 +150,9 @@ struct Rows32 {
       v[i] = ld4<VEC>(src + rowoff(r < valid ? r : valid - 1), 4 * (idx % CPR), d);
     }
   }
-  // PLANE: rows from one split plane to the next
+  // PLANE: rows from one split plane to the next; `watch` sees what is split
   template <bool SPLIT = false, int PLANE = ROWS>
-  __device__ inline void store(float* dst, int valid, int d, int tid) {
+  __device__ inline void store(float* dst, int valid, int d, int tid, Watch& watch) {
     if (valid < ROWS || d < D) {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
@@ -169,6 +169,7 @@ struct Rows32 {
         else *(f32x4*)(dst + r * kLd<D> + 4 * (idx % CPR)) = x;
       }
     }
+    if constexpr (SPLIT) watch.see_split(v);
   }
 };
 
@@ -177,7 +178,7 @@ template <int D, bool SPLIT>
 struct Query32 {
   f32x4 v[D / 16];
   template <bool VEC, typename T>
-  __device__ inline void load(const T* row, int d, int g) {
+  __device__ inline void load(const T* row, int d, int g, Watch&) {
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) v[ks] = ld4<VEC>(row, 16 * ks + 4 * g, d);
     if (d < D) {
@@ -190,7 +191,7 @@ template <int D>
 struct Query32<D, true> {
   Split8 v[D / 32];
   template <bool VEC, typename T>
-  __device__ inline void load(const T* row, int d, int g) {
+  __device__ inline void load(const T* row, int d, int g, Watch& watch) {
     f32x4 x[D / 16];
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) x[ks] = ld4<VEC>(row, 32 * (ks >> 1) + 8 * g + 4 * (ks & 1), d);
@@ -200,6 +201,7 @@ struct Query32<D, true> {
     }
 #pragma unroll
     for (int ks = 0; ks < D / 32; ++ks) v[ks] = split8(x[2 * ks], x[2 * ks + 1]);
+    watch.see_split(x);
   }
 };
 
@@ -271,8 +273,8 @@ struct Weights32<NT, true> {
   }
 };
 
-// A workgroup's work with split operands and, if a product was an infinity or a NaN anywhere in it,
-// once more with fp32 operands: the second run writes every result again.  work(std::bool_constant)
+// A workgroup's work with split operands and, if a product was an infinity or a NaN or an operand too small
+// to be split anywhere in it, once more with fp32 operands: the second run writes every result again.  work(std::bool_constant)
 // returns the lane's finding.
 struct Place {
   int x, y, z, tid;       // block and thread
@@ -305,7 +307,7 @@ __device__ inline void run_split(Work work) {
 template <int NT> constexpr int kRowsR = 32 * ((NT + 1) / 2);    // whole 32-row steps of the second product
 
 // SPLIT: products of split operands, the tile as three bf16 planes; returns whether one of them was
-// an infinity or a NaN.
+// an infinity or a NaN, or an operand too small to be split.
 template <int NT, int D, typename TIn, bool LAST, bool VEC, bool SPLIT>
 __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, float* tile) {
   constexpr int NTHR = 64 * NT, ROWS = SPLIT ? kRowsR<NT> : 16 * NT, STAGED = 16 * NT;
@@ -326,16 +328,17 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
   const size_t NKtot = (size_t)p.ntk * b1;
 
   const int j = 16 * wave + c, jc = j < b2 ? j : b2 - 1;
+  Watch watch;
   Rows32<D, STAGED, NTHR, VEC, TIn> rk, rv;
   rk.load(Kp, [&](int r) { return axis_offset(p.cmap, bn * b2 + r) * p.ks.token; }, b2, d, tid);
   Query32<D, SPLIT> q;
-  if (first) q.template load<VEC>(Qp + axis_offset(p.cmap, bq * b2 + jc) * p.qs.token, d, g);
-  else q.template load<VEC>((const float*)p.aR + ((((size_t)bhl * p.ntq + ml) * NKtot + nk) * b2 + jc) * d, d, g);
+  if (first) q.template load<VEC>(Qp + axis_offset(p.cmap, bq * b2 + jc) * p.qs.token, d, g, watch);
+  else q.template load<VEC>((const float*)p.aR + ((((size_t)bhl * p.ntq + ml) * NKtot + nk) * b2 + jc) * d, d, g, watch);
   auto load_v = [&]() {
     if (LAST) rv.load(Vp, [&](int r) { return axis_offset(p.cmap, bn * b2 + r) * p.vs.token; }, b2, d, tid);
   };
   if (EARLY_V) load_v();
-  rk.template store<SPLIT, ROWS>(tile, b2, d, tid);
+  rk.template store<SPLIT, ROWS>(tile, b2, d, tid, watch);
   if constexpr (ROWS > STAGED) {
     // the second half of the last step of the second products: zeros
     constexpr int PIECES = (ROWS - STAGED) * kLdS<D> / 8;
@@ -344,7 +347,6 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
   }
   __syncthreads();
 
-  Watch watch;
   f32x4 s[NT];
   if constexpr (SPLIT) {
 #pragma unroll
@@ -409,7 +411,7 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
   if (j < b2) o.template store<VEC>((float*)p.aL + row * d, 1.0f, g, d);
   if constexpr (LAST) {
     __syncthreads();                  // every wave is done with K: the tile now holds V
-    rv.template store<SPLIT, ROWS>(tile, b2, d, tid);
+    rv.template store<SPLIT, ROWS>(tile, b2, d, tid, watch);
     __syncthreads();
     w.template product<D, ROWS>(tile, o, g, c);
     o.show(watch);
@@ -453,7 +455,7 @@ struct Online32 {
 // NW waves; `wkeys`: the keys from here on are hidden from every query of this wave, which leaves out the
 // chunks that start there (0: the wave owns no query).  `cut`, then every `step` keys: a chunk ends there
 // too (0: nowhere).  bias(key) is subtracted from the scaled logits, hide(key) hides a key from the
-// lane's query.  `watch` sees the logits (SPLIT only).
+// lane's query.  `watch` sees the logits and what is split (SPLIT only).
 template <int D, int NW, bool WITH_V, bool VEC, bool SPLIT, typename TK, typename Bias, typename Hide>
 __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vbase, long long vstride, int nkeys, int d,
                                float scale, const Query32<D, SPLIT>& q, int wkeys, int cut, int step, float* lds, Bias bias,
@@ -478,12 +480,12 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
     if (WITH_V) rv.load(vbase + c0 * vstride, [&](int r) { return r * vstride; }, valid, d, tid);
   };
   auto commit_k = [&](float* slot) {
-    rk.template store<SPLIT>(slot, CH, d, tid);
+    rk.template store<SPLIT>(slot, CH, d, tid, watch);
     if (tid < CH) slot[BIAS + tid] = rb;
   };
   // value rows past the end are zeros: a copy of the last one times a weight of zero is NaN where it holds an infinity
   auto commit_v = [&](float* slot, int rows) {
-    if (WITH_V) rv.template store<SPLIT>(slot + KV, rows, d, tid);
+    if (WITH_V) rv.template store<SPLIT>(slot + KV, rows, d, tid, watch);
   };
   fetch_k(0);
   if constexpr (SPLIT) {
@@ -610,12 +612,12 @@ __device__ inline bool stage_l_out_32(const Place& at, int l0, const KParams& p,
   const int l = l0 + 16 * wave + c, b1 = col.b1, d = p.d;
   Query32<D, SPLIT> q;
   Out32<D, SPLIT> o;
+  Watch watch;
   // rows beyond b1 repeat the last one and are not stored
-  q.template load<VEC>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g);
+  q.template load<VEC>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
   o.clear();
   Online32 st;
   const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
-  Watch watch;
   flash32<D, NW, true, VEC, SPLIT>(col.aL, d, col.Y, d, col.NK, d, p.scale, q, l0 + 16 * wave < b1 ? col.NK : 0, 0, 0, lds,
                             [&](int key) { return col.cL[key]; }, [&](int key) { return key >= lim; }, st, o, watch, tid);
   o.show(watch);
@@ -647,6 +649,7 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   const int l = l0 + 16 * wave + c, b1 = col.b1, d = p.d, NK = col.NK, nch = (NK + 31) >> 5;
   float* bias = lds + 2 * SLOT;          // [16 NT]
   Rows32<D, 32, NTHR, true, float> rows;
+  Watch watch;
   // chunk i of alpha_L, then of Y (i >= nch)
   auto fetch = [&](int i) {
     const int r0 = 32 * (i < nch ? i : i - nch);
@@ -654,7 +657,7 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   };
   auto commit = [&](int i) {
     const int left = NK - 32 * (i < nch ? i : i - nch);
-    rows.template store<true>(lds + (i & 1) * SLOT, left < 32 ? left : 32, d, tid);      // rows past the end: zeros
+    rows.template store<true>(lds + (i & 1) * SLOT, left < 32 ? left : 32, d, tid, watch);      // rows past the end: zeros
   };
   // chunk i is done: i + 1 goes to the other slot, i + 2 is requested
   auto advance = [&](int i) {
@@ -664,11 +667,10 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   };
   fetch(0);
   for (int i = tid; i < 16 * NT; i += NTHR) bias[i] = i < NK ? -col.cL[i] : -INFINITY;
-  Watch watch;
   f32x4 z[NT];
   {
     Query32<D, true> q;
-    q.template load<true>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g);
+    q.template load<true>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
     commit(0);
     fetch(1);
     __syncthreads();
@@ -734,7 +736,8 @@ __global__ __launch_bounds__(64 * NW, NW > 4 ? 4 : 3) void k_f32_stage_l_out_res
 // The Q tile of a column in LDS: NLT * 16 rows (ROWS: the planes' stride where it is split), those
 // beyond b1 zero.
 template <int D, int ROWS, bool VEC, bool SPLIT, typename TIn>
-__device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, int rows, int b1, int d, int tid, int nthr) {
+__device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, int rows, int b1, int d, int tid, int nthr,
+                                 Watch& watch) {
   constexpr int CPR = D / 4, BATCH = 8;
   const int total = rows * CPR;
   for (int i0 = tid; i0 < total; i0 += BATCH * nthr) {
@@ -753,6 +756,7 @@ __device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, 
         else *(f32x4*)(Qs + r * kLd<D> + 4 * (idx % CPR)) = x;
       }
     }
+    if constexpr (SPLIT) watch.see_split(v);
   }
 }
 
@@ -796,8 +800,8 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
   f32x4 z[NLT];
   Watch watch;
   Query32<D, SPLIT> first;
-  first.template load<VEC>(col.aL + (size_t)nkc * d, d, g);
-  stage_q32<D, LROWS, VEC, SPLIT>(Qs, col.Q, tile_rows(p, col.a, p.qs.token), LROWS, b1, d, tid, nthr);
+  first.template load<VEC>(col.aL + (size_t)nkc * d, d, g, watch);
+  stage_q32<D, LROWS, VEC, SPLIT>(Qs, col.Q, tile_rows(p, col.a, p.qs.token), LROWS, b1, d, tid, nthr, watch);
   __syncthreads();
 
   auto logits = [&](const Query32<D, SPLIT>& kb) {
@@ -872,7 +876,7 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
     Query32<D, SPLIT> kb;               // read again rather than kept (nor its addresses)
     int again = nkc;
     asm("" : "+v"(again));
-    kb.template load<VEC>(col.aL + (size_t)again * d, d, g);
+    kb.template load<VEC>(col.aL + (size_t)again * d, d, g, watch);
     logits(kb);
     float cm = -INFINITY;
 #pragma unroll
@@ -930,7 +934,7 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
   {
     Query32<D, SPLIT> q;
     Out32<D, SPLIT> o;
-    q.template load<VEC>(col.Q + qrow(l < b1 ? l : b1 - 1), d, g);
+    q.template load<VEC>(col.Q + qrow(l < b1 ? l : b1 - 1), d, g, watch);
     Online32 st;
     const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
     flash32<D, NW, false, VEC, SPLIT>(col.aL, d, col.aL, d, NK, d, p.scale, q, 16 * wave < b1 ? NK : 0, 0, 0, dyn,
@@ -939,12 +943,12 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
     if (wave < nlt && g == 0) lse[l] = st.m + logf(lsum);
   }
   __syncthreads();
-  stage_q32<D, MAXROWS, VEC, SPLIT>(Qs, col.Q, qrow, 32 * ((nlt + 1) / 2), b1, d, tid, 64 * NW);
+  stage_q32<D, MAXROWS, VEC, SPLIT>(Qs, col.Q, qrow, 32 * ((nlt + 1) / 2), b1, d, tid, 64 * NW, watch);
   __syncthreads();
   for (int t = wave; 16 * t < NK; t += NW) {
     const int nk = 16 * t + c, nkc = nk < NK ? nk : NK - 1;
     Query32<D, SPLIT> kb;
-    kb.template load<VEC>(col.aL + (size_t)nkc * d, d, g);
+    kb.template load<VEC>(col.aL + (size_t)nkc * d, d, g, watch);
     const float cl = col.cL[nkc];
     // log L[l, nk] of query tiles lt and lt + 1 (rows beyond b1 and hidden keys: -inf)
     auto logits = [&](int lt, f32x4 (&z)[2]) {
@@ -1040,7 +1044,8 @@ __device__ inline bool dense_32(const Place& at, const KParams& p, float* lds) {
   const int qi = q0 + 16 * wave + c, qc = qi < p.Nq ? qi : p.Nq - 1;
   Query32<D, SPLIT> q;
   Out32<D, SPLIT> o;
-  q.template load<VEC>(Qp + (long long)qc * p.qs.token, d, g);
+  Watch watch;
+  q.template load<VEC>(Qp + (long long)qc * p.qs.token, d, g, watch);
   o.clear();
   // the keys query row r sees: a prefix, up to the end of its own chunk
   auto visible = [&](int r) {
@@ -1055,7 +1060,6 @@ __device__ inline bool dense_32(const Place& at, const KParams& p, float* lds) {
   Online32 st;
   // chunks end where a query of this workgroup stops seeing keys: a wave whose queries stop there leaves the
   // next chunk out, and no value hidden from all of them gets to meet their weights of zero (0 x inf)
-  Watch watch;
   flash32<D, kDenseWaves32, true, VEC, SPLIT>(Kp, p.ks.token, Vp, p.vs.token, nkeys, d, p.scale, q, wkeys, MASKED ? visible(q0) : 0,
                                        MASKED ? p.cc * p.hw : 0, lds, [](int) { return 0.f; },
                                        [&](int key) { return MASKED && key >= lim; }, st, o, watch, tid);

@@ -1,13 +1,15 @@
-// fp32 products on the bf16 matrix unit.  An fp32 number is the sum of three bf16 numbers, exactly:
-// h its rounding, m the rounding of what is left, l the rest (24 significant bits in 8 + 8 + 8, each
-// part within half a unit of the one before).  Of the nine products of two such sums six are formed
-// (h h, h m, m h, m m, h l, l h); the three left out are below 2^-25 of the product and change sign
-// with the roundings.  One 32-deep step of six products takes the matrix unit 96 clocks where
-// fp32 operands take 256, and unlike fp32 products they leave the vector ALU to a SIMD's other waves.
+// fp32 products on the bf16 matrix unit.  An fp32 number of magnitude 2^-100 to 2^127 is the sum of three
+// bf16 numbers, exactly: h its rounding, m the rounding of what is left, l the rest (24 significant bits in
+// 8 + 8 + 8, each part within half a unit of the one before).  Of the nine products of two such sums six are
+// formed (h h, h m, m h, m m, h l, l h); each of the three left out is at most about 2^-25 of the product,
+// their sum 2^-24, and they change sign with the roundings.  One 32-deep step of six products takes the
+// matrix unit 96 clocks where fp32 operands take 256, and unlike fp32 products they leave the vector ALU to
+// a SIMD's other waves.
 //
 // Infinities have no such sum (their m is inf - inf), and a number within 2^-9 of the largest has an
-// infinite h.  Both end as a NaN or an infinity in a product: every user looks at what it formed
-// (`Watch`) and, if it meets one, does the work again with fp32 operands.
+// infinite h: both end as a NaN or an infinity in a product.  Numbers below 2^-100 are seen as they are
+// split: from 2^-102 on l may be a bf16 subnormal, from 2^-110 on it may be none at all.  Every user looks at
+// both (`Watch`) and, if it meets one, does the work again with fp32 operands.
 #pragma once
 #include "mrt_bf16_tiles.hpp"
 
@@ -45,18 +47,41 @@ __device__ inline Split8 split8(f32x4 a, f32x4 b) {
 }
 
 // Was one of the numbers seen an infinity or a NaN?  Times zero, either is a NaN, which a sum keeps.  (The
-// zero and the sum's bits are opaque: the library is built without honouring NaNs.)
+// zero and the sum's bits are opaque: the library is built without honouring NaNs.)  And was a number that
+// was split too small for it?  The magnitudes' minimum costs half an instruction a number; only a wave that
+// finds a zero or less than 2^-100 tells the two apart.
 struct Watch {
   float zero = 0.f, sum = 0.f;
+  bool small = false;               // the same in all lanes
   __device__ inline Watch() { asm("" : "+s"(zero)); }
   __device__ inline void see(f32x4 x) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) sum = fmaf(x[r], zero, sum);
   }
+  // (called once the numbers are split, so that the first do not wait for the last)
+  template <int N>
+  __device__ inline void see_split(const f32x4 (&v)[N]) {
+    const float bound = 0x1p-100f;
+    float least = 1.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) least = fminf(fminf(fabsf(v[i][e]), fabsf(v[i][e + 1])), least);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < bound) == 0, 1)) return;
+    unsigned nonzero = ~0u;         // twice the least magnitude's bits, less one: zeros wrap to the largest
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned twice = (__float_as_uint(v[i][e]) << 1) - 1u;
+        nonzero = twice < nonzero ? twice : nonzero;
+      }
+    if (__builtin_amdgcn_ballot_w64(nonzero < (__float_as_uint(bound) << 1) - 1u) != 0) small = true;
+  }
   __device__ inline bool unusual() const {
     unsigned bits = __float_as_uint(sum);
     asm("" : "+v"(bits));
-    return (bits & 0x7fffffffu) >= 0x7f800000u;
+    return small || (bits & 0x7fffffffu) >= 0x7f800000u;
   }
 };
 

@@ -1,0 +1,88 @@
+"""The fp32 path over the whole range of fp32 numbers: inputs whose bf16 parts would fall below the smallest
+bf16 number.  Products of split operands (aligned rows) have to return what products of fp32 operands return
+(rows that start one element off).
+
+Bar of the 2-norm comparisons: that of the other fp32 tests, 5e-6."""
+import pytest
+import torch
+
+import paper_2602_12271_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+REL = 5e-6
+
+# f, h, w, b1, b2, tile, iters, d, heads, causal chunk
+SIZES = {
+    "three-tiles-40x33": (1, 40, 33, 40, 33, 0, 2, 128, 8, 0),
+    "wave-of-six-90x52": (3, 30, 52, 90, 52, 0, 2, 128, 2, 0),
+    "97-keys-two-parts": (1, 97, 20, 97, 20, 0, 2, 128, 2, 0),
+    "refine-of-twelve-d64": (1, 192, 17, 192, 17, 0, 2, 64, 2, 0),
+    "streamed-four-tiles": (2, 50, 48, 50, 24, 1, 2, 128, 2, 0),
+    "regular-mask-d36": (6, 7, 34, 42, 34, 0, 2, 36, 4, 2),
+    "dense": (2, 9, 13, 0, 0, 0, 0, 128, 2, 0),
+    "dense-masked": (6, 9, 13, 0, 0, 0, 0, 64, 2, 2),
+}
+
+
+def call(size, q, k, v, scale, out):
+    f, h, w, b1, b2, tile, iters, d, heads, chunk = size
+    args = dict(f_q=f, f_kv=f, h=h, w=w, causal_chunk=chunk, scale=scale, out=out)
+    if iters == 0:
+        return pkg.dense_attn_fwd(q, k, v, **args)
+    return pkg.monarch_attn_fwd(q, k, v, b1=b1, b2=b2, tile=tile, iters=iters, **args)
+
+
+def both(size, q, k, v, scale):
+    """The call on aligned tensors and on ones that start one element off."""
+    outs = []
+    for shift in (0, 1):
+        dev = [torch.zeros(x.numel() + 4, device="cuda:0")[shift:shift + x.numel()].view(x.shape).copy_(x) for x in (q, k, v)]
+        out = torch.zeros(q.numel() + 4, device="cuda:0")[shift:shift + q.numel()].view(q.shape)
+        outs.append(call(size, *dev, scale, out))
+    torch.cuda.synchronize()
+    return outs
+
+
+def inputs(size, seed):
+    f, h, w, d, heads = size[0], size[1], size[2], size[7], size[8]
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    return [torch.randn(1, heads, f * h * w, d, generator=gen, device="cuda:0") for _ in range(3)]
+
+
+def assert_same(split, plain):
+    assert torch.isfinite(plain).all() and plain.abs().max() > 0
+    a, b = (x.double().flatten(0, -2) for x in (split, plain))
+    err = ((a - b).norm(dim=0) / b.norm(dim=0)).max().item()
+    print(f"  rel {err:.2e}", flush=True)
+    assert err <= REL
+
+
+@pytest.mark.parametrize("factor", [1e-28, 1e-31, 1e-34, 1e-36])
+@pytest.mark.parametrize("name", list(SIZES))
+def test_tiny_values(name, factor):
+    size = SIZES[name]
+    q, k, v = inputs(size, 5)
+    print(f"{name} {factor}", flush=True)
+    assert_same(*both(size, q, k, factor * v, size[7] ** -0.5))
+
+
+@pytest.mark.parametrize("name", list(SIZES))
+def test_a_few_tiny_values_of_one_feature(name):
+    size = SIZES[name]
+    q, k, v = inputs(size, 6)
+    v[:, :, :, 2] *= 3e-36
+    v[:, :, ::3, 2] = 0
+    print(name, flush=True)
+    assert_same(*both(size, q, k, v, size[7] ** -0.5))
+
+
+@pytest.mark.parametrize("which", ["keys", "queries"])
+@pytest.mark.parametrize("name", list(SIZES))
+def test_tiny_keys_or_queries_against_huge_ones(name, which):
+    # logits of order one
+    size = SIZES[name]
+    q, k, v = inputs(size, 7)
+    q, k = (q * 1e30, k * 1e-35) if which == "keys" else (q * 1e-35, k * 1e30)
+    print(f"{name} {which}", flush=True)
+    assert_same(*both(size, q, k, v, 1e5 * size[7] ** -0.5))
