@@ -398,24 +398,25 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
     }
   sum = xsum(sum);
   ent = xsum(ent);
+  constexpr float W = SPLIT ? kWeight : 1.f;
   const float inv = 1.0f / sum;
   const size_t row = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot + nk;
-  if (g == 0 && j < b2) p.cL[row] = ent * inv - logf(sum);
+  if (g == 0 && j < b2) p.cL[row] = ent * inv - logf(sum * (1.f / W));
 #pragma unroll
-  for (int it = 0; it < NT; ++it) s[it] = s[it] * inv;
+  for (int it = 0; it < NT; ++it) s[it] = s[it] * (inv * W);
 
   Weights32<NT, SPLIT> w(s);
   Out32<D, SPLIT> o;
   w.template product<D, ROWS>(tile, o, g, c);
   o.show(watch);
-  if (j < b2) o.template store<VEC>((float*)p.aL + row * d, 1.0f, g, d);
+  if (j < b2) o.template store<VEC>((float*)p.aL + row * d, 1.f / W, g, d);
   if constexpr (LAST) {
     __syncthreads();                  // every wave is done with K: the tile now holds V
     rv.template store<SPLIT, ROWS>(tile, b2, d, tid, watch);
     __syncthreads();
     w.template product<D, ROWS>(tile, o, g, c);
     o.show(watch);
-    if (j < b2) o.template store<VEC>((float*)p.Y + row * d, 1.0f, g, d);
+    if (j < b2) o.template store<VEC>((float*)p.Y + row * d, 1.f / W, g, d);
   }
   return watch.unusual();
 }
@@ -449,7 +450,7 @@ constexpr int kRing32 = max_of(VEC ? kSlot32<D, WITH_V, true> : 0, 2 * kSlot32<D
 constexpr float kGrow32 = 8.0f;   // the reference is raised when a logit exceeds it by more than this
 
 struct Online32 {
-  float m = -INFINITY, l = 0.f;   // reference (same in the four lanes of a query), this lane's sum
+  float m = -INFINITY, l = 0.f;   // reference (same in the four lanes of a query), this lane's sum (SPLIT: with the weights' factor)
 };
 
 // NW waves; `wkeys`: the keys from here on are hidden from every query of this wave, which leaves out the
@@ -762,9 +763,10 @@ __device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, 
 
 // A column sum of weights below this may have lost terms to underflow: alpha_R / c_R is then formed
 // from the weights relative to the column's maximum (the same ratio).
-constexpr float kTinySum = 0x1p-80f;
+template <bool SPLIT> constexpr float kTinySum = 0x1p-80f * (SPLIT ? kWeight : 1.f);
 
-// alpha_R / c_R of the lane's key column and, for the backward pass, the statistics behind it.
+// alpha_R / c_R of the lane's key column and, for the backward pass, the statistics behind it.  `o` and
+// `csum` have the weights' factor.
 template <int D, bool VEC, bool SPLIT, typename TIn>
 __device__ inline void store_abar(const KParams& p, const Column32<TIn>& col, int nk, const Out32<D, SPLIT>& o,
                                   float csum, float shift, Watch& watch, int g) {
@@ -773,7 +775,7 @@ __device__ inline void store_abar(const KParams& p, const Column32<TIn>& col, in
   o.template store<VEC>((float*)p.aR + at * p.d, 1.0f / csum, g, p.d);
   if (p.cmx_out != nullptr && g == 0) {
     p.cmx_out[at] = shift;
-    p.cinv_out[at] = 1.0f / csum;
+    p.cinv_out[at] = (SPLIT ? kWeight : 1.f) / csum;
   }
   o.show(watch);
 }
@@ -855,13 +857,14 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
   }
   __syncthreads();
   // per row: log-sum-exp and, in place of every wave's sum, what turns its exponentials into weights
+  constexpr float W = SPLIT ? kWeight : 1.f;
   for (int l = tid; l < LROWS; l += nthr) {
     float M = -INFINITY, S = 0.f;
     for (int w = 0; w < nw; ++w) M = fmaxf(M, red_m[w * LROWS + l]);
     const float Ms = M == -INFINITY ? 0.f : M;
     for (int w = 0; w < nw; ++w) S = fmaf(red_s[w * LROWS + l], expf(red_m[w * LROWS + l] - Ms), S);
-    lse[l] = Ms + logf(S);
-    const float inv = l < b1 ? 1.0f / S : 0.f;
+    lse[l] = Ms + logf(S * (1.f / W));
+    const float inv = l < b1 ? W / S : 0.f;
     for (int w = 0; w < nw; ++w) red_s[w * LROWS + l] = expf(red_m[w * LROWS + l] - Ms) * inv;
   }
   __syncthreads();
@@ -872,7 +875,7 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
     csum += (z[lt][0] + z[lt][1]) + (z[lt][2] + z[lt][3]);
   }
   csum = xsum(csum);
-  if (__builtin_expect(__any(nk < NK && !(csum > kTinySum)), 0)) {
+  if (__builtin_expect(__any(nk < NK && !(csum > kTinySum<SPLIT>)), 0)) {
     Query32<D, SPLIT> kb;               // read again rather than kept (nor its addresses)
     int again = nkc;
     asm("" : "+v"(again));
@@ -894,7 +897,7 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
     for (int lt = 0; lt < NLT; ++lt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        z[lt][r] = expf(z[lt][r] - shift);
+        z[lt][r] = SPLIT ? exp_near(z[lt][r] - shift) : expf(z[lt][r] - shift);
         csum += z[lt][r];
       }
     csum = xsum(csum);
@@ -940,7 +943,7 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
     flash32<D, NW, false, VEC, SPLIT>(col.aL, d, col.aL, d, NK, d, p.scale, q, 16 * wave < b1 ? NK : 0, 0, 0, dyn,
                                [&](int key) { return col.cL[key]; }, [&](int key) { return key >= lim; }, st, o, watch, tid);
     const float lsum = xsum(st.l);
-    if (wave < nlt && g == 0) lse[l] = st.m + logf(lsum);
+    if (wave < nlt && g == 0) lse[l] = st.m + logf(lsum * (SPLIT ? 1.f / kWeight : 1.f));
   }
   __syncthreads();
   stage_q32<D, MAXROWS, VEC, SPLIT>(Qs, col.Q, qrow, 32 * ((nlt + 1) / 2), b1, d, tid, 64 * NW, watch);
@@ -998,7 +1001,7 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
       csum = xsum(csum);
     };
     run();
-    if (__builtin_expect(__any(nk < NK && !(csum > kTinySum)), 0)) {
+    if (__builtin_expect(__any(nk < NK && !(csum > kTinySum<SPLIT>)), 0)) {
       float cm = -INFINITY;
       for (int lt = 0; lt < nlt; lt += 2) {
         f32x4 z[2];

@@ -1,8 +1,9 @@
 """The fp32 path over the whole range of fp32 numbers: inputs whose bf16 parts would fall below the smallest
-bf16 number.  Products of split operands (aligned rows) have to return what products of fp32 operands return
-(rows that start one element off).
+bf16 number, weights of the softmaxes down to the smallest fp32 number.  Products of split operands (aligned
+rows) have to return what products of fp32 operands return (rows that start one element off).
 
-Bar of the 2-norm comparisons: that of the other fp32 tests, 5e-6."""
+Bar of the 2-norm comparisons: that of the other fp32 tests, 5e-6.  Single weights e^-z carry the rounding of
+their logit, z 2^-24 relative and as much again per product of the dot product: 1e-4 at z = 87 is 20 of them."""
 import pytest
 import torch
 
@@ -86,3 +87,44 @@ def test_tiny_keys_or_queries_against_huge_ones(name, which):
     q, k = (q * 1e30, k * 1e-35) if which == "keys" else (q * 1e-35, k * 1e30)
     print(f"{name} {which}", flush=True)
     assert_same(*both(size, q, k, v, 1e5 * size[7] ** -0.5))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_every_weight_of_the_dense_softmax(d):
+    # value row i has a one at feature i: the output is the matrix of the weights, e^0 .. e^-103
+    n = 64
+    q = torch.zeros(1, 2, n, d, device="cuda:0")
+    k, v = torch.zeros_like(q), torch.zeros_like(q)
+    q[..., 0] = 1 + torch.arange(n, device="cuda:0") / n
+    k[..., 0] = -51.5 * torch.arange(n, device="cuda:0") / n
+    v[:, :, torch.arange(n), torch.arange(n)] = 1
+    split, plain = both((1, 8, 8, 0, 0, 0, 0, d, 2, 0), q, k, v, 1.0)
+    expect = torch.softmax(torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()), -1)
+    for out in (split, plain):
+        w = out[..., :n].double()
+        normal = expect > 2.0 ** -125
+        assert ((w - expect).abs() <= 1e-4 * expect)[normal].all()
+        assert ((w - expect).abs() <= 2.0 ** -140)[~normal].all()
+
+
+@pytest.mark.parametrize("name,rows,cols", [("weights-of-r", 40, 64), ("weights-of-l", 64, 40), ("weights-of-l-streamed", 48, 40),
+                                            ("weights-of-l-wide", 128, 40)])
+def test_every_weight_of_one_iteration(name, rows, cols):
+    # the values of one block column (or row) are ones at their own feature, the others zeros
+    f = 3 if name.endswith("streamed") else 1
+    d, n = 128, rows * cols
+    heads = 8
+    x, y = torch.arange(f * n, device="cuda:0") // cols, torch.arange(f * n, device="cuda:0") % cols
+    along = y if name == "weights-of-r" else x
+    length = cols if name == "weights-of-r" else f * rows
+    q = torch.zeros(1, heads, f * n, d, device="cuda:0")
+    k, v = torch.zeros_like(q), torch.zeros_like(q)
+    q[..., 0] = 1.0
+    k[..., 0] = -103.0 * along / length
+    v[:, :, torch.arange(f * n), along % d] = 1
+    size = (f, rows, cols, rows, cols, 1 if f > 1 else 0, 1, d, heads, 0)
+    split, plain = both(size, q, k, v, 1.0)
+    assert plain.min() < 1e-30
+    normal = plain > 2.0 ** -125
+    assert ((split - plain).abs() <= 1e-4 * plain)[normal].all()
+    assert ((split - plain).abs() <= 2.0 ** -140)[~normal].all()
