@@ -127,7 +127,8 @@ size_t monarch_attn_workspace_bytes(const mrt_problem* p, int b1, int b2, int ti
 
 /* MonarchRT attention forward (Alg. 1 for tile = 0, Alg. 2 for tile = 1).
  *   Q [batch, heads, N_q, head_dim], K, V [batch, heads, N_kv, head_dim], O like Q; device
- *   memory, element strides in p.  O is fully overwritten.  workspace: device memory, 256-byte
+ *   memory, element strides in p.  O is fully overwritten.  O may be Q itself, with Q's strides (a
+ *   workgroup reads its rows of Q before it writes them); it overlaps no other input.  workspace: device memory, 256-byte
  *   aligned, contents undefined on entry and exit.  hip_stream: a hipStream_t (NULL = the
  *   default stream).  Calls sharing a workspace must be ordered on one stream.
  *   Accuracy.  MRT_F32 storage (and MRT_COMPUTE_F32): O differs from the exact result of App. A's
@@ -222,7 +223,7 @@ mrt_status monarch_attn_bwd_saved(const void* Q, const void* K, const void* V, c
 
 /* Dense baseline  O = softmax(scale * Q K^T + mask) V  (Sec. 2.2), flash-style, no workspace.
  * causal_chunk > 0 masks, per token, keys whose frame's chunk is later than the query frame's
- * chunk (query frames offset by q_frame_offset). */
+ * chunk (query frames offset by q_frame_offset).  O may be Q itself, as for monarch_attn_fwd. */
 mrt_status dense_attn_check(const mrt_problem* p, int causal_chunk);
 mrt_status dense_attn_fwd(const void* Q, const void* K, const void* V, void* O,
                           const mrt_problem* p, int causal_chunk, void* hip_stream);

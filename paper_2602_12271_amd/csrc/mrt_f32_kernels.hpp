@@ -274,8 +274,10 @@ struct Weights32<NT, true> {
 };
 
 // A workgroup's work with split operands and, if a product was an infinity or a NaN or an operand too small
-// to be split anywhere in it, once more with fp32 operands: the second run writes every result again.  work(std::bool_constant)
-// returns the lane's finding.
+// to be split anywhere in it, once more with fp32 operands.  work(std::bool_constant, place, again) passes
+// what it saw to again(watch) and returns the answer, the same in all threads: whether it will be called once
+// more.  Results that may take the place of an input (O that of Q) are stored after the question; others may
+// be stored before, as the second run writes them again.
 struct Place {
   int x, y, z, tid;       // block and thread
 };
@@ -283,16 +285,18 @@ template <bool SPLIT, typename Work>
 __device__ inline void run_split(Work work) {
   Place at{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)threadIdx.x};
   if constexpr (SPLIT) {
-    __shared__ int again;
-    if (threadIdx.x == 0) again = 0;       // seen by all after the first of the work's barriers
-    const bool bad = work(std::true_type{}, at);
-    if (__builtin_amdgcn_ballot_w64(bad) != 0) again = 1;
-    __syncthreads();
-    if (__builtin_expect(again == 0, 1)) return;
+    __shared__ int found;
+    if (threadIdx.x == 0) found = 0;       // seen by all after the first of the work's barriers
+    auto again = [&](const Watch& watch) {
+      if (__builtin_amdgcn_ballot_w64(watch.unusual()) != 0) found = 1;
+      __syncthreads();
+      return found != 0;
+    };
+    if (__builtin_expect(!work(std::true_type{}, at, again), 1)) return;
     // an opaque copy: addresses are formed again instead of kept in registers through the first run
     asm("" : "+s"(at.x), "+s"(at.y), "+s"(at.z), "+v"(at.tid));
   }
-  work(std::false_type{}, at);
+  work(std::false_type{}, at, [](const Watch&) { return false; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -306,10 +310,9 @@ __device__ inline void run_split(Work work) {
 // ---------------------------------------------------------------------------------------
 template <int NT> constexpr int kRowsR = 32 * ((NT + 1) / 2);    // whole 32-row steps of the second product
 
-// SPLIT: products of split operands, the tile as three bf16 planes; returns whether one of them was
-// an infinity or a NaN, or an operand too small to be split.
-template <int NT, int D, typename TIn, bool LAST, bool VEC, bool SPLIT>
-__device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, float* tile) {
+// SPLIT: products of split operands, the tile as three bf16 planes.
+template <int NT, int D, typename TIn, bool LAST, bool VEC, bool SPLIT, typename Again>
+__device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, float* tile, Again again) {
   constexpr int NTHR = 64 * NT, ROWS = SPLIT ? kRowsR<NT> : 16 * NT, STAGED = 16 * NT;
   constexpr bool EARLY_V = !SPLIT || NT * D <= 128;      // there are registers for the values beside the operand
   const int tid = at.tid, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -418,7 +421,7 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
     o.show(watch);
     if (j < b2) o.template store<VEC>((float*)p.Y + row * d, 1.f / W, g, d);
   }
-  return watch.unusual();
+  return again(watch);
 }
 
 template <int NT, int D, typename TIn, bool LAST, bool VEC, bool SPLIT>
@@ -430,7 +433,9 @@ __global__ __launch_bounds__(64 * NT, 3) void k_f32_stage_r(KParams p, int first
     const int an = (int)blockIdx.x / p.b1 / p.c2, a = (p.m0 + (int)blockIdx.y) / p.c2;
     if (an >= visible_key_tile_rows(a, p.c1k, p.ct, p.qt0)) return;
   }
-  run_split<SPLIT>([&](auto split, const Place& at) { return stage_r_32<NT, D, TIn, LAST, VEC, decltype(split)::value>(at, p, first, tile); });
+  run_split<SPLIT>([&](auto split, const Place& at, auto again) {
+    return stage_r_32<NT, D, TIn, LAST, VEC, decltype(split)::value>(at, p, first, tile, again);
+  });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -606,8 +611,8 @@ struct Column32 {
 // stage L, last iteration:  Z_L[l,nk] = scale * sum_v alpha_L[nk,v] Q[m,l,j,v] - c_L[nk];
 // L = softmax over visible nk;  O[l,:] = sum_nk L[l,nk] Y[nk,:].  NW >= ceil(b1 / 16) waves.
 // ---------------------------------------------------------------------------------------
-template <int NW, int D, typename TIn, bool VEC, bool SPLIT>
-__device__ inline bool stage_l_out_32(const Place& at, int l0, const KParams& p, float* lds) {
+template <int NW, int D, typename TIn, bool VEC, bool SPLIT, typename Again>
+__device__ inline bool stage_l_out_32(const Place& at, int l0, const KParams& p, float* lds, Again again) {
   const int tid = at.tid, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
   const Column32<TIn> col(at, p);
   const int l = l0 + 16 * wave + c, b1 = col.b1, d = p.d;
@@ -623,16 +628,17 @@ __device__ inline bool stage_l_out_32(const Place& at, int l0, const KParams& p,
                             [&](int key) { return col.cL[key]; }, [&](int key) { return key >= lim; }, st, o, watch, tid);
   o.show(watch);
   const float lsum = xsum(st.l);
+  if (again(watch)) return true;
   const TokRows orow = tile_rows(p, col.a, p.os.token);
   if (l < b1) o.template store<VEC>(col.O + orow(l), 1.0f / lsum, g, d);
-  return watch.unusual();
+  return false;
 }
 // fp32 operands; with split operands: longer key ranges than the kernel below takes
 template <int NW, int D, typename TIn, bool VEC, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, NW > 8 ? 3 : (NW > 2 ? 4 : 2)) void k_f32_stage_l_out(KParams p) {
   __shared__ __attribute__((aligned(16))) float lds[kRing32<D, true, SPLIT>];
-  run_split<SPLIT>([&](auto split, const Place& at) {
-    return stage_l_out_32<NW, D, TIn, VEC, decltype(split)::value>(at, 0, p, lds);
+  run_split<SPLIT>([&](auto split, const Place& at, auto again) {
+    return stage_l_out_32<NW, D, TIn, VEC, decltype(split)::value>(at, 0, p, lds, again);
   });
 }
 
@@ -642,8 +648,8 @@ __global__ __launch_bounds__(64 * NW, NW > 8 ? 3 : (NW > 2 ? 4 : 2)) void k_f32_
 // 32 rows through two LDS slots, alpha_L first: every logit stays in registers, the softmax is formed
 // once, then the rows of Y pass.  One chunk is in registers between global memory and LDS.
 // ---------------------------------------------------------------------------------------
-template <int NW, int NT, int D, typename TIn>
-__device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams& p, float* lds) {
+template <int NW, int NT, int D, typename TIn, typename Again>
+__device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams& p, float* lds, Again again) {
   constexpr int NTHR = 64 * NW, SLOT = 32 * kRowFloats<D>;
   const int tid = at.tid, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
   const Column32<TIn> col(at, p);
@@ -719,18 +725,19 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
     }
   o.show(watch);
   const float lsum = xsum(sum);
+  if (again(watch)) return true;
   if (l < b1) o.template store<true>(col.O + tile_rows(p, col.a, p.os.token)(l), 1.0f / lsum, g, d);
-  return watch.unusual();
+  return false;
 }
 // `parts` workgroups share a column's rows, 16 NW each
 template <int NW, int NT, int D, typename TIn>
 __global__ __launch_bounds__(64 * NW, NW > 4 ? 4 : 3) void k_f32_stage_l_out_res(KParams p, int parts) {
   __shared__ __attribute__((aligned(16))) float lds[max_of(2 * 32 * kRowFloats<D> + 16 * NT, 2 * kSlot32<D, true, false>)];
-  run_split<true>([&](auto split, const Place& at) {
+  run_split<true>([&](auto split, const Place& at, auto again) {
     const int j = at.x / parts, l0 = 16 * NW * (at.x - j * parts);
     const Place of{j, at.y, at.z, at.tid};
-    if constexpr (decltype(split)::value) return stage_l_out_res_32<NW, NT, D, TIn>(of, l0, p, lds);
-    else return stage_l_out_32<NW, D, TIn, true, false>(of, l0, p, lds);
+    if constexpr (decltype(split)::value) return stage_l_out_res_32<NW, NT, D, TIn>(of, l0, p, lds, again);
+    else return stage_l_out_32<NW, D, TIn, true, false>(of, l0, p, lds, again);
   });
 }
 
@@ -786,8 +793,8 @@ __device__ inline void store_abar(const KParams& p, const Column32<TIn>& col, in
 // and kept; row statistics are exchanged between the waves, then
 //   alpha_R[nk,:] / c_R[nk] = sum_l L[l,nk] Q[l,:] / sum_l L[l,nk].
 // ---------------------------------------------------------------------------------------
-template <int NLT, int D, typename TIn, bool VEC, bool SPLIT>
-__device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, float* dyn) {
+template <int NLT, int D, typename TIn, bool VEC, bool SPLIT, typename Again>
+__device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, float* dyn, Again again) {
   constexpr int LROWS = 16 * NLT, LD = kLd<D>;
   const int tid = at.tid, nthr = blockDim.x, nw = nthr >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -877,9 +884,9 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
   csum = xsum(csum);
   if (__builtin_expect(__any(nk < NK && !(csum > kTinySum<SPLIT>)), 0)) {
     Query32<D, SPLIT> kb;               // read again rather than kept (nor its addresses)
-    int again = nkc;
-    asm("" : "+v"(again));
-    kb.template load<VEC>(col.aL + (size_t)again * d, d, g, watch);
+    int reread = nkc;
+    asm("" : "+v"(reread));
+    kb.template load<VEC>(col.aL + (size_t)reread * d, d, g, watch);
     logits(kb);
     float cm = -INFINITY;
 #pragma unroll
@@ -906,7 +913,7 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
   const Weights32<NLT, SPLIT> w(z);
   w.template product<D, LROWS>(Qs, o, g, c);
   store_abar<D, VEC>(p, col, nk, o, csum, shift, watch, g);
-  return watch.unusual();
+  return again(watch);
 }
 template <int NLT, int D, bool SPLIT>
 constexpr size_t refine_one_32_lds(int nw) {
@@ -915,7 +922,9 @@ constexpr size_t refine_one_32_lds(int nw) {
 template <int NLT, int D, typename TIn, bool VEC, bool SPLIT>
 __global__ __launch_bounds__(768, NLT > 6 ? 3 : 4) void k_f32_stage_l_refine_one(KParams p) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];
-  run_split<SPLIT>([&](auto split, const Place& at) { return stage_l_refine_one_32<NLT, D, TIn, VEC, decltype(split)::value>(at, p, dyn); });
+  run_split<SPLIT>([&](auto split, const Place& at, auto again) {
+    return stage_l_refine_one_32<NLT, D, TIn, VEC, decltype(split)::value>(at, p, dyn, again);
+  });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -923,8 +932,8 @@ __global__ __launch_bounds__(768, NLT > 6 ? 3 : 4) void k_f32_stage_l_refine_one
 // values), pass 2 deals the key tiles to the waves and forms each tile's logits again, one query
 // tile at a time.  NW >= ceil(b1 / 16) waves.
 // ---------------------------------------------------------------------------------------
-template <int NW, int D, typename TIn, bool VEC, bool SPLIT>
-__device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, float* lse, float* dyn) {
+template <int NW, int D, typename TIn, bool VEC, bool SPLIT, typename Again>
+__device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, float* lse, float* dyn, Again again) {
   constexpr int LD = kLd<D>, MAXROWS = 16 * NW;
   const int tid = at.tid, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
   const Column32<TIn> col(at, p);
@@ -1017,15 +1026,15 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
     }
     store_abar<D, VEC>(p, col, nk, o, csum, shift, watch, g);
   }
-  return watch.unusual();
+  return again(watch);
 }
 template <int NW, int D, bool SPLIT>
 constexpr int kRefineFloats32 = max_of(kRing32<D, false, SPLIT>, 16 * NW * max_of(kLd<D>, SPLIT ? kRowFloats<D> : 0));
 template <int NW, int D, typename TIn, bool VEC, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, 3) void k_f32_stage_l_refine(KParams p) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];
-  run_split<SPLIT>([&](auto split, const Place& at) {
-    return stage_l_refine_32<NW, D, TIn, VEC, decltype(split)::value>(at, p, dyn + kRefineFloats32<NW, D, SPLIT>, dyn);
+  run_split<SPLIT>([&](auto split, const Place& at, auto again) {
+    return stage_l_refine_32<NW, D, TIn, VEC, decltype(split)::value>(at, p, dyn + kRefineFloats32<NW, D, SPLIT>, dyn, again);
   });
 }
 
@@ -1036,8 +1045,8 @@ constexpr int kDenseWaves32 = 8, kDenseQ32 = 16 * kDenseWaves32;
 
 // MASKED: chunk-causal (a kernel of its own: the shorter chunks' bookkeeping costs 4 % of a
 // call at 64 features)
-template <int D, typename TIn, bool VEC, bool MASKED, bool SPLIT>
-__device__ inline bool dense_32(const Place& at, const KParams& p, float* lds) {
+template <int D, typename TIn, bool VEC, bool MASKED, bool SPLIT, typename Again>
+__device__ inline bool dense_32(const Place& at, const KParams& p, float* lds, Again again) {
   const int tid = at.tid, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int q0 = at.x * kDenseQ32, bh = at.y, d = p.d;
   const int b = bh / p.H, hd = bh - b * p.H;
@@ -1068,14 +1077,17 @@ __device__ inline bool dense_32(const Place& at, const KParams& p, float* lds) {
                                        [&](int key) { return MASKED && key >= lim; }, st, o, watch, tid);
   o.show(watch);
   const float lsum = xsum(st.l);
+  if (again(watch)) return true;
   TIn* Op = (TIn*)p.O + b * p.os.batch + hd * p.os.head;
   if (qi < p.Nq) o.template store<VEC>(Op + (long long)qi * p.os.token, lsum > 0.f ? 1.0f / lsum : 0.f, g, d);
-  return watch.unusual();
+  return false;
 }
 template <int D, typename TIn, bool VEC, bool MASKED>
 __global__ __launch_bounds__(64 * kDenseWaves32, 4) void k_f32_dense(KParams p) {
   __shared__ __attribute__((aligned(16))) float lds[kRing32<D, true, VEC>];
-  run_split<VEC>([&](auto split, const Place& at) { return dense_32<D, TIn, VEC, MASKED, decltype(split)::value>(at, p, lds); });
+  run_split<VEC>([&](auto split, const Place& at, auto again) {
+    return dense_32<D, TIn, VEC, MASKED, decltype(split)::value>(at, p, lds, again);
+  });
 }
 
 
