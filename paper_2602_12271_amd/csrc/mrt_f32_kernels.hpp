@@ -393,7 +393,8 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool ok = 16 * it + 4 * g + r < b2;
-      const float z = ok ? s[it][r] - mx : 0.f;
+      // weights of e^-200 are 0; a difference of two huge logits may be infinite, and 0 times it is no entropy
+      const float z = ok ? fmaxf(s[it][r] - mx, -200.f) : 0.f;
       const float e = ok ? (SPLIT ? exp_near(z) : expf(z)) : 0.f;
       sum += e;
       ent = fmaf(e, z, ent);

@@ -128,3 +128,20 @@ def test_every_weight_of_one_iteration(name, rows, cols):
     normal = plain > 2.0 ** -125
     assert ((split - plain).abs() <= 1e-4 * plain)[normal].all()
     assert ((split - plain).abs() <= 2.0 ** -140)[~normal].all()
+
+
+@pytest.mark.parametrize("rows,cols,d,heads", [(24, 24, 64, 1), (40, 33, 128, 8), (90, 52, 128, 2), (10, 16, 64, 2)])
+def test_logits_near_the_largest_number(rows, cols, d, heads):
+    # one key of every block row has the logit 2e38, the others -2e38: R picks it, its entropy is 0, and L weighs
+    # the rows alike, so that the output is the mean of those keys' values over the rows
+    gen = torch.Generator(device="cuda:0").manual_seed(rows)
+    n = rows * cols
+    v = torch.randn(1, heads, n, d, generator=gen, device="cuda:0")
+    q, k = torch.zeros_like(v), torch.zeros_like(v)
+    pick = torch.randint(cols, (heads, rows), generator=gen, device="cuda:0") + cols * torch.arange(rows, device="cuda:0")
+    q[..., 0] = 1.4e19
+    k[..., 0] = -1.43e19
+    k[0, :, :, 0].scatter_(1, pick, 1.43e19)
+    expect = torch.gather(v[0].double(), 1, pick[..., None].expand(-1, -1, d)).mean(1, keepdim=True)
+    for out in both((1, rows, cols, rows, cols, 0, 1, d, heads, 0), q, k, v, 1.0):
+        assert (out[0].double() - expect).norm() <= REL * expect.norm() * n ** 0.5
