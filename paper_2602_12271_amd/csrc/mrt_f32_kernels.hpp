@@ -19,7 +19,7 @@
 // error against 64 bits 3.0e-7 -> 2.7e-7.
 //
 // fp32 operands remain where rows are moved element by element, for the smallest blocks (see run_r) and
-// where a product was an infinity or a NaN or an operand below 2^-100.  The layout feeds the matrix unit from registers and 16-byte
+// where a product was an infinity or a NaN or operands were very small or huge.  The layout feeds the matrix unit from registers and 16-byte
 // LDS reads with nothing in between: lane (g = lane / 16, c = lane % 16) supplies A[c][k = g] and
 // B[k = g][c] of a step and holds C[4g + r][c] in register r.
 //   * First products contract over features, which are contiguous in both operands: with feature
@@ -150,10 +150,12 @@ struct Rows32 {
       v[i] = ld4<VEC>(src + rowoff(r < valid ? r : valid - 1), 4 * (idx % CPR), d);
     }
   }
-  // PLANE: rows from one split plane to the next; `watch` sees what is split
-  template <bool SPLIT = false, int PLANE = ROWS>
+  // PLANE: rows from one split plane to the next; SEE: what `watch` looks for in the rows split
+  template <bool SPLIT, int SEE, int PLANE = ROWS>
   __device__ inline void store(float* dst, int valid, int d, int tid, Watch& watch) {
-    if (valid < ROWS || d < D) {
+    const bool blank = valid < ROWS || d < D;        // (as they were loaded: the zeros are not looked at)
+    if (blank) {
+      if constexpr (SPLIT) watch.see_split<SEE>(v);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const int idx = tid + i * NTHR;
@@ -169,15 +171,17 @@ struct Rows32 {
         else *(f32x4*)(dst + r * kLd<D> + 4 * (idx % CPR)) = x;
       }
     }
-    if constexpr (SPLIT) watch.see_split(v);
+    if constexpr (SPLIT)
+      if (!blank) watch.see_split<SEE>(v);
   }
 };
 
-// A wave's operand of the first product: sixteen rows, lane column c's at `row`.
+// A wave's operand of the first product: sixteen rows, lane column c's at `row`.  SEE: what `watch` looks for
+// in them.
 template <int D, bool SPLIT>
 struct Query32 {
   f32x4 v[D / 16];
-  template <bool VEC, typename T>
+  template <bool VEC, int SEE, typename T>
   __device__ inline void load(const T* row, int d, int g, Watch&) {
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) v[ks] = ld4<VEC>(row, 16 * ks + 4 * g, d);
@@ -190,18 +194,19 @@ struct Query32 {
 template <int D>
 struct Query32<D, true> {
   Split8 v[D / 32];
-  template <bool VEC, typename T>
+  template <bool VEC, int SEE, typename T>
   __device__ inline void load(const T* row, int d, int g, Watch& watch) {
     f32x4 x[D / 16];
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) x[ks] = ld4<VEC>(row, 32 * (ks >> 1) + 8 * g + 4 * (ks & 1), d);
     if (d < D) {
+      watch.see_split<SEE>(x);
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks) x[ks] = blank4<VEC>(x[ks], 32 * (ks >> 1) + 8 * g + 4 * (ks & 1), d);
     }
 #pragma unroll
     for (int ks = 0; ks < D / 32; ++ks) v[ks] = split8(x[2 * ks], x[2 * ks + 1]);
-    watch.see_split(x);
+    if (d == D) watch.see_split<SEE>(x);
   }
 };
 
@@ -273,8 +278,8 @@ struct Weights32<NT, true> {
   }
 };
 
-// A workgroup's work with split operands and, if a product was an infinity or a NaN or an operand too small
-// to be split anywhere in it, once more with fp32 operands.  work(std::bool_constant, place, again) passes
+// A workgroup's work with split operands and, if `Watch` met something unusual anywhere in it, once more with
+// fp32 operands.  work(std::bool_constant, place, again) passes
 // what it saw to again(watch) and returns the answer, the same in all threads: whether it will be called once
 // more.  Results that may take the place of an input (O that of Q) are stored after the question; others may
 // be stored before, as the second run writes them again.
@@ -331,17 +336,17 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
   const size_t NKtot = (size_t)p.ntk * b1;
 
   const int j = 16 * wave + c, jc = j < b2 ? j : b2 - 1;
-  Watch watch;
+  Watch watch(p.scale);
   Rows32<D, STAGED, NTHR, VEC, TIn> rk, rv;
   rk.load(Kp, [&](int r) { return axis_offset(p.cmap, bn * b2 + r) * p.ks.token; }, b2, d, tid);
   Query32<D, SPLIT> q;
-  if (first) q.template load<VEC>(Qp + axis_offset(p.cmap, bq * b2 + jc) * p.qs.token, d, g, watch);
-  else q.template load<VEC>((const float*)p.aR + ((((size_t)bhl * p.ntq + ml) * NKtot + nk) * b2 + jc) * d, d, g, watch);
+  if (first) q.template load<VEC, kSeeNone>(Qp + axis_offset(p.cmap, bq * b2 + jc) * p.qs.token, d, g, watch);
+  else q.template load<VEC, kSeeNone>((const float*)p.aR + ((((size_t)bhl * p.ntq + ml) * NKtot + nk) * b2 + jc) * d, d, g, watch);
   auto load_v = [&]() {
     if (LAST) rv.load(Vp, [&](int r) { return axis_offset(p.cmap, bn * b2 + r) * p.vs.token; }, b2, d, tid);
   };
   if (EARLY_V) load_v();
-  rk.template store<SPLIT, ROWS>(tile, b2, d, tid, watch);
+  rk.template store<SPLIT, kSeeSmall | kSeeHuge, ROWS>(tile, b2, d, tid, watch);
   if constexpr (ROWS > STAGED) {
     // the second half of the last step of the second products: zeros
     constexpr int PIECES = (ROWS - STAGED) * kLdS<D> / 8;
@@ -416,7 +421,7 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
   if (j < b2) o.template store<VEC>((float*)p.aL + row * d, 1.f / W, g, d);
   if constexpr (LAST) {
     __syncthreads();                  // every wave is done with K: the tile now holds V
-    rv.template store<SPLIT, ROWS>(tile, b2, d, tid, watch);
+    rv.template store<SPLIT, kSeeSmall, ROWS>(tile, b2, d, tid, watch);
     __syncthreads();
     w.template product<D, ROWS>(tile, o, g, c);
     o.show(watch);
@@ -462,7 +467,7 @@ struct Online32 {
 // NW waves; `wkeys`: the keys from here on are hidden from every query of this wave, which leaves out the
 // chunks that start there (0: the wave owns no query).  `cut`, then every `step` keys: a chunk ends there
 // too (0: nowhere).  bias(key) is subtracted from the scaled logits, hide(key) hides a key from the
-// lane's query.  `watch` sees the logits and what is split (SPLIT only).
+// lane's query.  `watch` sees the logits and the values that are split (SPLIT only; the caller has it see q).
 template <int D, int NW, bool WITH_V, bool VEC, bool SPLIT, typename TK, typename Bias, typename Hide>
 __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vbase, long long vstride, int nkeys, int d,
                                float scale, const Query32<D, SPLIT>& q, int wkeys, int cut, int step, float* lds, Bias bias,
@@ -487,12 +492,12 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
     if (WITH_V) rv.load(vbase + c0 * vstride, [&](int r) { return r * vstride; }, valid, d, tid);
   };
   auto commit_k = [&](float* slot) {
-    rk.template store<SPLIT>(slot, CH, d, tid, watch);
+    rk.template store<SPLIT, kSeeNone>(slot, CH, d, tid, watch);
     if (tid < CH) slot[BIAS + tid] = rb;
   };
   // value rows past the end are zeros: a copy of the last one times a weight of zero is NaN where it holds an infinity
   auto commit_v = [&](float* slot, int rows) {
-    if (WITH_V) rv.template store<SPLIT>(slot + KV, rows, d, tid, watch);
+    if (WITH_V) rv.template store<SPLIT, kSeeSmall>(slot + KV, rows, d, tid, watch);
   };
   fetch_k(0);
   if constexpr (SPLIT) {
@@ -619,9 +624,9 @@ __device__ inline bool stage_l_out_32(const Place& at, int l0, const KParams& p,
   const int l = l0 + 16 * wave + c, b1 = col.b1, d = p.d;
   Query32<D, SPLIT> q;
   Out32<D, SPLIT> o;
-  Watch watch;
+  Watch watch(p.scale);
   // rows beyond b1 repeat the last one and are not stored
-  q.template load<VEC>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
+  q.template load<VEC, kSeeSmall | kSeeHuge>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
   o.clear();
   Online32 st;
   const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
@@ -657,7 +662,7 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   const int l = l0 + 16 * wave + c, b1 = col.b1, d = p.d, NK = col.NK, nch = (NK + 31) >> 5;
   float* bias = lds + 2 * SLOT;          // [16 NT]
   Rows32<D, 32, NTHR, true, float> rows;
-  Watch watch;
+  Watch watch(p.scale);
   // chunk i of alpha_L, then of Y (i >= nch)
   auto fetch = [&](int i) {
     const int r0 = 32 * (i < nch ? i : i - nch);
@@ -665,7 +670,8 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   };
   auto commit = [&](int i) {
     const int left = NK - 32 * (i < nch ? i : i - nch);
-    rows.template store<true>(lds + (i & 1) * SLOT, left < 32 ? left : 32, d, tid, watch);      // rows past the end: zeros
+    rows.template store<true, kSeeNone>(lds + (i & 1) * SLOT, left < 32 ? left : 32, d, tid, watch);      // rows past the end: zeros
+    if (i >= nch) watch.see_split<kSeeSmall>(rows.v);
   };
   // chunk i is done: i + 1 goes to the other slot, i + 2 is requested
   auto advance = [&](int i) {
@@ -678,7 +684,7 @@ __device__ inline bool stage_l_out_res_32(const Place& at, int l0, const KParams
   f32x4 z[NT];
   {
     Query32<D, true> q;
-    q.template load<true>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
+    q.template load<true, kSeeSmall | kSeeHuge>(col.Q + tile_rows(p, col.a, p.qs.token)(l < b1 ? l : b1 - 1), d, g, watch);
     commit(0);
     fetch(1);
     __syncthreads();
@@ -744,7 +750,7 @@ __global__ __launch_bounds__(64 * NW, NW > 4 ? 4 : 3) void k_f32_stage_l_out_res
 
 // The Q tile of a column in LDS: NLT * 16 rows (ROWS: the planes' stride where it is split), those
 // beyond b1 zero.
-template <int D, int ROWS, bool VEC, bool SPLIT, typename TIn>
+template <int D, int ROWS, bool VEC, bool SPLIT, int SEE, typename TIn>
 __device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, int rows, int b1, int d, int tid, int nthr,
                                  Watch& watch) {
   constexpr int CPR = D / 4, BATCH = 8;
@@ -765,7 +771,7 @@ __device__ inline void stage_q32(float* Qs, const TIn* Qp, const TokRows& qrow, 
         else *(f32x4*)(Qs + r * kLd<D> + 4 * (idx % CPR)) = x;
       }
     }
-    if constexpr (SPLIT) watch.see_split(v);
+    if constexpr (SPLIT) watch.see_split<SEE>(v);
   }
 }
 
@@ -808,10 +814,10 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
   const int nk = 16 * wave + c, nkc = nk < NK ? nk : NK - 1;
   const float cl = col.cL[nkc];
   f32x4 z[NLT];
-  Watch watch;
+  Watch watch(p.scale);
   Query32<D, SPLIT> first;
-  first.template load<VEC>(col.aL + (size_t)nkc * d, d, g, watch);
-  stage_q32<D, LROWS, VEC, SPLIT>(Qs, col.Q, tile_rows(p, col.a, p.qs.token), LROWS, b1, d, tid, nthr, watch);
+  first.template load<VEC, kSeeNone>(col.aL + (size_t)nkc * d, d, g, watch);
+  stage_q32<D, LROWS, VEC, SPLIT, kSeeSmall | kSeeHuge>(Qs, col.Q, tile_rows(p, col.a, p.qs.token), LROWS, b1, d, tid, nthr, watch);
   __syncthreads();
 
   auto logits = [&](const Query32<D, SPLIT>& kb) {
@@ -887,7 +893,7 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
     Query32<D, SPLIT> kb;               // read again rather than kept (nor its addresses)
     int reread = nkc;
     asm("" : "+v"(reread));
-    kb.template load<VEC>(col.aL + (size_t)reread * d, d, g, watch);
+    kb.template load<VEC, kSeeNone>(col.aL + (size_t)reread * d, d, g, watch);
     logits(kb);
     float cm = -INFINITY;
 #pragma unroll
@@ -943,11 +949,11 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
   const int l = 16 * wave + c;
   // the chunks of the first pass and the Q tile of the second take the same LDS
   float* Qs = dyn;
-  Watch watch;
+  Watch watch(p.scale);
   {
     Query32<D, SPLIT> q;
     Out32<D, SPLIT> o;
-    q.template load<VEC>(col.Q + qrow(l < b1 ? l : b1 - 1), d, g, watch);
+    q.template load<VEC, kSeeSmall | kSeeHuge>(col.Q + qrow(l < b1 ? l : b1 - 1), d, g, watch);
     Online32 st;
     const int lim = p.rl > 0 ? visible_key_rows(p, l < b1 ? l : b1 - 1) : 0x7fffffff;
     flash32<D, NW, false, VEC, SPLIT>(col.aL, d, col.aL, d, NK, d, p.scale, q, 16 * wave < b1 ? NK : 0, 0, 0, dyn,
@@ -956,12 +962,12 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
     if (wave < nlt && g == 0) lse[l] = st.m + logf(lsum * (SPLIT ? 1.f / kWeight : 1.f));
   }
   __syncthreads();
-  stage_q32<D, MAXROWS, VEC, SPLIT>(Qs, col.Q, qrow, 32 * ((nlt + 1) / 2), b1, d, tid, 64 * NW, watch);
+  stage_q32<D, MAXROWS, VEC, SPLIT, kSeeNone>(Qs, col.Q, qrow, 32 * ((nlt + 1) / 2), b1, d, tid, 64 * NW, watch);
   __syncthreads();
   for (int t = wave; 16 * t < NK; t += NW) {
     const int nk = 16 * t + c, nkc = nk < NK ? nk : NK - 1;
     Query32<D, SPLIT> kb;
-    kb.template load<VEC>(col.aL + (size_t)nkc * d, d, g, watch);
+    kb.template load<VEC, kSeeNone>(col.aL + (size_t)nkc * d, d, g, watch);
     const float cl = col.cL[nkc];
     // log L[l, nk] of query tiles lt and lt + 1 (rows beyond b1 and hidden keys: -inf)
     auto logits = [&](int lt, f32x4 (&z)[2]) {
@@ -1057,8 +1063,8 @@ __device__ inline bool dense_32(const Place& at, const KParams& p, float* lds, A
   const int qi = q0 + 16 * wave + c, qc = qi < p.Nq ? qi : p.Nq - 1;
   Query32<D, SPLIT> q;
   Out32<D, SPLIT> o;
-  Watch watch;
-  q.template load<VEC>(Qp + (long long)qc * p.qs.token, d, g, watch);
+  Watch watch(p.scale);
+  q.template load<VEC, kSeeSmall | kSeeHuge>(Qp + (long long)qc * p.qs.token, d, g, watch);
   o.clear();
   // the keys query row r sees: a prefix, up to the end of its own chunk
   auto visible = [&](int r) {

@@ -7,9 +7,11 @@
 // a SIMD's other waves.
 //
 // Infinities have no such sum (their m is inf - inf), and a number within 2^-9 of the largest has an
-// infinite h: both end as a NaN or an infinity in a product.  Numbers below 2^-100 are seen as they are
-// split: from 2^-102 on l may be a bf16 subnormal, from 2^-110 on it may be none at all.  Every user looks at
-// both (`Watch`) and, if it meets one, does the work again with fp32 operands.
+// infinite h: both end as a NaN or an infinity in a product.  Below 2^-102 l may be a bf16 subnormal, below
+// 2^-110 it may be none at all: up to 2^-126 of the number is lost.  That shows where the number is a value
+// (of V, Y, or K and Q, whose averages alpha_L and alpha_R / c_R are), and in a logit where it meets a huge
+// one: an operand of the first products need not be looked at if the other one is neither small nor huge.
+// Every user looks at these (`Watch`) and, if it meets one, does the work again with fp32 operands.
 #pragma once
 #include "mrt_bf16_tiles.hpp"
 
@@ -46,43 +48,53 @@ __device__ inline Split8 split8(f32x4 a, f32x4 b) {
                 as_bf16x8(uint4{s[0].l, s[1].l, s[2].l, s[3].l})};
 }
 
-// Was one of the numbers seen an infinity or a NaN?  Times zero, either is a NaN, which a sum keeps.  (The
-// zero and the sum's bits are opaque: the library is built without honouring NaNs.)  And was a number that
-// was split too small for it?  The magnitudes' minimum costs half an instruction a number; only a wave that
-// finds a zero or less than 2^-100 tells the two apart (4680 tokens, 12 heads, T = 2: 139 -> 146 us; telling
-// them apart at once, without a branch, 163).
+// What makes a workgroup do its work again.  Was one of the numbers seen an infinity or a NaN?  Times zero,
+// either is a NaN, which a sum keeps.  (The zero and the sum's bits are opaque: the library is built without
+// honouring NaNs.)  Was an operand too small to be split?  The magnitudes' minimum costs half an instruction a
+// number; only a wave that finds a zero or less than 2^-100 tells the two apart.  Was one huge?  (Looking at
+// every operand for the second: 4680 tokens, 12 heads, T = 2, 139 -> 146 us; telling zeros apart at once,
+// without a branch, 163; as it is 142.)
+enum { kSeeNone = 0, kSeeSmall = 1, kSeeHuge = 2 };
 struct Watch {
   float zero = 0.f, sum = 0.f;
-  bool small = false;               // the same in all lanes
-  __device__ inline Watch() { asm("" : "+s"(zero)); }
+  float huge;                       // where what a small operand may have lost, 2^-126, is more than 2^-66 of a scaled logit
+  bool odd = false;                 // a small or huge operand; the same in all lanes
+  __device__ inline explicit Watch(float scale) : huge(0x1p60f / fmaxf(fabsf(scale), 1.f)) { asm("" : "+s"(zero)); }
   __device__ inline void see(f32x4 x) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) sum = fmaf(x[r], zero, sum);
   }
-  // (called once the numbers are split, so that the first do not wait for the last)
-  template <int N>
+  // operands; called once they are split, so that the first do not wait for the last
+  template <int SEE, int N>
   __device__ inline void see_split(const f32x4 (&v)[N]) {
-    const float bound = 0x1p-100f;
-    float least = 1.f;
+    if constexpr (SEE != kSeeNone) {
+      const float small = 0x1p-100f;
+      float least = 1.f, most = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i)
+      for (int i = 0; i < N; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; e += 2) least = fminf(fminf(fabsf(v[i][e]), fabsf(v[i][e + 1])), least);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < bound) == 0, 1)) return;
-    unsigned nonzero = ~0u;         // twice the least magnitude's bits, less one: zeros wrap to the largest
+        for (int e = 0; e < 4; e += 2) {
+          const float x = fabsf(v[i][e]), y = fabsf(v[i][e + 1]);
+          if constexpr ((SEE & kSeeSmall) != 0) least = fminf(fminf(x, y), least);
+          if constexpr ((SEE & kSeeHuge) != 0) most = fmaxf(fmaxf(x, y), most);
+        }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < small || most > huge) == 0, 1)) return;
+      unsigned nonzero = ~0u;       // twice the least magnitude's bits, less one: zeros wrap to the largest
 #pragma unroll
-    for (int i = 0; i < N; ++i)
+      for (int i = 0; i < N; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned twice = (__float_as_uint(v[i][e]) << 1) - 1u;
-        nonzero = twice < nonzero ? twice : nonzero;
-      }
-    if (__builtin_amdgcn_ballot_w64(nonzero < (__float_as_uint(bound) << 1) - 1u) != 0) small = true;
+        for (int e = 0; e < 4; ++e) {
+          const unsigned twice = (__float_as_uint(v[i][e]) << 1) - 1u;
+          nonzero = twice < nonzero ? twice : nonzero;
+        }
+      if (__builtin_amdgcn_ballot_w64(((SEE & kSeeSmall) != 0 && nonzero < (__float_as_uint(small) << 1) - 1u) || most > huge) != 0)
+        odd = true;
+    }
   }
   __device__ inline bool unusual() const {
     unsigned bits = __float_as_uint(sum);
     asm("" : "+v"(bits));
-    return small || (bits & 0x7fffffffu) >= 0x7f800000u;
+    return odd || (bits & 0x7fffffffu) >= 0x7f800000u;
   }
 };
 

@@ -89,6 +89,17 @@ def test_tiny_keys_or_queries_against_huge_ones(name, which):
     assert_same(*both(size, q, k, v, 1e5 * size[7] ** -0.5))
 
 
+@pytest.mark.parametrize("name", list(SIZES))
+def test_tiny_keys_against_some_huge_queries(name):
+    # averages of keys are formed where the queries are small and meet huge ones later
+    size = SIZES[name]
+    q, k, v = inputs(size, 8)
+    q[:, :, 1::3] *= 1e34
+    k *= 3e-36
+    print(name, flush=True)
+    assert_same(*both(size, q, k, v, size[7] ** -0.5))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_weight_of_the_dense_softmax(d):
     # value row i has a one at feature i: the output is the matrix of the weights, e^0 .. e^-103
