@@ -132,7 +132,9 @@ size_t monarch_attn_workspace_bytes(const mrt_problem* p, int b1, int b2, int ti
  *   aligned, contents undefined on entry and exit.  hip_stream: a hipStream_t (NULL = the
  *   default stream).  Calls sharing a workspace must be ordered on one stream.
  *   Accuracy.  MRT_F32 storage (and MRT_COMPUTE_F32): O differs from the exact result of App. A's
- *   iteration by at most 1e-4 (max-abs) for inputs of unit scale.  MRT_BF16 storage with
+ *   iteration by at most 1e-4 (max-abs) for inputs of unit scale.  A head's bits depend on the grid, the
+ *   blocks and whether its rows can be moved 16 bytes at a time (addresses and strides multiples of
+ *   that), not on the number of heads or sequences of the call nor on the workspace.  MRT_BF16 storage with
  *   MRT_COMPUTE_DEFAULT: the matrix operands (Q, K, V, the probabilities of R and L, alpha_L, Y,
  *   alpha_R / c_R) and O are rounded to bf16, 2^-9 relative each; the roundings of alpha_L and
  *   alpha_R enter the next logits, whose softmaxes amplify them.  For outputs of magnitude <= 1

@@ -1126,16 +1126,16 @@ hipError_t run_r_as(const KParams& kp, dim3 grid, bool first, bool last, hipStre
 }
 // Where fp32 operands stay: blocks of one tile, whose second products would fill half a step of split
 // operands and whose few products do not pay for the splitting (blocks of 16 x 16 at 64 features, one to
-// 32 heads: the call with split operands 13 % longer; at one head the last launch 5.4 against 7.3 us),
-// and small blocks where the heads' workgroups are one per compute unit or less, i.e. one chain of
-// latencies: stage R of two tiles (24 x 24, one head: 6.5 against 6.7 us; with 288 workgroups the call is
-// 7 % shorter split) and its last launch of three (40 x 33 at 128 features, one head: 11.2 against 12.1),
-// stage L of up to 32 query rows (24 x 24, output launch: 6.1 against 6.5).  Only the problem's sizes
-// count, not how many heads or tile rows a pass holds: the bits do not depend on the passes.
-inline bool short_chain(const KParams& kp, int per_head) { return (long long)kp.H * per_head <= compute_units(); }
+// 32 heads: the call with split operands 13 % longer; at one head the last launch 5.4 against 7.3 us), and
+// two tiles, or the last launch of three, where the key side is at most 48 rows: a few heads of them are one
+// chain of latencies (24 x 24 at 64 features, calls of 1 to 8 heads: all launches split 1.04 of the time, of
+// 12 to 40 heads 0.96 .. 0.98; 40 x 33 at 128 features, last launch split 1.02, 0.98; 90 rows of 26 columns,
+// 12 heads 0.98, 64 of 20, 24 heads 0.93).  The choice is the block's and the features', not the heads', the
+// sequences' or the passes': a head's bits do not depend on what shares its call.
+constexpr int kShortRows = 48;
 template <int NT, int D, typename TIn, bool VEC>
 hipError_t run_r(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s) {
-  const bool small = short_chain(kp, kp.ntk * kp.b1);
+  const bool small = kp.ntk * kp.b1 <= kShortRows;
   if (last) {
     constexpr bool ALWAYS = VEC && NT > 3;
     const bool split = VEC && NT > 1 && (ALWAYS || !small);
@@ -1190,7 +1190,7 @@ hipError_t run_l_as(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
   if (last) {
     if constexpr (SPLIT) {
       if (nk_max <= 96) {
-        if constexpr (NW <= 6) return run_out_res<NW, 6, D, TIn>(kp, grid, 1, s);
+        if constexpr (NW > 2 && NW <= 6) return run_out_res<NW, 6, D, TIn>(kp, grid, 1, s);      // (run_l: not two)
       } else if (nk_max <= 192) {
         // at most four waves a workgroup: three of them share a compute unit, where one of six to twelve
         // waves would have it alone (the logits of 192 keys leave 168 registers a wave)
@@ -1222,9 +1222,13 @@ hipError_t run_l_as(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
 template <int NW, int D, typename TIn, bool VEC>
 hipError_t run_l(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
   if constexpr (VEC && NW == 2) {
-    // one tile of keys (4 rows, 96 columns, 40 heads: output launch 12 us against 23, refine 14 against 16)
-    // or a short chain: fp32 operands
-    if (kp.ntk * kp.b1 > 16 && !short_chain(kp, kp.c2 * kp.b2)) return run_l_as<NW, D, TIn, true, true>(kp, grid, last, s);
+    // up to 32 query rows two waves would split what twelve times as many products do not pay for: fp32
+    // operands up to the key rows of the one-pass kernels (4 rows, 96 columns, 40 heads: output launch 12 us
+    // against 23, refine 14 against 16; calls with fp32 and with split operands here: 30 rows, 52 columns, 128
+    // features, one head 0.99 against 1.03 of fp32 operands everywhere, 40 heads 0.87 against 0.94; 144 key rows of
+    // 24 x 24 tiles, one head 0.98 against 1.04, 24 heads 0.97 against 0.99; 192 key rows 0.99 .. 1.04 against
+    // 0.98 .. 1.00)
+    if (kp.ntk * kp.b1 >= kOnePassRows) return run_l_as<NW, D, TIn, true, true>(kp, grid, last, s);
     return run_l_as<NW, D, TIn, true, false>(kp, grid, last, s);
   } else {
     return run_l_as<NW, D, TIn, VEC, VEC>(kp, grid, last, s);

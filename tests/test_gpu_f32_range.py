@@ -156,3 +156,17 @@ def test_logits_near_the_largest_number(rows, cols, d, heads):
     expect = torch.gather(v[0].double(), 1, pick[..., None].expand(-1, -1, d)).mean(1, keepdim=True)
     for out in both((1, rows, cols, rows, cols, 0, 1, d, heads, 0), q, k, v, 1.0):
         assert (out[0].double() - expect).norm() <= REL * expect.norm() * n ** 0.5
+
+
+@pytest.mark.parametrize("rows,cols,d", [(24, 24, 64), (32, 20, 64), (17, 33, 128), (40, 33, 128), (33, 48, 64), (30, 52, 128)])
+def test_same_bits_for_any_number_of_heads_and_sequences(rows, cols, d):
+    heads = 16
+    gen = torch.Generator(device="cuda:0").manual_seed(rows)
+    q, k, v = (torch.randn(1, heads, rows * cols, d, generator=gen, device="cuda:0") for _ in range(3))
+
+    def run(*x):
+        return pkg.monarch_attn_fwd(*x, f_q=1, f_kv=1, h=rows, w=cols, b1=rows, b2=cols, tile=0, iters=2, scale=d ** -0.5)
+    whole = run(q, k, v)
+    for some in (1, 5):
+        assert torch.equal(run(*(x[:, :some].contiguous() for x in (q, k, v))), whole[:, :some])
+    assert torch.equal(run(*(x.transpose(0, 1).contiguous() for x in (q, k, v))).transpose(0, 1), whole)
