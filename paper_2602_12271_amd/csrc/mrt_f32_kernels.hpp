@@ -926,8 +926,12 @@ template <int NLT, int D, bool SPLIT>
 constexpr size_t refine_one_32_lds(int nw) {
   return ((size_t)16 * NLT * ((SPLIT ? kRowFloats<D> : kLd<D>) + 1) + 2 * (size_t)nw * 16 * NLT) * 4;
 }
+// (Two query tiles, 64 features, fp32 operands: 82 registers without the bound of six waves a SIMD, and one
+// workgroup of six key tiles less a unit: 48 x 48 in tiles of 24 x 24, 8 heads 75 -> 71 us.)
+template <int NLT, int D, bool VEC, bool SPLIT>
+constexpr int kRefineOneWaves = NLT > 6 ? 3 : (NLT == 2 && D == 64 && VEC && !SPLIT ? 6 : 4);
 template <int NLT, int D, typename TIn, bool VEC, bool SPLIT>
-__global__ __launch_bounds__(768, NLT > 6 ? 3 : 4) void k_f32_stage_l_refine_one(KParams p) {
+__global__ __launch_bounds__(768, (kRefineOneWaves<NLT, D, VEC, SPLIT>)) void k_f32_stage_l_refine_one(KParams p) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];
   run_split<SPLIT>([&](auto split, const Place& at, auto again) {
     return stage_l_refine_one_32<NLT, D, TIn, VEC, decltype(split)::value>(at, p, dyn, again);
