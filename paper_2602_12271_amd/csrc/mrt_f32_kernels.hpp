@@ -282,12 +282,12 @@ struct Weights32<NT, true> {
 // fp32 operands.  work(std::bool_constant, place, again) passes
 // what it saw to again(watch) and returns the answer, the same in all threads: whether it will be called once
 // more.  Results that may take the place of an input (O that of Q) are stored after the question; others may
-// be stored before, as the second run writes them again.
+// be stored before, as the second run writes them again.  `split` = false: with fp32 operands only.
 struct Place {
   int x, y, z, tid;       // block and thread
 };
 template <bool SPLIT, typename Work>
-__device__ inline void run_split(Work work) {
+__device__ inline void run_split(Work work, bool split = true) {
   Place at{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)threadIdx.x};
   if constexpr (SPLIT) {
     __shared__ int found;
@@ -297,7 +297,8 @@ __device__ inline void run_split(Work work) {
       __syncthreads();
       return found != 0;
     };
-    if (__builtin_expect(!work(std::true_type{}, at, again), 1)) return;
+    if (__builtin_expect(split, 1))
+      if (__builtin_expect(!work(std::true_type{}, at, again), 1)) return;
     // an opaque copy: addresses are formed again instead of kept in registers through the first run
     asm("" : "+s"(at.x), "+s"(at.y), "+s"(at.z), "+v"(at.tid));
   }
@@ -1093,12 +1094,18 @@ __device__ inline bool dense_32(const Place& at, const KParams& p, float* lds, A
   if (qi < p.Nq) o.template store<VEC>(Op + (long long)qi * p.os.token, lsum > 0.f ? 1.0f / lsum : 0.f, g, d);
   return false;
 }
+// A few keys do not pay for splitting the queries: up to these the operands stay fp32 (us with split and with
+// fp32 operands, 12 heads; 64 features: 16 keys 4.4, 3.8, 32 keys 4.4, 4.8; 128 features: 16 keys 7.3, 4.8, 64 keys
+// 11.5, 10.4, 80 keys 17.0, 17.3, 96 keys 17.6, 20.2; masked, where chunks of 32 keys are cut short, two chunks
+// of 40 keys 21.3, 17.3, of 80 keys 30.7, about 27, of 96 keys 30.0, 30.6).
+template <int D, bool MASKED>
+constexpr int kFewKeys32 = D == 64 ? 16 : (MASKED ? 160 : 64);
 template <int D, typename TIn, bool VEC, bool MASKED>
 __global__ __launch_bounds__(64 * kDenseWaves32, 4) void k_f32_dense(KParams p) {
   __shared__ __attribute__((aligned(16))) float lds[kRing32<D, true, VEC>];
   run_split<VEC>([&](auto split, const Place& at, auto again) {
     return dense_32<D, TIn, VEC, MASKED, decltype(split)::value>(at, p, lds, again);
-  });
+  }, p.Nkv > kFewKeys32<D, MASKED>);
 }
 
 
