@@ -1129,12 +1129,7 @@ bool vec_ok(const KParams& kp) {
 // Rows that cannot be moved so take the element-by-element variants of the same sizes.  (One variant, of the
 // largest size, for all of them made small problems pay for it: blocks of 16 x 16 at 6 features 28 -> 91 us,
 // 40 heads of them 67 -> 256; unaligned 24 x 24 at 64 features 56 -> 88.)
-template <int NT, int D, typename TIn, bool VEC, bool SPLIT>
-hipError_t run_r_as(const KParams& kp, dim3 grid, bool first, bool last, hipStream_t s) {
-  if (last) k_f32_stage_r<NT, D, TIn, true, VEC, SPLIT><<<grid, 64 * NT, 0, s>>>(kp, first);
-  else k_f32_stage_r<NT, D, TIn, false, VEC, SPLIT><<<grid, 64 * NT, 0, s>>>(kp, first);
-  return hipGetLastError();
-}
+//
 // Where fp32 operands stay: blocks of one tile, whose second products would fill half a step of split
 // operands and whose few products do not pay for the splitting (blocks of 16 x 16 at 64 features, one to
 // 32 heads: the call with split operands 13 % longer; at one head the last launch 5.4 against 7.3 us), and
@@ -1186,9 +1181,15 @@ hipError_t run_r_t(const KParams& kp, dim3 grid, bool first, bool last, hipStrea
 
 // Key ranges the one-pass refine kernel takes: twelve waves of one key tile each is the largest
 // workgroup whose kept logits (48 registers at b1 = 192) leave three waves per SIMD.  It forms the
-// logits once, the streamed kernel twice.
+// logits once, the streamed kernel twice.  Twelve query tiles of split operands at 128 features are
+// 144 KB, and with the row statistics of eleven waves more than a compute unit has: those blocks (161 rows and
+// more) take the streamed kernel too, and are ahead of the one-pass kernel with fp32 operands by as much as
+// others (calls of 176 x 30, 1 to 24 heads 115 .. 432 us -> 87 .. 360).
 constexpr int kOnePassRows = 192;
 constexpr size_t kMaxLds = 160 * 1024;
+template <int NLT, int D, bool SPLIT> constexpr bool kOnePass = !(NLT == 12 && D == 128 && SPLIT);
+static_assert(refine_one_32_lds<12, 128, true>(11) > kMaxLds && refine_one_32_lds<10, 128, true>(12) + 16 <= kMaxLds &&
+              refine_one_32_lds<12, 128, false>(12) + 16 <= kMaxLds && refine_one_32_lds<12, 64, true>(12) + 16 <= kMaxLds, "");
 
 template <int NW, int NT, int D, typename TIn>
 hipError_t run_out_res(const KParams& kp, dim3 grid, int parts, hipStream_t s) {
@@ -1217,14 +1218,15 @@ hipError_t run_l_as(const KParams& kp, dim3 grid, bool last, hipStream_t s) {
     return hipGetLastError();
   }
   hipError_t e;
-  // one wave per key tile; NW here is the (even) number of query tiles
-  const int nw = (nk_max + 15) / 16;
-  const size_t lds1 = refine_one_32_lds<NW, D, SPLIT>(nw);
-  if (nk_max <= kOnePassRows && lds1 + 16 <= kMaxLds) {
-    if ((e = allow_lds(k_f32_stage_l_refine_one<NW, D, TIn, VEC, SPLIT>, lds1)) != hipSuccess) return e;
-    k_f32_stage_l_refine_one<NW, D, TIn, VEC, SPLIT><<<grid, 64 * nw, lds1, s>>>(kp);
-    return hipGetLastError();
-  }
+  if constexpr (kOnePass<NW, D, SPLIT>)
+    if (nk_max <= kOnePassRows) {
+      // one wave per key tile; NW here is the (even) number of query tiles
+      const int nw = (nk_max + 15) / 16;
+      const size_t lds1 = refine_one_32_lds<NW, D, SPLIT>(nw);
+      if ((e = allow_lds(k_f32_stage_l_refine_one<NW, D, TIn, VEC, SPLIT>, lds1)) != hipSuccess) return e;
+      k_f32_stage_l_refine_one<NW, D, TIn, VEC, SPLIT><<<grid, 64 * nw, lds1, s>>>(kp);
+      return hipGetLastError();
+    }
   const size_t lds = ((size_t)kRefineFloats32<NW, D, SPLIT> + 16 * NW) * 4;
   if ((e = allow_lds(k_f32_stage_l_refine<NW, D, TIn, VEC, SPLIT>, lds)) != hipSuccess) return e;
   k_f32_stage_l_refine<NW, D, TIn, VEC, SPLIT><<<grid, 64 * NW, lds, s>>>(kp);
