@@ -1,6 +1,6 @@
-"""Stage L backward on resident key ranges of five and six tiles, on either side of the grid sizes that
-pick six waves per workgroup instead of four (256 workgroups at t < T, 512 at t = T): all against the fp32 kernels on the
-same bf16 tensors.  Bar, in the 2-norm: one bf16 rounding is 1.1e-3 rms (2^-9 / sqrt 3), a gradient
+"""Stage L backward on resident key ranges of five and six tiles, with fewer workgroups than compute units up to more
+than two and a half for each (at 128 features and t < T 513 to 640 take two launches, here 40 heads of 15 columns):
+all against the fp32 kernels on the same bf16 tensors.  Bar, in the 2-norm: one bf16 rounding is 1.1e-3 rms (2^-9 / sqrt 3), a gradient
 crosses about a dozen of them (every intermediate of the forward pass, both factors of every product of
 the reverse sweep), 4e-3 in quadrature; four times that.  (The largest single error is no measure here:
 it comes from the one near-tied softmax among 40 heads, 2.2e-2 of the largest gradient, whichever
