@@ -713,7 +713,7 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
       bp.cmx = last ? nullptr : (const float*)arrS(L.off_cmx(t + 1), lo);
       bp.cinv = last ? nullptr : (const float*)arrS(L.off_cinv(t + 1), lo);
       bp.accumulate = last ? 0 : 1;
-      e = L.mfma ? launch_bwd_bf16_stage_l(bp, nbh, last, ws_bf16, arr(L.off_scratch()) + L.scratch * (size_t)lo, gs)
+      e = L.mfma ? launch_bwd_bf16_stage_l(bp, nbh, last, arr(L.off_scratch()) + L.scratch * (size_t)lo, gs)
                  : launch_bwd_stage_l(bp, pl.dtype, nbh, last, gs);
       if (e != hipSuccess) return hip_fail(e, "backward stage L launch");
       bp.k.aR = t >= 2 ? arrD(L.off_aR(t), lo) : nullptr;

@@ -1,7 +1,7 @@
 // Backward pass on the bf16 matrix unit (bf16 storage, b1 <= 144 for stage L, b2 <= 64 for stage R,
 // head_dim 64 or 128): bf16 MFMA operands, fp32 accumulation and fp32 softmax arithmetic, same
-// register layouts as the forward kernels (mrt_bf16.hip).  The workspace arrays are typed by TW:
-// fp32 when the fp32 forward kernels recomputed the intermediates (one of the two stages runs the
+// register layouts as the forward kernels (mrt_bf16.hip).  Stage R types the workspace arrays by TW:
+// fp32 when the fp32 forward kernels recomputed the intermediates (stage L runs the
 // fp32 kernels of mrt_bwd_f32.hip), bf16 when every stage runs here and the bf16 forward kernels
 // did; operands are rounded to bf16 at the latest when they are staged into LDS.
 //
@@ -11,8 +11,10 @@
 //   cols kernel  (lanes own key rows nk):   d aL[nk] = scale sum_l dZ[l,nk] Q[l],
 //                d cL[nk] = -sum_l dZ[l,nk], d Y[nk] = sum_l L[l,nk] dO[l]
 // so that every contraction has its summation index on the K side of an MFMA.  The rows kernel
-// holds the key range in LDS when it has at most 96 rows and streams it in segments otherwise.  On a bf16
-// workspace the two sides are one launch wherever LDS holds both (at most 96 key rows, or 96 query rows).
+// holds the key range in LDS when it has at most 96 rows and streams it in segments otherwise.  The two
+// sides are one launch, the transposed copies passing through LDS, except where two launches of five or six
+// resident key tiles fill the chip better (two_launches) and for more than 96 query rows at t = T.
+// Stage L backward always finds bf16 intermediates: every problem it takes has its stage R on the matrix unit too.
 #include "mrt_internal.hpp"
 #include <type_traits>
 
@@ -29,36 +31,8 @@ constexpr int kLPWide = 160;   // the same for 96 < b1 <= 144 (ten query tiles, 
 constexpr int kBRowsWide = 144;
 __host__ __device__ inline int lp_of(int b1) { return b1 <= kBRows ? kLP : kLPWide; }
 
-// fp32 rows -> bf16 LDS tile: row r of the tile comes from src + rowoff(r); rows >= valid are zero.
-template <int D, int LD, int ROWS, int NTHR, typename RowFn>
-__device__ inline void stage_rows_f32(u16* dst, const float* src, RowFn rowoff, int valid, int tid) {
-  constexpr int CPR = D / 8, TOTAL = ROWS * CPR, N = (TOTAL + NTHR - 1) / NTHR;
-  f32x4 lo[N], hi[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    int idx = tid + i * NTHR;
-    idx = idx < TOTAL ? idx : TOTAL - 1;
-    int r = idx / CPR;
-    const int c = idx - r * CPR;
-    r = r < valid ? r : valid - 1;
-    const float* p = src + rowoff(r) + 8 * c;
-    lo[i] = *(const f32x4*)p;
-    hi[i] = *(const f32x4*)(p + 4);
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int idx = tid + i * NTHR;
-    const int r = idx / CPR, c = idx - r * CPR;
-    if (idx < TOTAL) {
-      const bf16x8 v = pack8(lo[i], hi[i]);
-      *(uint4*)(dst + r * LD + 8 * c) = r < valid ? __builtin_bit_cast(uint4, v) : uint4{0u, 0u, 0u, 0u};
-    }
-  }
-}
-
-// Rows of a workspace array into a bf16 LDS tile, whichever type the array is stored in.
-// The same copy split into its two halves (see RowRegs): load() issues every global load,
-// store() converts and writes the tile.
+// fp32 rows -> bf16 LDS tile in two halves (see RowRegs): load() issues every global load, store() converts
+// and writes the tile; rows >= valid are zero.
 template <int D, int ROWS, int NTHR>
 struct RowRegsF32 {
   static constexpr int CPR = D / 8, TOTAL = ROWS * CPR, N = (TOTAL + NTHR - 1) / NTHR;
@@ -92,21 +66,7 @@ struct RowRegsF32 {
     }
   }
 };
-template <int D, int LD, int ROWS, int NTHR, typename RowFn>
-__device__ inline void stage_ws(u16* dst, const float* src, RowFn rowoff, int valid, int tid) {
-  stage_rows_f32<D, LD, ROWS, NTHR>(dst, src, rowoff, valid, tid);
-}
-template <int D, int LD, int ROWS, int NTHR, typename RowFn>
-__device__ inline void stage_ws(u16* dst, const u16* src, RowFn rowoff, int valid, int tid) {
-  stage_rows_batched<D, LD, ROWS, NTHR>(dst, src, rowoff, valid, tid);
-}
-__device__ inline float ldw(const float* p) { return *p; }
-__device__ inline float ldw(const u16* p) { return __uint_as_float((uint32_t)(*p) << 16); }
-// Eight consecutive workspace values (16-byte aligned for bf16, 32 for fp32) as two float vectors.
-__device__ inline void ldw8(const float* p, f32x4& lo, f32x4& hi) {
-  lo = *(const f32x4*)p;
-  hi = *(const f32x4*)(p + 4);
-}
+// Eight consecutive bf16 workspace values (16-byte aligned) as two float vectors.
 __device__ inline void ldw8(const u16* p, f32x4& lo, f32x4& hi) {
   const uint4 v = *(const uint4*)p;
   lo = f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
@@ -273,14 +233,13 @@ __device__ inline void store_tile_transposed(u16* arr, int pitch, int nk0, int N
 // ---------------------------------------------------------------------------------------
 // stage L backward, rows kernel, one workgroup per (m, j)
 // ---------------------------------------------------------------------------------------
-// TW: storage type of the forward intermediates alpha_L, Y and abar in the workspace (fp32 when
-// the fp32 kernels recomputed them, bf16 when the bf16 forward kernels did).
 // NW waves; six own one query tile each, four two on half of them.
 // COLS: the column side of the stage (k_bwdm_l_cols otherwise) follows in the same workgroup, at most one
 // query tile a wave: dZ reaches it through LDS, Q and dO take the places of alpha_L and Y, L follows dZ in
 // its place.  The contractions run in the order of the cols kernel: the same bits.
-template <int D, int NTK, bool LAST, typename TW, int NW, bool COLS = false>
-__global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* Pw, u16* Zw) {
+template <int D, int NTK, bool LAST, int NW, bool COLS>
+__global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* Zw) {
+  static_assert(COLS || !LAST, "L reaches the column side through LDS only");
   const KParams& p = bp.k;
   // dZ[l][nk]: rows of 224 (or 160, 96) bytes, conflict-free for the eight-byte writes and transposed reads
   constexpr int LZ = 16 * NTK + 16;
@@ -303,8 +262,8 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
   const int nlt = (b1 + 15) >> 4;
 
   const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot;
-  const TW* aLp = (const TW*)p.aL + row0 * d;
-  const TW* Yp = (const TW*)p.Y + row0 * d;
+  const u16* aLp = (const u16*)p.aL + row0 * d;
+  const u16* Yp = (const u16*)p.Y + row0 * d;
   const float* cLp = p.cL + row0;
   // rows (nk, j) of the [m][nk][j][d] arrays
   const size_t arow0 = ((size_t)bhl * p.ntq + ml) * NKtot * b2;
@@ -314,9 +273,9 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
   const u16* dOp = (const u16*)bp.dO + b * p.os.batch + hd * p.os.head + qcol * p.os.token;
   const TokRows qrow = tile_rows(p, a, p.qs.token), orow = tile_rows(p, a, p.os.token);
 
-  stage_ws<D, LD, ROWS, NTHR>(Ks, aLp, PlainRows{D}, NK, tid);
+  stage_rows_batched<D, LD, ROWS, NTHR>(Ks, aLp, PlainRows{D}, NK, tid);
   if (LAST) {
-    stage_ws<D, LD, ROWS, NTHR>(Vs, Yp, PlainRows{D}, NK, tid);
+    stage_rows_batched<D, LD, ROWS, NTHR>(Vs, Yp, PlainRows{D}, NK, tid);
   } else {
     // d abar rows (fp32) into LDS as bf16; d abar . abar is formed on the way: the D/8 consecutive
     // lanes that share a row hold 8 features each
@@ -331,9 +290,9 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
       f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
       float t = 0.f;
       if (ok) {
-        ldw8((const TW*)bp.dA + at, lo, hi);
+        ldw8((const u16*)bp.dA + at, lo, hi);
         f32x4 alo, ahi;
-        ldw8((const TW*)bp.Anext + at, alo, ahi);
+        ldw8((const u16*)bp.Anext + at, alo, ahi);
 #pragma unroll
         for (int e = 0; e < 4; ++e) t = fmaf(lo[e], alo[e], fmaf(hi[e], ahi[e], t));
       }
@@ -356,8 +315,7 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
 
   const float scale2 = p.scale * kLog2e;
   float* dQp = bp.dQ + (size_t)bh * p.Nq * d;
-  u16* Pt = Pw + row0 * kLP;
-  u16* Zt = Zw + row0 * kLP;
+  [[maybe_unused]] u16* Zt = Zw + row0 * kLP;      // (not COLS)
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   [[maybe_unused]] bf16x4 Lq[NTK];       // COLS, LAST: this wave's rows of L until the column side takes them
   // tile lt of X[l][nk] into LDS, four keys of a lane's row at a time
@@ -376,10 +334,7 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
       continue;
     }
     if (lt >= nlt) {
-      for (int nk = g; nk < NK; nk += 4) {
-        if (LAST) Pt[(size_t)nk * kLP + l] = 0;
-        Zt[(size_t)nk * kLP + l] = 0;
-      }
+      for (int nk = g; nk < NK; nk += 4) Zt[(size_t)nk * kLP + l] = 0;
       continue;
     }
     const int lc = l < b1 ? l : b1 - 1;
@@ -452,7 +407,6 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
 #pragma unroll
       for (int r = 0; r < 4; ++r) dl[kt][r] = dl[kt][r] - s[kt][r] * delta;
       if constexpr (COLS) continue;
-      if (LAST) store_tile_transposed(Pt, kLP, 16 * kt, NK, 16 * lt, wq[kt], c, g);   // only dY, at t = T, is formed from it
       store_tile_transposed(Zt, kLP, 16 * kt, NK, 16 * lt, dl[kt], c, g);
     }
     if constexpr (COLS) {
@@ -518,7 +472,7 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
       column(Ks, o, zsum);
       zsum = xsum(zsum);
       if (g == 0 && nk < NK) bp.dcL[row0 + nk] = -zsum;
-      if (nk < NK) store_ws_row<D>((TW*)bp.daL + (row0 + nk) * d, o[0], p.scale, g);
+      if (nk < NK) store_ws_row<D>((u16*)bp.daL + (row0 + nk) * d, o[0], p.scale, g);
     }
     if constexpr (LAST) {
       __syncthreads();                     // every wave is done with dZ
@@ -526,253 +480,13 @@ __global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows(BwdParams bp, u16* P
       __syncthreads();
       if (owns) {
         column(Vs, o, zsum);
-        if (nk < NK) store_ws_row<D>((TW*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
+        if (nk < NK) store_ws_row<D>((u16*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
       }
     }
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// stage L backward, rows kernel for key ranges that do not fit LDS: one workgroup per (m, j),
-// wave w owns query tile w, the key range is streamed in segments of 64 rows, twice.  The first
-// sweep forms the row statistics online (running maximum and sum of the logits for the
-// log-sum-exp, and delta[l] = sum_c (L dL)[l, c] against a running maximum of its own, so that the
-// column shift of the weights never meets a positive exponent); the second sweep forms L (or w),
-// dZ and the dQ products with them.
-// ---------------------------------------------------------------------------------------
 constexpr int kSegTiles = 4, kSeg = 16 * kSegTiles;
-// Segments staged per barrier pair: two segments' loads are in flight together and the exposed
-// load latency and the two barriers are paid once per 128 key rows (70 KB of LDS per workgroup,
-// two workgroups per compute unit).
-// (three or four segments at a time, which the ten-wave variant's LDS would allow, measured no
-// faster and slower)
-constexpr int kStageSegs = 2, kStage = kSeg * kStageSegs;
-
-// NW waves: 6 for b1 <= 96, 10 for b1 <= 144 (the pitch of the transposed arrays follows).
-template <int D, bool LAST, typename TW, int NW>
-__global__ __launch_bounds__(64 * NW, 3) void k_bwdm_l_rows_stream(BwdParams bp, u16* Pw, u16* Zw) {
-  const KParams& p = bp.k;
-  constexpr int LD = D + kBPad, KS1 = D / 32, NVT = D / 16, NTK = kSegTiles, KS2 = NTK / 2;
-  constexpr int CPR = D / 8, TOTAL = kStage * CPR, NTMAX = 64 * NW, NI = (TOTAL + NTMAX - 1) / NTMAX;
-  constexpr int LP = NW <= 6 ? kLP : kLPWide;
-  __shared__ __attribute__((aligned(16))) u16 Ks[kStage * LD];    // alpha_L rows of the segment
-  __shared__ __attribute__((aligned(16))) u16 Vs[kStage * LD];    // Y rows (LAST) or d abar rows
-  __shared__ __attribute__((aligned(16))) float bias[kStage];     // -c_L log2(e), -inf beyond NK
-  __shared__ __attribute__((aligned(16))) float tcs[kStage];      // d abar . abar                  (not LAST)
-  __shared__ __attribute__((aligned(16))) float cms[kStage];      // max_l log2 L[l, nk]            (not LAST)
-  __shared__ __attribute__((aligned(16))) float cis[kStage];      // 1 / sum_l 2^(log2 L - max)     (not LAST)
-
-  constexpr int nthr = NTMAX;                  // launched with exactly this many threads
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
-  const int b1 = p.b1, b2 = p.b2, d = D;
-  const int j = blockIdx.x, ml = blockIdx.y, m = p.m0 + ml, bhl = blockIdx.z, bh = p.bh0 + bhl;
-  const int a = m / p.c2, bq = m - a * p.c2;
-  const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;
-  const size_t NKtot = (size_t)p.ntk * b1;
-  const int b = bh / p.H, hd = bh - b * p.H;
-  const int nlt = (b1 + 15) >> 4;
-
-  const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot;
-  const TW* aLp = (const TW*)p.aL + row0 * d;
-  const TW* Yp = (const TW*)p.Y + row0 * d;
-  const float* cLp = p.cL + row0;
-  // rows (nk, j) of the [m][nk][j][d] arrays
-  const size_t arow0 = ((size_t)bhl * p.ntq + ml) * NKtot * b2;
-  const long long qcol = axis_offset(p.cmap, bq * b2 + j);
-  const u16* Qp = (const u16*)p.Q + b * p.qs.batch + hd * p.qs.head + qcol * p.qs.token;
-  const u16* dOp = (const u16*)bp.dO + b * p.os.batch + hd * p.os.head + qcol * p.os.token;
-  const TokRows qrow = tile_rows(p, a, p.qs.token), orow = tile_rows(p, a, p.os.token);
-
-  // one segment of the key side into LDS; d abar . abar is formed on the way from the fp32 rows
-  auto stage = [&](int k0) {
-    const int valid = NK - k0 < kStage ? NK - k0 : kStage;
-    stage_ws<D, LD, kStage, NTMAX>(Ks, aLp + (size_t)k0 * d, PlainRows{D}, valid, tid);
-    if (LAST) {
-      stage_ws<D, LD, kStage, NTMAX>(Vs, Yp + (size_t)k0 * d, PlainRows{D}, valid, tid);
-    } else {
-      // D/8 consecutive lanes share a row: 8 features each
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int idx = tid + i * nthr;
-        const bool in = idx < TOTAL;
-        const int r = (in ? idx : TOTAL - 1) / CPR, ch = idx % CPR;
-        const bool ok = in && r < valid;
-        const size_t at = (arow0 + (size_t)(k0 + (ok ? r : 0)) * b2 + j) * d + 8 * ch;
-        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-        float t = 0.f;
-        if (ok) {
-          ldw8((const TW*)bp.dA + at, lo, hi);
-          f32x4 alo, ahi;
-          ldw8((const TW*)bp.Anext + at, alo, ahi);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t = fmaf(lo[e], alo[e], fmaf(hi[e], ahi[e], t));
-        }
-        t = CPR == 16 ? row16_sum(t) : row8_sum(t);
-        if (in) {
-          *(uint4*)(Vs + r * LD + 8 * ch) = __builtin_bit_cast(uint4, pack8(lo, hi));
-          if (ch == 0) tcs[r] = t;
-        }
-      }
-    }
-    if (tid < kStage) {
-      const int nk = k0 + tid;
-      const bool ok = nk < NK;
-      bias[tid] = ok ? -cLp[nk] * kLog2e : -INFINITY;
-      if (!LAST) {
-        const size_t at = arow0 + (size_t)(ok ? nk : 0) * b2 + j;
-        cms[tid] = ok ? bp.cmx[at] * kLog2e : 0.f;
-        cis[tid] = ok ? bp.cinv[at] : 0.f;
-      }
-    }
-  };
-
-  const int lt = wave, l = 16 * lt + c;
-  const bool tile_live = lt < nlt;           // an odd tile count leaves one wave that only writes zeros
-  const bool live = l < b1;
-  const int lc = l < b1 ? l : b1 - 1;
-  bf16x8 qv[KS1], xv[KS1];
-#pragma unroll
-  for (int ks = 0; ks < KS1; ++ks) {
-    qv[ks] = ld_global_16B(Qp + qrow(lc) + 32 * ks + 8 * g);
-    xv[ks] = LAST ? ld_global_16B(dOp + orow(lc) + 32 * ks + 8 * g) : qv[ks];
-  }
-  const float scale2 = p.scale * kLog2e;
-  // regular Monarch under the chunk-causal mask: this lane's query row sees the keys below klim
-  // (key 0 is visible to every row, so the running maxima are finite after the first segment)
-  const int klim = p.rl > 0 ? visible_key_rows(p, lc) : 0x7fffffff;
-
-  // ---- sweep 1: lse2[l] and delta[l]
-  float mz = -INFINITY, sz = 0.f;            // running maximum / sum of 2^(z - mz)
-  float mw = -INFINITY, dw = 0.f;            // the same for the shifted logits, weighted sum of u
-  for (int kb = 0; kb < NK; kb += kStage) {
-    __syncthreads();
-    stage(kb);
-    __syncthreads();
-    for (int h = 0; h < kStageSegs && kb + h * kSeg < NK; ++h) {
-    const int k0 = kb + h * kSeg;
-    const u16* Ksh = Ks + h * kSeg * LD;
-    const u16* Vsh = Vs + h * kSeg * LD;
-    const float *biash = bias + h * kSeg, *tcsh = tcs + h * kSeg, *cmsh = cms + h * kSeg, *cish = cis + h * kSeg;
-    if (!tile_live) continue;
-    f32x4 s[NTK], dl[NTK];
-    rows_dot<D, NTK, LD>(Ksh, qv, s, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    rows_dot<D, NTK, LD>(Vsh, xv, dl, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    float mx = -INFINITY, mxw = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < NTK; ++kt) {
-      const f32x4 bi = mask_bias(*(const f32x4*)(biash + 16 * kt + 4 * g), k0 + 16 * kt + 4 * g, klim);
-      f32x4 cm = {0.f, 0.f, 0.f, 0.f};
-      if (!LAST) cm = *(const f32x4*)(cmsh + 16 * kt + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        s[kt][r] = fmaf(s[kt][r], scale2, bi[r]);
-        mx = fmaxf(mx, s[kt][r]);
-        if (!LAST) mxw = fmaxf(mxw, s[kt][r] - cm[r]);
-      }
-    }
-    const float mzn = fmaxf(mz, xmax(mx));
-    const float mwn = LAST ? mzn : fmaxf(mw, xmax(mxw));
-    float ps = 0.f, pd = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < NTK; ++kt) {
-      f32x4 cm = {0.f, 0.f, 0.f, 0.f}, ci = {1.f, 1.f, 1.f, 1.f}, tc = {0.f, 0.f, 0.f, 0.f};
-      if (!LAST) {
-        cm = *(const f32x4*)(cmsh + 16 * kt + 4 * g);
-        ci = *(const f32x4*)(cish + 16 * kt + 4 * g);
-        tc = *(const f32x4*)(tcsh + 16 * kt + 4 * g);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float e = exp2_fast(s[kt][r] - mzn);
-        ps += e;
-        const float ew = LAST ? e : exp2_fast(s[kt][r] - cm[r] - mwn) * ci[r];
-        pd = fmaf(ew, dl[kt][r] - tc[r], pd);
-      }
-    }
-    sz = fmaf(sz, exp2_fast(mz - mzn), xsum(ps));
-    dw = fmaf(dw, exp2_fast((LAST ? mz : mw) - mwn), xsum(pd));
-    mz = mzn;
-    mw = mwn;
-    }
-  }
-  const float lse2 = mz + log2_fast(sz);
-  const float delta = dw * exp2_fast((LAST ? mz : mw) - lse2);
-
-  // ---- sweep 2: L (or w), dZ, their transposed copies, dQ
-  float* dQp = bp.dQ + (size_t)bh * p.Nq * d;
-  u16* Pt = Pw + row0 * LP;
-  u16* Zt = Zw + row0 * LP;
-  f32x4 o[NVT];
-#pragma unroll
-  for (int vt = 0; vt < NVT; ++vt) o[vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kb = 0; kb < NK; kb += kStage) {
-    __syncthreads();
-    stage(kb);
-    __syncthreads();
-    for (int h = 0; h < kStageSegs && kb + h * kSeg < NK; ++h) {
-    const int k0 = kb + h * kSeg;
-    const u16* Ksh = Ks + h * kSeg * LD;
-    const u16* Vsh = Vs + h * kSeg * LD;
-    const float *biash = bias + h * kSeg, *tcsh = tcs + h * kSeg, *cmsh = cms + h * kSeg, *cish = cis + h * kSeg;
-    if (!tile_live) {
-      // the cols kernel reads as many query tiles as its template holds (2, 4, 6, or all ten of
-      // the wide pitch): the tiles beyond the last query tile are zeros
-      if (lt < (NW <= 6 ? 2 * ((nlt + 1) / 2) : NW))
-        for (int nk = k0 + g; nk < NK && nk < k0 + kSeg; nk += 4) {
-          if (LAST) Pt[(size_t)nk * LP + l] = 0;
-          Zt[(size_t)nk * LP + l] = 0;
-        }
-      continue;
-    }
-    f32x4 s[NTK], dl[NTK], wq[NTK];
-    rows_dot<D, NTK, LD>(Ksh, qv, s, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    rows_dot<D, NTK, LD>(Vsh, xv, dl, lane);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kt = 0; kt < NTK; ++kt) {
-      const f32x4 bi = mask_bias(*(const f32x4*)(biash + 16 * kt + 4 * g), k0 + 16 * kt + 4 * g, klim);
-      f32x4 cm = {0.f, 0.f, 0.f, 0.f}, ci = {0.f, 0.f, 0.f, 0.f}, tc = {0.f, 0.f, 0.f, 0.f};
-      if (!LAST) {
-        cm = *(const f32x4*)(cmsh + 16 * kt + 4 * g);
-        ci = *(const f32x4*)(cish + 16 * kt + 4 * g);
-        tc = *(const f32x4*)(tcsh + 16 * kt + 4 * g);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float logl = fmaf(s[kt][r], scale2, bi[r]) - lse2;           // log2 L, -inf beyond NK
-        const float L = live ? exp2_fast(logl) : 0.f;
-        const float w = LAST ? L : (live ? exp2_fast(logl - cm[r]) * ci[r] : 0.f);
-        const float dz = w * (dl[kt][r] - tc[r]) - L * delta;
-        wq[kt][r] = w;
-        dl[kt][r] = dz;
-        const int nk = k0 + 16 * kt + 4 * g + r;
-        if (nk < NK) {
-          if (LAST) Pt[(size_t)nk * LP + l] = f2bf(w);       // only dY, at t = T, is formed from it
-          Zt[(size_t)nk * LP + l] = f2bf(dz);
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // dQ[l] += scale sum_nk dZ[l,nk] aL[nk] (+ sum_nk w[l,nk] dA[nk])
-#pragma unroll
-    for (int st = 0; st < KS2; ++st) {
-      const bf16x8 pz = pack8(dl[2 * st] * p.scale, dl[2 * st + 1] * p.scale);
-      pv_step<D, LD>(Ksh + 32 * st * LD, pz, o, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!LAST) {
-        const bf16x8 pw = pack8(wq[2 * st], wq[2 * st + 1]);
-        pv_step<D, LD>(Vsh + 32 * st * LD, pw, o, lane);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    }
-  }
-  if (tile_live && live)
-    store_rows_f32<D>(dQp + (row_offset(p, a, l) + qcol) * d, o, 1.0f, g, bp.accumulate != 0);
-}
 
 // Sum of the products of the eight bf16 pairs of two 16-byte pieces.
 __device__ inline float dot8_bf16(uint4 a, uint4 b) {
@@ -787,8 +501,11 @@ __device__ inline float dot8_bf16(uint4 a, uint4 b) {
 }
 
 // ---------------------------------------------------------------------------------------
-// The streamed rows kernel for a bf16 workspace, software-pipelined.  Same two sweeps over the key
-// range and the same arithmetic as k_bwdm_l_rows_stream, but the segments of 64 key rows travel
+// Rows kernel for key ranges that do not fit LDS, one workgroup per (m, j), software-pipelined.  Two
+// sweeps over the key range: the first forms the row statistics online (running maximum and sum of the
+// logits for the log-sum-exp, and delta[l] = sum_c (L dL)[l, c] against a running maximum of its own, so
+// that the column shift of the weights never meets a positive exponent); the second forms L (or w), dZ and
+// the dQ products with them.  Segments of 64 key rows travel
 // through a ring of two LDS slots behind one set of registers: while the waves work on segment s
 // (slot s mod 2), the global loads of segment s + 1 are in flight; they are written to the other
 // slot when the wave is done with s, the loads of s + 2 are issued, and one barrier ends the step.
@@ -804,7 +521,8 @@ __device__ inline float dot8_bf16(uint4 a, uint4 b) {
 // query tile is owned by two waves, each taking half of a segment's key tiles, twelve waves in
 // all.  The two halves' row statistics are merged after the first sweep and their partial dQ rows
 // after the second, through LDS.  (KSPLIT = 2 needs every row to see key 32 of the range, which
-// holds unless regular Monarch runs under the chunk-causal mask: the host picks KSPLIT = 1 then.)
+// holds unless regular Monarch runs under the chunk-causal mask; its one key tile is streamed from 97
+// rows on, and so has more than six query tiles.)
 // ---------------------------------------------------------------------------------------
 template <int D, bool LAST, int NQT, int KSPLIT>
 __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdParams bp, u16* Pw, u16* Zw) {
@@ -1166,16 +884,12 @@ __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdPa
 // ---------------------------------------------------------------------------------------
 // stage L backward, cols kernel, one workgroup per (m, j)
 // ---------------------------------------------------------------------------------------
-template <int D, int NLT, bool LAST, typename TW>
+template <int D, int NLT, bool LAST>
 __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams bp, const u16* Pw, const u16* Zw) {
   const KParams& p = bp.k;
   constexpr int LD = D + kBPad, NVT = D / 16, KS2 = (NLT + 1) / 2, QROWS = 32 * KS2;
   constexpr int LP = NLT <= 6 ? kLP : kLPWide;
-  // up to six query tiles: Q and dO side by side; ten: one tile's worth of LDS, used for Q first
-  // and for dO afterwards
-  constexpr bool kTwoTiles = LAST && NLT <= 6;
-  __shared__ __attribute__((aligned(16))) u16 Qs[QROWS * LD];
-  __shared__ __attribute__((aligned(16))) u16 Xs_two[kTwoTiles ? QROWS * LD : 8];
+  __shared__ __attribute__((aligned(16))) u16 Qs[QROWS * LD];     // Q, then (LAST) dO
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int b1 = p.b1, b2 = p.b2, d = D;
@@ -1191,7 +905,6 @@ __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams
   const u16* Qp = (const u16*)p.Q + b * p.qs.batch + hd * p.qs.head + qcol * p.qs.token;
   const u16* dOp = (const u16*)bp.dO + b * p.os.batch + hd * p.os.head + qcol * p.os.token;
   stage_rows_batched<D, LD, QROWS, 256>(Qs, Qp, tile_rows(p, a, p.qs.token), b1, tid);
-  if (kTwoTiles) stage_rows_batched<D, LD, QROWS, 256>(Xs_two, dOp, tile_rows(p, a, p.os.token), b1, tid);
   __syncthreads();
 
   const u16* Pt = Pw + row0 * LP;
@@ -1219,20 +932,9 @@ __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams
       pv_step_nat<D, 1, LD>(Qs + 32 * st * LD, one, 1, o, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (nk < NK) store_ws_row<D>((TW*)bp.daL + (row0 + nk) * d, o[0], p.scale, g);
-    if constexpr (kTwoTiles) {
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) o[0][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < KS2; ++st) {
-        const bf16x8 one[1] = {ld_global_16B(Pt + (size_t)nkc * LP + 32 * st + 8 * g)};
-        pv_step_nat<D, 1, LD>(Xs_two + 32 * st * LD, one, 1, o, lane);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (nk < NK) store_ws_row<D>((TW*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
-    }
+    if (nk < NK) store_ws_row<D>((u16*)bp.daL + (row0 + nk) * d, o[0], p.scale, g);
   }
-  if constexpr (LAST && !kTwoTiles) {
+  if constexpr (LAST) {
     // dY[nk] = sum_l L[l, nk] dO[l], with dO in the tile Q has just left
     __syncthreads();
     stage_rows_batched<D, LD, QROWS, 256>(Qs, dOp, tile_rows(p, a, p.os.token), b1, tid);
@@ -1249,7 +951,7 @@ __global__ __launch_bounds__(256, NLT <= 6 ? 3 : 2) void k_bwdm_l_cols(BwdParams
         pv_step_nat<D, 1, LD>(Qs + 32 * st * LD, one, 1, o, lane);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (nk < NK) store_ws_row<D>((TW*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
+      if (nk < NK) store_ws_row<D>((u16*)bp.dY + (row0 + nk) * d, o[0], 1.0f, g);
     }
   }
 }
@@ -1662,31 +1364,13 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
 
 bool bwd_bf16_fits(const KParams& kp) { return kp.b1 <= kBRowsWide && (kp.d == 64 || kp.d == 128); }
 size_t bwd_bf16_scratch_bytes(const KParams& kp, int ntq_total) {
-  // the transposed L and dZ arrays: (m, j, nk) rows of 96 or 160 bf16 each, two arrays
-  return (size_t)ntq_total * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1) * 2 * 2;
+  // what a cols launch reads: the transposed dZ and, at t = T, L, (m, j, nk) rows of 96 or 160 bf16 each (whether a
+  // resident key range takes two launches depends on the heads of a launch)
+  const int nkt = (kp.ntk * kp.b1 + 15) / 16;
+  const int arrays = 16 * nkt > kBRows ? (kp.b1 > kBRows ? 2 : 0) : (kp.d == 128 && nkt > 4 ? 1 : 0);
+  return (size_t)ntq_total * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1) * 2 * arrays;
 }
 
-template <int D, bool LAST, typename TW>
-static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, u16* Zw, hipStream_t s) {
-  switch (nkt) {
-    case 1: case 2: k_bwdm_l_rows<D, 2, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 3: case 4: k_bwdm_l_rows<D, 4, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 5: case 6:
-      // (fp32 workspace; the figures are those of the bf16 one, before its two sides were one launch)
-      // two six-wave workgroups fit a compute unit, three of four waves.  Up to one workgroup per unit six
-      // waves shorten a training step by 7 to 10 % (3 heads of 52 columns, T = 2: 119 -> 110 us; 14 heads of
-      // 16: 130 -> 121), up to two per unit only this kernel's t = T launches (T = 1, 8 heads of 48: 81.2 ->
-      // 79.9; 20 heads of 14: 65.6 -> 63.1; T = 2 with both: 9 heads of 52 174 -> 177, 32 of 16 186 -> 190),
-      // beyond that a second round costs more (12 heads of 52 218 -> 234)
-      if ((long long)grid.x * grid.y * grid.z <= (LAST ? 2LL : 1LL) * compute_units())
-        k_bwdm_l_rows<D, 6, LAST, TW, 6><<<grid, 384, 0, s>>>(bp, Pw, Zw);
-      else
-        k_bwdm_l_rows<D, 6, LAST, TW, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
 // Rows and columns of the resident stage L backward in one launch (bf16 workspace): no transposed scratch
 // (65 MB written and read in a step of the 480p chunk), no second read of Q and dO from global memory, one
 // launch less an iteration.  One query tile a wave, so six waves for five and six tiles: two such workgroups
@@ -1695,24 +1379,11 @@ static hipError_t launch_rows(const BwdParams& bp, dim3 grid, int nkt, u16* Pw, 
 // (64,40), 12: 129 -> 117; (32,32), 12: 78 -> 71; (96,16) of 64 features, 12: 79 -> 67.
 template <int D, bool LAST>
 static hipError_t launch_rows_and_cols(const BwdParams& bp, dim3 grid, int nkt, hipStream_t s) {
-  if (nkt <= 2) k_bwdm_l_rows<D, 2, LAST, u16, 4, true><<<grid, 256, 0, s>>>(bp, nullptr, nullptr);
-  else if (nkt <= 4) k_bwdm_l_rows<D, 4, LAST, u16, 4, true><<<grid, 256, 0, s>>>(bp, nullptr, nullptr);
-  else k_bwdm_l_rows<D, 6, LAST, u16, 6, true><<<grid, 384, 0, s>>>(bp, nullptr, nullptr);
+  if (nkt <= 2) k_bwdm_l_rows<D, 2, LAST, 4, true><<<grid, 256, 0, s>>>(bp, nullptr);
+  else if (nkt <= 4) k_bwdm_l_rows<D, 4, LAST, 4, true><<<grid, 256, 0, s>>>(bp, nullptr);
+  else k_bwdm_l_rows<D, 6, LAST, 6, true><<<grid, 384, 0, s>>>(bp, nullptr);
   return hipGetLastError();
 }
-template <int D, bool LAST, typename TW>
-static hipError_t launch_cols(const BwdParams& bp, dim3 grid, int nlt, const u16* Pw, const u16* Zw,
-                              hipStream_t s) {
-  switch (nlt) {
-    case 1: case 2: k_bwdm_l_cols<D, 2, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 3: case 4: k_bwdm_l_cols<D, 4, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 5: case 6: k_bwdm_l_cols<D, 6, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    case 7: case 8: case 9: case 10: k_bwdm_l_cols<D, 10, LAST, TW><<<grid, 256, 0, s>>>(bp, Pw, Zw); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 bool bwd_bf16_r_fits(const KParams& kp) { return kp.b2 <= 96 && (kp.d == 64 || kp.d == 128); }
 
 // Workgroups of `kernel` the current device keeps resident at once (its compute units times the
@@ -1791,71 +1462,59 @@ hipError_t launch_bwd_bf16_stage_r(const BwdParams& bp, int nbh, bool first, boo
                      : launch_r_d<64, float>(bp, nitems, first, last, s);
 }
 
-// Stage L backward on the matrix unit; scratch = bwd_bf16_scratch_bytes() of device memory.
-template <int D, typename TW>
-static hipError_t launch_l_d(const BwdParams& bp, dim3 grid, int nkt, int nlt, bool last, u16* Pw, u16* Zw,
-                             hipStream_t s) {
-  hipError_t e;
-  if (16 * nkt > kBRows) {
-    // key range beyond the resident kernel: streamed, one wave per query tile (always six or ten
-    // waves: the staging loops are laid out for the full workgroup)
-    if constexpr (sizeof(TW) == 2) {
-      // bf16 workspace: the pipelined kernel
-      if (nlt <= 6 && bp.k.rl == 0) {
-        // twelve waves, and the column side of the stage in the same kernel: no cols launch
-        if (last) k_bwdm_l_rows_ring<D, true, 6, 2><<<grid, 768, 0, s>>>(bp, Pw, Zw);
-        else k_bwdm_l_rows_ring<D, false, 6, 2><<<grid, 768, 0, s>>>(bp, Pw, Zw);
-        return hipGetLastError();
-      } else if (nlt <= 6) {
-        if (last) k_bwdm_l_rows_ring<D, true, 6, 1><<<grid, 384, 0, s>>>(bp, Pw, Zw);
-        else k_bwdm_l_rows_ring<D, false, 6, 1><<<grid, 384, 0, s>>>(bp, Pw, Zw);
-      } else {
-        if (last) k_bwdm_l_rows_ring<D, true, 10, 1><<<grid, 640, 0, s>>>(bp, Pw, Zw);
-        else {
-          // t < T: column side in the same kernel
-          k_bwdm_l_rows_ring<D, false, 10, 1><<<grid, 640, 0, s>>>(bp, Pw, Zw);
-          return hipGetLastError();
-        }
-      }
-    } else if (nlt <= 6) {
-      if (last) k_bwdm_l_rows_stream<D, true, TW, 6><<<grid, 384, 0, s>>>(bp, Pw, Zw);
-      else k_bwdm_l_rows_stream<D, false, TW, 6><<<grid, 384, 0, s>>>(bp, Pw, Zw);
-    } else {
-      if (last) k_bwdm_l_rows_stream<D, true, TW, 10><<<grid, 640, 0, s>>>(bp, Pw, Zw);
-      else k_bwdm_l_rows_stream<D, false, TW, 10><<<grid, 640, 0, s>>>(bp, Pw, Zw);
-    }
-    e = hipGetLastError();
-  } else if constexpr (sizeof(TW) == 2) {
-    if (last) return launch_rows_and_cols<D, true>(bp, grid, nkt, s);
-    // Five and six tiles at 128 features, t < T: where one launch would leave less than a quarter of a second
-    // round, the two launches (three workgroups of four waves a unit, one round) are ahead (training steps, one
-    // launch, two: 10 heads of (90,52) 199 -> 192 us, 12 222 -> 220, 13 of (80,40) 196 -> 189; beyond 2.5 a unit
-    // 14 heads of (90,52) 230 -> 231, 19 of (80,40) 220 -> 224).  Same bits.
-    const long long wgs = (long long)grid.x * grid.y * grid.z, cus = compute_units();
-    if (!(D == 128 && nkt > 4 && wgs > 2 * cus && 2 * wgs <= 5 * cus)) return launch_rows_and_cols<D, false>(bp, grid, nkt, s);
-    k_bwdm_l_rows<D, 6, false, u16, 4><<<grid, 256, 0, s>>>(bp, Pw, Zw);
-    e = hipGetLastError();
-  } else {
-    e = last ? launch_rows<D, true, TW>(bp, grid, nkt, Pw, Zw, s)
-             : launch_rows<D, false, TW>(bp, grid, nkt, Pw, Zw, s);
-  }
-  if (e != hipSuccess) return e;
-  return last ? launch_cols<D, true, TW>(bp, grid, nlt, Pw, Zw, s)
-              : launch_cols<D, false, TW>(bp, grid, nlt, Pw, Zw, s);
+// Five and six resident key tiles at 128 features, t < T: where one launch would leave less than a quarter of a
+// second round, two launches (three workgroups of four waves a unit, one round) are ahead (training steps, one
+// launch, two: 10 heads of (90,52) 199 -> 192 us, 12 222 -> 220, 13 of (80,40) 196 -> 189; beyond 2.5 a unit
+// 14 heads of (90,52) 230 -> 231, 19 of (80,40) 220 -> 224).  Same bits.
+static bool two_launches(int d, int nkt, long long wgs) {
+  const long long cus = compute_units();
+  return d == 128 && (nkt == 5 || nkt == 6) && wgs > 2 * cus && 2 * wgs <= 5 * cus;
 }
 
-hipError_t launch_bwd_bf16_stage_l(const BwdParams& bp, int nbh, bool last, bool ws_bf16, void* scratch,
-                                   hipStream_t s) {
+// Stage L backward on the matrix unit (bf16 workspace); scratch = bwd_bf16_scratch_bytes() of device memory.
+template <int D>
+static hipError_t launch_l_d(const BwdParams& bp, dim3 grid, int nkt, int nlt, bool last, u16* Pw, u16* Zw,
+                             hipStream_t s) {
+  if (16 * nkt > kBRows) {
+    // key range beyond the resident kernel: streamed (always all waves: the staging loops are laid out for
+    // the full workgroup)
+    if (nlt <= 6) {
+      // twelve waves, and the column side of the stage in the same kernel: no cols launch
+      if (last) k_bwdm_l_rows_ring<D, true, 6, 2><<<grid, 768, 0, s>>>(bp, nullptr, nullptr);
+      else k_bwdm_l_rows_ring<D, false, 6, 2><<<grid, 768, 0, s>>>(bp, nullptr, nullptr);
+    } else if (!last) {
+      // t < T: column side in the same kernel
+      k_bwdm_l_rows_ring<D, false, 10, 1><<<grid, 640, 0, s>>>(bp, nullptr, nullptr);
+    } else {
+      k_bwdm_l_rows_ring<D, true, 10, 1><<<grid, 640, 0, s>>>(bp, Pw, Zw);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      k_bwdm_l_cols<D, 10, true><<<grid, 256, 0, s>>>(bp, Pw, Zw);
+    }
+    return hipGetLastError();
+  }
+  if (last) return launch_rows_and_cols<D, true>(bp, grid, nkt, s);
+  if constexpr (D == 128)
+    if (two_launches(D, nkt, (long long)grid.x * grid.y * grid.z)) {
+      k_bwdm_l_rows<D, 6, false, 4, false><<<grid, 256, 0, s>>>(bp, Zw);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      if (nlt <= 2) k_bwdm_l_cols<D, 2, false><<<grid, 256, 0, s>>>(bp, nullptr, Zw);
+      else if (nlt <= 4) k_bwdm_l_cols<D, 4, false><<<grid, 256, 0, s>>>(bp, nullptr, Zw);
+      else k_bwdm_l_cols<D, 6, false><<<grid, 256, 0, s>>>(bp, nullptr, Zw);
+      return hipGetLastError();
+    }
+  return launch_rows_and_cols<D, false>(bp, grid, nkt, s);
+}
+
+hipError_t launch_bwd_bf16_stage_l(const BwdParams& bp, int nbh, bool last, void* scratch, hipStream_t s) {
   const KParams& kp = bp.k;
   dim3 grid(kp.b2, kp.ntq, nbh);
   const int nkt = (kp.ntk * kp.b1 + 15) / 16, nlt = (kp.b1 + 15) / 16;
-  u16* Pw = (u16*)scratch;
-  u16* Zw = Pw + (size_t)nbh * kp.ntq * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1);
-  if (kp.d == 128)
-    return ws_bf16 ? launch_l_d<128, u16>(bp, grid, nkt, nlt, last, Pw, Zw, s)
-                   : launch_l_d<128, float>(bp, grid, nkt, nlt, last, Pw, Zw, s);
-  return ws_bf16 ? launch_l_d<64, u16>(bp, grid, nkt, nlt, last, Pw, Zw, s)
-                 : launch_l_d<64, float>(bp, grid, nkt, nlt, last, Pw, Zw, s);
+  u16* Zw = (u16*)scratch;
+  u16* Pw = Zw + (size_t)nbh * kp.ntq * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1);
+  return kp.d == 128 ? launch_l_d<128>(bp, grid, nkt, nlt, last, Pw, Zw, s)
+                     : launch_l_d<64>(bp, grid, nkt, nlt, last, Pw, Zw, s);
 }
 
 }  // namespace mrt
