@@ -1364,11 +1364,10 @@ __global__ __launch_bounds__(64 * NT + (LW ? kLoaderThreads<NT> : 0), LW ? 2 : (
 
 bool bwd_bf16_fits(const KParams& kp) { return kp.b1 <= kBRowsWide && (kp.d == 64 || kp.d == 128); }
 size_t bwd_bf16_scratch_bytes(const KParams& kp, int ntq_total) {
-  // what a cols launch reads: the transposed dZ and, at t = T, L, (m, j, nk) rows of 96 or 160 bf16 each (whether a
-  // resident key range takes two launches depends on the heads of a launch)
-  const int nkt = (kp.ntk * kp.b1 + 15) / 16;
-  const int arrays = 16 * nkt > kBRows ? (kp.b1 > kBRows ? 2 : 0) : (kp.d == 128 && nkt > 4 ? 1 : 0);
-  return (size_t)ntq_total * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1) * 2 * arrays;
+  // room for what a cols launch reads, the transposed dZ and, at t = T, L: (m, j, nk) rows of 96 or 160 bf16
+  // each.  One size for all blocks, though only those of more than 96 query rows and two_launches use it: how
+  // many launches a resident key range takes depends on the heads of a launch.
+  return (size_t)ntq_total * kp.b2 * kp.ntk * kp.b1 * lp_of(kp.b1) * 2 * 2;
 }
 
 // Rows and columns of the resident stage L backward in one launch (bf16 workspace): no transposed scratch
