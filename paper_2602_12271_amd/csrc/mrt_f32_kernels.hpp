@@ -13,15 +13,18 @@
 // and a product is six bf16 products (mrt_f32_split.hpp; layout as in the bf16 path).  What bounds the
 // split kernels is the vector ALU: eleven instructions split two numbers, against which the products
 // take a third of the time.  A compute unit must hold two or three workgroups, or their loads and
-// barriers show: six waves (2, 2, 1, 1 on the SIMDs) only double up at 128 registers a wave.
-// 4680 tokens, 12 heads of 128, regular (90,52), T = 2: stage R 35 -> 29 us and 52 -> 40 us (last),
-// refine 59 -> 40 us, output 58 -> 36 us, the call 195 -> 138..144 us; dense baseline 1318 -> 1010 us; the
-// error against 64 bits 3.0e-7 -> 2.7e-7.
+// barriers show: six waves (2, 2, 1, 1 on the SIMDs, every workgroup's alike) only double up at 128 registers a
+// wave (measured with waves that only wait: 128 registers, 512 workgroups in one round, 136 in two).  The bounds cost
+// local memory: the refine of six, eight and ten query tiles at 128 features keeps 150 to 290 bytes a lane there, most
+// of them for its rare second logits, the output of six and eight tiles with more than 192 keys 260 and 180.
+// 4680 tokens, 12 heads of 128, regular (90,52), T = 2: stage R 35 -> 31 us and 52 -> 42 us (last),
+// refine 59 -> 42 us, output 58 -> 41 us, the call 195 -> 145 us (in graphs 141); dense baseline 1318 -> 975 us;
+// the error against 64 bits 3.0e-7 -> 2.7e-7.
 //
 // fp32 operands remain where rows are moved element by element, for the smallest blocks (see run_r) and
-// where a product was an infinity or a NaN or operands were very small or huge.  The layout feeds the matrix unit from registers and 16-byte
-// LDS reads with nothing in between: lane (g = lane / 16, c = lane % 16) supplies A[c][k = g] and
-// B[k = g][c] of a step and holds C[4g + r][c] in register r.
+// where a product was an infinity or a NaN or operands were very small or huge.  The layout feeds the
+// matrix unit from registers and 16-byte LDS reads with nothing in between: lane (g = lane / 16,
+// c = lane % 16) supplies A[c][k = g] and B[k = g][c] of a step and holds C[4g + r][c] in register r.
 //   * First products contract over features, which are contiguous in both operands: with feature
 //     16 ks + 4 g + e as slot g of step (ks, e), a lane's operands of four steps are 16 contiguous
 //     bytes.
@@ -43,11 +46,21 @@ namespace mrt {
 
 namespace {
 
-__device__ inline f32x4 mfma4(f32x4 a, f32x4 b, f32x4 acc) {
+// A tile of a first product with fp32 operands: four sums side by side, each of every fourth step (one sum of all
+// steps rounds as often as there are steps, up to 32: over 36 calls of small blocks, drawn, the error against 64 bits
+// is 0.91 of what it was; small calls are 0.5 % longer, others not).
+struct Sums4 {
+  f32x4 s[4];
+  __device__ inline Sums4() {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
-  return acc;
-}
+    for (int e = 0; e < 4; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ inline void add(f32x4 a, f32x4 b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], s[e], 0, 0, 0);
+  }
+  __device__ inline f32x4 total() const { return (s[0] + s[1]) + (s[2] + s[3]); }
+};
 
 // ---- rows of four features -------------------------------------------------------------------
 template <typename T> struct Quad;
@@ -370,17 +383,11 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
     if (!EARLY_V) load_v();           // into the registers the operand had
   } else {
 #pragma unroll
-    for (int it = 0; it < NT; ++it) s[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int it = 0; it < NT; ++it) {
+      Sums4 sums;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      f32x4 ka[NT];
-#pragma unroll
-      for (int it = 0; it < NT; ++it) ka[it] = *(const f32x4*)(tile + (16 * it + c) * kLd<D> + 16 * ks + 4 * g);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int it = 0; it < NT; ++it)
-          s[it] = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[it][e], q.v[ks][e], s[it], 0, 0, 0);
+      for (int ks = 0; ks < D / 16; ++ks) sums.add(*(const f32x4*)(tile + (16 * it + c) * kLd<D> + 16 * ks + 4 * g), q.v[ks]);
+      s[it] = sums.total();
     }
   }
   // softmax over i and sum_i R log R = (sum_i e z) / sum - log(sum)
@@ -528,13 +535,10 @@ __device__ inline void flash32(const TK* kbase, long long kstride, const TK* vba
 #pragma unroll
         for (int t = 0; t < NT; ++t) watch.see(z[t]);
       } else {
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        Sums4 sums;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ks += 2) {
-          s0 = mfma4(*(const f32x4*)(slot + c * kLd<D> + 16 * ks + 4 * g), q.v[ks], s0);
-          s1 = mfma4(*(const f32x4*)(slot + c * kLd<D> + 16 * ks + 16 + 4 * g), q.v[ks + 1], s1);
-        }
-        z[0] = s0 + s1;
+        for (int ks = 0; ks < D / 16; ++ks) sums.add(*(const f32x4*)(slot + c * kLd<D> + 16 * ks + 4 * g), q.v[ks]);
+        z[0] = sums.total();
       }
       float zm = -INFINITY;
 #pragma unroll
@@ -829,15 +833,14 @@ __device__ inline bool stage_l_refine_one_32(const Place& at, const KParams& p, 
         watch.see(z[lt]);
         watch.see(z[lt + 1]);
       } else {
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
         const float* at = Qs + (16 * lt + c) * LD + 4 * g;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          s0 = mfma4(*(const f32x4*)(at + 16 * ks), kb.v[ks], s0);
-          s1 = mfma4(*(const f32x4*)(at + 16 * LD + 16 * ks), kb.v[ks], s1);
+        for (int i = 0; i < 2; ++i) {
+          Sums4 sums;
+#pragma unroll
+          for (int ks = 0; ks < D / 16; ++ks) sums.add(*(const f32x4*)(at + 16 * i * LD + 16 * ks), kb.v[ks]);
+          z[lt + i] = sums.total();
         }
-        z[lt] = s0;
-        z[lt + 1] = s1;
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -982,11 +985,13 @@ __device__ inline bool stage_l_refine_32(const Place& at, const KParams& p, floa
         watch.see(z[1]);
       } else {
         const float* at = Qs + (16 * lt + c) * LD + 4 * g;
-        z[0] = z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks)
+        for (int i = 0; i < 2; ++i) {
+          Sums4 sums;
 #pragma unroll
-          for (int i = 0; i < 2; ++i) z[i] = mfma4(*(const f32x4*)(at + 16 * i * LD + 16 * ks), kb.v[ks], z[i]);
+          for (int ks = 0; ks < D / 16; ++ks) sums.add(*(const f32x4*)(at + 16 * i * LD + 16 * ks), kb.v[ks]);
+          z[i] = sums.total();
+        }
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
