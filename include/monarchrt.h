@@ -47,7 +47,8 @@ typedef enum {
 typedef enum { MRT_F32 = 0, MRT_BF16 = 1 } mrt_dtype;
 
 /* Arithmetic used inside the kernels.
- *   MRT_COMPUTE_DEFAULT : f32 storage -> fp32 arithmetic throughout;
+ *   MRT_COMPUTE_DEFAULT : f32 storage -> fp32 arithmetic throughout, products either of fp32 operands or, no less
+ *                         accurate, of operands that are sums of three bf16 numbers, accumulated in fp32;
  *                         bf16 storage -> bf16 MFMA operands, fp32 accumulation and softmax.
  *   MRT_COMPUTE_F32     : fp32 arithmetic and fp32 intermediates whatever the storage type
  *                         (slow; a device-side cross-check). */

@@ -1132,7 +1132,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_st
   const int b1 = p.b1, b2 = p.b2;
   const int j = blockIdx.x, ml = blockIdx.y, m = p.m0 + ml, bhl = last_head_first(), bh = p.bh0 + bhl;
   const int a = m / p.c2, bq = m - a * p.c2;
-  const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;   // <= 64 * PT
+  const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;   // <= 16 * PT * NW
   const size_t NKtot = (size_t)p.ntk * b1;
   const int b = bh / p.H, hd = bh - b * p.H;
 
@@ -1422,7 +1422,9 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 
 // ---------------------------------------------------------------------------------------
 // stage L for medium key ranges (96 < NK <= 192; b1 <= 128 with four waves, b1 > 144 with six): still one
-// workgroup per (m, j) and three (of four waves) or two (of six) workgroups per compute unit, with ONE 52 KB LDS tile used twice.  Last iteration: the
+// workgroup per (m, j), three of four waves to a compute unit, with ONE 52 KB LDS tile used twice.  (Six waves lie
+// 2, 2, 1, 1 on the SIMDs, every workgroup's alike: two of them share a unit up to 128 registers a wave, as here at
+// 64 features and with one query tile a wave; the others, with 132 to 164, have a unit to themselves.)  Last iteration: the
 // tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one or two query
 // tiles against all keys and keeps the probabilities as packed bf16 in registers), then Y[m, j]
 // (second product).  Earlier iterations: the tile holds alpha_L for the row log-sum-exp, then Q
@@ -1432,8 +1434,8 @@ constexpr int kMidRows = 192;
 constexpr int kMidWideB1 = 144;   // beyond: no bf16 backward pass
 
 // Last iterations of at most 192 key rows that take the one-tile-twice kernel: b1 <= 128 with four waves,
-// three workgroups per compute unit; b1 > 144 with six, two workgroups per compute unit where the
-// streamed kernel's eight waves have it to themselves (b1 = 156, 12 heads of 30 columns: launch 28.0 ->
+// three workgroups per compute unit; b1 > 144 with six, without the streamed kernel's chunk pipeline
+// (b1 = 156, 12 heads of 30 columns: launch 28.0 ->
 // 22.2 us; b1 = 180, 40 columns: 33.9 -> 30.0 us; masked b1 = 156, one to 40 heads: calls 4 to 7 %
 // shorter).  In between the streamed kernel stays: a training step's saving forward call needs its row
 // statistics there, and it returns the bits of the plain call.  It also stays for masked blocks of more
@@ -1613,7 +1615,7 @@ hipError_t launch_l_out_mid(const KParams& kp, dim3 grid, hipStream_t s) {
 
 template <int D>
 hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t s) {
-  // b1 > 144 (then nkt >= 10): six waves, two workgroups per compute unit
+  // b1 > 144 (then nkt >= 10): six waves
   const bool wide = kp.b1 > kMidWideB1;
   switch (nkt) {
     case 7: case 8: return launch_l_out_mid<D, 8, 4>(kp, grid, s);
@@ -1621,12 +1623,13 @@ hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t
     case 11: case 12:
       if constexpr (D == 128) {
         // eleven and twelve tiles on six waves are two on every wave: with one, the rows in two workgroups, the
-        // chain of a workgroup is half as long (192 rows, 8 columns, calls of 1 to 40 heads 33.9 -> 30.5 us
-        // .. 81.3 -> 75.8; 180 rows, 40 columns, 8 heads 79.3 -> 73.2, 20 heads 160 -> 150), unless a launch
-        // of the whole columns fills the places of one round by itself (12 heads of them: 93.9 against
-        // 95.1).  Ten tiles leave two waves with one, and two workgroups of five waves gain nothing.
-        const long long wgs = (long long)grid.x * grid.y * grid.z, places = 2LL * compute_units();
-        if (wide && (4 * wgs <= 3 * places || wgs > places)) return launch_l_out_mid<D, 12, 6, 1>(kp, grid, s);
+        // chain of a workgroup is half as long and two workgroups fit a compute unit (117 registers against 152;
+        // 192 rows, 8 columns, calls of 1 to 40 heads 33.9 -> 30.5 us .. 81.3 -> 75.8; 180 rows, 40 columns, 8
+        // heads 79.3 -> 73.2, 20 heads 160 -> 150).  Between one and a half and two whole columns a unit (two full
+        // rounds of them; 12 heads of 40 columns) they stay whole: 93.9 against 95.1.  Ten tiles leave two waves
+        // with one, and two workgroups of five waves gain nothing.
+        const long long wgs = (long long)grid.x * grid.y * grid.z, two = 2LL * compute_units();
+        if (wide && (4 * wgs <= 3 * two || wgs > two)) return launch_l_out_mid<D, 12, 6, 1>(kp, grid, s);
       }
       return wide ? launch_l_out_mid<D, 12, 6>(kp, grid, s) : launch_l_out_mid<D, 12, 4>(kp, grid, s);
   }
@@ -1745,10 +1748,12 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
 }
 // 7 .. 12 query tiles (one key tile per query tile, so as many key tiles); an odd tile count runs as the
 // next even one (the extra tile is masked rows).  Eight: a wave per key tile (the rows of a wave are the
-// chain a workgroup waits for, and two such workgroups, or three, still share a compute unit; 112 rows, 40
+// chain a workgroup waits for; two such workgroups share a compute unit, 89 registers a wave, and under a mask, with
+// 168, one has it to itself, as the one of six waves had; 112 rows, 40
 // columns, calls of 1 to 40 heads 0.98 .. 0.88 of the time of six waves with two tiles each, 12 heads 57.6
-// -> 52.6 us; 128 rows, 24 columns, 64 features 0.98 .. 0.92).  Ten and twelve: six waves with two key tiles
-// each (a wave per tile: 0.99 .. 1.02, a unit then holds one workgroup).
+// -> 52.6 us, masked 0.97 .. 0.94; 128 rows, 24 columns, 64 features 0.98 .. 0.92, masked 0.94 .. 0.92).  Ten and
+// twelve: six waves with two key tiles each (a wave per tile: 0.99 .. 1.02), one workgroup to a unit (150 to 256
+// registers).
 template <int D>
 hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
   switch ((nlt + 1) / 2) {

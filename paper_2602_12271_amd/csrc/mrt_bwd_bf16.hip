@@ -1372,10 +1372,11 @@ size_t bwd_bf16_scratch_bytes(const KParams& kp, int ntq_total) {
 
 // Rows and columns of the resident stage L backward in one launch (bf16 workspace): no transposed scratch
 // (65 MB written and read in a step of the 480p chunk), no second read of Q and dO from global memory, one
-// launch less an iteration.  One query tile a wave, so six waves for five and six tiles: two such workgroups
-// share a compute unit with their 74 KB of LDS.  Training steps, T = 2, rows and cols launches before, now: heads of
-// (90,52) 1: 89 -> 81 us, 4: 115 -> 103, 12: 225 -> 220, 24: 433 -> 408; 64 features, 12: 141 -> 135;
-// (64,40), 12: 129 -> 117; (32,32), 12: 78 -> 71; (96,16) of 64 features, 12: 79 -> 67.
+// launch less an iteration.  One query tile a wave, so six waves for five and six tiles: a workgroup has a compute
+// unit to itself (150 and 168 registers; t = T at 64 features, 122: two share it).  Training steps, T = 2, as graphs, of
+// the library before this (two launches; its forward kernels were up to 2 % slower) and of this one: heads of (90,52)
+// 1: 93 -> 83 us, 4: 117 -> 104, 12: 239 -> 228, 24: 434 -> 409; 64 features, 12: 149 -> 140; (64,40), 12: 136 -> 122;
+// (32,32), 12: 81 -> 74; (96,16) of 64 features, 12: 80 -> 69.
 template <int D, bool LAST>
 static hipError_t launch_rows_and_cols(const BwdParams& bp, dim3 grid, int nkt, hipStream_t s) {
   if (nkt <= 2) k_bwdm_l_rows<D, 2, LAST, 4, true><<<grid, 256, 0, s>>>(bp, nullptr);
@@ -1461,10 +1462,11 @@ hipError_t launch_bwd_bf16_stage_r(const BwdParams& bp, int nbh, bool first, boo
                      : launch_r_d<64, float>(bp, nitems, first, last, s);
 }
 
-// Five and six resident key tiles at 128 features, t < T: where one launch would leave less than a quarter of a
-// second round, two launches (three workgroups of four waves a unit, one round) are ahead (training steps, one
-// launch, two: 10 heads of (90,52) 199 -> 192 us, 12 222 -> 220, 13 of (80,40) 196 -> 189; beyond 2.5 a unit
-// 14 heads of (90,52) 230 -> 231, 19 of (80,40) 220 -> 224).  Same bits.
+// Five and six resident key tiles at 128 features, t < T: where one launch would leave less than half of a
+// third round (a workgroup of six waves has its compute unit to itself), two launches (three workgroups of four
+// waves a unit, one round) are ahead (training steps as graphs, one launch, two: 10 heads of (90,52) 203.7 -> 200.2 us,
+// 12 228.9 -> 228.3, 13 of (80,40) 200.4 -> 195.4; in back-to-back calls 199 -> 192, 222 -> 220, 196 -> 189, and beyond
+// 2.5 a unit 14 heads of (90,52) 230 -> 231, 19 of (80,40) 220 -> 224).  Same bits.
 static bool two_launches(int d, int nkt, long long wgs) {
   const long long cus = compute_units();
   return d == 128 && (nkt == 5 || nkt == 6) && wgs > 2 * cus && 2 * wgs <= 5 * cus;

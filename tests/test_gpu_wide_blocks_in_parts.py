@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("rows", [161, 176, 177, 192])
 def test_same_bits_for_any_number_of_heads(rows):
-    w, d, heads = 8, 128, 56                 # 448 columns: one round of whole columns; 2 or 112 heads: in parts
+    w, d, heads = 8, 128, 56                 # 448 columns: whole; 2 or 112 heads: in parts
     gen = torch.Generator(device="cuda:0").manual_seed(rows)
     q, k, v = (torch.randn(1, heads, rows * w, d, generator=gen, device="cuda:0").bfloat16() for _ in range(3))
 
