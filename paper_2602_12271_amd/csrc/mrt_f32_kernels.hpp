@@ -388,6 +388,7 @@ __device__ inline bool stage_r_32(const Place& at, const KParams& p, int first, 
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks) sums.add(*(const f32x4*)(tile + (16 * it + c) * kLd<D> + 16 * ks + 4 * g), q.v[ks]);
       s[it] = sums.total();
+      if (NT > 3) __builtin_amdgcn_sched_barrier(0);      // (the second run of a split kernel: few registers, not speed)
     }
   }
   // softmax over i and sum_i R log R = (sum_i e z) / sum - log(sum)
