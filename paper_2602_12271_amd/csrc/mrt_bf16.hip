@@ -1126,6 +1126,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_st
   __shared__ __attribute__((aligned(16))) float red_m[NW][LROWS];
   __shared__ __attribute__((aligned(16))) float red_s[NW][LROWS];
   __shared__ __attribute__((aligned(16))) float lse[LROWS];
+  __shared__ __attribute__((aligned(16))) int limit[RMASK ? LROWS : 4];   // visible_key_rows of every query row
   __shared__ int redo;
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -1160,6 +1161,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_st
     cl[pt] = cLp[nkc] * kLog2e;
   }
   rq.template store<LD, SWZ>(Qs, tid);
+  if constexpr (RMASK)
+    for (int l = tid; l < LROWS; l += 64 * NW) limit[l] = visible_key_rows(p, l);
   __syncthreads();
   MRT_STAMP(1);
 
@@ -1188,16 +1191,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_st
       if (lt % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (RMASK) {
-      // regular Monarch under the chunk-causal mask: key rows of later chunks are zeros of L
+      // regular Monarch under the chunk-causal mask: key rows of later chunks are zeros of L.  The rows'
+      // limits come from LDS, one division a row of the workgroup instead of one a row and lane (112
+      // rows, 40 columns, 12 heads, two iterations: call 63.3 -> 55.1 us; 64 rows 41.5 -> 40.5)
 #pragma unroll
-      for (int lt = 0; lt < NLT; ++lt)
+      for (int lt = 0; lt < NLT; ++lt) {
+        const int4 lim4 = *(const int4*)(limit + 16 * lt + 4 * g);
+        const int lim[4] = {lim4.x, lim4.y, lim4.z, lim4.w};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int lim = visible_key_rows(p, 16 * lt + 4 * g + r);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int pt = 0; pt < PT; ++pt)
-            if (16 * (tile0 + pt) + c >= lim) z[pt][lt][r] = -INFINITY;
-        }
+            if (16 * (tile0 + pt) + c >= lim[r]) z[pt][lt][r] = -INFINITY;
+      }
     }
   };
   logits();
