@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_res(KParams p) {
 // the key range are reduced inside the wave and exchanged between the NW waves through LDS;
 // alpha_L goes from global memory straight into the matrix operands, only Q is staged.
 template <int D, int NLT, int PT, int NW, bool RMASK>
-__global__ __launch_bounds__(64 * NW, NW == 4 || PT == 1 ? 3 : 2) void k_bf16_stage_l_refine_one(KParams p) {
+__global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) void k_bf16_stage_l_refine_one(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, QROWS = 32 * ((NLT + 1) / 2), LROWS = 16 * NLT;
   constexpr bool SWZ = ResTile<D>::SWZ;
   __shared__ __attribute__((aligned(16))) u16 Qs[QROWS * LD];
@@ -1427,10 +1427,10 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------
-// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 with four waves, b1 > 144 with six): still one
-// workgroup per (m, j), three of four waves to a compute unit, with ONE 52 KB LDS tile used twice.  (Six waves lie
-// 2, 2, 1, 1 on the SIMDs, every workgroup's alike: two of them share a unit up to 128 registers a wave, as here at
-// 64 features and with one query tile a wave; the others, with 132 to 164, have a unit to themselves.)  Last iteration: the
+// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 or b1 > 144): still one
+// workgroup per (m, j), three of four waves to a compute unit (b1 > 144: two, of three query tiles a wave), with
+// ONE 52 KB LDS tile used twice.  (Six waves lie 2, 2, 1, 1 on the SIMDs, every workgroup's alike: two of them
+// share a unit up to 128 registers a wave; with more they have it to themselves.)  Last iteration: the
 // tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one or two query
 // tiles against all keys and keeps the probabilities as packed bf16 in registers), then Y[m, j]
 // (second product).  Earlier iterations: the tile holds alpha_L for the row log-sum-exp, then Q
@@ -1440,7 +1440,7 @@ constexpr int kMidRows = 192;
 constexpr int kMidWideB1 = 144;   // beyond: no bf16 backward pass
 
 // Last iterations of at most 192 key rows that take the one-tile-twice kernel: b1 <= 128 with four waves,
-// three workgroups per compute unit; b1 > 144 with six, without the streamed kernel's chunk pipeline
+// three workgroups per compute unit; b1 > 144 (launch_l_out_mid_d), without the streamed kernel's chunk pipeline
 // (b1 = 156, 12 heads of 30 columns: launch 28.0 ->
 // 22.2 us; b1 = 180, 40 columns: 33.9 -> 30.0 us; masked b1 = 156, one to 40 heads: calls 4 to 7 %
 // shorter).  In between the streamed kernel stays: a training step's saving forward call needs its row
@@ -1504,12 +1504,15 @@ __device__ inline float mid_logits(const u16* Ks, const float* bias, const bf16x
   return mx;
 }
 
-// Six waves take the place of the streamed kernel and its reference (FIRST): where the bf16 roundings of
-// the weights fall depends on it, and against the maximum over all keys the error of two and three
+// Blocks of more than 144 rows (QT != 2 or six waves) take the place of the streamed kernel and its reference
+// (FIRST): where the bf16 roundings of the weights fall depends on it, and against the maximum over all keys the error of two and three
 // iterations came out 0.4 to 1 % larger (unit-normal queries and keys; 0.2 % smaller for one).
 // QT = 1: two workgroups share a column's rows, one query tile a wave.
-template <int D, int NTK, int NW, bool RMASK, int QT>
-__global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_mid(KParams p) {
+// EARLY: the values are requested ahead of the logits and wait in registers for the tile, where a workgroup has
+// its compute unit to itself and nothing else would cover their way (150 to 160 rows, 65 to 256 workgroups: the call
+// 0.3 us shorter; one head of 30 columns 29.5 -> 29.2; with two workgroups to a unit up to 1.5 % longer).
+template <int D, int NTK, int NW, bool RMASK, int QT, bool EARLY>
+__global__ __launch_bounds__(64 * NW, (EARLY || QT == 3 ? 2 : QT == 1 ? 4 : 3)) void k_bf16_stage_l_out_mid(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, NVT = D / 16, KS2 = (NTK + 1) / 2, ROWS = 32 * KS2;
   constexpr bool SWZ = ResTile<D>::SWZ;
   __shared__ __attribute__((aligned(16))) u16 tile[ROWS * LD];
@@ -1546,6 +1549,8 @@ __global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_m
     for (int ks = 0; ks < KS1; ++ks) qv[q][ks] = ld_global_16B(Qp + qrow(lc) + 32 * ks + 8 * g);
   }
   stage_rows_batched<D, LD, ROWS, nthr, SWZ>(tile, aLp, PlainRows{D}, NK, tid);
+  RowRegs<D, EARLY ? ROWS : 1, nthr> ry;
+  if constexpr (EARLY) ry.load(Yp, PlainRows{D}, NK, tid);
   for (int i = tid; i < ROWS; i += nthr) bias[i] = i < NK ? -cLp[i] * kLog2e : -INFINITY;
   __syncthreads();
   MRT_STAMP(1);
@@ -1561,7 +1566,7 @@ __global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_m
       f32x4 s[2 * KS2];
       const int lq = 16 * wt.lt[q] + c;
       const int klim = RMASK ? visible_key_rows(p, lq < b1 ? lq : b1 - 1) : 0;
-      const float mx = mid_logits<D, NTK, LD, SWZ, RMASK, (NW == 6)>(tile, bias, qv[q], scale2, klim, s, lane);
+      const float mx = mid_logits<D, NTK, LD, SWZ, RMASK, (QT != 2 || NW == 6)>(tile, bias, qv[q], scale2, klim, s, lane);
       float sm = 0.f;
 #pragma unroll
       for (int kt = 0; kt < 2 * KS2; ++kt)
@@ -1581,7 +1586,8 @@ __global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_m
   }
   __syncthreads();                      // every wave is done with alpha_L
   MRT_STAMP(2);
-  stage_rows_batched<D, LD, ROWS, nthr, SWZ>(tile, Yp, PlainRows{D}, NK, tid);
+  if constexpr (EARLY) ry.template store<LD, SWZ>(tile, tid);
+  else stage_rows_batched<D, LD, ROWS, nthr, SWZ>(tile, Yp, PlainRows{D}, NK, tid);
   __syncthreads();
   MRT_STAMP(3);
 
@@ -1606,38 +1612,39 @@ __global__ __launch_bounds__(64 * NW, QT == 1 ? 4 : 3) void k_bf16_stage_l_out_m
   MRT_STAMP(4);
 }
 
-template <int D, int NTK, int NW, int QT = 2>
+template <int D, int NTK, int NW, int QT = 2, bool EARLY = false>
 hipError_t launch_l_out_mid(const KParams& kp, dim3 grid, hipStream_t s) {
-  constexpr bool kMasked = !(D == 128 && NTK == 12 && NW == 6);        // (l_out_mid)
+  constexpr bool kMasked = !(D == 128 && NTK == 12 && (QT != 2 || NW == 6));        // (l_out_mid)
   if (QT == 1) grid.x *= 2;
   if (kp.rl > 0) {
-    if constexpr (kMasked) k_bf16_stage_l_out_mid<D, NTK, NW, true, QT><<<grid, 64 * NW, 0, s>>>(kp);
+    if constexpr (kMasked) k_bf16_stage_l_out_mid<D, NTK, NW, true, QT, EARLY><<<grid, 64 * NW, 0, s>>>(kp);
     else return hipErrorInvalidValue;
   } else {
-    k_bf16_stage_l_out_mid<D, NTK, NW, false, QT><<<grid, 64 * NW, 0, s>>>(kp);
+    k_bf16_stage_l_out_mid<D, NTK, NW, false, QT, EARLY><<<grid, 64 * NW, 0, s>>>(kp);
   }
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t s) {
-  // b1 > 144 (then nkt >= 10): six waves
+  // b1 > 144 (then nkt >= 10).  More columns than compute units: four waves of up to three query tiles, two
+  // workgroups to a unit (175 and 187 registers), where six waves of two (132 to 164) had it to themselves and took a
+  // second round ((156,30), 12 heads: launch 20.6 -> 17.1 us, and eleven and twelve tiles 1 to 3 % of the call).
+  // Fewer: a wave's chain is what the launch takes, so six waves, or halves of the rows in two workgroups, one tile a
+  // wave: twelve tiles always (24 columns x 1 head 33.9 -> 30.5 us when it came), ten up to a quarter of the units
+  // (30 columns, one head: call 30.8 -> 29.5; at four heads, 240 such workgroups, 39.6 -> 40.3).
   const bool wide = kp.b1 > kMidWideB1;
+  const long long wgs = (long long)grid.x * grid.y * grid.z, cus = compute_units();
   switch (nkt) {
     case 7: case 8: return launch_l_out_mid<D, 8, 4>(kp, grid, s);
-    case 9: case 10: return wide ? launch_l_out_mid<D, 10, 6>(kp, grid, s) : launch_l_out_mid<D, 10, 4>(kp, grid, s);
+    case 9: case 10:
+      if (!wide) return launch_l_out_mid<D, 10, 4>(kp, grid, s);
+      if (4 * wgs <= cus) return launch_l_out_mid<D, 10, 5, 1, true>(kp, grid, s);
+      return wgs <= cus ? launch_l_out_mid<D, 10, 6, 2, true>(kp, grid, s) : launch_l_out_mid<D, 10, 4, 3>(kp, grid, s);
     case 11: case 12:
-      if constexpr (D == 128) {
-        // eleven and twelve tiles on six waves are two on every wave: with one, the rows in two workgroups, the
-        // chain of a workgroup is half as long and two workgroups fit a compute unit (117 registers against 152;
-        // 192 rows, 8 columns, calls of 1 to 40 heads 33.9 -> 30.5 us .. 81.3 -> 75.8; 180 rows, 40 columns, 8
-        // heads 79.3 -> 73.2, 20 heads 160 -> 150).  Between one and a half and two whole columns a unit (two full
-        // rounds of them; 12 heads of 40 columns) they stay whole: 93.9 against 95.1.  Ten tiles leave two waves
-        // with one, and two workgroups of five waves gain nothing.
-        const long long wgs = (long long)grid.x * grid.y * grid.z, two = 2LL * compute_units();
-        if (wide && (4 * wgs <= 3 * two || wgs > two)) return launch_l_out_mid<D, 12, 6, 1>(kp, grid, s);
-      }
-      return wide ? launch_l_out_mid<D, 12, 6>(kp, grid, s) : launch_l_out_mid<D, 12, 4>(kp, grid, s);
+      if (!wide) return launch_l_out_mid<D, 12, 4>(kp, grid, s);
+      if (2 * wgs <= cus) return launch_l_out_mid<D, 12, 6, 1, true>(kp, grid, s);
+      return wgs <= cus ? launch_l_out_mid<D, 12, 6, 1>(kp, grid, s) : launch_l_out_mid<D, 12, 4, 3>(kp, grid, s);
   }
   return hipErrorInvalidValue;
 }
@@ -1754,18 +1761,20 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
 }
 // 7 .. 12 query tiles (one key tile per query tile, so as many key tiles); an odd tile count runs as the
 // next even one (the extra tile is masked rows).  Eight: a wave per key tile (the rows of a wave are the
-// chain a workgroup waits for; two such workgroups share a compute unit, 89 registers a wave, and under a mask, with
-// 168, one has it to itself, as the one of six waves had; 112 rows, 40
+// chain a workgroup waits for; two such workgroups share a compute unit, 89 to 100 registers a wave; 112 rows, 40
 // columns, calls of 1 to 40 heads 0.98 .. 0.88 of the time of six waves with two tiles each, 12 heads 57.6
 // -> 52.6 us, masked 0.97 .. 0.94; 128 rows, 24 columns, 64 features 0.98 .. 0.92, masked 0.94 .. 0.92).  Ten and
-// twelve: six waves with two key tiles each (a wave per tile: 0.99 .. 1.02), one workgroup to a unit (150 to 256
-// registers).
+// twelve: four waves with up to three key tiles each, two workgroups to a unit (204 to 256 registers).  Six waves
+// with two tiles each (150 to 171 registers) had a unit to themselves, so that 360 workgroups of (156,30), 12 heads,
+// took two rounds: launch 25.6 -> 19.9 us; from 257 workgroups on calls of 150 to 192 rows take 0.80 .. 0.93 of their
+// time together with the last launch's four waves; below that a launch is half a microsecond longer (a head's
+// bits depend on which key tiles share a wave, so the number of workgroups must not choose).
 template <int D>
 hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
   switch ((nlt + 1) / 2) {
     case 4: launch_refine_one_k<D, 8, 1, 8>(kp, grid, s); break;
-    case 5: launch_refine_one_k<D, 10, 2, 6>(kp, grid, s); break;
-    case 6: launch_refine_one_k<D, 12, 2, 6>(kp, grid, s); break;
+    case 5: launch_refine_one_k<D, 10, 3, 4>(kp, grid, s); break;
+    case 6: launch_refine_one_k<D, 12, 3, 4>(kp, grid, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
