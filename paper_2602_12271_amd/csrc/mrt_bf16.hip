@@ -1217,25 +1217,42 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
   // are formed again and the statistics redone with every row's own maximum; with S >= 2^-64 a
   // flushed e stands for a weight below 2^-62.
   auto stats = [&](bool per_row) {
+    float top[NLT];
+    if (!per_row) {
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) {
+        top[lt] = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int pt = 0; pt < PT; ++pt) top[lt] = fmaxf(top[lt], z[pt][lt][r]);
+      }
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) top[lt] = fmaxf(top[lt], dpp_mov<0xB1>(top[lt]));
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) top[lt] = fmaxf(top[lt], dpp_mov<0x4E>(top[lt]));
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) top[lt] = fmaxf(top[lt], dpp_mov<0x141>(top[lt]));
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) top[lt] = fmaxf(top[lt], dpp_mov<0x140>(top[lt]));
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) top[lt] = xmax(top[lt]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int lt = 0; lt < NLT; ++lt) {
       f32x4 vr;
-      float vt = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float v = z[0][lt][r];
-#pragma unroll
-        for (int pt = 1; pt < PT; ++pt) v = fmaxf(v, z[pt][lt][r]);
-        vr[r] = v;
-        vt = fmaxf(vt, v);
-      }
       if (per_row) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) vr[r] = row16_max(vr[r]);
-      } else {
-        vt = xmax(row16_max(vt));
+        for (int r = 0; r < 4; ++r) {
+          float v = z[0][lt][r];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) vr[r] = vt;
+          for (int pt = 1; pt < PT; ++pt) v = fmaxf(v, z[pt][lt][r]);
+          vr[r] = row16_max(v);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vr[r] = top[lt];
       }
       f32x4 sm;
 #pragma unroll
