@@ -231,6 +231,15 @@ mrt_status dense_attn_check(const mrt_problem* p, int causal_chunk);
 mrt_status dense_attn_fwd(const void* Q, const void* K, const void* V, void* O,
                           const mrt_problem* p, int causal_chunk, void* hip_stream);
 
+/* The same call with scratch memory (device, 256-byte aligned, contents undefined on entry and exit):
+ * where a bf16 call has too few queries to fill the GPU, several workgroups share the keys of a query
+ * tile and leave their partial results there.  dense_attn_workspace_bytes: what the call would use, 0
+ * where it splits nothing (every fp32 call).  With workspace NULL or smaller than that the call is
+ * dense_attn_fwd; the results of the two agree to fp32 rounding before O's. */
+size_t dense_attn_workspace_bytes(const mrt_problem* p, int causal_chunk);
+mrt_status dense_attn_fwd_ws(const void* Q, const void* K, const void* V, void* O, const mrt_problem* p,
+                             int causal_chunk, void* workspace, size_t workspace_bytes, void* hip_stream);
+
 /* Number of head groups monarch_attn_fwd and monarch_attn_bwd run concurrently: 1..4, or 0 (default) to let the library
  * choose per call (one group unless the launches are long and their grids small).  With more than one
  * group the library forks helper HIP streams from hip_stream and joins them back before it

@@ -25,6 +25,7 @@ EXPORTED = [
     "monarch_attn_bwd", "monarch_attn_bwd_workspace_bytes", "monarch_attn_bwd_workspace_min_bytes",
     "monarch_attn_fwd_noalloc",
     "monarch_attn_bwd_saved_workspace_bytes", "monarch_attn_fwd_save", "monarch_attn_bwd_saved",
+    "dense_attn_workspace_bytes", "dense_attn_fwd_ws",
 ]
 NOALLOC_SCRATCH_BYTES = 128 << 20
 ASSIGNMENTS = {"fh_w": 0, "w_fh": 1, "fw_h": 2, "h_fw": 3, "f_hw": 4, "hw_f": 5}
@@ -93,6 +94,10 @@ def load_library() -> ctypes.CDLL:
     lib.dense_attn_check.restype = ci
     lib.dense_attn_fwd.argtypes = [vp, vp, vp, vp, P, ci, vp]
     lib.dense_attn_fwd.restype = ci
+    lib.dense_attn_workspace_bytes.argtypes = [P, ci]
+    lib.dense_attn_workspace_bytes.restype = sz
+    lib.dense_attn_fwd_ws.argtypes = [vp, vp, vp, vp, P, ci, vp, sz, vp]
+    lib.dense_attn_fwd_ws.restype = ci
     lib.mrt_status_string.argtypes = [ci]
     lib.mrt_status_string.restype = ctypes.c_char_p
     lib.mrt_last_error.argtypes = []
@@ -332,16 +337,38 @@ def monarch_attn_bwd_saved(Q, K, V, dO, workspace, *, f_q, f_kv, h, w, b1, b2, t
     return dQ, dK, dV
 
 
+def dense_attn_workspace_bytes(prob: MrtProblem, causal_chunk=0) -> int:
+    """Scratch a dense call makes use of (0: none)."""
+    return int(load_library().dense_attn_workspace_bytes(ctypes.byref(prob), causal_chunk))
+
+
+def _dense_scratch(prob, causal_chunk, Q, s):
+    """Scratch of one dense call, or None.  Only on the stream that torch's allocator orders it by, and not
+    under a graph capture, whose replays would find the memory in other hands: such calls split no keys
+    unless they bring a workspace."""
+    import torch
+    known = prob.__dict__.setdefault("dense_bytes", {})      # by value, like the descriptor itself
+    nbytes = known.get(causal_chunk)
+    if nbytes is None:
+        nbytes = known[causal_chunk] = dense_attn_workspace_bytes(prob, causal_chunk)
+    if nbytes == 0 or s != _stream_of(Q, None) or torch.cuda.is_current_stream_capturing():
+        return None
+    return torch.empty(nbytes, dtype=torch.uint8, device=Q.device)
+
+
 def dense_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, causal_chunk=0, q_frame_offset=0, scale=1.0,
-                   compute=MRT_COMPUTE_DEFAULT, out=None, stream=None):
+                   compute=MRT_COMPUTE_DEFAULT, out=None, stream=None, workspace=None):
     """Dense softmax attention baseline on device tensors [batch, heads, tokens, head_dim]."""
     import torch
     lib = load_library()
     O = torch.empty_like(Q) if out is None else out
     prob = _call_problem(Q, K, V, O, f_q, f_kv, h, w, q_frame_offset, scale, compute)
     s = _stream_of(Q, stream)
-    st = lib.dense_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                            ctypes.byref(prob), causal_chunk, s)
+    if workspace is None:
+        workspace = _dense_scratch(prob, causal_chunk, Q, s)
+    ws, nbytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.numel() * workspace.element_size())
+    st = lib.dense_attn_fwd_ws(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
+                               ctypes.byref(prob), causal_chunk, ws, nbytes, s)
     if st != MRT_OK:
         _raise(lib, st)
     return O

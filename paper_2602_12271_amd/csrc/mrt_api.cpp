@@ -818,8 +818,30 @@ mrt_status dense_attn_check(const mrt_problem* p, int causal_chunk) {
   return MRT_OK;
 }
 
+// Everything of a dense call but its tensors.
+static KParams dense_params(const mrt_problem* p, int causal_chunk) {
+  KParams kp;
+  memset(&kp, 0, sizeof(kp));
+  kp.qs = p->q; kp.ks = p->k; kp.vs = p->v; kp.os = p->o;
+  kp.H = p->heads; kp.d = p->head_dim;
+  kp.Nq = p->f_q * p->h * p->w; kp.Nkv = p->f_kv * p->h * p->w; kp.hw = p->h * p->w;
+  kp.cc = causal_chunk; kp.qoff = p->q_frame_offset; kp.scale = p->scale;
+  return kp;
+}
+
+size_t dense_attn_workspace_bytes(const mrt_problem* p, int causal_chunk) {
+  if (dense_attn_check(p, causal_chunk) != MRT_OK) return 0;
+  if (p->dtype == MRT_F32 || p->compute == MRT_COMPUTE_F32) return 0;
+  return bf16_dense_workspace_bytes(dense_params(p, causal_chunk), p->batch * p->heads);
+}
+
 mrt_status dense_attn_fwd(const void* Q, const void* K, const void* V, void* O,
                           const mrt_problem* p, int causal_chunk, void* hip_stream) {
+  return dense_attn_fwd_ws(Q, K, V, O, p, causal_chunk, nullptr, 0, hip_stream);
+}
+
+mrt_status dense_attn_fwd_ws(const void* Q, const void* K, const void* V, void* O, const mrt_problem* p,
+                             int causal_chunk, void* workspace, size_t workspace_bytes, void* hip_stream) {
   mrt_status st = dense_attn_check(p, causal_chunk);
   if (st != MRT_OK) return st;
   if (!Q || !K || !V || !O) { set_error("Q, K, V and O must be non-NULL"); return MRT_ERR_NULL; }
@@ -829,17 +851,13 @@ mrt_status dense_attn_fwd(const void* Q, const void* K, const void* V, void* O,
     for (const void* q : ptrs)
       if ((uintptr_t)q % 16) { set_error("bf16 path needs 16-byte aligned tensors"); return MRT_ERR_SHAPE; }
   }
-  KParams kp;
-  memset(&kp, 0, sizeof(kp));
+  if ((uintptr_t)workspace % 256) { set_error("workspace must be 256-byte aligned"); return MRT_ERR_WORKSPACE; }
+  KParams kp = dense_params(p, causal_chunk);
   kp.Q = Q; kp.K = K; kp.V = V; kp.O = O;
-  kp.qs = p->q; kp.ks = p->k; kp.vs = p->v; kp.os = p->o;
-  kp.H = p->heads; kp.d = p->head_dim;
-  kp.Nq = p->f_q * p->h * p->w; kp.Nkv = p->f_kv * p->h * p->w; kp.hw = p->h * p->w;
-  kp.cc = causal_chunk; kp.qoff = p->q_frame_offset; kp.scale = p->scale;
   const int BH = p->batch * p->heads;
   hipError_t e = timed_launch((hipStream_t)hip_stream, MRT_KERNEL_DENSE, [&] {
     return f32 ? launch_f32_dense(kp, p->dtype, BH, (hipStream_t)hip_stream)
-               : launch_bf16_dense(kp, BH, (hipStream_t)hip_stream);
+               : launch_bf16_dense(kp, BH, workspace, workspace_bytes, (hipStream_t)hip_stream);
   });
   if (e != hipSuccess) return hip_fail(e, "dense launch");
   return MRT_OK;

@@ -19,8 +19,14 @@
 // WK = 1: every wave sees all keys.  WK = 2: waves w and w + 4 share their queries and take one half of
 // every 64 keys (half the queries per workgroup, so twice the workgroups); the halves are merged at the
 // end.
+//
+// PART: a workgroup takes one of `parts` runs of 64-key pairs and leaves its accumulators, references and
+// sums in fp32 for k_dense_merge; for calls of few queries (dense_shape).
 #include "mrt_internal.hpp"
 #include "mrt_bf16_tiles.hpp"
+
+#include <algorithm>
+#include <cmath>
 
 namespace mrt {
 
@@ -71,9 +77,17 @@ __host__ __device__ inline int dense_visible(const KParams& p, int q) {
   return lim < p.Nkv ? (int)lim : p.Nkv;
 }
 
+// Partial results of a call whose keys are split over `n` workgroups per query tile: every part's
+// accumulators, softmax reference and sum of a query (row = (part, head, query)).
+struct DenseParts {
+  float* o;     // [part][bh][q][D]
+  float2* ml;   // [part][bh][q]
+  int n;
+};
+
 // (64 features: two workgroups to a compute unit)
-template <int D, int QT, int WK>
-__global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(KParams p) {
+template <int D, int QT, int WK, bool PART>
+__global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(KParams p, DenseParts parts) {
   using Tile = DenseTile<D>;
   constexpr int KS1 = D / 32, NVT = D / 16, LD = kDenseLd<D>, WQ = kDenseWaves / WK, WGQ = 16 * QT * WQ;
   constexpr int NS = 2 / WK, NT = 2 * NS;                 // 32-key chunks / 16-key tiles of a wave's step
@@ -88,7 +102,8 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   const int nx = (p.Nq + WGQ - 1) / WGQ, total = gridDim.x, xcd = blockIdx.x & 7;
   int unit = blockIdx.x;
   if (visible(0) == visible(p.Nq - 1)) unit = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)) + (blockIdx.x >> 3);
-  const int bh = unit / nx, q0 = (unit - bh * nx) * WGQ;
+  const int run = unit / nx, q0 = (unit - run * nx) * WGQ;         // run = (head, part)
+  const int bh = PART ? run / parts.n : run, part = PART ? run - bh * parts.n : 0;
   const int b = bh / p.H, hd = bh - b * p.H;
   const int qw0 = q0 + 16 * QT * wq;                      // this wave's first query
   const int nkeys = visible(q0 + WGQ - 1 < p.Nq ? q0 + WGQ - 1 : p.Nq - 1), nfree = visible(q0);
@@ -108,6 +123,7 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   const int mid = WK == 1 ? visible(q0 + WGQ / 2 - 1 < p.Nq ? q0 + WGQ / 2 - 1 : p.Nq - 1) : nkeys;
   const int nmid = (mid + 63) >> 6, npairs = nmid + ((nkeys - mid + 63) >> 6);
   auto first_key = [&](int pr) { return pr < nmid ? 64 * pr : mid + 64 * (pr - nmid); };
+  const int p0 = PART ? part * npairs / parts.n : 0, p1 = PART ? (part + 1) * npairs / parts.n : npairs;   // this part's pairs
   const u16* Kp = (const u16*)p.K + b * p.ks.batch + hd * p.ks.head;
   const u16* Vp = (const u16*)p.V + b * p.vs.batch + hd * p.vs.head;
   const unsigned kvoff = (unsigned)(tid / Tile::CPR) * krow + 16u * (tid % Tile::CPR);
@@ -115,7 +131,7 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   Tile kt, vt;
   // (pairs past the end re-read the last one; nobody reads their slot, or only as masked keys)
   auto fetch = [&](int pr) {
-    const int at = pr < npairs ? pr : npairs - 1, end = at < nmid ? mid : nkeys;
+    const int last = PART && p1 > p0 ? p1 : npairs, at = pr < last ? pr : last - 1, end = at < nmid ? mid : nkeys;
     const unsigned key = (unsigned)first_key(at), rows = (unsigned)(end - 1);
     kt.load(__builtin_amdgcn_make_buffer_rsrc((void*)Kp, 0, rows * krow + 2 * D, 0x00020000), kvoff, key * krow, krow);
     vt.load(__builtin_amdgcn_make_buffer_rsrc((void*)Vp, 0, rows * vrow + 2 * D, 0x00020000), vvoff, key * vrow, vrow);
@@ -241,13 +257,17 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  fetch(0);
-  commit(0);
-  fetch(1);
-  commit(1);
-  fetch(2);
+  fetch(p0);
+  const Tile k0 = kt, v0 = vt;
+  fetch(p0 + 1);
+  const Tile k1 = kt, v1 = vt;
+  fetch(p0 + 2);
+  k0.store(dense_lds + (p0 & (kDenseSlots - 1)) * kDenseSlot<D>, tid);
+  v0.store(dense_lds + (p0 & (kDenseSlots - 1)) * kDenseSlot<D> + 64 * LD, tid);
+  k1.store(dense_lds + ((p0 + 1) & (kDenseSlots - 1)) * kDenseSlot<D>, tid);
+  v1.store(dense_lds + ((p0 + 1) & (kDenseSlots - 1)) * kDenseSlot<D> + 64 * LD, tid);
   __syncthreads();
-  matrix(0, 0, false);
+  matrix(p0 & (kDenseSlots - 1), 0, false);
   if (second) __syncthreads();
   auto step = [&](int i, int end, bool mine) {
     if (mine) soften(first_key(i) + (WK == 2 ? 32 * wk : 0), end);
@@ -261,9 +281,9 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
     __builtin_amdgcn_s_setprio(0);
     phase_end();
   };
-  for (int i = 0; i < nmid; ++i) step(i, mid, true);
+  for (int i = p0; i < (PART && p1 < nmid ? p1 : nmid); ++i) step(i, mid, true);
   if constexpr (WK == 1) {
-    for (int i = nmid; i < npairs; ++i) step(i, nkeys, second);
+    for (int i = PART && p0 > nmid ? p0 : nmid; i < p1; ++i) step(i, nkeys, second);
   }
   if (!second) __syncthreads();
 
@@ -286,9 +306,25 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
       const f32x4 ml = xo[(q * (NVT + 1) + NVT) * 64];
       const float m = fmaxf(mref[q], ml[0]), f0 = exp2_fast(mref[q] - m), f1 = exp2_fast(ml[0] - m);
       lrun[q] = lrun[q] * f0 + ml[1] * f1;
+      mref[q] = m;
 #pragma unroll
       for (int vt = 0; vt < NVT; ++vt) o[q][vt] = o[q][vt] * f0 + xo[(q * (NVT + 1) + vt) * 64] * f1;
     }
+  }
+  if constexpr (PART) {
+    const long long row0 = ((long long)part * (total / (nx * parts.n)) + bh) * p.Nq;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      const int qi = qw0 + 16 * q + c;
+      const float lsum = xsum(lrun[q]);
+      if (qi < p.Nq) {
+        float* row = parts.o + (row0 + qi) * D + 4 * g;
+#pragma unroll
+        for (int vt = 0; vt < NVT; ++vt) *(f32x4*)(row + 16 * vt) = o[q][vt];
+        if (g == 0) parts.ml[row0 + qi] = make_float2(mref[q], lsum);
+      }
+    }
+    return;
   }
   u16* Op = (u16*)p.O + b * p.os.batch + hd * p.os.head;
 #pragma unroll
@@ -307,13 +343,58 @@ __global__ __launch_bounds__(kDenseThreads, D == 64 ? 4 : 2) void k_bf16_dense(K
   }
 }
 
-template <int D, int QT, int WK>
-hipError_t run_dense(const KParams& kp, int nbh, hipStream_t s) {
-  const hipError_t e = hipFuncSetAttribute((const void*)k_bf16_dense<D, QT, WK>,
+// O from the parts: every part's sum and accumulators against the largest reference.  A thread owns
+// four features of a query and has eight parts in flight at once: what it waits for is memory.
+template <int D>
+__global__ __launch_bounds__(256) void k_dense_merge(KParams p, DenseParts parts, int rows) {
+  constexpr int TPR = D / 4, AHEAD = 8;
+  const int row = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, f = 4 * (threadIdx.x % TPR);
+  if (row >= rows) return;
+  float m = kNoKey, lsum = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < parts.n; i0 += AHEAD) {
+    float2 ml[AHEAD];
+    f32x4 po[AHEAD];
+#pragma unroll
+    for (int e = 0; e < AHEAD; ++e) {
+      const size_t at = (size_t)(i0 + e < parts.n ? i0 + e : parts.n - 1) * rows + row;
+      ml[e] = parts.ml[at];
+      po[e] = *(const f32x4*)(parts.o + at * D + f);
+    }
+    float top = m;
+#pragma unroll
+    for (int e = 0; e < AHEAD; ++e) top = fmaxf(top, ml[e].x);
+    const float keep = exp2_fast(m - top);
+    m = top;
+    lsum *= keep;
+    o = o * keep;
+#pragma unroll
+    for (int e = 0; e < AHEAD; ++e)
+      if (i0 + e < parts.n) {
+        const float w = exp2_fast(ml[e].x - m);
+        lsum += ml[e].y * w;
+        o = o + po[e] * w;
+      }
+  }
+  const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+  const f32x4 x = o * inv;
+  const int bh = row / p.Nq, q = row - bh * p.Nq, b = bh / p.H, hd = bh - b * p.H;
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  *(bf16x4*)((u16*)p.O + b * p.os.batch + hd * p.os.head + (long long)q * p.os.token + f) =
+      bf16x4{(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+}
+
+template <int D, int QT, int WK, bool PART>
+hipError_t run_dense(const KParams& kp, int nbh, const DenseParts& parts, hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute((const void*)k_bf16_dense<D, QT, WK, PART>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDenseLds<D>);
   if (e != hipSuccess) return e;
   constexpr int wgq = 16 * QT * kDenseWaves / WK;
-  k_bf16_dense<D, QT, WK><<<(kp.Nq + wgq - 1) / wgq * nbh, kDenseThreads, kDenseLds<D>, s>>>(kp);
+  k_bf16_dense<D, QT, WK, PART><<<(kp.Nq + wgq - 1) / wgq * nbh * parts.n, kDenseThreads, kDenseLds<D>, s>>>(kp, parts);
+  if constexpr (PART) {
+    const int rows = nbh * kp.Nq, rpw = 256 / (D / 4);
+    k_dense_merge<D><<<(rows + rpw - 1) / rpw, 256, 0, s>>>(kp, parts, rows);
+  }
   return hipGetLastError();
 }
 
@@ -332,28 +413,104 @@ hipError_t run_dense(const KParams& kp, int nbh, hipStream_t s) {
 // 88 a round: never ahead of 128 by more than 3 %, behind by up to 1.5 x.  Under a mask the workgroups
 // count by their share of the longest one's keys (12 heads of 3 chunks of 1040 tokens 50 | 63, 16 heads
 // 63 | 64, 32 heads 101 | 98).
-template <int D>
-hipError_t run_dense_d(const KParams& kp, int nbh, hipStream_t s) {
+//
+// Splitting the keys.  Calls of few queries leave most of the chip idle however small their workgroups
+// are (one head of 816 queries, 3264 keys: 26 workgroups of 64 queries, 43.6 us), so `parts` workgroups
+// share the keys of a query tile and a second launch merges their partial results.  `time` is a model of
+// a call fitted to 700 measured shapes of 29 calls, 6 % rms from them (rounds x steps of 64 keys x
+// microseconds a step, the merge launch, the partial results' bytes); the shape it picks is 1 % behind the
+// best one on average.  A split has to promise 6 % (2 heads of 816 queries of 3264 keys 43.6 -> 19 us, one
+// head of 7080 of 21240 244 -> 88, 4 heads of 1989 of 7956 96 -> 49, 6 heads of 7020 of 21060 501 -> 415;
+// 64 features: one head of 3240 of 12960 96 -> 30).  No split: 384 keys 10.6 (two parts 12.6), 12 heads of
+// 4680 of 4680 132 (155).
+constexpr int kMostParts = 32;
+constexpr size_t kMostPartsBytes = (size_t)128 << 20;       // of partial results
+constexpr long long kMostSplitRows = 1 << 18;               // 2^18 rows of two parts are more than that
+
+size_t dense_parts_bytes(int rows, int parts, int d) { return (size_t)rows * parts * (d + 2) * sizeof(float); }
+
+struct DenseShape {
+  int queries, parts;    // queries per workgroup, workgroups that share the keys of one query tile
+};
+
+DenseShape dense_shape(const KParams& kp, int nbh, bool may_split) {
   const long long cus = compute_units(), first = dense_visible(kp, 0), last = dense_visible(kp, kp.Nq - 1);
   auto wgs = [&](int queries) { return (long long)((kp.Nq + queries - 1) / queries) * nbh; };
-  if constexpr (D == 64) {
+  DenseShape best;
+  if (kp.d == 64) {
     auto cost = [&](int queries, long long one, long long two) {
       const long long n = (wgs(queries) * (first + last) + 2 * last - 1) / (2 * last), rest = n % (2 * cus);
       return n / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0);
     };
-    return cost(64, 40, 54) < cost(128, 57, 90) ? run_dense<64, 1, 2>(kp, nbh, s) : run_dense<64, 2, 2>(kp, nbh, s);
+    best = {cost(64, 40, 54) < cost(128, 57, 90) ? 64 : 128, 1};
   } else {
     auto cost = [&](int queries, long long unit) { return (wgs(queries) + cus - 1) / cus * unit; };
     const long long c256 = cost(256, first == last ? 126 : 112), c128 = cost(128, 79), c64 = cost(64, 61);
-    if (c64 < c128 && c64 < c256) return run_dense<D, 1, 2>(kp, nbh, s);
-    return c128 < c256 ? run_dense<D, 2, 2>(kp, nbh, s) : run_dense<D, 2, 1>(kp, nbh, s);
+    best = {c64 < c128 && c64 < c256 ? 64 : c128 < c256 ? 128 : 256, 1};
   }
+  if (!may_split || (long long)kp.Nq * nbh > kMostSplitRows) return best;
+  const long long pairs = (last + 63) / 64;
+  auto time = [&](int queries, int parts) {
+    const double steps = (double)((pairs + parts - 1) / parts), share = (double)(first + last) / (2 * last);
+    const long long n = wgs(queries) * parts;
+    double us = 0;
+    if (kp.d == 64) {
+      const long long busy = (long long)std::ceil(n * share), rest = busy % (2 * cus);
+      const double one = queries == 64 ? 0.45 : 0.72, two = queries == 64 ? 0.67 : 1.12;
+      us = 6.0 + steps * (busy / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0));
+      if (parts > 1) us += 4.2;
+    } else {
+      const long long rounds = (n + cus - 1) / cus;
+      const double full = first == last ? (double)rounds : std::max(1.0, n * share / cus + 0.6);
+      us = 3.4 + 4.1 * rounds + full * steps * (queries == 64 ? 0.71 : queries == 128 ? 1.02 : 1.56);
+      if (parts > 1) us += 5.5;
+    }
+    const double mb = 1e-6 * 2 * dense_parts_bytes(kp.Nq * nbh, parts, kp.d);      // written, read
+    return parts > 1 ? us + mb / (kp.d == 64 ? 3.0 : 5.7) : us;
+  };
+  const DenseShape one = best;
+  // Queries of one run (a workgroup, or its half if it has 256) meet the values of every key that one of
+  // them sees, with weights of zero where they don't: an infinite value hidden from some of them shows in
+  // them all.  A split takes no run longer than the unsplit call's that a chunk could end inside.
+  auto run_ok = [&](int queries) {
+    const long long run = std::min(queries, 128);
+    return first == last || run <= one.queries || ((long long)kp.cc * kp.hw % run == 0 && (long long)kp.qoff * kp.hw % run == 0);
+  };
+  double least = time(one.queries, 1) / 1.06;
+  for (int queries = 64; queries <= (kp.d == 64 ? 128 : 256); queries *= 2) {
+    if (!run_ok(queries)) continue;
+    for (int parts = 2; parts <= kMostParts && parts <= pairs; ++parts) {
+      if (dense_parts_bytes(kp.Nq * nbh, parts, kp.d) > kMostPartsBytes || wgs(queries) * parts > 6 * cus) break;
+      const double us = time(queries, parts);
+      if (us < least) { least = us; best = {queries, parts}; }
+    }
+  }
+  return best;
+}
+
+template <int D, bool PART>
+hipError_t run_dense_d(const KParams& kp, int nbh, int queries, const DenseParts& parts, hipStream_t s) {
+  if (queries == 64) return run_dense<D, 1, 2, PART>(kp, nbh, parts, s);
+  if constexpr (D == 128)
+    if (queries == 256) return run_dense<D, 2, 1, PART>(kp, nbh, parts, s);
+  return run_dense<D, 2, 2, PART>(kp, nbh, parts, s);
 }
 
 }  // namespace
 
-hipError_t launch_bf16_dense(const KParams& kp, int nbh, hipStream_t s) {
-  return kp.d == 128 ? run_dense_d<128>(kp, nbh, s) : run_dense_d<64>(kp, nbh, s);
+size_t bf16_dense_workspace_bytes(const KParams& kp, int nbh) {
+  const DenseShape shape = dense_shape(kp, nbh, true);
+  return shape.parts > 1 ? dense_parts_bytes(kp.Nq * nbh, shape.parts, kp.d) : 0;
+}
+
+hipError_t launch_bf16_dense(const KParams& kp, int nbh, void* workspace, size_t workspace_bytes, hipStream_t s) {
+  DenseShape shape = dense_shape(kp, nbh, workspace != nullptr);
+  if (shape.parts > 1 && workspace_bytes < dense_parts_bytes(kp.Nq * nbh, shape.parts, kp.d)) shape = dense_shape(kp, nbh, false);
+  const size_t rows = (size_t)kp.Nq * nbh * shape.parts;
+  const DenseParts parts = {(float*)workspace, (float2*)((float*)workspace + rows * kp.d), shape.parts};
+  if (kp.d == 128)
+    return shape.parts > 1 ? run_dense_d<128, true>(kp, nbh, shape.queries, parts, s) : run_dense_d<128, false>(kp, nbh, shape.queries, parts, s);
+  return shape.parts > 1 ? run_dense_d<64, true>(kp, nbh, shape.queries, parts, s) : run_dense_d<64, false>(kp, nbh, shape.queries, parts, s);
 }
 
 }  // namespace mrt

@@ -168,6 +168,9 @@ hipError_t launch_bwd_bf16_stage_r(const BwdParams& bp, int nbh, bool first, boo
 hipError_t launch_bf16_stage_r(const KParams& kp, int nbh, bool first, bool last, hipStream_t s);
 hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s);
 bool bf16_stage_l_out_streams(const KParams& kp);   // its last-iteration kernel fills lse_out / o32_out
-hipError_t launch_bf16_dense(const KParams& kp, int nbh, hipStream_t s);
+// workspace: null, or scratch for the parts of a call whose keys are split (used if it holds
+// bf16_dense_workspace_bytes(), 0 for a call that is not split)
+size_t bf16_dense_workspace_bytes(const KParams& kp, int nbh);
+hipError_t launch_bf16_dense(const KParams& kp, int nbh, void* workspace, size_t workspace_bytes, hipStream_t s);
 
 }  // namespace mrt
