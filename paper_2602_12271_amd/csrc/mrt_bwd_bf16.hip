@@ -18,7 +18,7 @@
 #include "mrt_internal.hpp"
 #include <type_traits>
 
-#include "mrt_bf16_tiles.hpp"
+#include "mrt_bwd_tiles.hpp"
 
 namespace mrt {
 
@@ -135,15 +135,6 @@ __device__ inline void rows_dot_add(const u16* rows, const bf16x8 (*const (&qv)[
   }
 }
 
-// Matrix operand from a row-major LDS tile X[j][i]: lane (g, c) receives column i0 + c of the rows
-// j = 16 (e / 4) + 4 g + e % 4, e = 0 .. 7 (the slots of pv_step).
-template <int PITCH>
-__device__ inline bf16x8 ld_columns(const u16* tile, int i0, int lane) {
-  const int g = lane >> 4, s = lane & 15;
-  const u16* at = tile + (4 * g + (s >> 2)) * PITCH + i0 + 4 * (s & 3);
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(ld_lds_tr(at), ld_lds_tr(at + 16 * PITCH), 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 // Second-product step with the contraction slots in natural order (slot (g, e) <-> row 8g + e of
 // the 32-row step), for B operands that come from memory rather than from accumulator registers.
 template <int D, int NB, int LD>
@@ -171,40 +162,6 @@ __device__ inline void pv_step_nat(const u16* vals, const bf16x8 (&pb)[NB], int 
         if (b < nb) acc[b][h * HALF + i] = mfma(av, pb[b], acc[b][h * HALF + i]);
     }
   }
-}
-
-// A lane's D/16 accumulator tiles as fp32: 8 consecutive features at 32q + 8g per pair of tiles.
-// The same rows with non-temporal stores: gradients that no later kernel of the call reads or adds
-// to (they would only displace the workspace arrays from the caches).
-template <int D>
-__device__ inline void store_rows_f32_nt(float* row, const f32x4* acc, float mul, int g) {
-#pragma unroll
-  for (int q = 0; q < D / 32; ++q) {
-    f32x4* p = (f32x4*)(row + 32 * q + 8 * g);
-    __builtin_nontemporal_store(acc[2 * q] * mul, p);
-    __builtin_nontemporal_store(acc[2 * q + 1] * mul, p + 1);
-  }
-}
-template <int D>
-__device__ inline void store_rows_f32(float* row, const f32x4* acc, float mul, int g, bool add) {
-#pragma unroll
-  for (int q = 0; q < D / 32; ++q) {
-    f32x4* p = (f32x4*)(row + 32 * q + 8 * g);
-    f32x4 a = acc[2 * q] * mul, b = acc[2 * q + 1] * mul;
-    if (add) { a += p[0]; b += p[1]; }
-    p[0] = a;
-    p[1] = b;
-  }
-}
-
-// A lane's row of D/16 accumulator tiles into a workspace array of either type (overwriting).
-template <int D>
-__device__ inline void store_ws_row(float* row, const f32x4* acc, float mul, int g) {
-  store_rows_f32<D>(row, acc, mul, g, false);
-}
-template <int D>
-__device__ inline void store_ws_row(u16* row, const f32x4* acc, float mul, int g) {
-  store_rows<D>(row, acc, mul, g);
 }
 
 // Transposed store of one accumulator tile: lane (c, g) holds v[r] for query row l = l16 + c and
@@ -883,244 +840,6 @@ __global__ __launch_bounds__(64 * NQT * KSPLIT, 3) void k_bwdm_l_rows_ring(BwdPa
 }
 
 // ---------------------------------------------------------------------------------------
-// Stage L backward at t = T of streamed key ranges, up to six query tiles, after a forward call that left
-// its row statistics: rows and columns in one sweep, one workgroup of four waves per (m, j).
-//
-// A wave owns 32 key rows at a time and every query row, so L and dZ of those keys never leave it: the
-// logits are formed with the queries on the accumulator rows (Q and dO of the column sit in LDS, alpha_L
-// and Y rows go from global memory straight into matrix operands), which makes L and dZ the operands of
-// dY = L^T dO and d alpha_L = scale dZ^T Q as they are.  Only dQ += scale dZ alpha_L contracts over the
-// keys: dZ and alpha_L pass through LDS of the wave's own for that, and every wave keeps a dQ of its own,
-// added up at the end.  The sweep has no barrier; the loads of a wave's next 32 keys are in flight while it
-// forms the results of these.  A compute unit holds one workgroup (two with up to two query tiles; four and
-// three at 64 features), so what is left over its bytes is the load of Q, dO and O ahead of the sweep and
-// the sum of the four dQ behind it, which nothing overlaps.
-//
-// Against the rows of twelve waves with LDS rings and two barriers every 64 keys (k_bwdm_l_rows_ring, which
-// stays for calls without the statistics): 480p clip, 90 rows, 642 -> 535 us (its bytes take 416 at the copy
-// rate); 20 rows of 17 columns, 12 tiles, 21 heads 292 -> 151; 64 features, 36 rows, 10 heads 74 -> 46, 16
-// rows, 2 heads 34 -> 18.  Longest key ranges first (all heads) cost 2 % of the clip's step, non-temporal
-// loads 3 %.
-// ---------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
-template <int D, int NLT>
-__global__ __launch_bounds__(256, NLT == 2 ? 2 : 1) void k_bwdm_l_keys(BwdParams bp) {
-  const KParams& p = bp.k;
-  constexpr int NW = 4, KEYS = 32, LD = D + 16, KS1 = D / 32, NVT = D / 16, ROWS = 16 * NLT, LZ = ROWS + 8, NS = NLT / 2;
-  constexpr int CPR = D / 8;
-  // Q | dO | per wave alpha_L rows, dZ [nk][l] | row statistics; afterwards the waves' dQ tiles
-  constexpr int kTiles = 2 * ROWS * LD + NW * KEYS * (LD + LZ);
-  __shared__ __attribute__((aligned(16))) u16 lds[kTiles];
-  __shared__ __attribute__((aligned(16))) float lse_s[ROWS], delta_s[ROWS];
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int g = lane >> 4, c = lane & 15;
-  u16 *Qs = lds, *dOs = lds + ROWS * LD, *Kt = lds + 2 * ROWS * LD + wave * KEYS * (LD + LZ), *Zt = Kt + KEYS * LD;
-  const int b1 = p.b1, b2 = p.b2;
-  const int j = blockIdx.x, ml = blockIdx.y, m = p.m0 + ml, bhl = blockIdx.z, bh = p.bh0 + bhl;
-  const int a = m / p.c2, bq = m - a * p.c2;
-  const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;
-  const size_t NKtot = (size_t)p.ntk * b1;
-  const int b = bh / p.H, hd = bh - b * p.H;
-  const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot, qr0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * b1;
-  const u16* aLp = (const u16*)p.aL + row0 * D;
-  const u16* Yp = (const u16*)p.Y + row0 * D;
-  const float* cLp = p.cL + row0;
-  const long long qcol = axis_offset(p.cmap, bq * b2 + j);
-  const u16* Qp = (const u16*)p.Q + b * p.qs.batch + hd * p.qs.head + qcol * p.qs.token;
-  const u16* dOp = (const u16*)bp.dO + b * p.os.batch + hd * p.os.head + qcol * p.os.token;
-
-  // a wave's 32 keys: operand rows (lane column = key) and c_L.  Lanes beyond the range repeat its last key,
-  // results included, which they store once more (a branch around a store would make the next loads' waits
-  // include every store); only dQ must not count it again.
-  bf16x8 ka[2][KS1], ya[2][KS1];
-  float cl[2];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const int nk = k0 + 16 * kt + c, at = nk < NK ? nk : NK - 1;
-#pragma unroll
-      for (int ks = 0; ks < KS1; ++ks) {
-        ka[kt][ks] = ld_global_16B(aLp + (size_t)at * D + 32 * ks + 8 * g);
-        ya[kt][ks] = ld_global_16B(Yp + (size_t)at * D + 32 * ks + 8 * g);
-      }
-      cl[kt] = cLp[at];
-    }
-  };
-  // the point where a chunk's loads are waited for: at the end of the loop body, where the count of the stores
-  // issued after them is exact (at its head the first pass, which has none, would make it wait for those too)
-  auto landed = [&]() {
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-      for (int ks = 0; ks < KS1; ++ks) {
-        u32x4 k4 = __builtin_bit_cast(u32x4, ka[kt][ks]), y4 = __builtin_bit_cast(u32x4, ya[kt][ks]);
-        asm volatile("" : "+v"(k4), "+v"(y4));
-        ka[kt][ks] = __builtin_bit_cast(bf16x8, k4);
-        ya[kt][ks] = __builtin_bit_cast(bf16x8, y4);
-      }
-      asm volatile("" : "+v"(cl[kt]));
-    }
-  };
-  {
-    RowRegs<D, ROWS, 256> rq, ro;
-    rq.load(Qp, tile_rows(p, a, p.qs.token), b1, tid);
-    ro.load(dOp, tile_rows(p, a, p.os.token), b1, tid);
-    f32x4 o32[RowRegs<D, ROWS, 256>::N][2];
-#pragma unroll
-    for (int i = 0; i < RowRegs<D, ROWS, 256>::N; ++i) {
-      const int r = (tid + 256 * i) / CPR, rc = r < b1 ? r : b1 - 1;
-      const float* at = bp.o32 + (qr0 + rc) * D + 8 * (tid % CPR);
-      o32[i][0] = *(const f32x4*)at;
-      o32[i][1] = *(const f32x4*)(at + 4);
-    }
-    if (tid < ROWS) lse_s[tid] = tid < b1 ? bp.lse[qr0 + tid] : INFINITY;      // (rows beyond b1: weights of zero)
-    fetch(KEYS * wave);
-    rq.template store<LD>(Qs, tid);
-    ro.template store<LD>(dOs, tid);
-    // delta[l] = sum_nk L[l, nk] (dO[l] . Y[nk]) = dO[l] . O[l]
-#pragma unroll
-    for (int i = 0; i < RowRegs<D, ROWS, 256>::N; ++i) {
-      const bf16x8 x = as_bf16x8(ro.v[i]);
-      float t = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t = fmaf((float)x[e], o32[i][e / 4][e % 4], t);
-      t = CPR == 16 ? row16_sum(t) : row8_sum(t);
-      const int r = (tid + 256 * i) / CPR;
-      if (tid % CPR == 0) delta_s[r] = r < b1 ? t : 0.f;
-    }
-  }
-  const float scale2 = p.scale * kLog2e;
-  f32x4 dq[NLT][NVT];
-#pragma unroll
-  for (int lt = 0; lt < NLT; ++lt)
-#pragma unroll
-    for (int vt = 0; vt < NVT; ++vt) dq[lt][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  __syncthreads();
-  landed();
-
-  for (int k0 = KEYS * wave; k0 < NK; k0 += KEYS * NW) {
-    bf16x8 zb[NS][2], lb[NS][2];              // dZ and L as operands: 32 query rows x 16 keys
-    float zsum[2] = {0.f, 0.f}, bias[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      bias[kt] = -cl[kt] * kLog2e;
-#pragma unroll
-      for (int ks = 0; ks < KS1; ++ks) *(uint4*)(Kt + (16 * kt + c) * LD + 32 * ks + 8 * g) = __builtin_bit_cast(uint4, ka[kt][ks]);
-    }
-#pragma unroll
-    for (int st = 0; st < NS; ++st) {
-      f32x4 s[2][2], dp[2][2];                // [query tile of the pair][key tile]
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u16 *qa = Qs + (32 * st + 16 * h + c) * LD + 8 * g, *oa = dOs + (32 * st + 16 * h + c) * LD + 8 * g;
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) s[h][kt] = dp[h][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-          const bf16x8 q = ld_lds_16B(qa + 32 * ks), o = ld_lds_16B(oa + 32 * ks);
-#pragma unroll
-          for (int kt = 0; kt < 2; ++kt) {
-            s[h][kt] = mfma(q, ka[kt][ks], s[h][kt]);
-            dp[h][kt] = mfma(o, ya[kt][ks], dp[h][kt]);
-          }
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4 lse = *(const f32x4*)(lse_s + 32 * st + 16 * h + 4 * g), delta = *(const f32x4*)(delta_s + 32 * st + 16 * h + 4 * g);
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float L = exp2_fast(fmaf(s[h][kt][r], scale2, bias[kt]) - lse[r]);
-            s[h][kt][r] = L;
-            dp[h][kt][r] = L * (dp[h][kt][r] - delta[r]);
-            zsum[kt] += dp[h][kt][r];
-          }
-        }
-      }
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        lb[st][kt] = pack8(s[0][kt], s[1][kt]);
-        zb[st][kt] = pack8(dp[0][kt], dp[1][kt]);
-        const uint4 z = k0 + 16 * kt + c < NK ? __builtin_bit_cast(uint4, zb[st][kt]) : uint4{0u, 0u, 0u, 0u};
-        u16* at = Zt + (16 * kt + c) * LZ + 32 * st + 4 * g;
-        *(uint2*)at = uint2{z.x, z.y};
-        *(uint2*)(at + 16) = uint2{z.z, z.w};
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(k0 + KEYS * NW);
-    __builtin_amdgcn_sched_barrier(0);
-    // dQ[l] += dZ[l, nk] alpha_L[nk]
-    {
-      bf16x8 zq[NLT];
-#pragma unroll
-      for (int lt = 0; lt < NLT; ++lt) zq[lt] = ld_columns<LZ>(Zt, 16 * lt, lane);
-      pv_step_multi<D, NLT, LD>(Kt, zq, NLT, dq, lane);
-    }
-    // d alpha_L[nk] = scale sum_l dZ[l, nk] Q[l], then dY[nk] = sum_l L[l, nk] dO[l]
-#pragma unroll
-    for (int out = 0; out < 2; ++out) {
-      f32x4 oc[2][NVT];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int vt = 0; vt < NVT; ++vt) oc[kt][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < NS; ++st) {
-        pv_step_multi<D, 2, LD>((out ? dOs : Qs) + 32 * st * LD, out ? lb[st] : zb[st], 2, oc, lane);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const size_t at = row0 + (k0 + 16 * kt + c < NK ? k0 + 16 * kt + c : NK - 1);
-        if (out) {
-          store_ws_row<D>((u16*)bp.dY + at * D, oc[kt], 1.0f, g);
-        } else {
-          store_ws_row<D>((u16*)bp.daL + at * D, oc[kt], p.scale, g);
-          bp.dcL[at] = -xsum(zsum[kt]);
-        }
-      }
-    }
-    landed();
-  }
-
-  // dQ: the waves' tiles through LDS, as many query tiles at a time as fit
-  constexpr int kTileBytes = NW * NVT * 64 * 16, kAtOnce = kTiles * 2 / kTileBytes, PAIRS = D / 32;
-  static_assert(kAtOnce >= 1, "LDS of a query tile's four parts");
-  f32x4* part = (f32x4*)lds;
-  const TokRows drow = tile_rows(p, a, D);
-  float* dQp = bp.dQ + ((size_t)bh * p.Nq + qcol) * D;
-#pragma unroll
-  for (int l0 = 0; l0 < NLT; l0 += kAtOnce) {
-    __syncthreads();
-#pragma unroll
-    for (int lt = l0; lt < (l0 + kAtOnce < NLT ? l0 + kAtOnce : NLT); ++lt)
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) part[(((lt - l0) * NW + wave) * NVT + vt) * 64 + lane] = dq[lt][vt];
-    __syncthreads();
-    const int n = (l0 + kAtOnce < NLT ? kAtOnce : NLT - l0) * PAIRS;
-    for (int i = wave; i < n; i += NW) {
-      const int lt = i / PAIRS, q = i - lt * PAIRS, l = 16 * (l0 + lt) + c;
-      f32x4 x[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4* at = part + (lt * NW * NVT + 2 * q + h) * 64 + lane;
-        x[h] = ((at[0] + at[NVT * 64]) + (at[2 * NVT * 64] + at[3 * NVT * 64])) * p.scale;
-      }
-      if (l < b1) {
-        f32x4* to = (f32x4*)(dQp + drow(l) + 32 * q + 8 * g);
-        if (bp.accumulate) { x[0] += to[0]; x[1] += to[1]; }
-        to[0] = x[0];
-        to[1] = x[1];
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------
 // stage L backward, cols kernel, one workgroup per (m, j)
 // ---------------------------------------------------------------------------------------
 template <int D, int NLT, bool LAST>
@@ -1625,19 +1344,6 @@ static hipError_t launch_rows_and_cols(const BwdParams& bp, dim3 grid, int nkt, 
 }
 bool bwd_bf16_r_fits(const KParams& kp) { return kp.b2 <= 96 && (kp.d == 64 || kp.d == 128); }
 
-// Workgroups of `kernel` the current device keeps resident at once (its compute units times the
-// workgroups of `threads` threads that fit one): the size of a persistent grid.
-template <typename K>
-static int resident_workgroups(K kernel, int threads) {
-  int per_cu = 0, dev = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
-    per_cu = 1;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
-  return per_cu * cus;
-}
-
 template <int NT, int D, typename TW>
 static hipError_t launch_r_nt(const BwdParams& bp, int nitems, bool first, bool last, hipStream_t s) {
   // persistent grid: as many workgroups as stay resident, each striding over the key blocks
@@ -1676,7 +1382,9 @@ static hipError_t launch_r_nt(const BwdParams& bp, int nitems, bool first, bool 
 template <int D, typename TW>
 static hipError_t launch_r_d(const BwdParams& bp, int nitems, bool first, bool last, hipStream_t s) {
   switch ((bp.k.b2 + 15) / 16) {
-    case 1: return launch_r_nt<1, D, TW>(bp, nitems, first, last, s);
+    case 1:
+      if constexpr (sizeof(TW) == 4) return launch_r_nt<1, D, TW>(bp, nitems, first, last, s);
+      else return launch_bwd_bf16_r_wave(bp, nitems, first, last, s);
     case 2: return launch_r_nt<2, D, TW>(bp, nitems, first, last, s);
     case 3: return launch_r_nt<3, D, TW>(bp, nitems, first, last, s);
     case 4: return launch_r_nt<4, D, TW>(bp, nitems, first, last, s);
@@ -1719,10 +1427,7 @@ static hipError_t launch_l_d(const BwdParams& bp, dim3 grid, int nkt, int nlt, b
     // key range beyond the resident kernel: streamed (always all waves: the staging loops are laid out for
     // the full workgroup)
     if (nlt <= 6 && last && bp.lse != nullptr && bp.k.rl == 0) {
-      // one sweep from the row statistics; by the query tiles, padded to pairs (an operand holds two)
-      if (nlt <= 2) k_bwdm_l_keys<D, 2><<<grid, 256, 0, s>>>(bp);
-      else if (nlt <= 4) k_bwdm_l_keys<D, 4><<<grid, 256, 0, s>>>(bp);
-      else k_bwdm_l_keys<D, 6><<<grid, 256, 0, s>>>(bp);
+      return launch_bwd_bf16_keys(bp, grid, nlt, s);
     } else if (nlt <= 6) {
       // twelve waves, and the column side of the stage in the same kernel: no cols launch
       if (last) k_bwdm_l_rows_ring<D, true, 6, 2><<<grid, 768, 0, s>>>(bp, nullptr, nullptr);

@@ -164,6 +164,11 @@ bool bwd_bf16_r_fits(const KParams& kp);
 hipError_t launch_bwd_bf16_stage_r(const BwdParams& bp, int nbh, bool first, bool last, bool ws_bf16,
                                    hipStream_t s);
 
+// ... its kernels of independent waves (mrt_bwd_waves_bf16.hip): stage L backward at t = T from the forward
+// call's row statistics (up to 96 query rows), stage R backward of up to 16 columns (bf16 workspace)
+hipError_t launch_bwd_bf16_keys(const BwdParams& bp, dim3 grid, int nlt, hipStream_t s);
+hipError_t launch_bwd_bf16_r_wave(const BwdParams& bp, int nitems, bool first, bool last, hipStream_t s);
+
 // bf16 MFMA path (mrt_bf16.hip)
 hipError_t launch_bf16_stage_r(const KParams& kp, int nbh, bool first, bool last, hipStream_t s);
 hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s);
