@@ -467,6 +467,7 @@ mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const m
       hipStream_t gs = gi == 0 ? s : pool->side[gi - 1];
       KParams kg = kp;
       kg.bh0 = bh0 + lo;
+      kg.beside = nbh - (hi - lo);
       kg.aL = (char*)kp.aL + pl.slab_aL * na * lo;
       kg.Y = (char*)kp.Y + pl.slab_Y * na * lo;
       kg.aR = (char*)kp.aR + pl.slab_aR * na * lo;
@@ -646,11 +647,11 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
   auto arrS = [&](size_t off, int lo) { return arr(off) + headS * (size_t)lo; };
 
   // the whole backward pass of heads [bh0 + lo, bh0 + hi) of a pass, on stream gs
-  auto run_heads = [&](int bh0, int lo, int hi, hipStream_t gs) -> mrt_status {
+  auto run_heads = [&](int bh0, int lo, int hi, int beside, hipStream_t gs) -> mrt_status {
     const int nbh = hi - lo;
     KParams kp = pl.kp;
     kp.Q = Q; kp.K = K; kp.V = V; kp.O = mode == kBwdForwardOnly ? O : nullptr;
-    kp.bh0 = bh0 + lo; kp.m0 = 0; kp.ntq = pl.ntq_total;
+    kp.bh0 = bh0 + lo; kp.beside = beside; kp.m0 = 0; kp.ntq = pl.ntq_total;
     kp.Y = arrD(L.off_Y(), lo);
     hipError_t e;
     // forward intermediates of every iteration (the last iteration's stage L only when O is asked
@@ -766,7 +767,7 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
     for (int gi = 0; gi < ngroups && status == MRT_OK; ++gi) {
       int lo = (int)((long long)nbh * gi / ngroups), hi = (int)((long long)nbh * (gi + 1) / ngroups);
       if (first_group > 0) { lo = gi == 0 ? 0 : first_group; hi = gi == 0 ? first_group : nbh; }
-      status = run_heads(bh0, lo, hi, gi == 0 ? s : pool->side[gi - 1]);
+      status = run_heads(bh0, lo, hi, nbh - (hi - lo), gi == 0 ? s : pool->side[gi - 1]);
     }
     // join even after a failed launch, so that the helper streams never run ahead of the caller
     for (int gi = 1; gi < ngroups; ++gi) {

@@ -373,8 +373,9 @@ __device__ inline bool flash_logits(f32x4 (&s)[QT][2], const float* bias, const 
   return grow;
 }
 
-// The rare step: raise every query's reference to its running maximum (the old reference or the
-// chunk's largest logit) and rescale its sum and, when WITH_V, its accumulators.
+// The rare step: raise the references of a query tile that has a logit more than kGrow above one to the
+// queries' running maxima (the old reference or the chunk's largest logit) and rescale its sums and, when
+// WITH_V, its accumulators.  A tile decides for itself: its bits do not depend on which tiles share a wave.
 template <int D, int QT, int NQ, bool WITH_V>
 __device__ inline void flash_grow(const f32x4 (&s)[QT][2], FlashState<QT>& st, f32x4 (&o)[QT][D / 16]) {
 #pragma unroll
@@ -384,6 +385,7 @@ __device__ inline void flash_grow(const f32x4 (&s)[QT][2], FlashState<QT>& st, f
     for (int it = 0; it < 2; ++it)
 #pragma unroll
       for (int r = 0; r < 4; ++r) zm = fmaxf(zm, s[q][it][r]);
+    if (__builtin_amdgcn_ballot_w64(zm > st.mrun[q] + kGrow) == 0) continue;
     const float mnew = fmaxf(st.mrun[q], xmax(zm));
     // mnew == -inf only if every key so far is hidden from this query: the state stays empty
     const float alpha = mnew == -INFINITY ? 1.0f : exp2_fast(st.mrun[q] - mnew);   // mrun = -inf -> 0
@@ -1430,7 +1432,7 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
   if (kp.rl > 0) {
     // (regular Monarch: one key tile of b1 rows, and up to eight query tiles of it are resident or take
     // the one-tile-twice kernel)
-    if constexpr (NT == 512) {
+    if constexpr (NT == 512 && QT == 2) {
       if (stats) k_bf16_stage_l_out<D, QT, NT, true, true><<<grid, NT, 0, s>>>(kp);
       else k_bf16_stage_l_out<D, QT, NT, true><<<grid, NT, 0, s>>>(kp);
     } else {
@@ -1666,12 +1668,22 @@ hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t
   return hipErrorInvalidValue;
 }
 
-// Streamed refine kernel: always four waves (one per SIMD, so that two workgroups fit a compute
-// unit however their waves are dealt to the SIMDs), each owning up to QT query tiles.  The chunk
+// The launch's workgroups (and those of the other head groups that run beside it) leave compute units with one
+// workgroup or none.  The streamed stage L kernels then take eight waves instead of four: nobody else is
+// there to fill a wave's waits, and the chain of a workgroup is what the launch takes (calls, four -> eight
+// waves: one head of 5 x 17 columns of 90 rows, 450 keys 59.4 -> 55.6 us; 4 heads of 17, 630 keys 68 -> 62; 126 rows, 36
+// columns 99 -> 90; 135 rows, 50 columns, T = 3 188 -> 172; 16 to 45 rows 1 to 4 %; beyond one a unit the two of four
+// waves are ahead: the part-filled group of the 480p KV-cache step, run so, made it 443 -> 450).
+static bool one_a_unit(const KParams& kp, dim3 grid) {
+  return (long long)grid.x * grid.y * (grid.z + kp.beside) <= compute_units();
+}
+
+// Streamed refine kernel: four waves (one per SIMD, so that two workgroups fit a compute
+// unit however their waves are dealt to the SIMDs), or eight (one_a_unit), each owning up to QT query tiles.  The chunk
 // ring of pass 1 and the Q tile of pass 2 share one LDS region (at most 56 KB for b1 = 192).
-template <int D, int NLT>
-hipError_t launch_l_refine(const KParams& kp, dim3 grid, hipStream_t s) {
-  constexpr int QT = (NLT + 3) / 4, MAXT = 256, PT = 2, PAD = kPad;
+template <int D, int NLT, int MAXT>
+hipError_t launch_l_refine_waves(const KParams& kp, dim3 grid, hipStream_t s) {
+  constexpr int QT = (NLT + MAXT / 64 - 1) / (MAXT / 64), PT = 2, PAD = kPad;
   const size_t tile = (size_t)32 * ((NLT + 1) / 2) * (D + PAD) * 2, ring = FlashLds<D, false, PAD>::kBytes;
   const size_t lds = kRefineHead + (tile > ring ? tile : ring);
   hipError_t e;
@@ -1679,8 +1691,13 @@ hipError_t launch_l_refine(const KParams& kp, dim3 grid, hipStream_t s) {
       (e = hipFuncSetAttribute((const void*)k_bf16_stage_l_refine<D, QT, MAXT, NLT, PT, PAD>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
     return e;
-  k_bf16_stage_l_refine<D, QT, MAXT, NLT, PT, PAD><<<grid, 256, lds, s>>>(kp);
+  k_bf16_stage_l_refine<D, QT, MAXT, NLT, PT, PAD><<<grid, MAXT, lds, s>>>(kp);
   return hipGetLastError();
+}
+
+template <int D, int NLT>
+hipError_t launch_l_refine(const KParams& kp, dim3 grid, hipStream_t s) {
+  return one_a_unit(kp, grid) ? launch_l_refine_waves<D, NLT, 512>(kp, grid, s) : launch_l_refine_waves<D, NLT, 256>(kp, grid, s);
 }
 
 template <int D, int NTK>
@@ -1840,6 +1857,8 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
                                 : launch_l_refine_d<64>(kp, grid, nlt, s);
   if (nlt <= 4) return kp.d == 128 ? launch_l_out<128, 1, 256>(kp, grid, s)
                                    : launch_l_out<64, 1, 256>(kp, grid, s);
+  if (nlt <= 8 && one_a_unit(kp, grid))
+    return kp.d == 128 ? launch_l_out<128, 1, 512>(kp, grid, s) : launch_l_out<64, 1, 512>(kp, grid, s);
   if (nlt <= 8) return kp.d == 128 ? launch_l_out<128, 2, 256>(kp, grid, s)
                                    : launch_l_out<64, 2, 256>(kp, grid, s);
   return kp.d == 128 ? launch_l_out<128, 2, 512>(kp, grid, s)

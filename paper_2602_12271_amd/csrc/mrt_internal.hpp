@@ -43,6 +43,7 @@ struct KParams {
   float* o32_out;   //   log-sum-exp of every query row's logits [bh][m][j][l] and O in fp32 [bh][m][j][l][d]
   int H;        // heads (to split the flat batch*head index)
   int bh0;      // first flat (batch,head) index of this pass
+  int beside;   // (batch,head) entries of the pass whose launches run beside this one, on other streams
   int d;
   int b1, b2;
   int c2;       // column tiles
