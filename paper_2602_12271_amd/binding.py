@@ -353,7 +353,10 @@ def _dense_scratch(prob, causal_chunk, Q, s):
         nbytes = known[causal_chunk] = dense_attn_workspace_bytes(prob, causal_chunk)
     if nbytes == 0 or s != _stream_of(Q, None) or torch.cuda.is_current_stream_capturing():
         return None
-    return torch.empty(nbytes, dtype=torch.uint8, device=Q.device)
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=Q.device)
+    except torch.cuda.OutOfMemoryError:       # a call that fits without its scratch still runs
+        return None
 
 
 def dense_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, causal_chunk=0, q_frame_offset=0, scale=1.0,

@@ -114,6 +114,20 @@ def test_captured_and_other_stream_calls():
         assert torch.equal(out, one) and torch.equal(split, pkg.dense_attn_fwd(*tensors, **args))
 
 
+def test_no_memory_for_the_scratch(monkeypatch):
+    # (the allocator's refusal is raised by a stand-in: no memory is filled)
+    tensors, args = inputs("64")
+    one, out = unsplit(tensors, args), torch.empty_like(tensors[0])
+
+    def refuse(*a, **kw):
+        raise torch.cuda.OutOfMemoryError("no memory")
+
+    with monkeypatch.context() as patch:
+        patch.setattr(torch, "empty", refuse)
+        pkg.dense_attn_fwd(*tensors, **args, out=out)
+    assert torch.equal(out, one)
+
+
 def test_which_calls_are_split():
     assert binding.dense_attn_workspace_bytes(*problem("64")) == 816 * 2 * 9 * 130 * 4
     for kw in (dict(dtype=binding.MRT_F32), dict(compute=binding.MRT_COMPUTE_F32)):
