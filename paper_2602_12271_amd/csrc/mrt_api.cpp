@@ -467,7 +467,6 @@ mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const m
       hipStream_t gs = gi == 0 ? s : pool->side[gi - 1];
       KParams kg = kp;
       kg.bh0 = bh0 + lo;
-      kg.beside = nbh - (hi - lo);
       kg.aL = (char*)kp.aL + pl.slab_aL * na * lo;
       kg.Y = (char*)kp.Y + pl.slab_Y * na * lo;
       kg.aR = (char*)kp.aR + pl.slab_aR * na * lo;
@@ -484,7 +483,7 @@ mrt_status fwd_run(const void* Q, const void* K, const void* V, void* O, const m
         trace_next_launch(gs);
         e = timed_launch(gs, MRT_KERNEL_STAGE_L | (last ? MRT_KERNEL_LAST : 0), [&] {
           return pl.f32_path() ? launch_f32_stage_l(kg, pl.dtype, hi - lo, last, gs)
-                               : launch_bf16_stage_l(kg, hi - lo, last, gs);
+                               : launch_bf16_stage_l(kg, hi - lo, nbh - (hi - lo), last, gs);
         }, may_time);
         if (e != hipSuccess) { status = hip_fail(e, "stage L launch"); break; }
       }
@@ -651,7 +650,7 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
     const int nbh = hi - lo;
     KParams kp = pl.kp;
     kp.Q = Q; kp.K = K; kp.V = V; kp.O = mode == kBwdForwardOnly ? O : nullptr;
-    kp.bh0 = bh0 + lo; kp.beside = beside; kp.m0 = 0; kp.ntq = pl.ntq_total;
+    kp.bh0 = bh0 + lo; kp.m0 = 0; kp.ntq = pl.ntq_total;
     kp.Y = arrD(L.off_Y(), lo);
     hipError_t e;
     // forward intermediates of every iteration (the last iteration's stage L only when O is asked
@@ -669,7 +668,7 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
         kp.aR = arrD(L.off_aR(t + 1), lo);
         kp.cmx_out = (float*)arrS(L.off_cmx(t + 1), lo);
         kp.cinv_out = (float*)arrS(L.off_cinv(t + 1), lo);
-        e = ws_bf16 ? launch_bf16_stage_l(kp, nbh, false, gs) : launch_f32_stage_l(kp, pl.dtype, nbh, false, gs);
+        e = ws_bf16 ? launch_bf16_stage_l(kp, nbh, beside, false, gs) : launch_f32_stage_l(kp, pl.dtype, nbh, false, gs);
         if (e != hipSuccess) return hip_fail(e, "backward: forward stage L launch");
       } else if (mode == kBwdForwardOnly) {
         kp.cmx_out = nullptr; kp.cinv_out = nullptr;
@@ -678,7 +677,7 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
           kp.lse_out = (float*)(arr(L.off_lse()) + headL * (size_t)lo);
           kp.o32_out = (float*)(arr(L.off_o32()) + headO * (size_t)lo);
         }
-        e = ws_bf16 ? launch_bf16_stage_l(kp, nbh, true, gs) : launch_f32_stage_l(kp, pl.dtype, nbh, true, gs);
+        e = ws_bf16 ? launch_bf16_stage_l(kp, nbh, beside, true, gs) : launch_f32_stage_l(kp, pl.dtype, nbh, true, gs);
         kp.lse_out = nullptr; kp.o32_out = nullptr;
         if (e != hipSuccess) return hip_fail(e, "forward stage L launch");
       }

@@ -1674,8 +1674,8 @@ hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t
 // waves: one head of 5 x 17 columns of 90 rows, 450 keys 59.4 -> 55.6 us; 4 heads of 17, 630 keys 68 -> 62; 126 rows, 36
 // columns 99 -> 90; 135 rows, 50 columns, T = 3 188 -> 172; 16 to 45 rows 1 to 4 %; beyond one a unit the two of four
 // waves are ahead: the part-filled group of the 480p KV-cache step, run so, made it 443 -> 450).
-static bool one_a_unit(const KParams& kp, dim3 grid) {
-  return (long long)grid.x * grid.y * (grid.z + kp.beside) <= compute_units();
+static bool one_a_unit(dim3 grid, int beside) {
+  return (long long)grid.x * grid.y * (grid.z + beside) <= compute_units();
 }
 
 // Streamed refine kernel: four waves (one per SIMD, so that two workgroups fit a compute
@@ -1696,8 +1696,8 @@ hipError_t launch_l_refine_waves(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 
 template <int D, int NLT>
-hipError_t launch_l_refine(const KParams& kp, dim3 grid, hipStream_t s) {
-  return one_a_unit(kp, grid) ? launch_l_refine_waves<D, NLT, 512>(kp, grid, s) : launch_l_refine_waves<D, NLT, 256>(kp, grid, s);
+hipError_t launch_l_refine(const KParams& kp, dim3 grid, bool eight, hipStream_t s) {
+  return eight ? launch_l_refine_waves<D, NLT, 512>(kp, grid, s) : launch_l_refine_waves<D, NLT, 256>(kp, grid, s);
 }
 
 template <int D, int NTK>
@@ -1721,20 +1721,20 @@ hipError_t launch_l_out_res_d(const KParams& kp, dim3 grid, int nkt, hipStream_t
 }
 
 template <int D>
-hipError_t launch_l_refine_d(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
+hipError_t launch_l_refine_d(const KParams& kp, dim3 grid, int nlt, bool eight, hipStream_t s) {
   switch (nlt) {
-    case 1: return launch_l_refine<D, 1>(kp, grid, s);
-    case 2: return launch_l_refine<D, 2>(kp, grid, s);
-    case 3: return launch_l_refine<D, 3>(kp, grid, s);
-    case 4: return launch_l_refine<D, 4>(kp, grid, s);
-    case 5: return launch_l_refine<D, 5>(kp, grid, s);
-    case 6: return launch_l_refine<D, 6>(kp, grid, s);
-    case 7: return launch_l_refine<D, 7>(kp, grid, s);
-    case 8: return launch_l_refine<D, 8>(kp, grid, s);
-    case 9: return launch_l_refine<D, 9>(kp, grid, s);
-    case 10: return launch_l_refine<D, 10>(kp, grid, s);
-    case 11: return launch_l_refine<D, 11>(kp, grid, s);
-    case 12: return launch_l_refine<D, 12>(kp, grid, s);
+    case 1: return launch_l_refine<D, 1>(kp, grid, eight, s);
+    case 2: return launch_l_refine<D, 2>(kp, grid, eight, s);
+    case 3: return launch_l_refine<D, 3>(kp, grid, eight, s);
+    case 4: return launch_l_refine<D, 4>(kp, grid, eight, s);
+    case 5: return launch_l_refine<D, 5>(kp, grid, eight, s);
+    case 6: return launch_l_refine<D, 6>(kp, grid, eight, s);
+    case 7: return launch_l_refine<D, 7>(kp, grid, eight, s);
+    case 8: return launch_l_refine<D, 8>(kp, grid, eight, s);
+    case 9: return launch_l_refine<D, 9>(kp, grid, eight, s);
+    case 10: return launch_l_refine<D, 10>(kp, grid, eight, s);
+    case 11: return launch_l_refine<D, 11>(kp, grid, eight, s);
+    case 12: return launch_l_refine<D, 12>(kp, grid, eight, s);
   }
   return hipErrorInvalidValue;
 }
@@ -1821,7 +1821,7 @@ bool bf16_stage_l_out_streams(const KParams& kp) {
   return nlt <= kMaxLT && nk_max > kResRows && !l_out_mid(kp);
 }
 
-hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s) {
+hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last, hipStream_t s) {
   dim3 grid(kp.b2, kp.ntq, nbh);
   const int nlt = (kp.b1 + 15) / 16;
   if (nlt > kMaxLT) return hipErrorInvalidValue;
@@ -1853,11 +1853,12 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_
   // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), each wave owning up to two
   // query tiles, so that two workgroups fit a compute unit whatever order their waves are dealt
   // to the SIMDs in; only b1 > 128 needs a fifth and sixth wave.
-  if (!last) return kp.d == 128 ? launch_l_refine_d<128>(kp, grid, nlt, s)
-                                : launch_l_refine_d<64>(kp, grid, nlt, s);
+  const bool eight = one_a_unit(grid, beside);
+  if (!last) return kp.d == 128 ? launch_l_refine_d<128>(kp, grid, nlt, eight, s)
+                                : launch_l_refine_d<64>(kp, grid, nlt, eight, s);
   if (nlt <= 4) return kp.d == 128 ? launch_l_out<128, 1, 256>(kp, grid, s)
                                    : launch_l_out<64, 1, 256>(kp, grid, s);
-  if (nlt <= 8 && one_a_unit(kp, grid))
+  if (nlt <= 8 && eight)
     return kp.d == 128 ? launch_l_out<128, 1, 512>(kp, grid, s) : launch_l_out<64, 1, 512>(kp, grid, s);
   if (nlt <= 8) return kp.d == 128 ? launch_l_out<128, 2, 256>(kp, grid, s)
                                    : launch_l_out<64, 2, 256>(kp, grid, s);

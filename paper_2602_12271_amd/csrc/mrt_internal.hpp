@@ -43,7 +43,6 @@ struct KParams {
   float* o32_out;   //   log-sum-exp of every query row's logits [bh][m][j][l] and O in fp32 [bh][m][j][l][d]
   int H;        // heads (to split the flat batch*head index)
   int bh0;      // first flat (batch,head) index of this pass
-  int beside;   // (batch,head) entries of the pass whose launches run beside this one, on other streams
   int d;
   int b1, b2;
   int c2;       // column tiles
@@ -172,7 +171,9 @@ hipError_t launch_bwd_bf16_r_wave(const BwdParams& bp, int nitems, bool first, b
 
 // bf16 MFMA path (mrt_bf16.hip)
 hipError_t launch_bf16_stage_r(const KParams& kp, int nbh, bool first, bool last, hipStream_t s);
-hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, bool last, hipStream_t s);
+// beside: (batch,head) entries of the pass whose launches run beside this one, on other streams (an argument of the
+// host's: one more int in the middle of KParams, in every kernel's arguments, made small calls 0.2 to 0.3 us longer)
+hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last, hipStream_t s);
 bool bf16_stage_l_out_streams(const KParams& kp);   // its last-iteration kernel fills lse_out / o32_out
 // workspace: null, or scratch for the parts of a call whose keys are split (used if it holds
 // bf16_dense_workspace_bytes(), 0 for a call that is not split)
