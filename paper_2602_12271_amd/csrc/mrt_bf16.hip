@@ -1801,7 +1801,8 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
 // twelve: four waves with up to three key tiles each, two workgroups to a unit (204 to 256 registers).  Six waves
 // with two tiles each (150 to 171 registers) had a unit to themselves, so that 360 workgroups of (156,30), 12 heads,
 // took two rounds: launch 25.6 -> 19.9 us; from 257 workgroups on calls of 150 to 192 rows take 0.80 .. 0.93 of their
-// time together with the last launch's four waves; below that a launch is half a microsecond longer (a head's
+// time together with the last launch's four waves; below that a launch is half a microsecond to a good one longer
+// (two frames as (148,32), 7 heads, T = 3: call 68.3 -> 71.0; a head's
 // bits depend on which key tiles share a wave, so the number of workgroups must not choose).
 template <int D>
 hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
