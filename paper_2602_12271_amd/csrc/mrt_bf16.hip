@@ -1120,15 +1120,25 @@ __global__ __launch_bounds__(256, 3) void k_bf16_stage_l_out_res(KParams p) {
 // tile once, with queries on the accumulator rows.  The row statistics of the joint softmax over
 // the key range are reduced inside the wave and exchanged between the NW waves through LDS;
 // alpha_L goes from global memory straight into the matrix operands, only Q is staged.
+//
+// More than eight query tiles (THREES): the key tiles are taken by threes, which share a reference, and a sum of
+// weights is that of the first two plus that of the third, whichever waves they lie on: four waves of three
+// tiles (PT = 3), or eight (SHARED), the first four with the first two tiles of each three and the others with
+// the third, which exchange their maxima.  A column gets the same bits from both layouts, so the number of
+// workgroups may choose (launch_l_refine_one_wide).
 template <int D, int NLT, int PT, int NW, bool RMASK>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) void k_bf16_stage_l_refine_one(KParams p) {
   constexpr int LD = ResTile<D>::LD, KS1 = D / 32, QROWS = 32 * ((NLT + 1) / 2), LROWS = 16 * NLT;
   constexpr bool SWZ = ResTile<D>::SWZ;
+  constexpr bool THREES = NLT > 8, SHARED = THREES && PT == 2;
+  static_assert(!THREES || (PT == 3 && NW == 4) || (PT == 2 && NW == 8), "layouts of nine and more query tiles");
+  constexpr int NM = THREES ? 4 : NW, NS = THREES ? 8 : NW;         // references and sums of a row
   __shared__ __attribute__((aligned(16))) u16 Qs[QROWS * LD];
-  __shared__ __attribute__((aligned(16))) float red_m[NW][LROWS];
-  __shared__ __attribute__((aligned(16))) float red_s[NW][LROWS];
+  __shared__ __attribute__((aligned(16))) float red_m[NM][LROWS];
+  __shared__ __attribute__((aligned(16))) float red_s[NS][LROWS];
+  __shared__ __attribute__((aligned(16))) float red_t[SHARED ? NW : 1][SHARED ? LROWS : 4];   // maxima of a wave's own tiles
   __shared__ __attribute__((aligned(16))) float lse[LROWS];
-  __shared__ __attribute__((aligned(16))) int limit[RMASK ? LROWS : 4];   // visible_key_rows of every query row
+  __shared__ __attribute__((aligned(16))) int limit[RMASK ? LROWS : 4];   // key rows that every query row sees
   __shared__ int redo;
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -1147,24 +1157,31 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
   const float* cLp = p.cL + row0;
 
   MRT_STAMP(0);
-  const int tile0 = PT * wave;
+  const bool third = SHARED && wave >= NW / 2;
+  const int tile0 = !SHARED ? PT * wave : third ? 3 * (wave - NW / 2) + 2 : 3 * wave, most = third ? 1 : PT;
   const int ntiles = (NK + 15) >> 4;
-  const int npt = ntiles - tile0 < PT ? (ntiles - tile0 > 0 ? ntiles - tile0 : 0) : PT;
+  const int npt = ntiles - tile0 < most ? (ntiles - tile0 > 0 ? ntiles - tile0 : 0) : most;
   RowRegs<D, QROWS, 64 * NW> rq;
   rq.load(Qp, qrow, b1, tid);
   bf16x8 kb[PT][KS1];
   float cl[PT];
+  // (key tiles [from, to) of the wave, here and below)
+  const std::integral_constant<int, 0> t0;
+  const std::integral_constant<int, PT> t1;
+  auto load_keys = [&](auto from, auto to) __attribute__((always_inline)) {
 #pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    const int nk = 16 * (tile0 + pt) + c;
-    const int nkc = nk < NK ? nk : NK - 1;
+    for (int pt = from; pt < to; ++pt) {
+      const int nk = 16 * (tile0 + (pt < most ? pt : 0)) + c;
+      const int nkc = nk < NK ? nk : NK - 1;
 #pragma unroll
-    for (int ks = 0; ks < KS1; ++ks) kb[pt][ks] = ld_global_16B(aLp + (size_t)nkc * D + 32 * ks + 8 * g);
-    cl[pt] = cLp[nkc] * kLog2e;
-  }
+      for (int ks = 0; ks < KS1; ++ks) kb[pt][ks] = ld_global_16B(aLp + (size_t)nkc * D + 32 * ks + 8 * g);
+      cl[pt] = cLp[nkc] * kLog2e;
+    }
+  };
+  load_keys(t0, t1);
   rq.template store<LD, SWZ>(Qs, tid);
   if constexpr (RMASK)
-    for (int l = tid; l < LROWS; l += 64 * NW) limit[l] = visible_key_rows(p, l);
+    for (int l = tid; l < LROWS; l += 64 * NW) limit[l] = min(visible_key_rows(p, l), NK);
   __syncthreads();
   MRT_STAMP(1);
 
@@ -1172,22 +1189,22 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
   // (a lambda: the two rare underflow paths below form them a second time)
   const float scale2 = p.scale * kLog2e;
   f32x4 z[PT][NLT];
-  auto logits = [&]() {
+  auto logits = [&](auto from, auto to) __attribute__((always_inline)) {
 #pragma unroll
     for (int lt = 0; lt < NLT; ++lt) {
       bf16x8 av[KS1];
 #pragma unroll
       for (int ks = 0; ks < KS1; ++ks) av[ks] = ld_lds_16B(Qs + tile_off<LD, SWZ>(16 * lt + c, 4 * ks + g));
 #pragma unroll
-      for (int pt = 0; pt < PT; ++pt) {
+      for (int pt = from; pt < to; ++pt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (pt < npt) {
+        if ((THREES && !SHARED && !RMASK) || pt < npt) {       // (a tile that is not there: the last key's, not used)
 #pragma unroll
           for (int ks = 0; ks < KS1; ++ks) acc = mfma(av[ks], kb[pt][ks], acc);
         }
-        const bool col = 16 * (tile0 + pt) + c < NK;
+        const bool col = pt < most && 16 * (tile0 + pt) + c < NK;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = col ? fmaf(acc[r], scale2, -cl[pt]) : -INFINITY;
+        for (int r = 0; r < 4; ++r) acc[r] = col || RMASK ? fmaf(acc[r], scale2, -cl[pt]) : -INFINITY;
         z[pt][lt] = acc;
       }
       if (lt % 2 == 1) __builtin_amdgcn_sched_barrier(0);
@@ -1203,12 +1220,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int pt = 0; pt < PT; ++pt)
-            if (16 * (tile0 + pt) + c >= lim[r]) z[pt][lt][r] = -INFINITY;
+          for (int pt = from; pt < to; ++pt)
+            if ((pt < most ? 16 * (tile0 + pt) : NK) + c >= lim[r]) z[pt][lt][r] = -INFINITY;
       }
     }
   };
-  logits();
+  logits(t0, t1);
   // This wave's share of every query row's sum of 2^z, relative to a reference the waves then
   // reconcile; the exponentials e = 2^(z - reference) are kept in place of the logits, and a weight
   // is L = 2^(z - lse) = e * 2^(reference - M) / S with M the largest reference of the row and S
@@ -1240,11 +1257,32 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
 #pragma unroll
       for (int lt = 0; lt < NLT; ++lt) top[lt] = xmax(top[lt]);
       __builtin_amdgcn_sched_barrier(0);
-    }
+      if constexpr (SHARED) {
+        if (lane == 0) {
 #pragma unroll
-    for (int lt = 0; lt < NLT; ++lt) {
+          for (int lt = 0; lt < NLT; ++lt) red_t[wave][lt] = top[lt];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int lt = 0; lt < NLT; ++lt) top[lt] = fmaxf(top[lt], red_t[wave ^ (NW / 2)][lt]);
+      }
+    } else if constexpr (SHARED) {
+#pragma unroll
+      for (int lt = 0; lt < NLT; ++lt) {
+        f32x4 vr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vr[r] = row16_max(fmaxf(z[0][lt][r], z[1][lt][r]));
+        if (c == 0) *(f32x4*)(&red_t[wave][16 * lt + 4 * g]) = vr;
+      }
+      __syncthreads();
+    }
+    auto reference = [&](int lt) {
       f32x4 vr;
-      if (per_row) {
+      if (per_row && SHARED) {
+        const f32x4 a = *(const f32x4*)(&red_t[wave % 4][16 * lt + 4 * g]), b = *(const f32x4*)(&red_t[SHARED ? wave % 4 + 4 : 0][16 * lt + 4 * g]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vr[r] = fmaxf(a[r], b[r]);
+      } else if (per_row) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           float v = z[0][lt][r];
@@ -1256,6 +1294,25 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
 #pragma unroll
         for (int r = 0; r < 4; ++r) vr[r] = top[lt];
       }
+      return vr;
+    };
+    if constexpr (SHARED) {
+      // (the second tiles of the waves that have one; an exponential takes four times an addition's time)
+      if (third) {
+#pragma unroll
+        for (int lt = 0; lt < NLT; ++lt) z[1][lt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      } else {
+#pragma unroll
+        for (int lt = 0; lt < NLT; ++lt) {
+          const f32x4 vr = reference(lt);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z[1][lt][r] = exp2_fast(z[1][lt][r] - (vr[r] == -INFINITY ? 0.f : vr[r]));
+        }
+      }
+    }
+#pragma unroll
+    for (int lt = 0; lt < NLT; ++lt) {
+      const f32x4 vr = reference(lt);
       f32x4 sm;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -1263,13 +1320,19 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
         float e = 0.f;
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) {
-          z[pt][lt][r] = exp2_fast(z[pt][lt][r] - ref);
-          e += z[pt][lt][r];
+          if (!SHARED || pt == 0) z[pt][lt][r] = exp2_fast(z[pt][lt][r] - ref);
+          if (!THREES) e += z[pt][lt][r];
         }
-        sm[r] = row16_sum(e);
+        if constexpr (THREES) e = z[0][lt][r] + z[1][lt][r];
+        sm[r] = !THREES ? row16_sum(e) : row16_sums(e, SHARED ? e : z[PT - 1][lt][r], c >= 8);
       }
-      if (c == 0) {
-        *(f32x4*)(&red_m[wave][16 * lt + 4 * g]) = vr;
+      if constexpr (THREES && !SHARED) {
+        if ((c & 7) == 0) {                    // (both write the same reference)
+          *(f32x4*)(&red_m[wave][16 * lt + 4 * g]) = vr;
+          *(f32x4*)(&red_s[wave + (c >= 8 ? NW : 0)][16 * lt + 4 * g]) = sm;
+        }
+      } else if (c == 0) {
+        if (!third) *(f32x4*)(&red_m[wave][16 * lt + 4 * g]) = vr;
         *(f32x4*)(&red_s[wave][16 * lt + 4 * g]) = sm;
       }
     }
@@ -1280,18 +1343,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
     if (tid < LROWS) {
       float M = red_m[0][tid];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) M = fmaxf(M, red_m[w][tid]);
+      for (int w = 1; w < NM; ++w) M = fmaxf(M, red_m[w][tid]);
       const float Ms = M == -INFINITY ? 0.f : M;
-      float f[NW], S = 0.f;
+      float f[NM], S = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
+      for (int w = 0; w < NM; ++w) {
         f[w] = exp2_fast(red_m[w][tid] - Ms);
-        S = fmaf(red_s[w][tid], f[w], S);
+        S = fmaf(THREES ? red_s[w][tid] + red_s[THREES ? NM + w : 0][tid] : red_s[w][tid], f[w], S);
       }
       lse[tid] = Ms + log2_fast(S);
       const float inv = tid < b1 ? 1.0f / S : 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) red_s[w][tid] = f[w] * inv;
+      for (int w = 0; w < (SHARED ? NS : NM); ++w) red_s[w][tid] = f[w % NM] * inv;
       if (!(S > 0x1p-64f) && tid < b1) redo = 1;
     }
   };
@@ -1301,7 +1364,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
   combine();
   __syncthreads();
   if (__builtin_expect(redo, 0)) {            // uniform: read after the barrier
-    logits();
+    if constexpr (THREES) load_keys(t0, t1);  // (kept until here they were spilled)
+    logits(t0, t1);
     stats(true);
     __syncthreads();
     combine();
@@ -1327,21 +1391,19 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
       pb[st2][pt] = pack8(lo, hi);
     }
   }
-  bool under = false;
 #pragma unroll
-  for (int pt = 0; pt < PT; ++pt) {
-    csum[pt] = xsum(csum[pt]);
-    under |= (pt < npt && 16 * (tile0 + pt) + c < NK && csum[pt] == 0.f);
-  }
+  for (int pt = 0; pt < PT; ++pt) csum[pt] = xsum(csum[pt]);
   float shift[PT];
 #pragma unroll
   for (int pt = 0; pt < PT; ++pt) shift[pt] = 0.f;
-  if (__builtin_expect(__any(under), 0)) {
-    // a whole column of weights underflowed: the ratio alpha_R / c_R is formed from log2 L relative
-    // to the column's maximum instead (logits formed again; rare)
-    logits();
+  // a whole column of weights underflowed: the ratio alpha_R / c_R is formed from log2 L relative
+  // to the column's maximum instead (logits formed again; rare), for every column of the wave or (THREES)
+  // of the tile
+  auto from_logs = [&](auto from, auto to) __attribute__((always_inline)) {
+    if constexpr (THREES) load_keys(from, to);
+    logits(from, to);
 #pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
+    for (int pt = from; pt < to; ++pt) {
       float cm = -INFINITY;
 #pragma unroll
       for (int lt = 0; lt < NLT; ++lt) {
@@ -1371,6 +1433,19 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
       }
       csum[pt] = xsum(csum[pt]);
     }
+  };
+  if constexpr (!THREES) {
+    bool under = false;
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt) under |= (pt < npt && 16 * (tile0 + pt) + c < NK && csum[pt] == 0.f);
+    if (__builtin_expect(__any(under), 0)) from_logs(t0, t1);
+  } else {
+    auto tile = [&](auto pt) __attribute__((always_inline)) {
+      if (__builtin_expect(__any(pt < npt && 16 * (tile0 + pt) + c < NK && csum[pt] == 0.f), 0)) from_logs(pt, std::integral_constant<int, pt + 1>());
+    };
+    tile(t0);
+    tile(std::integral_constant<int, 1>());
+    if constexpr (PT == 3) tile(std::integral_constant<int, 2>());
   }
   MRT_STAMP(4);
   u16* aRout = (u16*)p.aR + ((size_t)bhl * p.ntq + ml) * NKtot * b2 * D;
@@ -1798,18 +1873,25 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
 // chain a workgroup waits for; two such workgroups share a compute unit, 89 to 100 registers a wave; 112 rows, 40
 // columns, calls of 1 to 40 heads 0.98 .. 0.88 of the time of six waves with two tiles each, 12 heads 57.6
 // -> 52.6 us, masked 0.97 .. 0.94; 128 rows, 24 columns, 64 features 0.98 .. 0.92, masked 0.94 .. 0.92).  Ten and
-// twelve: four waves with up to three key tiles each, two workgroups to a unit (204 to 256 registers).  Six waves
-// with two tiles each (150 to 171 registers) had a unit to themselves, so that 360 workgroups of (156,30), 12 heads,
-// took two rounds: launch 25.6 -> 19.9 us; from 257 workgroups on calls of 150 to 192 rows take 0.80 .. 0.93 of their
-// time together with the last launch's four waves; below that a launch is half a microsecond to a good one longer
-// (two frames as (148,32), 7 heads, T = 3: call 68.3 -> 71.0; a head's
-// bits depend on which key tiles share a wave, so the number of workgroups must not choose).
+// twelve: four waves of up to three key tiles, two workgroups to a unit (209 to 253 registers), where a launch has
+// more workgroups than units: a workgroup of more waves with fewer tiles has a unit to itself, so that the 360
+// workgroups of (156,30), 12 heads, take two rounds (six waves of two tiles: call 70.1 us, four of three 59.9; 150
+// to 192 rows from 257 workgroups on 0.72 .. 0.93, together with the last launch's four waves).  Up to one a unit
+// (one_a_unit) eight waves of two tiles and of one (152 to 193 registers): a wave's chain is what the launch takes
+// ((148,32), 7 heads, T = 3: call 70.4 -> 68.8 us; (154,55), 4 heads, T = 3: 73.0 -> 70.0; (156,30), 8 heads 45.3 ->
+// 44.8; six waves of two 68.6, 70.4 and 45.1).  No variant keeps anything in local memory.
 template <int D>
-hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, hipStream_t s) {
+hipError_t launch_l_refine_one_wide(const KParams& kp, dim3 grid, int nlt, bool eight, hipStream_t s) {
   switch ((nlt + 1) / 2) {
     case 4: launch_refine_one_k<D, 8, 1, 8>(kp, grid, s); break;
-    case 5: launch_refine_one_k<D, 10, 3, 4>(kp, grid, s); break;
-    case 6: launch_refine_one_k<D, 12, 3, 4>(kp, grid, s); break;
+    case 5:
+      if (eight) launch_refine_one_k<D, 10, 2, 8>(kp, grid, s);
+      else launch_refine_one_k<D, 10, 3, 4>(kp, grid, s);
+      break;
+    case 6:
+      if (eight) launch_refine_one_k<D, 12, 2, 8>(kp, grid, s);
+      else launch_refine_one_k<D, 12, 3, 4>(kp, grid, s);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1839,9 +1921,10 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last
     return kp.d == 128 ? launch_l_refine_one<128, 3>(kp, grid, nlt, s)
                        : launch_l_refine_one<64, 3>(kp, grid, nlt, s);
   }
+  const bool eight = one_a_unit(grid, beside);
   if (!last && nk_max <= kMidRows && nlt <= kMaxLT)
-    return kp.d == 128 ? launch_l_refine_one_wide<128>(kp, grid, nlt, s)
-                       : launch_l_refine_one_wide<64>(kp, grid, nlt, s);
+    return kp.d == 128 ? launch_l_refine_one_wide<128>(kp, grid, nlt, eight, s)
+                       : launch_l_refine_one_wide<64>(kp, grid, nlt, eight, s);
   // last iteration, short key ranges: everything resident, three workgroups per compute unit
   if (nk_max <= kResRows) {
     return kp.d == 128 ? launch_l_out_res_d<128>(kp, grid, (nk_max + 15) / 16, s)
@@ -1854,7 +1937,6 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last
   // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), each wave owning up to two
   // query tiles, so that two workgroups fit a compute unit whatever order their waves are dealt
   // to the SIMDs in; only b1 > 128 needs a fifth and sixth wave.
-  const bool eight = one_a_unit(grid, beside);
   if (!last) return kp.d == 128 ? launch_l_refine_d<128>(kp, grid, nlt, eight, s)
                                 : launch_l_refine_d<64>(kp, grid, nlt, eight, s);
   if (nlt <= 4) return kp.d == 128 ? launch_l_out<128, 1, 256>(kp, grid, s)

@@ -95,6 +95,16 @@ __device__ inline float row16_sum(float x) {
   x += dpp_mov<0x141>(x);
   return x + dpp_mov<0x140>(x);
 }
+// Two such sums side by side: of a in lanes 0 .. 7 of the 16, of b in the others (hi: lane 8 .. 15), five steps and
+// a select instead of eight.  A number alone (a and b the same) comes out in the same order.
+__device__ inline float row16_sums(float a, float b, bool hi) {
+  a += dpp_mov<0x140>(a);
+  b += dpp_mov<0x140>(b);
+  float x = hi ? b : a;
+  x += dpp_mov<0x141>(x);
+  x += dpp_mov<0x4E>(x);
+  return x + dpp_mov<0xB1>(x);
+}
 // Sum over aligned groups of 8 lanes (the first three steps of the above).
 __device__ inline float row8_sum(float x) {
   x += dpp_mov<0xB1>(x);
