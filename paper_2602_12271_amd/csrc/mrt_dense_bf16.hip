@@ -26,7 +26,6 @@
 #include "mrt_bf16_tiles.hpp"
 
 #include <algorithm>
-#include <cmath>
 
 namespace mrt {
 
@@ -417,12 +416,16 @@ hipError_t run_dense(const KParams& kp, int nbh, const DenseParts& parts, hipStr
 // Splitting the keys.  Calls of few queries leave most of the chip idle however small their workgroups
 // are (one head of 816 queries, 3264 keys: 26 workgroups of 64 queries, 43.6 us), so `parts` workgroups
 // share the keys of a query tile and a second launch merges their partial results.  `time` is a model of
-// a call fitted to 700 measured shapes of 29 calls, 6 % rms from them (rounds x steps of 64 keys x
-// microseconds a step, the merge launch, the partial results' bytes); the shape it picks is 1 % behind the
-// best one on average.  A split has to promise 6 % (2 heads of 816 queries of 3264 keys 43.6 -> 19 us, one
+// a call fitted to 700 measured shapes of 29 calls (rounds x steps of 64 keys x microseconds a step, the merge
+// launch, the partial results' bytes) and, for calls under a mask, to another 1600: there one round lasts as long
+// as its longest workgroup, and of several the units that finish early take the next one's workgroups.  A split
+// has to promise 6 %: 928 drawn calls that are split so take 0.64 of the unsplit time on average, four of them
+// more than that time, up to 1.034.  (Counted as if units could finish early in a single round, 128 features, or as if
+// workgroups beyond the last full round cost nothing, 64, calls under a mask took up to 1.43 of the unsplit time.)
+// (2 heads of 816 queries of 3264 keys 43.6 -> 19 us, one
 // head of 7080 of 21240 244 -> 88, 4 heads of 1989 of 7956 96 -> 49, 6 heads of 7020 of 21060 501 -> 415;
-// 64 features: one head of 3240 of 12960 96 -> 30).  No split: 384 keys 10.6 (two parts 12.6), 12 heads of
-// 4680 of 4680 132 (155).
+// 64 features: one head of 3240 of 12960 96 -> 30.  No split: 384 keys 10.6 (two parts 12.6), 12 heads of
+// 4680 of 4680 132 (155), under a mask 15 heads of 3240 of 6480 172 (201).)
 constexpr int kMostParts = 32;
 constexpr size_t kMostPartsBytes = (size_t)128 << 20;       // of partial results
 constexpr long long kMostSplitRows = 1 << 18;               // 2^18 rows of two parts are more than that
@@ -455,13 +458,17 @@ DenseShape dense_shape(const KParams& kp, int nbh, bool may_split) {
     const long long n = wgs(queries) * parts;
     double us = 0;
     if (kp.d == 64) {
-      const long long busy = (long long)std::ceil(n * share), rest = busy % (2 * cus);
       const double one = queries == 64 ? 0.45 : 0.72, two = queries == 64 ? 0.67 : 1.12;
-      us = 6.0 + steps * (busy / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0));
+      const long long rest = n % (2 * cus);
+      double full = n / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0);
+      if (first != last)
+        full = n > 2 * cus ? std::max(two, n * share / (2 * cus) * two + 0.7 * one)
+                           : one + (two - one) * std::min(1.0, std::max(0.0, (n - cus) / 64.0));
+      us = 6.0 + full * steps;
       if (parts > 1) us += 4.2;
     } else {
       const long long rounds = (n + cus - 1) / cus;
-      const double full = first == last ? (double)rounds : std::max(1.0, n * share / cus + 0.6);
+      const double full = first == last ? (double)rounds : std::min((double)rounds, std::max(1.0, n * share / cus + 0.8));
       us = 3.4 + 4.1 * rounds + full * steps * (queries == 64 ? 0.71 : queries == 128 ? 1.02 : 1.56);
       if (parts > 1) us += 5.5;
     }
