@@ -235,7 +235,10 @@ mrt_status dense_attn_fwd(const void* Q, const void* K, const void* V, void* O,
  * where a bf16 call has too few queries to fill the GPU, several workgroups share the keys of a query
  * tile and leave their partial results there.  dense_attn_workspace_bytes: what the call would use, 0
  * where it splits nothing (every fp32 call).  With workspace NULL or smaller than that the call is
- * dense_attn_fwd; the results of the two agree to fp32 rounding before O's. */
+ * dense_attn_fwd, which never splits.  The two round the softmax weights to bf16 relative to other
+ * references and add in another order, so their results are two roundings to bf16 apart (3e-3 in the
+ * 2-norm), equally far from the exact ones.  How many workgroups share the keys depends on the whole call,
+ * also on batch x heads, so the last bits of one head may; the same call gives the same bits every time. */
 size_t dense_attn_workspace_bytes(const mrt_problem* p, int causal_chunk);
 mrt_status dense_attn_fwd_ws(const void* Q, const void* K, const void* V, void* O, const mrt_problem* p,
                              int causal_chunk, void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -343,9 +343,10 @@ def dense_attn_workspace_bytes(prob: MrtProblem, causal_chunk=0) -> int:
 
 
 def _dense_scratch(prob, causal_chunk, Q, s):
-    """Scratch of one dense call, or None.  Only on the stream that torch's allocator orders it by, and not
-    under a graph capture, whose replays would find the memory in other hands: such calls split no keys
-    unless they bring a workspace."""
+    """Scratch of one dense call, or None: on a stream that is not the current one, by which torch's allocator
+    orders the memory; under a graph capture, because torch does not tell whether its allocator knows of the
+    capture (then the graph would keep the memory) or not (then an allocation could end the capture, and replays
+    would find the memory in other hands); where the allocator refuses."""
     import torch
     known = prob.__dict__.setdefault("dense_bytes", {})      # by value, like the descriptor itself
     nbytes = known.get(causal_chunk)
@@ -361,7 +362,15 @@ def _dense_scratch(prob, causal_chunk, Q, s):
 
 def dense_attn_fwd(Q, K, V, *, f_q, f_kv, h, w, causal_chunk=0, q_frame_offset=0, scale=1.0,
                    compute=MRT_COMPUTE_DEFAULT, out=None, stream=None, workspace=None):
-    """Dense softmax attention baseline on device tensors [batch, heads, tokens, head_dim]."""
+    """Dense softmax attention baseline on device tensors [batch, heads, tokens, head_dim].
+
+    bf16 calls of few queries split their keys over several workgroups if they have scratch memory
+    (dense_attn_workspace_bytes): `workspace`, or memory of torch's allocator.  Without `workspace` a call under a
+    graph capture, with a `stream` that is not torch's current one, or one whose scratch the allocator refuses
+    splits nothing: it takes longer (2 heads of 816 queries of 3264 keys 44 us instead of 19), and its results are
+    two roundings to bf16 from a split call's (3e-3 in the 2-norm), equally far from the exact ones.  Give such
+    calls a workspace to have them split like the others.  How the keys are split also depends on the number of
+    heads, so a head's last bits may."""
     import torch
     lib = load_library()
     O = torch.empty_like(Q) if out is None else out

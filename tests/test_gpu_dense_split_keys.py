@@ -3,7 +3,7 @@ shape at ragged sizes, under the mask with hidden keys, with query ranges whose 
 some parts of a workgroup's keys are empty and one workgroup's halves end at different keys), and with
 infinite values that only the last chunk sees.  Against plain torch in float64 with the bar of the
 unsplit kernels (output and probabilities rounded once each to 2^-9: 2.4e-3 in the 2-norm; four times
-that), and against the unsplit call, from which only fp32 roundings and the one of O part it: two
+that), and against the unsplit call, whose probabilities are rounded relative to other references: two
 roundings of 2^-9 apart in the 2-norm at most."""
 import ctypes
 
