@@ -11,7 +11,7 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 // ---------------------------------------------------------------------------------------
-// Stage L backward at t = T of streamed key ranges, up to six query tiles, after a forward call that left
+// Stage L backward at t = T (nothing in dQ to add to) of streamed key ranges, up to six query tiles, after a forward call that left
 // its row statistics: rows and columns in one sweep, one workgroup of four waves per (m, j).
 //
 // A wave owns 32 key rows at a time and every query row, so L and dZ of those keys never leave it: the
@@ -20,9 +20,9 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 // dY = L^T dO and d alpha_L = scale dZ^T Q as they are.  Only dQ += scale dZ alpha_L contracts over the
 // keys: dZ and alpha_L pass through LDS of the wave's own for that, and every wave keeps a dQ of its own,
 // added up at the end.  The sweep has no barrier; the loads of a wave's next 32 keys are in flight while it
-// forms the results of these.  A compute unit holds one workgroup (two with up to two query tiles; four and
-// three at 64 features), so what is left over its bytes is the load of Q, dO and O ahead of the sweep and
-// the sum of the four dQ behind it, which nothing overlaps.
+// forms the results of these.  A compute unit holds one workgroup (two with up to two query tiles; at 64
+// features three, two and one of two, four and six tiles), so what is left over its bytes is the load of Q, dO
+// and O ahead of the sweep and the sum of the four dQ behind it, which nothing overlaps.
 //
 // Against the rows of twelve waves with LDS rings and two barriers every 64 keys (k_bwdm_l_rows_ring, which
 // stays for calls without the statistics): 480p clip, 90 rows, 642 -> 535 us (its bytes take 416 at the copy
@@ -238,7 +238,6 @@ __global__ __launch_bounds__(256, NLT == 2 ? 2 : 1) void k_bwdm_l_keys(BwdParams
       }
       if (l < b1) {
         f32x4* to = (f32x4*)(dQp + drow(l) + 32 * q + 8 * g);
-        if (bp.accumulate) { x[0] += to[0]; x[1] += to[1]; }
         to[0] = x[0];
         to[1] = x[1];
       }
@@ -256,21 +255,21 @@ __global__ __launch_bounds__(256, NLT == 2 ? 2 : 1) void k_bwdm_l_keys(BwdParams
 // with the columns on the lanes, are transposed through LDS too.  Nothing is shared with another wave, so
 // there is no barrier, and the next step's rows are in flight while this one is formed.
 //
-// What bounds it is how many of these chains run side by side: eight to twelve a compute unit (registers),
+// What bounds it is how many of these chains run side by side: eight to sixteen a compute unit (registers),
 // five before, when tiles padded to 32 rows took 28 KB (64 features) or 48 KB of LDS (36 rows of 8 columns, 12 tiles,
 // 10 heads, 64 features 110 -> 46 us).  For two to four key tiles the workgroups of k_bwdm_r stay, whose waves
-// share a step: written for NT tiles, one wave took 407 us instead of 357 (20 rows of 17 columns, 21
+// share a step: written for several tiles, one wave took 407 us instead of 357 (20 rows of 17 columns, 21
 // heads), 43 instead of 41 ((90,37), 18 heads), 640 instead of 597 (480p clip, 52 columns), few blocks most of
 // all (43 rows of 20 columns, one head 47 instead of 28).
 // ---------------------------------------------------------------------------------------
 __device__ inline f32x4 mfma16(s16x4 a, s16x4 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
 
-template <int NT, int D, bool LAST>
-__global__ __launch_bounds__(64, NT <= 2 ? 2 : 1) void k_bwdm_r_wave(BwdParams bp, int first, int nitems) {
+template <int D, bool LAST>
+__global__ __launch_bounds__(64, 2) void k_bwdm_r_wave(BwdParams bp, int first, int nitems) {
   const KParams& p = bp.k;
-  constexpr int LD = D + 16, KS1 = D / 32, NVT = D / 16, LR = 16 * NT + 8;
-  __shared__ __attribute__((aligned(16))) u16 Ks[16 * NT * LD];          // K[n, k, i, :]
-  __shared__ __attribute__((aligned(16))) u16 As[16 * LD];               // abar[m, n, k, j, :] of 16 columns j
+  constexpr int LD = D + 16, KS1 = D / 32, NVT = D / 16, LR = 16 + 8;
+  __shared__ __attribute__((aligned(16))) u16 Ks[16 * LD];               // K[n, k, i, :]
+  __shared__ __attribute__((aligned(16))) u16 As[16 * LD];               // abar[m, n, k, j, :]
   __shared__ __attribute__((aligned(16))) u16 Gs[16 * LD];               // d alpha_L[m, n, j, k, :]
   __shared__ __attribute__((aligned(16))) u16 Ys[LAST ? 16 * LD : 8];    // dY[m, n, j, k, :]
   __shared__ __attribute__((aligned(16))) u16 RT[16 * LR], ST[16 * LR];  // R[j][i], scale dS[j][i]
@@ -303,12 +302,12 @@ __global__ __launch_bounds__(64, NT <= 2 ? 2 : 1) void k_bwdm_r_wave(BwdParams b
     return it;
   };
 
-  // 16 columns of a step (lane column = j); lanes beyond b2 repeat the last column
+  // the columns of a step (lane column = j); lanes beyond b2 repeat the last one
   bf16x8 qv[KS1], gv[KS1], yv[LAST ? KS1 : 1];
   float dcl = 0.f;
-  auto fetch = [&](const Item& it, int ml, int jt) {
+  auto fetch = [&](const Item& it, int ml) {
     const int m = p.m0 + ml, a = m / p.c2, bq = m - a * p.c2;
-    const int j = 16 * jt + c, jc = j < b2 ? j : b2 - 1;
+    const int jc = c < b2 ? c : b2 - 1;
     const size_t jr = (((size_t)it.bhl * p.ntq + ml) * b2 + jc) * NKtot + it.nk;
     const u16* ap;
     if (first) {
@@ -345,63 +344,48 @@ __global__ __launch_bounds__(64, NT <= 2 ? 2 : 1) void k_bwdm_r_wave(BwdParams b
 
   int w = blockIdx.x;                     // the host launches at most nitems workgroups
   Item cur = decode(w);
-  if (cur.ml0 < p.ntq) fetch(cur, cur.ml0, 0);
+  if (cur.ml0 < p.ntq) fetch(cur, cur.ml0);
+  const bool live = c < b2;               // this lane's column, and its key
   while (true) {
     // K into LDS, V into operands; rows beyond b2 are zeros
-    bf16x8 vv[LAST ? NT : 1][KS1];
+    bf16x8 vv[KS1];
     {
       const int b = cur.bh / p.H, hd = cur.bh - b * p.H;
       const u16* Kp = (const u16*)p.K + b * p.ks.batch + hd * p.ks.head;
       const u16* Vp = (const u16*)p.V + b * p.vs.batch + hd * p.vs.head;
-      bf16x8 kk[NT][KS1];
+      bf16x8 kk[KS1];
+      const long long tok = cur.krow + axis_offset(p.cmap, cur.bn * b2 + (live ? c : b2 - 1));
 #pragma unroll
-      for (int it = 0; it < NT; ++it) {
-        const int i = 16 * it + c;
-        const long long tok = cur.krow + axis_offset(p.cmap, cur.bn * b2 + (i < b2 ? i : b2 - 1));
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-          kk[it][ks] = ld_global_16B(Kp + tok * p.ks.token + 32 * ks + 8 * g);
-          if (LAST) vv[it][ks] = ld_global_16B(Vp + tok * p.vs.token + 32 * ks + 8 * g);
-        }
+      for (int ks = 0; ks < KS1; ++ks) {
+        kk[ks] = ld_global_16B(Kp + tok * p.ks.token + 32 * ks + 8 * g);
+        if (LAST) vv[ks] = ld_global_16B(Vp + tok * p.vs.token + 32 * ks + 8 * g);
       }
 #pragma unroll
-      for (int it = 0; it < NT; ++it) {
-        const bool in = 16 * it + c < b2;
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-          const uint4 zero = {0u, 0u, 0u, 0u};
-          *(uint4*)(Ks + (16 * it + c) * LD + 32 * ks + 8 * g) = in ? __builtin_bit_cast(uint4, kk[it][ks]) : zero;
-          if (LAST) vv[it][ks] = as_bf16x8(in ? __builtin_bit_cast(uint4, vv[it][ks]) : zero);
-        }
+      for (int ks = 0; ks < KS1; ++ks) {
+        const uint4 zero = {0u, 0u, 0u, 0u};
+        *(uint4*)(Ks + c * LD + 32 * ks + 8 * g) = live ? __builtin_bit_cast(uint4, kk[ks]) : zero;
+        if (LAST) vv[ks] = as_bf16x8(live ? __builtin_bit_cast(uint4, vv[ks]) : zero);
       }
     }
     const int w2 = w + (int)gridDim.x;
     const bool more = w2 < nitems;
     const Item nxt = more ? decode(w2) : cur;
-    f32x4 oK[NT][NVT], oV[LAST ? NT : 1][NVT];
+    f32x4 oK[NVT], oV[LAST ? NVT : 1];
 #pragma unroll
-    for (int it = 0; it < NT; ++it)
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) {
-        oK[it][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (LAST) oV[it][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    for (int vt = 0; vt < NVT; ++vt) {
+      oK[vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (LAST) oV[vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     landed();
-    for (int ml = cur.ml0, jt = 0; ml < p.ntq;) {
-      const int j = 16 * jt + c;
-      const bool live = j < b2;
-      // S^T and dR^T: rows i (4 g + r of a tile), lane column j
-      f32x4 s[NT], dr[NT];
+    for (int ml = cur.ml0; ml < p.ntq; ++ml) {
+      // S^T and dR^T: rows i = 4 g + r, lane column j
+      f32x4 s = {0.f, 0.f, 0.f, 0.f}, dr = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int it = 0; it < NT; ++it) {
-        s[it] = dr[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-          const bf16x8 k = ld_lds_16B(Ks + (16 * it + c) * LD + 32 * ks + 8 * g);
-          s[it] = mfma(k, qv[ks], s[it]);
-          dr[it] = mfma(k, gv[ks], dr[it]);
-          if (LAST) dr[it] = mfma(vv[it][ks], yv[ks], dr[it]);
-        }
+      for (int ks = 0; ks < KS1; ++ks) {
+        const bf16x8 k = ld_lds_16B(Ks + c * LD + 32 * ks + 8 * g);
+        s = mfma(k, qv[ks], s);
+        dr = mfma(k, gv[ks], dr);
+        if (LAST) dr = mfma(vv[ks], yv[ks], dr);
       }
       const float dc = dcl;
 #pragma unroll
@@ -413,127 +397,95 @@ __global__ __launch_bounds__(64, NT <= 2 ? 2 : 1) void k_bwdm_r_wave(BwdParams b
         if (LAST) *(uint4*)(Ys + at) = live ? __builtin_bit_cast(uint4, yv[ks]) : zero;
       }
       __builtin_amdgcn_sched_barrier(0);
-      // the next step: 16 columns on, the next query tile, or the next block's first
-      int jt2 = jt + 1, ml2 = ml;
-      if (jt2 == NT) { jt2 = 0; ++ml2; }
-      if (ml2 < p.ntq) fetch(cur, ml2, jt2);
-      else fetch(nxt, nxt.ml0 < p.ntq ? nxt.ml0 : p.ntq - 1, 0);
+      // the next step: the next query tile, or the next block's first
+      if (ml + 1 < p.ntq) fetch(cur, ml + 1);
+      else fetch(nxt, nxt.ml0 < p.ntq ? nxt.ml0 : p.ntq - 1);
       __builtin_amdgcn_sched_barrier(0);
 
       float mx = -INFINITY;
 #pragma unroll
-      for (int it = 0; it < NT; ++it)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          s[it][r] = 16 * it + 4 * g + r < b2 ? s[it][r] * scale2 : -INFINITY;
-          mx = fmaxf(mx, s[it][r]);
-        }
+      for (int r = 0; r < 4; ++r) {
+        s[r] = 4 * g + r < b2 ? s[r] * scale2 : -INFINITY;
+        mx = fmaxf(mx, s[r]);
+      }
       mx = xmax(mx);
       float sum = 0.f;
-      f32x4 ex[NT];                                  // 2^(logit - maximum): R times the sum
+      f32x4 ex;                                      // 2^(logit - maximum): R times the sum
 #pragma unroll
-      for (int it = 0; it < NT; ++it)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          s[it][r] -= mx;
-          ex[it][r] = exp2_fast(s[it][r]);
-          sum += ex[it][r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        s[r] -= mx;
+        ex[r] = exp2_fast(s[r]);
+        sum += ex[r];
+      }
       sum = xsum(sum);
       const float inv = 1.0f / sum, lsum = log2_fast(sum);
       float dot = 0.f;
 #pragma unroll
-      for (int it = 0; it < NT; ++it)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float R = ex[it][r] * inv;                         // 0 beyond b2
-          const float dR = 16 * it + 4 * g + r < b2 ? dr[it][r] + dc * fmaf(s[it][r] - lsum, kLn2, 1.0f) : 0.f;
-          ex[it][r] = R;
-          dr[it][r] = dR;
-          dot = fmaf(R, dR, dot);
-        }
+      for (int r = 0; r < 4; ++r) {
+        const float R = ex[r] * inv;                               // 0 beyond b2
+        const float dR = 4 * g + r < b2 ? dr[r] + dc * fmaf(s[r] - lsum, kLn2, 1.0f) : 0.f;
+        ex[r] = R;
+        dr[r] = dR;
+        dot = fmaf(R, dR, dot);
+      }
       dot = xsum(dot);
 #pragma unroll
-      for (int it = 0; it < NT; ++it) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dr[it][r] = p.scale * ex[it][r] * (dr[it][r] - dot);   // scale dS
-        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+      for (int r = 0; r < 4; ++r) dr[r] = p.scale * ex[r] * (dr[r] - dot);   // scale dS
+      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+      const bf16x4 R = {(__bf16)ex[0], (__bf16)ex[1], (__bf16)ex[2], (__bf16)ex[3]};
+      const bf16x4 S = {(__bf16)dr[0], (__bf16)dr[1], (__bf16)dr[2], (__bf16)dr[3]};
+      {
         const uint2 zero = {0u, 0u};
-        const bf16x4 R = {(__bf16)ex[it][0], (__bf16)ex[it][1], (__bf16)ex[it][2], (__bf16)ex[it][3]};
-        const bf16x4 S = {(__bf16)dr[it][0], (__bf16)dr[it][1], (__bf16)dr[it][2], (__bf16)dr[it][3]};
-        *(uint2*)(RT + c * LR + 16 * it + 4 * g) = live ? __builtin_bit_cast(uint2, R) : zero;
-        *(uint2*)(ST + c * LR + 16 * it + 4 * g) = live ? __builtin_bit_cast(uint2, S) : zero;
+        *(uint2*)(RT + c * LR + 4 * g) = live ? __builtin_bit_cast(uint2, R) : zero;
+        *(uint2*)(ST + c * LR + 4 * g) = live ? __builtin_bit_cast(uint2, S) : zero;
       }
       // d abar[j] = sum_i (scale dS[j, i]) K[i]
       {
         f32x4 o[NVT];
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) o[vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const u16* at = Ks + (4 * g + (c >> 2)) * LD + 8 * (c & 3);
 #pragma unroll
-        for (int st = 0; st < NT / 2; ++st) {
-          pv_step<D, LD>(Ks + 32 * st * LD, pack8(dr[2 * st], dr[2 * st + 1]), o, lane);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (NT % 2 == 1) {
-          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-          const bf16x4 S = {(__bf16)dr[NT - 1][0], (__bf16)dr[NT - 1][1], (__bf16)dr[NT - 1][2], (__bf16)dr[NT - 1][3]};
-          const u16* at = Ks + (16 * (NT - 1) + 4 * g + (c >> 2)) * LD + 8 * (c & 3);
-#pragma unroll
-          for (int vt = 0; vt < NVT; ++vt)
-            o[vt] = mfma16(ld_lds_tr(at + 32 * (vt >> 1) + 4 * (vt & 1)), __builtin_bit_cast(s16x4, S), o[vt]);
-        }
+        for (int vt = 0; vt < NVT; ++vt)
+          o[vt] = mfma16(ld_lds_tr(at + 32 * (vt >> 1) + 4 * (vt & 1)), __builtin_bit_cast(s16x4, S), o[vt]);
         const int nk = cur.nk;
         if (first && bp.dq_from_r) {
           const int m = p.m0 + ml, a = m / p.c2, bq = m - a * p.c2;
           if (live) {
-            const long long tok = row_offset(p, a, cur.k) + axis_offset(p.cmap, bq * b2 + j);
+            const long long tok = row_offset(p, a, cur.k) + axis_offset(p.cmap, bq * b2 + c);
             store_rows_f32<D>(bp.dQ + ((size_t)cur.bh * p.Nq + tok) * D, o, 1.0f, g, true);
           }
         } else {
           const size_t ablk = (((size_t)cur.bhl * p.ntq + ml) * NKtot + nk) * b2;
-          store_ws_row<D>((u16*)bp.dA + (ablk + (live ? j : b2 - 1)) * D, o, 1.0f, g);   // (the last column, once more)
+          store_ws_row<D>((u16*)bp.dA + (ablk + (live ? c : b2 - 1)) * D, o, 1.0f, g);   // (the last column, once more)
         }
       }
-      // dK += R^T d alpha_L + scale dS^T abar, dV += R^T dY over the step's 16 columns
+      // dK += R^T d alpha_L + scale dS^T abar, dV += R^T dY over the step's columns
       {
-        s16x4 bR[NT], bS[NT];
         const int rc = (4 * g + (c >> 2)) * LR + 4 * (c & 3), xc = (4 * g + (c >> 2)) * LD + 8 * (c & 3);
-#pragma unroll
-        for (int it = 0; it < NT; ++it) {
-          bR[it] = ld_lds_tr(RT + rc + 16 * it);
-          bS[it] = ld_lds_tr(ST + rc + 16 * it);
-        }
+        const s16x4 bR = ld_lds_tr(RT + rc), bS = ld_lds_tr(ST + rc);
 #pragma unroll
         for (int vt = 0; vt < NVT; ++vt) {
           const int at = xc + 32 * (vt >> 1) + 4 * (vt & 1);
           const s16x4 xg = ld_lds_tr(Gs + at), xa = ld_lds_tr(As + at);
           s16x4 xy;
           if (LAST) xy = ld_lds_tr(Ys + at);
-#pragma unroll
-          for (int it = 0; it < NT; ++it) {
-            oK[it][vt] = mfma16(xg, bR[it], oK[it][vt]);
-            oK[it][vt] = mfma16(xa, bS[it], oK[it][vt]);
-            if (LAST) oV[it][vt] = mfma16(xy, bR[it], oV[it][vt]);
-          }
+          oK[vt] = mfma16(xg, bR, oK[vt]);
+          oK[vt] = mfma16(xa, bS, oK[vt]);
+          if (LAST) oV[vt] = mfma16(xy, bR, oV[vt]);
         }
       }
       landed();
-      jt = jt2;
-      ml = ml2;
     }
-#pragma unroll
-    for (int it = 0; it < NT; ++it) {
-      const int i = 16 * it + c;
-      if (i < b2) {
-        const long long tok = cur.krow + axis_offset(p.cmap, cur.bn * b2 + i);
-        float* to = bp.dK + ((size_t)cur.bh * p.Nkv + tok) * D;
-        if (first && !bp.accumulate) store_rows_f32_nt<D>(to, oK[it], 1.0f, g);
-        else store_rows_f32<D>(to, oK[it], 1.0f, g, bp.accumulate != 0);
-        if (LAST) store_rows_f32_nt<D>(bp.dV + ((size_t)cur.bh * p.Nkv + tok) * D, oV[it], 1.0f, g);
-      }
+    if (live) {
+      const long long tok = cur.krow + axis_offset(p.cmap, cur.bn * b2 + c);
+      float* to = bp.dK + ((size_t)cur.bh * p.Nkv + tok) * D;
+      if (first && !bp.accumulate) store_rows_f32_nt<D>(to, oK, 1.0f, g);
+      else store_rows_f32<D>(to, oK, 1.0f, g, bp.accumulate != 0);
+      if (LAST) store_rows_f32_nt<D>(bp.dV + ((size_t)cur.bh * p.Nkv + tok) * D, oV, 1.0f, g);
     }
     if (!more) break;
-    if (cur.ml0 >= p.ntq && nxt.ml0 < p.ntq) fetch(nxt, nxt.ml0, 0);     // (a block that no query tile sees fetched nothing)
+    if (cur.ml0 >= p.ntq && nxt.ml0 < p.ntq) fetch(nxt, nxt.ml0);     // (a block that no query tile sees fetched nothing)
     cur = nxt;
     w = w2;
   }
@@ -549,8 +501,8 @@ hipError_t keys_d(const BwdParams& bp, dim3 grid, int nlt, hipStream_t s) {
 
 template <int D, bool LAST>
 hipError_t r_wave_d(const BwdParams& bp, int nitems, bool first, hipStream_t s) {
-  static const int resident = resident_workgroups(k_bwdm_r_wave<1, D, LAST>, 64);
-  k_bwdm_r_wave<1, D, LAST><<<dim3(nitems < resident ? nitems : resident), 64, 0, s>>>(bp, first ? 1 : 0, nitems);
+  static const int resident = resident_workgroups(k_bwdm_r_wave<D, LAST>, 64);
+  k_bwdm_r_wave<D, LAST><<<dim3(nitems < resident ? nitems : resident), 64, 0, s>>>(bp, first ? 1 : 0, nitems);
   return hipGetLastError();
 }
 
