@@ -733,9 +733,13 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
   // shapes); otherwise the pass runs on the caller's stream.
   int want_groups = requested_groups(p);
   if (want_groups == 0) {
-    // stage L backward keeps two workgroups per compute unit resident for b1 <= 96, one beyond:
-    // groups pay while a launch is fewer than four rounds of them (measured: 12 heads of the 480p
-    // KV-cache step -10 %, 10 heads per pass of the 720p one +5 %)
+    // Groups pay while a launch of stage L backward is a few rounds of workgroups (2048 of them up to 96 rows, 1024
+    // beyond; one to three fit a compute unit, by rows and features).  Two groups against one, 133 calls inside
+    // these lines: sweep from saved intermediates, 128 features 0.98 of the time on average (0.90 .. 1.045; 12 heads
+    // of the 480p KV-cache step 368 | 361 us, with two iterations 699 | 750), 64 features whole clips 0.96
+    // (0.80 .. 1.09), KV-cache steps of one iteration 1.04 (0.93 .. 1.17; no sizes that part the longer ones from
+    // the others), of two 0.99 (0.93 .. 1.07); the whole backward pass 0.90 .. 1.00 (12 heads of the 480p KV-cache step
+    // 487 | 505).
     const long long l_wgs = (long long)pl.ntq_total * pl.kp.b2 * G, slots = pl.kp.b1 <= 96 ? 512 : 256;
     want_groups = (L.rowsD * (size_t)G >= (size_t(256) << 20) && l_wgs < 4 * slots) ? 2 : 1;
   }
@@ -752,10 +756,10 @@ mrt_status bwd_run(BwdMode mode, const void* Q, const void* K, const void* V, vo
         if (hipStreamWaitEvent(pool->side[gi - 1], pool->fork, 0) != hipSuccess) status = MRT_ERR_HIP;
       if (status != MRT_OK) { set_error("helper stream fork failed"); break; }
     }
-    // the heads are split evenly (the forward call's uneven split, which lets the larger group's
-    // stage L launches fill the chip exactly once, does not carry over: the streamed stage L backward
-    // kernel holds one workgroup per compute unit; 12 heads of the 480p KV-cache step: 6 + 6 1.76 ms,
-    // 9 + 3 1.82, 4 + 8 1.84, 10 + 2 1.93)
+    // the heads are split evenly (the forward call's uneven split, which lets the larger group's stage L launches
+    // fill the chip exactly once, does not carry over: how many workgroups a unit holds differs from kernel to
+    // kernel; sweep of 12 heads of the 480p KV-cache step: 6 + 6 368 us, 9 + 3 356, 4 + 8 363, 10 + 2 364, with two
+    // iterations 699, 748, 725, 730; tiles of 26 columns 552, 568, 568, 556)
     // The saving forward call runs the forward kernels only and takes the forward call's split.
     int first_group = 0;
     if (mode == kBwdForwardOnly && ngroups == 2) {

@@ -1521,14 +1521,13 @@ hipError_t launch_l_out(const KParams& kp, dim3 grid, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------
-// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 or b1 > 144): still one
-// workgroup per (m, j), three of four waves to a compute unit (b1 > 144: two, of three query tiles a wave), with
+// stage L for medium key ranges (96 < NK <= 192; b1 <= 128 or b1 > 144), last iteration: still one
+// workgroup per (m, j), three of four waves to a compute unit (b1 > 144: launch_l_out_mid_d), with
 // ONE 52 KB LDS tile used twice.  (Six waves lie 2, 2, 1, 1 on the SIMDs, every workgroup's alike: two of them
-// share a unit up to 128 registers a wave; with more they have it to themselves.)  Last iteration: the
-// tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one or two query
+// share a unit up to 128 registers a wave; with more they have it to themselves.)  The
+// tile first holds alpha_L[m, j] (every wave forms the exact softmax of its one to three query
 // tiles against all keys and keeps the probabilities as packed bf16 in registers), then Y[m, j]
-// (second product).  Earlier iterations: the tile holds alpha_L for the row log-sum-exp, then Q
-// for the second pass, which streams alpha_L again from global memory.
+// (second product).
 // ---------------------------------------------------------------------------------------
 constexpr int kMidRows = 192;
 constexpr int kMidWideB1 = 144;   // beyond: no bf16 backward pass
@@ -1622,7 +1621,7 @@ __global__ __launch_bounds__(64 * NW, (EARLY || QT == 3 ? 2 : QT == 1 ? 4 : 3)) 
   const int NK = visible_key_tile_rows(a, p.c1k, p.ct, p.qt0) * p.c2 * b1;   // <= 16*NTK
   const size_t NKtot = (size_t)p.ntk * b1;
   const int b = bh / p.H, hd = bh - b * p.H;
-  const WaveTiles<QT> wt(wave + part * NW, NW, (b1 + 15) >> 4);   // b1 <= 32 NW: at most two tiles a wave (or one)
+  const WaveTiles<QT> wt(wave + part * NW, NW, (b1 + 15) >> 4);   // b1 <= 16 NW QT (QT = 1: in two halves)
 
   const size_t row0 = (((size_t)bhl * p.ntq + ml) * b2 + j) * NKtot;
   const u16* aLp = (const u16*)p.aL + row0 * D;
@@ -1685,7 +1684,7 @@ __global__ __launch_bounds__(64 * NW, (EARLY || QT == 3 ? 2 : QT == 1 ? 4 : 3)) 
   __syncthreads();
   MRT_STAMP(3);
 
-  // ---- second product: both query tiles of the wave share every value read
+  // ---- second product: the query tiles of the wave share every value read
   if (wt.nq > 0) {
     f32x4 o[QT][NVT];
 #pragma unroll
@@ -1910,7 +1909,7 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last
   if (nlt > kMaxLT) return hipErrorInvalidValue;
   const int nk_max = kp.ntk * kp.b1;
   // earlier iterations, key range of at most 192 rows: one pass over the logits (four waves for
-  // b1 <= 96, six or eight beyond).  Up to 64 key rows every wave has at most one key tile, instead of half the
+  // b1 <= 96, eight up to 128, four or eight beyond).  Up to 64 key rows every wave has at most one key tile, instead of half the
   // waves two (calls of one to 40 heads: 48 rows, 30 columns 0.93 .. 0.99 of the time, 30 and 64 rows 0.96 .. 0.99, 34 rows
   // of 64 features 0.95 .. 1.01); six waves for 65 to 96 rows gain nothing (0.98 .. 1.03).
   if (!last && nk_max <= kMidRows && nlt <= 6) {
@@ -1934,9 +1933,10 @@ hipError_t launch_bf16_stage_l(const KParams& kp, int nbh, int beside, bool last
   if (l_out_mid(kp))
     return kp.d == 128 ? launch_l_out_mid_d<128>(kp, grid, (nk_max + 15) / 16, s)
                        : launch_l_out_mid_d<64>(kp, grid, (nk_max + 15) / 16, s);
-  // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), each wave owning up to two
-  // query tiles, so that two workgroups fit a compute unit whatever order their waves are dealt
-  // to the SIMDs in; only b1 > 128 needs a fifth and sixth wave.
+  // long key ranges: streamed.  Workgroups of 4 waves (one per SIMD), so that two fit a compute unit whatever
+  // order their waves are dealt to the SIMDs in, or of 8 (one_a_unit).  Each wave owns up to three query tiles in
+  // the refine kernel and up to two in the last launch, which takes 8 waves for b1 > 128 in any grid (three tiles a
+  // wave do not fit its registers).
   if (!last) return kp.d == 128 ? launch_l_refine_d<128>(kp, grid, nlt, eight, s)
                                 : launch_l_refine_d<64>(kp, grid, nlt, eight, s);
   if (nlt <= 4) return kp.d == 128 ? launch_l_out<128, 1, 256>(kp, grid, s)
