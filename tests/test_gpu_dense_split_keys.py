@@ -1,7 +1,7 @@
 """bf16 dense calls whose keys are split over several workgroups (few queries, many keys): every workgroup
 shape at ragged sizes, under the mask with hidden keys, with query ranges whose key counts differ (where
-some parts of a workgroup's keys are empty and one workgroup's halves end at different keys), and with
-infinite values that only the last chunk sees.  Against plain torch in float64 with the bar of the
+some parts of a workgroup's keys are empty and one workgroup's halves end at different keys), with infinite
+values that only the last chunk sees, and with softmax references beyond 2^20.  Against plain torch in float64 with the bar of the
 unsplit kernels (output and probabilities rounded once each to 2^-9: 2.4e-3 in the 2-norm; four times
 that), and against the unsplit call, whose probabilities are rounded relative to other references: two
 roundings of 2^-9 apart in the 2-norm at most."""
@@ -83,6 +83,26 @@ def test_infinite_values_of_the_last_chunk(name):
     out, one = pkg.dense_attn_fwd(q, k, v, **args)[:, :, :seen], unsplit((q, k, v), args)[:, :, :seen]
     assert not (out.isnan() & ~one.isnan()).any() and not out.isinf().any()
     assert torch.equal(out[~out.isnan()], expect[~out.isnan()]) and out.isnan().sum() < 128 * q.shape[1] * q.shape[3]
+
+
+@pytest.mark.parametrize("name", ["64", "64-ragged-steps", "128-steps", "256-steps", "256-hidden", "d64-64-steps", "d64-128"])
+def test_references_far_from_zero(name):
+    # Logits around 2^22 (their products exact in fp32), where a reference is a rounded logit: of two queries in
+    # three the parts of the first keys have such a reference and those of the others zero, the weight lying once
+    # on the former and once on the latter, on keys of one logit (the next is 2^18 below); of the third query all
+    # logits are zero.  Weights are then equal or zero in any precision; O's rounding is left.
+    (q, k, v), args = inputs(name)
+    args["scale"] = 1.0
+    q.zero_(), k.zero_()
+    at = torch.arange(q.shape[2], device="cuda:0")
+    q[..., 0] = (at % 3 - 1) * 2.0 ** 12
+    at = torch.arange(k.shape[2], device="cuda:0")
+    k[..., 0] = torch.where(at < k.shape[2] // 2, 64.0 * (16 - at % 7), torch.zeros(()).to(at.device))
+    out, one = pkg.dense_attn_fwd(q, k, v, **args).double(), unsplit((q, k, v), args).double()
+    ref = reference(q, k, v, args["h"] * args["w"], args["causal_chunk"], args["q_frame_offset"], 1.0)
+    err, apart = ((out - x).norm() / x.norm() for x in (ref, one))
+    print(f"case {name}: rel {err:.2e}, from the unsplit call {apart:.2e}", flush=True)
+    assert err <= 1e-2 and apart <= 2.0 ** -8
 
 
 def test_output_in_the_place_of_the_queries():
