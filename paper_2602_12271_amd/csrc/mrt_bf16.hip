@@ -1198,7 +1198,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && NLT <= 6) || PT == 1 ? 3 : 2) 
 #pragma unroll
       for (int pt = from; pt < to; ++pt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if ((THREES && !SHARED && !RMASK) || pt < npt) {       // (a tile that is not there: the last key's, not used)
+        if (pt < npt) {       // (without the test 0.98 .. 1.00 of a wide call up to 376 workgroups and at 64 features, up to 1.03 beyond)
 #pragma unroll
           for (int ks = 0; ks < KS1; ++ks) acc = mfma(av[ks], kb[pt][ks], acc);
         }
@@ -1722,7 +1722,7 @@ template <int D>
 hipError_t launch_l_out_mid_d(const KParams& kp, dim3 grid, int nkt, hipStream_t s) {
   // b1 > 144 (then nkt >= 10).  More columns than compute units: four waves of up to three query tiles, two
   // workgroups to a unit (175 and 187 registers), where six waves of two (132 to 164) had it to themselves and took a
-  // second round ((156,30), 12 heads: launch 20.6 -> 17.1 us, and eleven and twelve tiles 1 to 3 % of the call).
+  // second round ((156,30), 12 heads: launch 20.5 -> 16.2 us, and eleven and twelve tiles 1 to 3 % of the call).
   // Fewer: a wave's chain is what the launch takes, so six waves, or halves of the rows in two workgroups, one tile a
   // wave: twelve tiles always (24 columns x 1 head 33.9 -> 30.5 us when it came), ten up to a quarter of the units
   // (30 columns, one head: call 30.8 -> 29.5; at four heads, 240 such workgroups, 39.6 -> 40.3).
@@ -1872,10 +1872,10 @@ hipError_t launch_l_refine_one(const KParams& kp, dim3 grid, int nlt, hipStream_
 // chain a workgroup waits for; two such workgroups share a compute unit, 89 to 100 registers a wave; 112 rows, 40
 // columns, calls of 1 to 40 heads 0.98 .. 0.88 of the time of six waves with two tiles each, 12 heads 57.6
 // -> 52.6 us, masked 0.97 .. 0.94; 128 rows, 24 columns, 64 features 0.98 .. 0.92, masked 0.94 .. 0.92).  Ten and
-// twelve: four waves of up to three key tiles, two workgroups to a unit (209 to 253 registers), where a launch has
+// twelve: four waves of up to three key tiles, two workgroups to a unit (206 to 253 registers), where a launch has
 // more workgroups than units: a workgroup of more waves with fewer tiles has a unit to itself, so that the 360
-// workgroups of (156,30), 12 heads, take two rounds (six waves of two tiles: call 70.1 us, four of three 59.9; 150
-// to 192 rows from 257 workgroups on 0.72 .. 0.93, together with the last launch's four waves).  Up to one a unit
+// workgroups of (156,30), 12 heads, take two rounds (six waves of two tiles: call 70.1 us, four of three 60.9; 130
+// to 192 rows from 257 workgroups on, 34 calls, 0.82 .. 0.92, together with the last launch's four waves).  Up to one a unit
 // (one_a_unit) eight waves of two tiles and of one (152 to 193 registers): a wave's chain is what the launch takes
 // ((148,32), 7 heads, T = 3: call 70.4 -> 68.8 us; (154,55), 4 heads, T = 3: 73.0 -> 70.0; (156,30), 8 heads 45.3 ->
 // 44.8; six waves of two 68.6, 70.4 and 45.1).  No variant keeps anything in local memory.
